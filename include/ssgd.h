@@ -166,8 +166,8 @@ ssgd_status ssgd_full_loss(ssgd_ctx *ctx, int32_t replica, double *loss_out);
 /* The gradient of that objective, grad F(w) = (1/N) sum_n grad f(w, xi_n), at the replica's current
  * parameters: the quantity in which the staleness bound (fifth assumption of Sec. 4.1) is stated
  * (E||grad F(w_j) - grad F(w_tau)||^2 <= gamma E||grad F(w_j)||^2).  grad_out: HOST, |w| floats in the
- * layout of the parameters.  Two passes over X in fp32 with fp64 sums over chunks of samples, through
- * temporary device buffers (SSGD_ENOMEM if they do not fit).  Linear models need d % 4 == 0, else
+ * layout of the parameters.  fp32 with fp64 sums over chunks of samples, through a work area that the
+ * context allocates at the first call and keeps (SSGD_ENOMEM if it does not fit).  Linear models need d % 4 == 0, else
  * SSGD_EINVAL.  The two-layer network: with the arithmetic of its training gradients (bf16 operands in
  * the two large contractions, fp32 accumulation), the data set in blocks of up to 256 x 64 rows that are
  * added on the host in fp64; parameters, trace and mini-batches in flight are untouched. */
@@ -175,13 +175,12 @@ ssgd_status ssgd_full_gradient(ssgd_ctx *ctx, int32_t replica, float *grad_out);
 
 /* ssgd_full_gradient for callers that cannot allocate device memory (code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc): the same kernels in the same launch shape,
- * hence the same values bit for bit, but the intermediate results (16 floats per sample and up to
- * 64 partial gradients) live in a static device array of the library, 4 Mi floats = 16 MiB that every
- * GPU the library runs on holds until the process ends, and the gradient is written to
+ * hence the same values bit for bit, but the intermediate results (partial gradients) live in a static
+ * device array of the library, 36 MiB that every GPU the library runs on holds until the process ends, and the gradient is written to
  * grad_out_device (DEVICE, |w| floats, layout of the parameters).  The call allocates and frees
  * nothing, copies nothing to the host and does not wait: the work is enqueued on the context's stream
- * and the result is complete when that stream reaches the end of it.  Data sets that need more than
- * the array holds (16 N + min(64, ceil(N / 256)) * classes * (d + 1) floats > 4 Mi) give SSGD_EINVAL,
+ * and the result is complete when that stream reaches the end of it.  Data sets that the array is not
+ * meant for (16 N + min(64, ceil(N / 256)) * classes * (d + 1) > 4 Mi) give SSGD_EINVAL,
  * as do the shapes ssgd_full_gradient refuses.  All calls on one GPU, from any context, share that
  * GPU's array: calls that overlap on one GPU (different streams or threads) race; calls on one stream
  * are ordered.  Nothing in the array has to be zero at entry: a call writes every word before it

@@ -25,7 +25,7 @@ struct DevBuf {
         bytes = n;
         return hipMalloc(&p, n ? n : 1);
     }
-    void release() { if (p) (void)hipFree(p); p = nullptr; }
+    void release() { if (p) (void)hipFree(p); p = nullptr; bytes = 0; }
     template <class T> T* as() const { return reinterpret_cast<T*>(p); }
 };
 
@@ -43,6 +43,9 @@ struct ssgd_ctx {
     hipStream_t side = nullptr;     // second stream for the schedule of the network's next piece (default priority)
     int32_t* host_rows = nullptr;   // pinned: copies of replica 0's K, tau and sel rows of the segment being run (network)
     size_t host_rows_words = 0;
+    void* host_out = nullptr;       // pinned: kernels leave results here that a call hands to the caller (host_out_room)
+    size_t host_out_bytes = 0;
+    DevBuf fg_work;                 // partial gradients of ssgd_full_gradient, kept from its first call on
     int device = 0;
     int64_t nw = 0;
     int32_t Kcap = 0, S = 0, G = 0, nbw = 0, maxrows = 0, table_ord = 1;
@@ -83,6 +86,17 @@ ssgd_status fail(ssgd_ctx* c, ssgd_status st, const std::string& msg) {
             return fail((c), e_ == hipErrorOutOfMemory ? SSGD_ENOMEM : SSGD_EDEVICE,          \
                         std::string(#call) + ": " + hipGetErrorString(e_));                  \
     } while (0)
+
+// Pinned host memory of at least `bytes` for results that a kernel writes and the host reads after a synchronisation:
+// saves the copy command and its staging.
+hipError_t host_out_room(ssgd_ctx* c, size_t bytes) {
+    if (c->host_out_bytes >= bytes) return hipSuccess;
+    if (c->host_out) (void)hipHostFree(c->host_out);
+    c->host_out = nullptr; c->host_out_bytes = 0;
+    const hipError_t e = hipHostMalloc(&c->host_out, bytes, hipHostMallocDefault);
+    if (e == hipSuccess) c->host_out_bytes = bytes;
+    return e;
+}
 
 __global__ void init_workers_kernel(WorkerState ws, Dist dist, uint64_t seed, int P, int R, int K, int variant,
                                     int table_ord) {
@@ -712,17 +726,14 @@ ssgd_status ssgd_full_loss(ssgd_ctx* c, int32_t replica, double* loss_out) {
         return fail(c, SSGD_EINVAL, "the full objective of the linear models needs d % 4 == 0");
     HIP_OK(c, hipSetDevice(c->device));
     const int blocks = std::max(1, c->cu_count);
-    DevBuf partial;
-    HIP_OK(c, partial.alloc(sizeof(double) * blocks));
+    HIP_OK(c, host_out_room(c, sizeof(double) * blocks));
+    double* h = static_cast<double*>(c->host_out);
     hipError_t e = launch_full_loss(c->model.kind, c->model.X, c->model.y, c->model.N, c->model.d, C,
-                                    c->params.as<float>() + (int64_t)replica * c->nw, partial.as<double>(), blocks, c->stream);
-    std::vector<double> h(blocks);
-    if (e == hipSuccess) e = hipMemcpyAsync(h.data(), partial.p, sizeof(double) * blocks, hipMemcpyDeviceToHost, c->stream);
+                                    c->params.as<float>() + (int64_t)replica * c->nw, h, blocks, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    partial.release();
     if (e != hipSuccess) return fail(c, SSGD_EDEVICE, std::string("full objective: ") + hipGetErrorString(e));
     double s = 0.0;
-    for (double v : h) s += v;
+    for (int b = 0; b < blocks; ++b) s += h[b];
     *loss_out = s / (double)c->model.N;
     return SSGD_OK;
 }
@@ -744,16 +755,18 @@ ssgd_status ssgd_full_gradient(ssgd_ctx* c, int32_t replica, float* grad_out) {
     if (!full_grad_supports(c->model.kind, c->model.d, C))
         return fail(c, SSGD_EINVAL, "the full gradient of the linear models needs d % 4 == 0");
     HIP_OK(c, hipSetDevice(c->device));
-    DevBuf scratch, out;
-    hipError_t e = scratch.alloc(sizeof(float) * (size_t)full_grad_scratch_floats(c->model.N, c->model.d, C, nullptr));
-    if (e == hipSuccess) e = out.alloc(sizeof(float) * (size_t)c->nw);
-    if (e != hipSuccess) { scratch.release(); out.release(); return fail(c, SSGD_ENOMEM, "full gradient: device allocation failed"); }
-    e = launch_full_grad(c->model.kind, c->model.X, c->model.y, c->model.N, c->model.d, C,
-                         c->params.as<float>() + (int64_t)replica * c->nw, scratch.as<float>(), out.as<float>(), c->cu_count, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(grad_out, out.p, sizeof(float) * (size_t)c->nw, hipMemcpyDeviceToHost, c->stream);
+    const size_t work = sizeof(float) * (size_t)full_grad_work_floats(c->model.N, c->model.d, C, c->cu_count);
+    if (c->fg_work.bytes < work) {
+        c->fg_work.release();
+        if (c->fg_work.alloc(work) != hipSuccess) { c->fg_work.release(); return fail(c, SSGD_ENOMEM, "full gradient: device allocation failed"); }
+    }
+    if (host_out_room(c, sizeof(float) * (size_t)c->nw) != hipSuccess) return fail(c, SSGD_ENOMEM, "full gradient: host allocation failed");
+    hipError_t e = launch_full_grad(c->model.kind, c->model.X, c->model.y, c->model.N, c->model.d, C,
+                                    c->params.as<float>() + (int64_t)replica * c->nw, c->fg_work.as<float>(),
+                                    static_cast<float*>(c->host_out), c->cu_count, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    scratch.release(); out.release();
     if (e != hipSuccess) return fail(c, SSGD_EDEVICE, std::string("full gradient: ") + hipGetErrorString(e));
+    memcpy(grad_out, c->host_out, sizeof(float) * (size_t)c->nw);
     return SSGD_OK;
 }
 
@@ -1031,10 +1044,11 @@ void ssgd_destroy(ssgd_ctx* c) {
     for (size_t r = c->mlp.size(); r-- > 0;) mlp_destroy(c->mlp[r]);   // the first one owns what the others share
     if (c->side) (void)hipStreamDestroy(c->side);
     if (c->host_rows) (void)hipHostFree(c->host_rows);
+    if (c->host_out) (void)hipHostFree(c->host_out);
     DevBuf* bufs[] = {&c->table, &c->tr_t, &c->tr_loss, &c->tr_K, &c->tr_sel, &c->tr_tau, &c->tr_ord, &c->ws_finish,
                       &c->ws_tau, &c->ws_ord, &c->ws_clock, &c->ws_curK, &c->ws_winprev, &c->ws_winidx, &c->ws_F0,
                       &c->ws_intstart, &c->ws_crossed, &c->ws_ndone, &c->params, &c->park, &c->park_small, &c->zpart, &c->zx, &c->dx, &c->fallback,
-                      &c->arrive, &c->abort_flag, &c->xcc_ids, &c->prof};
+                      &c->arrive, &c->abort_flag, &c->xcc_ids, &c->prof, &c->fg_work};
     for (DevBuf* b : bufs) b->release();
     delete c;
 }

@@ -129,12 +129,14 @@ size_t linear_defer_lds_bytes(int C, int S);
 int linear_defer_replicas_per_launch(int G, int cus);
 hipError_t launch_linear_defer(const LinArgs& a, hipStream_t s);
 
-// Gradient of that objective (full_grad.hip): `scratch` holds full_grad_scratch_floats floats, `out` |w| floats (device).
+// Gradient of that objective (full_grad.hip): the work area holds full_grad_work_floats floats, `out` |w| floats (device
+// or mapped host memory).  full_grad_scratch_floats is the figure that ssgd_full_gradient_static states its limit in.
 bool full_grad_supports(int kind, int d, int C);
 int64_t full_grad_scratch_floats(int64_t N, int d, int C, int* chunks_out);
+int64_t full_grad_work_floats(int64_t N, int d, int C, int cus);
 hipError_t launch_full_grad(int kind, const float* X, const void* y, int64_t N, int d, int C, const float* w,
-                            float* scratch, float* out, int cus, hipStream_t s);
-// The static scratch array of full_grad.hip (one copy per GPU, held until the process ends): its size, the per-device
+                            float* work, float* out, int cus, hipStream_t s);
+// The static scratch array of full_grad.hip (one copy per GPU, held until the process ends): its limit, the per-device
 // look-up of its address (call once with the device current), and the address on the current device.
 int64_t full_grad_static_scratch_floats();
 hipError_t full_grad_static_scratch_prepare();

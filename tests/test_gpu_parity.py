@@ -1124,6 +1124,28 @@ def test_full_gradient_against_the_oracle(ssgd, oracle, torch_cuda, kind, N, d, 
     ctx.close()
 
 
+@pytest.mark.parametrize("kind,N,d,classes", [
+    ("lsq", 1, 4, 1), ("softmax", 17, 60, 2), ("softmax", 4099, 68, 10), ("lsq", 3000, 132, 1), ("softmax", 15, 260, 16),
+    ("softmax", 33, 512, 15), ("lsq", 40000, 16, 1), ("softmax", 5000, 516, 3), ("softmax", 700, 772, 10), ("lsq", 500, 1028, 1),
+    ("softmax", 300, 1540, 12), ("softmax", 257, 2052, 11), ("softmax", 48, 2564, 10),
+    ("softmax", 300, 3072, 15), ("lsq", 270, 3076, 1),      # the weights beside the tile do not fit the LDS: two passes
+])
+def test_full_gradient_at_the_edges_of_its_shapes(ssgd, oracle, torch_cuda, kind, N, d, classes):
+    """One row, a row past a block of 16, every number of column blocks per wave, shares that end inside a block.
+    Tolerance: fp32 products and sums over d <= 3076 columns and the rows of one workgroup, sqrt(3076) 2^-24 = 3e-6."""
+    torch = torch_cuda
+    if kind == "lsq":
+        X, y, _ = synth.lsq_data(N, d, 46)
+    else:
+        X, y = synth.mixture_data(N, d, classes, seed=46)
+    Xd, yd = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
+    ctx = ssgd.Context(kind, Xd, yd, 4, 2, 8, "k_sync", ssgd.delay_dist("exp", 1.0), 0.0, seed=45, classes=classes)
+    w = (0.05 * np.random.default_rng(7).standard_normal(ctx.nw)).astype(np.float32)
+    ctx.set_params(w)
+    assert rel(ctx.full_gradient(), oracle.Model(kind, X, y, classes=classes).full_grad(w)) <= 1e-5
+    ctx.close()
+
+
 def test_staleness_gamma_estimate_for_the_network(ssgd, torch_cuda):
     """The same estimate on the two-layer network with two replicas: zero for K-sync, positive for K-async."""
     from paper_2003_10579_amd import staleness_gamma
