@@ -155,6 +155,7 @@ hipError_t make_dist(const ssgd_delay_dist* d, DevBuf* table, Dist* out) {
     out->kind = d->kind;
     out->shift = (float)d->shift; out->rate = (float)d->rate;
     out->alpha = (float)d->alpha; out->scale = (float)d->scale;
+    out->inv_div = quotient_reciprocal(d->kind == SSGD_PARETO ? out->alpha : out->rate);
     out->table = nullptr; out->table_len = 0;
     if (d->kind == SSGD_TABLE) {
         hipError_t e = table->alloc(sizeof(float) * (size_t)d->table_len);

@@ -64,6 +64,17 @@ def test_delays_bit_exact(ssgd, oracle, torch_cuda, spec):
     assert np.array_equal(got.view(np.uint32), ref.view(np.uint32))
 
 
+@pytest.mark.parametrize("spec", [("exp", 1.0), ("exp", 3.0), ("exp", 1.0 / 3.0), ("shifted_exp", 0.5, 1.7), ("pareto", 2.5, 1.0),
+                                  ("exp", 1e-30), ("exp", 3e30)])     # the last two: outside the range of the short division
+def test_delays_bit_exact_for_every_uniform_value(ssgd, oracle, torch_cuda, spec):
+    """The delay depends on the top 23 bits only: all 2^23 of them (the divisions on the device are residue-corrected
+    products and have to equal the rounded quotient everywhere)."""
+    gd, od = dist_pair(ssgd, oracle, spec)
+    bits = np.arange(2 ** 23, dtype=np.uint32) << np.uint32(9)
+    got, ref = ssgd.debug_delays(gd, bits), od.from_bits(bits)
+    assert np.array_equal(got.view(np.uint32), ref.view(np.uint32))
+
+
 def test_batch_indices_bit_exact(ssgd, oracle, torch_cuda):
     for (seed, rep, w, o, v, m, N) in [(0, 0, 0, 0, 0, 32, 50000), (7, 3, 255, 2, 19999, 128, 50000),
                                        (2 ** 40 + 5, 63, 17, 0, 4999, 17, 4096), (1, 0, 1, 0, 1, 1, 1),
@@ -429,6 +440,35 @@ def test_mc_ten_thousand_trials_bit_exact(ssgd, oracle, torch_cuda, variant):
     o = oracle.runtime_mc(variant, 16, 1, 16, od, 10000, 4, seed=3, per_trial=True)
     assert np.array_equal(g["per_trial"], o["per_trial"])
     assert np.allclose(g["sum"], o["sum"], rtol=1e-12) and np.allclose(g["sumsq"], o["sumsq"], rtol=1e-12)
+
+
+@pytest.mark.parametrize("variant,P,Kmin,Kmax,L,trials,spec", [
+    ("k_async", 1, 1, 1, 3, 40, ("exp", 1.0)), ("k_async", 64, 63, 64, 5, 40, ("exp", 2.0)), ("k_async", 65, 1, 65, 4, 20, ("pareto", 2.5, 1.0)),
+    ("k_async", 129, 120, 129, 6, 20, ("shifted_exp", 0.5, 1.0)), ("k_async", 256, 250, 256, 9, 10, ("exp", 1.0)),
+    ("k_async", 5, 2, 4, 130, 10, ("exp", 1.0)),                       # chains longer than a wavefront has lanes
+    ("k_async", 200, 90, 90, 4, 20, ("exp", 1.0)),                     # a single K: selected, not sorted
+    ("k_sync", 3, 1, 3, 70, 20, ("pareto", 1.1, 1.0)), ("k_sync", 256, 1, 256, 3, 5, ("exp", 1.0)), ("k_sync", 100, 77, 77, 5, 20, ("exp", 1.0)),
+    ("k_batch_sync", 1, 1, 5, 4, 20, ("exp", 1.0)), ("k_batch_sync", 130, 66, 70, 3, 10, ("shifted_exp", 0.2, 1.0)),
+    ("k_batch_sync", 3, 600, 601, 2, 5, ("exp", 1.0)),                 # more draws per update than the window holds
+    ("k_batch_async", 1, 1, 4, 5, 20, ("exp", 1.0)), ("k_batch_async", 200, 1, 200, 6, 5, ("shifted_exp", 5.0, 50.0)),
+    ("k_batch_async", 70, 64, 64, 8, 10, ("pareto", 0.3, 1.0)), ("k_batch_async", 2, 300, 300, 20, 3, ("exp", 1.0)),
+    ("k_batch_async", 4, 700, 700, 1, 3, ("pareto", 0.02, 1.0)),       # delays up to infinity
+])
+def test_mc_trials_at_the_edges_of_the_shapes(ssgd, oracle, torch_cuda, variant, P, Kmin, Kmax, L, trials, spec):
+    """Every trial's T_l bit for bit where registers, windows and lists are just full or just exceeded."""
+    gd, od = dist_pair(ssgd, oracle, spec)
+    g = ssgd.runtime_mc(variant, P, Kmin, Kmax, gd, trials, L, seed=6, per_trial=True)
+    o = oracle.runtime_mc(variant, P, Kmin, Kmax, od, trials, L, seed=6, per_trial=True)
+    assert np.array_equal(g["per_trial"], o["per_trial"], equal_nan=True)
+
+
+def test_mc_with_tied_finish_times(ssgd, oracle, torch_cuda):
+    """Delays rounded to a few values (a huge shift swallows the exponential part): ties at every selection."""
+    for variant in ("k_async", "k_sync", "k_batch_sync", "k_batch_async"):
+        gd, od = dist_pair(ssgd, oracle, ("shifted_exp", 2.0e6, 1.0))      # fp32 spacing 1/8 at 2e6
+        g = ssgd.runtime_mc(variant, 80, 1, 80, gd, 6, 5, seed=8, per_trial=True)
+        o = oracle.runtime_mc(variant, 80, 1, 80, od, 6, 5, seed=8, per_trial=True)
+        assert np.array_equal(g["per_trial"], o["per_trial"]), variant
 
 
 def test_mc_closed_forms_at_scale(ssgd, torch_cuda):
