@@ -30,6 +30,7 @@ namespace ssgd {
 namespace {
 
 constexpr int kWindow = 512;      // delays drawn ahead per wavefront (fp32, LDS)
+constexpr int kFew = 32;          // candidates that are ranked against each other instead of narrowed further
 constexpr int kList = 512;        // K-batch-async: renewals listed before they are sorted (fp64, LDS)
 
 struct McArgs {
@@ -38,7 +39,7 @@ struct McArgs {
     int32_t variant, P, Kmin, Kmax, chain_len;
     int32_t nslices;     // block b takes the values K = Kmin + b % nslices, + nslices, ...: small accumulators, many waves per CU
     int64_t trial0, trials;
-    double mean_delay;   // K-batch-async: sizes the lists (a rough value is enough)
+    double mean_delay;   // a rough value: first guess of a selection, size of the K-batch-async lists
     double* partial;     // [blocks][nK*chain_len][2]
     double* per_trial;   // nullable
 };
@@ -170,32 +171,46 @@ __device__ __forceinline__ int count(const u64 (&m)[NQ]) {
     return c;
 }
 
-// The K-th smallest key (K from 1, wave-uniform) of all 64 NQ.  lo <= hi: where it is expected.  Every comparison is
-// exact and equal keys are told apart by position, so the result does not depend on the guess.
+__device__ __forceinline__ bool in_mask(u64 mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
+template <typename T> __device__ __forceinline__ T unbounded();
+template <> __device__ __forceinline__ double unbounded<double>() { return inf64(); }
+template <> __device__ __forceinline__ float unbounded<float>() { return __uint_as_float(0x7F800000u); }
+
+// The K-th smallest key (K from 1, wave-uniform) of all 64 NQ.  [lo, hi): where it is expected, extended by w, 2 w, 4 w ...
+// until it holds the key wanted (w > 0); few: kFew keys of LDS.  The mask arithmetic is scalar work, which a CU issues
+// once per cycle for all its waves, so it ends as soon as at most kFew candidates are left; those go to LDS and each is
+// counted against all.  (With pivots to the end an update took 198 scalar and 165 vector instructions at P = 128, and the
+// scalar unit was what the kernel waited for.)  Every comparison is exact, so the result does not depend on the guess.
 template <int NQ, typename T>
-__device__ __forceinline__ T select_kth(const T (&key)[NQ], int K, T lo, T hi) {
-    u64 act[NQ];
-    int r = K;
-    {
-        u64 below[NQ], upto[NQ];
+__device__ __forceinline__ T select_kth(const T (&key)[NQ], int K, T lo, T hi, T w, T* few, int lane) {
+    u64 below[NQ], upto[NQ];
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) { below[q] = __ballot(key[q] < lo); upto[q] = __ballot(key[q] < hi); }
-        const int cl = count(below), ch = count(upto);
-        if (r <= cl) {
+    for (int q = 0; q < NQ; ++q) { below[q] = __ballot(key[q] < lo); upto[q] = __ballot(key[q] < hi); }
+    int cl = count(below), ch = count(upto);
+    for (int it = 0; it < 100 && (K <= cl || K > ch); ++it) {
+        if (K <= cl) {
+            ch = cl; lo -= w;
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) act[q] = below[q];
-        } else if (r <= ch) {
-            r -= cl;
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) act[q] = upto[q] & ~below[q];
+            for (int q = 0; q < NQ; ++q) { upto[q] = below[q]; below[q] = __ballot(key[q] < lo); }
+            cl = count(below);
         } else {
-            r -= ch;
+            cl = ch; hi += w;
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) act[q] = ~upto[q];
+            for (int q = 0; q < NQ; ++q) { below[q] = upto[q]; upto[q] = __ballot(key[q] < hi); }
+            ch = count(upto);
         }
+        w += w;
     }
-    int n = count(act);
-    for (;;) {
+    if (K <= cl || K > ch) {                   // an infinite finish time
+        cl = 0; ch = 64 * NQ;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) { below[q] = 0; upto[q] = ~0ull; }
+    }
+    u64 act[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) act[q] = upto[q] & ~below[q];
+    int n = ch - cl, r = K - cl;
+    while (n > kFew) {
         // the first candidate by position as the pivot if the one wanted is in the lower half, else the last: fresh
         // delays lie in no order, what is left of a sorted list lies in ascending order
         T pivot = key[0];
@@ -203,7 +218,7 @@ __device__ __forceinline__ T select_kth(const T (&key)[NQ], int K, T lo, T hi) {
             bool found = false;
 #pragma unroll
             for (int q = 0; q < NQ; ++q)
-                if (!found && act[q] != 0) { found = true; const int l = __builtin_ctzll(act[q]); pivot = lane_value(key[q], l); act[q] &= act[q] - 1; }
+                if (!found && act[q] != 0) { found = true; const int l = __builtin_ctzll(act[q]); pivot = lane_value(key[q], l); act[q] &= ~(1ull << l); }
         } else {
             bool found = false;
 #pragma unroll
@@ -224,6 +239,29 @@ __device__ __forceinline__ T select_kth(const T (&key)[NQ], int K, T lo, T hi) {
 #pragma unroll
             for (int q = 0; q < NQ; ++q) act[q] &= ~lt[q];
         }
+    }
+    wave_fence();
+    if (lane < kFew) few[lane] = unbounded<T>();
+    wave_fence();
+    int at = 0;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        if (in_mask(act[q])) few[at + rank_in(act[q])] = key[q];
+        at += __popcll(act[q]);
+    }
+    wave_fence();
+    const T v = few[lane & (kFew - 1)];
+    int rank = 0;
+    for (int j = 0; j < n; j += 4) {
+        T c[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) c[u] = few[j + u];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) rank += (c[u] < v) ? 1 : 0;
+    }
+    for (;; --r) {                             // equal keys have the rank of the first of them
+        const u64 m = __ballot(rank == r - 1);
+        if (m != 0) return lane_value(v, __builtin_ctzll(m));
     }
 }
 
@@ -371,14 +409,15 @@ __global__ __launch_bounds__(64, VARIANT == kBatchAsync ? 4 : 8) void mc_kernel(
         const bool sorted = VARIANT != kBatchSync && mineK > 2;
         if (sorted) sort_keys<NQ>(base, lane);
 
-        float* window = reinterpret_cast<float*>(acc + 2 * cells_max);
-        for (int K = a.Kmin + slice; K <= a.Kmax; K += a.nslices) {
+        double* few = acc + 2 * cells_max;
+        float* window = reinterpret_cast<float*>(few + kFew);
+        for (int K = a.Kmin + slice, kk = 0; K <= a.Kmax; K += a.nslices, ++kk) {
             // The chain's delays in the order it takes them: per update from the second on K restarts (K-async) or P
             // fresh ones (K-sync); K-batch-sync: P fresh ones, then the K - 1 restarts, from the first update on (whose
             // fresh ones are `base`).  Element i of that sequence is element i % per of update i / per.
             const int per = VARIANT == kAsync ? K : (VARIANT == kSync ? P : P + K - 1);
             const int total = per * (VARIANT == kBatchSync ? L : L - 1);
-            const uint32_t recip = ((1u << 20) + per - 1) / (uint32_t)per;      // exact quotients for i < 1024, per < 512
+            const float recip = __builtin_amdgcn_rcpf((float)per);      // (i + 1/2) / per rounds down to the quotient for i < 1024, per < 512
             int win_lo = 0, win_hi = 0, next = VARIANT == kBatchSync ? P : 0;
             auto need = [&](int n) {           // the next n elements are in the window (n <= kWindow)
                 if (next + n <= win_hi) return;
@@ -389,7 +428,7 @@ __global__ __launch_bounds__(64, VARIANT == kBatchAsync ? 4 : 8) void mc_kernel(
                 wave_fence();
                 for (int i0 = 0; i0 < win_hi - win_lo; i0 += 64) {
                     const int i = r0 + i0 + lane;
-                    const uint32_t u = per < 512 ? ((uint32_t)i * recip) >> 20 : (i >= per ? 1u : 0u);
+                    const uint32_t u = per < 512 ? (uint32_t)(((float)i + 0.5f) * recip) : (i >= per ? 1u : 0u);
                     const int r = i - (int)u * per;
                     const uint32_t upd = u0 + u;
                     const bool restart = VARIANT == kBatchSync && r >= P;
@@ -398,7 +437,9 @@ __global__ __launch_bounds__(64, VARIANT == kBatchAsync ? 4 : 8) void mc_kernel(
                 }
                 wave_fence();
             };
-            const float narrow = sqrtf((1.02f - (float)K / (float)(P + 1)) / (float)K);    // expected relative spread of T
+            // expected relative spread of T, roughly (a guess)
+            const float narrow = 1.3f * __builtin_amdgcn_sqrtf((1.02f - (float)K * __builtin_amdgcn_rcpf((float)(P + 1))) * __builtin_amdgcn_rcpf((float)K));
+            const int cell0 = kk * L;
 
             double t = 0.0, T = 0.0, kept = 0.0;
             double key[NQ];
@@ -415,7 +456,7 @@ __global__ __launch_bounds__(64, VARIANT == kBatchAsync ? 4 : 8) void mc_kernel(
                         int first = 0;
 #pragma unroll
                         for (int q = 0; q < NQ; ++q) {
-                            const bool mine = (gone[q] >> lane) & 1ull;
+                            const bool mine = in_mask(gone[q]);
                             const double restart = t + (double)x[mine ? first + rank_in(gone[q]) : 0];
                             key[q] = mine ? restart : key[q];
                             first += __popcll(gone[q]);
@@ -429,8 +470,8 @@ __global__ __launch_bounds__(64, VARIANT == kBatchAsync ? 4 : 8) void mc_kernel(
                         for (int q = 0; q < NQ; ++q)
                             if (p % NQ == q) t_new = lane_value(key[q], p / NQ);
                     } else {
-                        const double w = T * (double)narrow;
-                        t_new = select_kth<NQ>(key, K, t + T - w, t + T + w);
+                        const double w = T * (double)narrow, at = t + T;
+                        t_new = select_kth<NQ>(key, K, at - w, at + w, l == 0 ? 0.125 * a.mean_delay : w + w, few, lane);
                     }
                     if (l + 1 < L) {
 #pragma unroll
@@ -465,7 +506,7 @@ __global__ __launch_bounds__(64, VARIANT == kBatchAsync ? 4 : 8) void mc_kernel(
                             if (p % NQ == q) s = lane_value(f[q], p / NQ);
                     } else {
                         const float Tf = (float)T, w = Tf * narrow;
-                        s = select_kth<NQ>(f, K, Tf - w, Tf + w);
+                        s = select_kth<NQ>(f, K, Tf - w, Tf + w, l == 0 ? 0.125f * (float)a.mean_delay : w + w, reinterpret_cast<float*>(few), lane);
                     }
                     t_new = t + (double)s;
                 } else {
@@ -504,7 +545,7 @@ __global__ __launch_bounds__(64, VARIANT == kBatchAsync ? 4 : 8) void mc_kernel(
                 // lane l % 64 keeps the T of update l; they are added up 64 at a time
                 if (lane == (l & 63)) kept = T;
                 if (l + 1 == L || (l & 63) == 63) {
-                    const int c = ((K - a.Kmin) / a.nslices) * L + (l & ~63) + lane;
+                    const int c = cell0 + (l & ~63) + lane;
                     if (lane <= (l & 63)) {
                         acc[2 * c] += kept;
                         acc[2 * c + 1] += kept * kept;
@@ -596,7 +637,7 @@ extern "C" __attribute__((visibility("default"))) ssgd_status ssgd_runtime_mc(in
     size_t lds = sizeof(double) * 2 * cells_max;
     if (variant == SSGD_K_BATCH_ASYNC) lds += sizeof(double) * ((size_t)chain_len * Kmax + 1);   // the push sequence of a trial
     if (lds > 64 * 1024) { mc_fail("chain_len (K-batch-async: chain_len * Kmax) too large for one launch"); return SSGD_EINVAL; }
-    lds += variant == SSGD_K_BATCH_ASYNC ? sizeof(double) * kList : sizeof(float) * kWindow;
+    lds += variant == SSGD_K_BATCH_ASYNC ? sizeof(double) * kList : sizeof(double) * kFew + sizeof(float) * kWindow;
     if (per_trial && trials * cells > (1ll << 27)) { mc_fail("per_trial output limited to 2^27 values"); return SSGD_EINVAL; }
     hipStream_t st = (hipStream_t)hip_stream;
     McArgs a{};
