@@ -15,9 +15,9 @@
 //   * K-batch-async: the renewals of all workers up to a bound are listed unsorted in LDS, lane by lane in parallel, and
 //     a list is sorted in registers (the push sequence is the same for every K); one argmin per push is kept for lists
 //     that do not fit.
-// 10^5 trials, P = 128, all K, chains of 8 (K-async, Exp(1)): 46 ms a call, 110 ms with sorted arrays and restarts drawn
-// in place (15 of them host additions of the blocks' sums); K-batch-async, P = 64, K = 32, chains of 8: 0.4 ms, 6 with an
-// argmin and a draw per push.
+// 10^5 trials, P = 128, all K, chains of 8 (K-async, Exp(1)): 35.6 ms a call, 110 ms with sorted arrays and restarts
+// drawn in place (15 of them host additions of the blocks' sums); 169 vector instructions per update, issued 85 % of the
+// time; K-batch-async, P = 64, K = 32, chains of 8: 0.4 ms, 6 with an argmin and a draw per push.
 #include <algorithm>
 #include <cmath>
 #include <string>
@@ -560,15 +560,18 @@ __global__ __launch_bounds__(64, VARIANT == kBatchAsync ? 4 : 8) void mc_kernel(
     for (int c = lane; c < 2 * cells; c += 64) a.partial[(int64_t)blockIdx.x * 2 * cells_max + c] = acc[c];
 }
 
-// Sums of the blocks' accumulators: out[2 cell], out[2 cell + 1].  Workgroup = (64 words of one slice's accumulators),
-// each of its four waves takes a quarter of the slice's blocks in order, eight loads in flight.
-__global__ __launch_bounds__(256) void mc_reduce_kernel(McArgs a, int groups, int cells_max, double* out) {
-    __shared__ double quarters[4][64];
-    const int lane = threadIdx.x & 63, part = threadIdx.x >> 6;
-    const int slice = blockIdx.y, c = blockIdx.x * 64 + lane;
+// Sums of the blocks' accumulators: out[2 cell], out[2 cell + 1].  A workgroup takes `width` (a power of two up to 64)
+// words of one slice's accumulators; its 1024 / width groups of threads take consecutive runs of the slice's blocks, eight
+// loads in flight, and the runs' sums are added in order, pairs first.  (A single value of K has 16 words and 8192 blocks:
+// 64 words wide and four runs this took 120 us, as long as a small estimate itself.)
+constexpr int kReduceThreads = 1024;
+__global__ __launch_bounds__(kReduceThreads) void mc_reduce_kernel(McArgs a, int groups, int cells_max, int width, double* out) {
+    __shared__ double runs[kReduceThreads];
+    const int w = threadIdx.x & (width - 1), part = threadIdx.x / width, parts = kReduceThreads / width;
+    const int slice = blockIdx.y, c = blockIdx.x * width + w;
     const int nK = a.Kmax - a.Kmin + 1, L = a.chain_len;
     const int words = 2 * ((nK - slice + a.nslices - 1) / a.nslices) * L;
-    const int per = (groups + 3) / 4, g0 = part * per, g1 = min(groups, g0 + per);
+    const int per = (groups + parts - 1) / parts, g0 = part * per, g1 = min(groups, g0 + per);
     const int64_t step = (int64_t)a.nslices * 2 * cells_max;
     double sum = 0.0;
     if (c < words) {
@@ -583,11 +586,14 @@ __global__ __launch_bounds__(256) void mc_reduce_kernel(McArgs a, int groups, in
         }
         for (; g < g1; ++g) sum += src[g * step];
     }
-    quarters[part][lane] = sum;
-    __syncthreads();
+    runs[threadIdx.x] = sum;
+    for (int stride = 1; stride < parts; stride *= 2) {
+        __syncthreads();
+        if (part % (2 * stride) == 0) runs[threadIdx.x] += runs[threadIdx.x + stride * width];
+    }
     if (part == 0 && c < words) {
         const int local = c >> 1, kk = local / L, l = local - kk * L;
-        out[2 * ((int64_t)(slice + kk * a.nslices) * L + l) + (c & 1)] = ((quarters[0][lane] + quarters[1][lane]) + quarters[2][lane]) + quarters[3][lane];
+        out[2 * ((int64_t)(slice + kk * a.nslices) * L + l) + (c & 1)] = runs[w];
     }
 }
 
@@ -666,7 +672,10 @@ extern "C" __attribute__((visibility("default"))) ssgd_status ssgd_runtime_mc(in
         double* d_sums = a.partial + partial_words;
         hipError_t e = P <= 64 ? launch_mc<1>(a, (unsigned)blocks, lds, st) : (P <= 128 ? launch_mc<2>(a, (unsigned)blocks, lds, st) : launch_mc<4>(a, (unsigned)blocks, lds, st));
         if (e == hipSuccess) {
-            hipLaunchKernelGGL(mc_reduce_kernel, dim3((unsigned)((2 * cells_max + 63) / 64), (unsigned)nslices), dim3(256), 0, st, a, (int)groups, (int)cells_max, d_sums);
+            int width = 2;
+            while (width < 64 && width < 2 * cells_max) width *= 2;
+            hipLaunchKernelGGL(mc_reduce_kernel, dim3((unsigned)((2 * cells_max + width - 1) / width), (unsigned)nslices), dim3(kReduceThreads), 0, st,
+                               a, (int)groups, (int)cells_max, width, d_sums);
             e = hipGetLastError();
         }
         if (e == hipSuccess) e = hipMemcpyAsync(host.data(), d_sums, sizeof(double) * host.size(), hipMemcpyDeviceToHost, st);
