@@ -45,6 +45,8 @@ struct ssgd_ctx {
     size_t host_rows_words = 0;
     void* host_out = nullptr;       // pinned: kernels leave results here that a call hands to the caller (host_out_room)
     size_t host_out_bytes = 0;
+    int32_t* host_flags = nullptr;  // pinned: abort flag and one fall-back flag per replica, written by flags_kernel behind the kernels that raise them
+    bool flags_seen = false;        // host_flags holds the flags of everything queued so far (the stream has been waited for)
     DevBuf fg_work;                 // partial gradients of ssgd_full_gradient, kept from its first call on
     int device = 0;
     int64_t nw = 0;
@@ -96,6 +98,64 @@ hipError_t host_out_room(ssgd_ctx* c, size_t bytes) {
     const hipError_t e = hipHostMalloc(&c->host_out, bytes, hipHostMallocDefault);
     if (e == hipSuccess) c->host_out_bytes = bytes;
     return e;
+}
+
+// Rows of several device arrays, one behind the other, to memory that the host reads: one launch and one wait where a
+// copy command per array takes 14 us each (a trace of six arrays: 90 us with commands).
+constexpr int kMaxSegments = 6;
+struct Segments {
+    const uint32_t* src[kMaxSegments];
+    int64_t dst[kMaxSegments], words[kMaxSegments];
+    int n;
+};
+__global__ __launch_bounds__(256) void gather_segments_kernel(Segments g, uint32_t* out) {
+    const int sgm = blockIdx.y;
+    const uint32_t* src = g.src[sgm];
+    uint32_t* dst = out + g.dst[sgm];
+    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < g.words[sgm]; q += (int64_t)gridDim.x * blockDim.x) dst[q] = src[q];
+}
+constexpr size_t kGatherBytes = 4 << 20;   // above this a copy command per array is as fast
+
+// Enqueues the gather and waits for the stream; c->host_out then holds the words.
+hipError_t gather_to_host(ssgd_ctx* c, const Segments& g) {
+    int64_t most = 0, total = 0;
+    for (int i = 0; i < g.n; ++i) { most = std::max(most, g.words[i]); total = std::max(total, g.dst[i] + g.words[i]); }
+    hipError_t e = host_out_room(c, sizeof(uint32_t) * (size_t)total);
+    if (e != hipSuccess) return e;
+    const unsigned blocks = (unsigned)std::max<int64_t>(1, std::min<int64_t>(256, (most + 1023) / 1024));
+    hipLaunchKernelGGL(gather_segments_kernel, dim3(blocks, g.n), dim3(256), 0, c->stream, g, static_cast<uint32_t*>(c->host_out));
+    e = hipGetLastError();
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    return e;
+}
+
+__global__ void flags_kernel(const int32_t* abort_flag, const int32_t* fallback, int R, int32_t* out) {
+    const int q = blockIdx.x * blockDim.x + threadIdx.x;
+    if (q == 0) out[0] = *abort_flag;
+    if (fallback != nullptr && q < R) out[1 + q] = fallback[q];
+}
+
+// Waits for the stream with the flags in c->host_flags.
+hipError_t read_flags(ssgd_ctx* c) {
+    if (c->flags_seen) return hipSuccess;
+    const int32_t* fallback = c->fallback.as<int32_t>();
+    hipLaunchKernelGGL(flags_kernel, dim3((unsigned)(c->R + 255) / 256), dim3(256), 0, c->stream, c->abort_flag.as<int32_t>(), fallback, c->R, c->host_flags);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    c->flags_seen = e == hipSuccess;
+    return e;
+}
+
+// The exchange buffers of the cluster kernels as they have to be when a launch begins: counters and flags zero, every
+// exchanged word the sentinel (all ones).  One launch instead of a memset each.
+__global__ __launch_bounds__(256) void arm_exchange_kernel(uint32_t* arrive, int64_t n_arrive, uint32_t* zx, int64_t n_zx, uint32_t* dx, int64_t n_dx,
+                                                           uint32_t* fallback, int64_t n_fallback) {
+    const int64_t q0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t q = q0; q < n_arrive; q += step) arrive[q] = 0u;
+    for (int64_t q = q0; q < n_fallback; q += step) fallback[q] = 0u;
+    const uint4 ones = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
+    for (int64_t q = q0; q < n_zx / 4; q += step) reinterpret_cast<uint4*>(zx)[q] = ones;
+    for (int64_t q = q0; q < n_dx / 4; q += step) reinterpret_cast<uint4*>(dx)[q] = ones;
 }
 
 __global__ void init_workers_kernel(WorkerState ws, Dist dist, uint64_t seed, int P, int R, int K, int variant,
@@ -206,6 +266,13 @@ int chunks_for(int n_rec, int mp) {
     return n_rec * ((mp + 63) / 64);
 }
 
+void arm_exchange(ssgd_ctx* c, bool tile, bool helper) {
+    const int64_t n_zx = tile ? 3 * 1024 * (int64_t)c->R * c->G : 0, n_dx = helper ? 4 * 1024 * (int64_t)c->R : 0;
+    const unsigned blocks = (unsigned)std::max<int64_t>(1, std::min<int64_t>(1024, (n_zx + n_dx) / 4096));
+    hipLaunchKernelGGL(arm_exchange_kernel, dim3(blocks), dim3(256), 0, c->stream, c->arrive.as<uint32_t>(), (int64_t)kArriveStride * c->R, c->zx.as<uint32_t>(), n_zx,
+                       c->dx.as<uint32_t>(), n_dx, c->fallback.as<uint32_t>(), helper ? (int64_t)c->R : (int64_t)0);
+}
+
 // One launch per group of co-resident replicas; `mode` selects the kernel.
 enum LinearKernel { kGeneralKernel = 0, kTileKernel = 1, kDeferKernel = 2 };
 ssgd_status launch_steps(ssgd_ctx* c, int64_t v0, int64_t n, float* agg_out, int mode,
@@ -214,12 +281,9 @@ ssgd_status launch_steps(ssgd_ctx* c, int64_t v0, int64_t n, float* agg_out, int
     // a cluster stays on one XCD (block ids congruent modulo 8), so the resident slots count per XCD
     const int resident = tile ? c->tile_resident_groups : c->resident_groups;
     const int per_launch = mode == kDeferKernel ? c->defer_per_launch : std::max(1, 8 * ((resident / 8) / c->G));
-    HIP_OK(c, hipMemsetAsync(c->arrive.p, 0, sizeof(unsigned int) * kArriveStride * c->R, c->stream));
-    if (tile) HIP_OK(c, hipMemsetAsync(c->zx.p, 0xFF, sizeof(uint32_t) * 3 * 1024 * (size_t)c->R * c->G, c->stream));
-    if (mode == kDeferKernel) {
-        HIP_OK(c, hipMemsetAsync(c->dx.p, 0xFF, sizeof(uint32_t) * 4 * 1024 * (size_t)c->R, c->stream));
-        HIP_OK(c, hipMemsetAsync(c->fallback.p, 0, sizeof(int32_t) * (size_t)c->R, c->stream));
-    }
+    arm_exchange(c, tile, mode == kDeferKernel);
+    HIP_OK(c, hipGetLastError());
+    c->flags_seen = false;
     if (getenv("SSGD_DEBUG"))
         fprintf(stderr, "ssgd launch: v0=%lld n=%lld tile=%d resident=%d per_launch=%d R=%d\n", (long long)v0, (long long)n,
                 (int)tile, resident, per_launch, c->R);
@@ -254,14 +318,14 @@ ssgd_status launch_steps(ssgd_ctx* c, int64_t v0, int64_t n, float* agg_out, int
     if (mode == kDeferKernel) {
         // A cluster that found itself spread over XCDs has left its replica untouched: those replicas take the same
         // updates through the kernel that can exchange across XCDs.
-        std::vector<int32_t> fb((size_t)c->R);
-        HIP_OK(c, hipMemcpyAsync(fb.data(), c->fallback.p, sizeof(int32_t) * fb.size(), hipMemcpyDeviceToHost, c->stream));
-        HIP_OK(c, hipStreamSynchronize(c->stream));
+        HIP_OK(c, read_flags(c));
+        const std::vector<int32_t> fb(c->host_flags + 1, c->host_flags + 1 + c->R);
         bool any = false;
         for (int r = 0; r < c->R; ++r) any = any || fb[r] != 0;
         if (any) {
-            HIP_OK(c, hipMemsetAsync(c->arrive.p, 0, sizeof(unsigned int) * kArriveStride * c->R, c->stream));
-            HIP_OK(c, hipMemsetAsync(c->zx.p, 0xFF, sizeof(uint32_t) * 3 * 1024 * (size_t)c->R * c->G, c->stream));
+            arm_exchange(c, true, false);
+            HIP_OK(c, hipGetLastError());
+            c->flags_seen = false;
             for (int r = 0; r < c->R; ++r) {
                 if (!fb[r]) continue;
                 LinArgs a = c->lin;
@@ -337,6 +401,7 @@ ssgd_status run_updates(ssgd_ctx* c, int64_t J, float* agg_out) {
     HIP_OK(c, hipSetDevice(c->device));
     std::vector<std::pair<hipEvent_t, hipEvent_t>> events;
     c->last_ms = 0; c->last_launches = 0;
+    c->flags_seen = false;
     int64_t remaining = J;
     while (remaining > 0) {
         int64_t seg = remaining;
@@ -461,15 +526,14 @@ ssgd_status run_updates(ssgd_ctx* c, int64_t J, float* agg_out) {
             HIP_OK(c, hipGetLastError());
         }
     }
-    HIP_OK(c, hipStreamSynchronize(c->stream));
+    if (c->ada.mode != 0) c->flags_seen = false;       // the controller's kernel is behind the flags
+    HIP_OK(c, read_flags(c));
     for (auto& ev : events) {
         float ms = 0;
         if (hipEventElapsedTime(&ms, ev.first, ev.second) == hipSuccess) { c->last_ms += ms; c->last_launches += 1; }
         (void)hipEventDestroy(ev.first); (void)hipEventDestroy(ev.second);
     }
-    int32_t aborted = 0;
-    HIP_OK(c, hipMemcpy(&aborted, c->abort_flag.p, sizeof(aborted), hipMemcpyDeviceToHost));
-    if (aborted) {
+    if (c->host_flags[0] != 0) {
         c->broken = true;
         return fail(c, SSGD_EDEVICE, "cluster exchange timed out: the workgroups of a replica were not co-resident");
     }
@@ -562,6 +626,7 @@ ssgd_status ssgd_create(const ssgd_model* model, int32_t P, int32_t K, int32_t m
     }
     c->tr.Kcap = Kcap; c->tr.cap = 0;
     HIP_C(c->abort_flag.alloc(sizeof(int32_t)));
+    HIP_C(hipHostMalloc((void**)&c->host_flags, sizeof(int32_t) * (size_t)(1 + R), hipHostMallocDefault));
     HIP_C(hipMemsetAsync(c->abort_flag.p, 0, sizeof(int32_t), c->stream));
 
     if (model->kind == SSGD_MLP2) {
@@ -661,15 +726,27 @@ ssgd_status ssgd_get_trace(ssgd_ctx* c, int32_t replica, int64_t from, int64_t n
     if (replica < 0 || replica >= c->R || from < 0 || n < 0 || from + n > c->j) return fail(c, SSGD_EINVAL, "trace range out of bounds");
     if (n == 0) return SSGD_OK;
     HIP_OK(c, hipSetDevice(c->device));
-    HIP_OK(c, hipStreamSynchronize(c->stream));
     const int64_t cap = c->tr.cap, W = c->Kcap, base = (int64_t)replica * cap + from;
-    if (t) HIP_OK(c, hipMemcpy(t, c->tr.t + base, sizeof(double) * n, hipMemcpyDeviceToHost));
-    if (loss) HIP_OK(c, hipMemcpy(loss, c->tr.loss + base, sizeof(float) * n, hipMemcpyDeviceToHost));
-    if (K) HIP_OK(c, hipMemcpy(K, c->tr.K + base, sizeof(int32_t) * n, hipMemcpyDeviceToHost));
-    if (sel) HIP_OK(c, hipMemcpy(sel, c->tr.sel + base * W, sizeof(int32_t) * n * W, hipMemcpyDeviceToHost));
-    if (ordinal) HIP_OK(c, hipMemcpy(ordinal, c->tr.ord + base * W, sizeof(int32_t) * n * W, hipMemcpyDeviceToHost));
+    const void* src[kMaxSegments] = {c->tr.t + base, c->tr.loss + base, c->tr.K + base, c->tr.sel + base * W, c->tr.ord + base * W, c->tr.tau + base * W};
+    void* dst[kMaxSegments] = {t, loss, K, sel, ordinal, staleness};
+    const int64_t words[kMaxSegments] = {2 * n, n, n, n * W, n * W, n * W};
+    Segments g{};
+    int64_t total = 0;
+    for (int i = 0; i < kMaxSegments; ++i) {
+        if (!dst[i]) continue;
+        g.src[g.n] = static_cast<const uint32_t*>(src[i]); g.dst[g.n] = total; g.words[g.n] = words[i]; ++g.n;
+        total += words[i];
+    }
+    if (g.n > 0 && sizeof(uint32_t) * (size_t)total <= kGatherBytes) {
+        HIP_OK(c, gather_to_host(c, g));
+        for (int i = 0, m = 0; i < kMaxSegments; ++i)
+            if (dst[i]) { memcpy(dst[i], static_cast<uint32_t*>(c->host_out) + g.dst[m], sizeof(uint32_t) * (size_t)words[i]); ++m; }
+    } else {
+        HIP_OK(c, hipStreamSynchronize(c->stream));
+        for (int i = 0; i < kMaxSegments; ++i)
+            if (dst[i]) HIP_OK(c, hipMemcpy(dst[i], src[i], sizeof(uint32_t) * (size_t)words[i], hipMemcpyDeviceToHost));
+    }
     if (staleness) {
-        HIP_OK(c, hipMemcpy(staleness, c->tr.tau + base * W, sizeof(int32_t) * n * W, hipMemcpyDeviceToHost));
         for (int64_t q = 0; q < n; ++q)
             for (int64_t l = 0; l < W; ++l) {
                 int32_t& v = staleness[q * W + l];
@@ -683,8 +760,15 @@ ssgd_status ssgd_get_params(ssgd_ctx* c, int32_t replica, float* w_out) {
     if (!c || !w_out) return fail(c, SSGD_EINVAL, "null argument");
     if (replica < 0 || replica >= c->R) return fail(c, SSGD_EINVAL, "replica out of range");
     HIP_OK(c, hipSetDevice(c->device));
-    HIP_OK(c, hipStreamSynchronize(c->stream));
     const float* src = c->model.kind == SSGD_MLP2 ? mlp_params(c->mlp[(size_t)replica]) : c->params.as<float>() + (int64_t)replica * c->nw;
+    if (sizeof(float) * (size_t)c->nw <= kGatherBytes) {
+        Segments g{};
+        g.src[0] = reinterpret_cast<const uint32_t*>(src); g.words[0] = c->nw; g.n = 1;
+        HIP_OK(c, gather_to_host(c, g));
+        memcpy(w_out, c->host_out, sizeof(float) * (size_t)c->nw);
+        return SSGD_OK;
+    }
+    HIP_OK(c, hipStreamSynchronize(c->stream));
     HIP_OK(c, hipMemcpy(w_out, src, sizeof(float) * c->nw, hipMemcpyDeviceToHost));
     return SSGD_OK;
 }
@@ -1046,6 +1130,7 @@ void ssgd_destroy(ssgd_ctx* c) {
     if (c->side) (void)hipStreamDestroy(c->side);
     if (c->host_rows) (void)hipHostFree(c->host_rows);
     if (c->host_out) (void)hipHostFree(c->host_out);
+    if (c->host_flags) (void)hipHostFree(c->host_flags);
     DevBuf* bufs[] = {&c->table, &c->tr_t, &c->tr_loss, &c->tr_K, &c->tr_sel, &c->tr_tau, &c->tr_ord, &c->ws_finish,
                       &c->ws_tau, &c->ws_ord, &c->ws_clock, &c->ws_curK, &c->ws_winprev, &c->ws_winidx, &c->ws_F0,
                       &c->ws_intstart, &c->ws_crossed, &c->ws_ndone, &c->params, &c->park, &c->park_small, &c->zpart, &c->zx, &c->dx, &c->fallback,
