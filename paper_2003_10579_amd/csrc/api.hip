@@ -368,8 +368,8 @@ ssgd_status run_segment_linear(ssgd_ctx* c, int64_t v0, int64_t n, float* agg_ou
     a.prof = c->prof.as<unsigned long long>();
     a.agg_out = agg_out;
 
-    // The steady-state kernel runs the steps whose mini-batches fit one tile; step 0 of K-async
-    // (all P workers start) and every other shape go through the general kernel.
+    // The steady-state kernel takes a step's mini-batches in 64-row tiles.  Where every later step of K-async fits one
+    // tile, step 0 (all P workers start) goes through the general kernel, which has no list of records to follow.
     bool tile = c->nbw == 4 && c->tile_resident_groups >= c->G;
     bool defer = c->nbw == 4 && c->defer_per_launch >= 1 && c->tile_resident_groups >= c->G;
     if (const char* e = getenv("SSGD_KERNEL")) {          // diagnostics: "general" or "tile" keep the later kernels out
@@ -380,7 +380,7 @@ ssgd_status run_segment_linear(ssgd_ctx* c, int64_t v0, int64_t n, float* agg_ou
     a.v0 = v0;
     a.chunked = 0;
     if (tile || defer) {
-        if (c->variant == SSGD_K_ASYNC && v0 == 0) { head = 1; a.v0 = 1; }
+        if (c->variant == SSGD_K_ASYNC && v0 == 0 && a.mp * c->Kcap <= 64) { head = 1; a.v0 = 1; }
         a.chunked = ((c->variant == SSGD_K_SYNC || c->variant == SSGD_K_BATCH_SYNC) && a.mp * c->Kcap > 64) ? 1 : 0;
         tile = tile && linear_tile_supports(a, c->Kcap);
         defer = defer && linear_defer_supports(a);

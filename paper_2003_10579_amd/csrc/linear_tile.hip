@@ -1,8 +1,10 @@
 // Steady-state kernel of the linear models (Sec. 2.2, Eq. (2), Eq. (3)) for the common shapes:
-// at most 15 classes, rows readable 16 bytes at a time, and either every step's mini-batches
-// fit one 64-row tile (records * padded m <= 64) or the variant is synchronous, in which case
-// the rows of an iteration's K mini-batches are taken 64 at a time: every tile goes through the
-// schedule below, the gradient is summed over the tiles and the update follows the last one.
+// at most 15 classes, at least 4 columns, at most 64 contributors.  A step whose mini-batches do not
+// fit one 64-row tile takes several: the synchronous variants take the rows of an iteration's K
+// mini-batches 64 at a time, the gradient is summed over the tiles and the update follows the last
+// one; the asynchronous ones take whole records per tile, or 64-row blocks of one record.
+// (K-async of several tiles and rows of odd length took the general kernel before: P = 20, K = 5, m = 25, d = 785,
+// 10 classes, 8 replicas: 50 us per update there, 23 here.)
 // Same cluster decomposition, state layout and arithmetic as the general kernel (linear.hip),
 // which runs every other shape and may be mixed with this one launch by launch; what differs
 // is the schedule inside a step:
@@ -128,8 +130,9 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
     // (read from the arguments where it is possible at all: as a compile-time constant it led the compiler to keep
     // two tiles of gathered rows alive and spill them)
     const bool chunked = CHUNKED && a.chunked != 0;
-    // K-batch-async with mini-batches of more than 64 rows: a tile is one block of 64 rows of one record; the record's
-    // gradient is summed over its tiles in the slot of its worker
+    // Records described one by one (BATCH: K-batch-async, and K-async when a version may have more records than a tile
+    // holds), mini-batches of more than 64 rows: a tile is one block of 64 rows of one record; the record's gradient is
+    // summed over its tiles in the slot of its worker
     const int spr = (BATCH && mp > ROWS) ? (mp + ROWS - 1) / ROWS : 1;      // tiles per record
     const int mpt = (chunked || spr > 1) ? ROWS : mp;
 
@@ -150,13 +153,20 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
         const int r_of = lane / mp, s_of = lane % mp;
         // Row lw + 4 i of the tile is fetched by instruction i of this wave, one 16-byte chunk per lane.
         // The swizzle is applied on the global side: lane l fetches chunk l ^ key and writes position l.
+        // A row may start at any 4-byte address, which is all that a 16-byte buffer load asks for.  The last chunk of a row
+        // of odd length is read as the row's last four columns and moved into place on its way to LDS, zeros behind them:
+        // nothing is read past the row.
         int goff[4];
+        bool tail[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int key = (lw + 4 * q) & 15;
             const int col = col0 + 4 * (lane ^ key);
-            goff[q] = (col < d) ? col * 4 : kOutOfRange;    // past the end of the row: zeros
+            tail[q] = col < d && col + 4 > d;
+            goff[q] = (col < d) ? min(col, d - 4) * 4 : kOutOfRange;    // past the end of the row: zeros
         }
+        const int d_rem = d & 3;
+        const bool has_tail = d_rem != 0 && slice == G - 1;
         float* const my_tile = L.tile + lw * SL + lane * 4;
 
         f32x4 pref[LLOADS];
@@ -206,9 +216,17 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
                 for (int l = 0; l < K; ++l)
                     if (__builtin_amdgcn_readlane(l_tau, l) == (int32_t)ver && __builtin_amdgcn_readlane(l_sel, l) == rec_slot) fr = 1;
             if constexpr (BATCH) {
-                // Mini-batches that start at version ver: at ver = 0 every worker's first one, later the one of the
-                // worker whose push triggered update ver - 1; then, for each of the first K - 1 pushes of update ver,
-                // the next mini-batch of the pushing worker (ordinal: how many it has started at this version).
+                // Mini-batches that start at version ver: at ver = 0 every worker's first one.  Later, K-async: those of
+                // the workers that update ver - 1 consumed, all listed as restarts.
+                if (async) {
+                    h_first = (ver == 0) ? a.P : 0;
+                    nrec = (ver == 0) ? a.P : nrec;
+                    h_trig = 0; h_trig_fresh = 0;
+                    h_rw = rec_slot; h_ro = 0; h_rf = fr;
+                } else {
+                // K-batch-async: the one of the worker whose push triggered update ver - 1; then, for each of the first
+                // K - 1 pushes of update ver, the next mini-batch of the pushing worker (ordinal: how many it has started
+                // at this version).
                 const int Kprev = __popcll(__ballot(cur_sel >= 0));
                 h_first = (ver == 0) ? a.P : 1;
                 nrec = h_first + K - 1;
@@ -222,6 +240,7 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
                               co = __builtin_amdgcn_readlane(l_ord, q);
                     if (ct == (int32_t)ver && cs == h_rw && co == h_ro) h_rf = 1;
                     if (ct == (int32_t)ver && cs == h_trig && co == 0) h_trig_fresh = 1;
+                }
                 }
                 h_csel = l_sel; h_ctau = l_tau; h_cord = l_ord;
             }
@@ -316,6 +335,15 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
         };
         // flags: bit 0 last tile of its update, bit 1 first tile of its update
         auto publish = [&](int flags) {
+            if (has_tail) {
+#pragma unroll
+                for (int i = 0; i < LLOADS; ++i) {
+                    const f32x4 r = pref[i];
+                    const f32x4 moved = {d_rem == 1 ? r.w : (d_rem == 2 ? r.z : r.y), d_rem == 1 ? 0.0f : (d_rem == 2 ? r.w : r.z),
+                                         d_rem == 3 ? r.w : 0.0f, 0.0f};
+                    pref[i] = tail[i & 3] ? moved : r;
+                }
+            }
 #pragma unroll
             for (int i = 0; i < LLOADS; ++i) *reinterpret_cast<f32x4*>(my_tile + 4 * i * SL) = pref[i];
             if (lw == 0) {
@@ -385,7 +413,7 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
 
         lds_barrier();                               // the compute waves have set up the control words
         if (L.ctl[0] != 0) return;
-        if ((async || (BATCH && a.v0 >= 1)) && lane < Kcap) cur_sel = tr_sel[(a.v0 - 1) * Kcap + lane];   // v0 >= 1 for K-async
+        if ((async || BATCH) && a.v0 >= 1 && lane < Kcap) cur_sel = tr_sel[(a.v0 - 1) * Kcap + lane];
         issue_lists(a.v0);
         take_lists(a.v0, a.nsteps > 1);
         make_tile(a.v0, 0);
@@ -516,7 +544,7 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
         const int n_stale = __builtin_amdgcn_readfirstlane(ctl4.z);
         const int tile_flags = __builtin_amdgcn_readfirstlane(ctl4.w);
         last_tile = (tile_flags & 1) != 0;
-        const int par = (int)(step & 1);
+        const int par = (int)(n_fenced & 1u);               // buffer of a fenced exchange: a step may have several of them
         // An opaque zero: addresses built from it are recomputed every step instead of being kept in
         // registers across the whole loop (they would be spilled to scratch memory).
         int opq = 0;
@@ -982,13 +1010,16 @@ hipError_t launch_w(const LinArgs& a, size_t lds, hipStream_t s) {
     return hipGetLastError();
 }
 
+// K-async whose versions may have more records than a tile holds; version 0, at which all P workers start, is one.
+bool records_one_by_one(const LinArgs& a) { return a.variant == kBatchAsync || (a.variant == kAsync && (a.v0 < 1 || a.mp * a.tr.Kcap > ROWS)); }
+
 // WHOLE: every record is a whole number of 32-row blocks, so the gradient contraction is fully unrolled;
-// CHUNKED: an iteration spans several tiles; BATCH: K-batch-async record lists
+// CHUNKED: an iteration of a synchronous variant spans several tiles; BATCH: records described one by one
 template <int KIND, bool PROF>
 hipError_t launch_k(const LinArgs& a, size_t lds, hipStream_t s) {
     if (a.chunked) return launch_w<KIND, PROF, true, true, false>(a, lds, s);      // tiles of one 64-row record
     const bool whole = a.mp == 32 || a.mp == 64;
-    if (a.variant == kBatchAsync)        // (no phase profile for this variant)
+    if (records_one_by_one(a))           // (no phase profile for this form)
         return whole ? launch_w<KIND, false, true, false, true>(a, lds, s) : launch_w<KIND, false, false, false, true>(a, lds, s);
     return whole ? launch_w<KIND, PROF, true, false, false>(a, lds, s) : launch_w<KIND, PROF, false, false, false>(a, lds, s);
 }
@@ -1001,15 +1032,12 @@ size_t linear_tile_lds_bytes(int C, int S, int Kcap) {
 }
 
 bool linear_tile_supports(const LinArgs& a, int max_records) {
-    if (a.C > 15 || (a.d % 4) != 0 || a.tr.Kcap > KC || max_records > KC) return false;
-    if (a.mp * max_records > ROWS && !a.chunked && a.variant != kBatchAsync) return false;
-    if (a.chunked && a.variant == kAsync) return false;
+    // the consume list and the restarts of an update sit in one lane each; the last chunk of a row is read as its last four columns
+    if (a.C > 15 || a.d < 4 || a.tr.Kcap > KC || max_records > KC) return false;
+    const bool synchronous = a.variant == kSync || a.variant == kBatchSync;
+    if (synchronous && a.mp * max_records > ROWS && !a.chunked) return false;
+    if (!synchronous && a.chunked) return false;
     if ((uint64_t)a.N * (uint64_t)a.d * 4u >= (1ull << 32)) return false;   // one buffer descriptor spans the sample matrix
-    if (a.variant == kBatchAsync) {
-        // whole records per tile, or tiles of one record; the consume list and the restarts of an update sit in one lane each
-        return linear_tile_lds_bytes(a.C, a.S, a.tr.Kcap) <= 160 * 1024;
-    }
-    if (a.variant == kAsync && a.v0 < 1) return false;    // step 0 of K-async starts all P workers
     return linear_tile_lds_bytes(a.C, a.S, a.tr.Kcap) <= 160 * 1024;
 }
 

@@ -849,6 +849,30 @@ def test_iterations_of_several_tiles(ssgd, oracle, torch_cuda, kind, variant, P,
               classes=classes, check_steps=20)
 
 
+@pytest.mark.parametrize("kind,variant,P,K,m,d,classes,fenced", [
+    ("softmax", "k_async", 20, 5, 25, 785, 10, False),   # two padded 28-row records per tile, three tiles; one column in the last chunk
+    ("softmax", "k_async", 12, 6, 32, 258, 4, False),    # whole 32-row records; two columns in a slice of their own
+    ("lsq", "k_async", 9, 3, 72, 515, 1, False),         # a full tile and one of 8 rows per record; three columns in the last chunk
+    ("softmax", "k_async", 7, 7, 64, 260, 15, False),    # every worker waited for: no gradient is ever parked
+    ("lsq", "k_async", 70, 64, 5, 257, 1, False),        # 64 contributors, the most a wave's lanes hold; 70 records at version 0
+    ("softmax", "k_async", 6, 4, 40, 132, 3, True),      # tiles exchanged through the counter: buffers alternate from tile to tile
+    ("softmax", "k_sync", 5, 4, 48, 519, 10, True),      # the same for an iteration of several tiles
+    ("lsq", "k_sync", 4, 2, 16, 131, 1, False),          # one tile, one slice, odd row length
+    ("lsq", "k_async", 4, 2, 8, 129, 1, False),          # one tile, the row's last column alone in its chunk
+])
+def test_several_tiles_and_odd_row_lengths(ssgd, oracle, torch_cuda, monkeypatch, kind, variant, P, K, m, d, classes, fenced):
+    """K-async versions with more records than a tile holds, and rows of any length from four columns, in the
+    steady-state kernel."""
+    if fenced:
+        monkeypatch.setenv("SSGD_EXCHANGE", "fenced")
+    if kind == "lsq":
+        X, y, _ = synth.lsq_data(700, d, 8)
+    else:
+        X, y = synth.mixture_data(700, d, classes, seed=8)
+    _run_pair(ssgd, oracle, torch_cuda, kind, X, y, P, K, m, variant, ("shifted_exp", 0.5, 1.0), 0.01, 80, seed=9,
+              classes=classes, check_steps=30)
+
+
 def test_adasync_ksync_rule_with_growing_tile_count(ssgd, oracle, torch_cuda):
     """K-sync under the paper's rule for K (Appendix D): K grows from 2 to 16 during the run, so the iterations go
     from one tile to two; trace and parameters against the oracle."""
