@@ -352,6 +352,7 @@ ssgd_status run_segment_linear(ssgd_ctx* c, int64_t v0, int64_t n, float* agg_ou
     a.X = c->model.X; a.y = c->model.y; a.N = (uint32_t)c->model.N;
     a.lr = (float)c->lr; a.seed = c->seed;
     a.G = c->G; a.S = c->S;
+    a.park_threads = 64 * c->nbw;
     a.tr = c->tr;
     a.params = c->params.as<float>(); a.park = c->park.as<float>(); a.park_small = c->park_small.as<float>();
     a.zpart = c->zpart.as<float>(); a.maxrows = c->maxrows;
@@ -370,7 +371,8 @@ ssgd_status run_segment_linear(ssgd_ctx* c, int64_t v0, int64_t n, float* agg_ou
 
     // The steady-state kernel takes a step's mini-batches in 64-row tiles.  Where every later step of K-async fits one
     // tile, step 0 (all P workers start) goes through the general kernel, which has no list of records to follow.
-    bool tile = c->nbw == 4 && c->tile_resident_groups >= c->G;
+    // One slice (d <= 256) goes through it whatever its width.
+    bool tile = (c->nbw == 4 || c->G == 1) && c->tile_resident_groups >= c->G;
     bool defer = c->nbw == 4 && c->defer_per_launch >= 1 && c->tile_resident_groups >= c->G;
     if (const char* e = getenv("SSGD_KERNEL")) {          // diagnostics: "general" or "tile" keep the later kernels out
         tile = tile && strcmp(e, "general") != 0;
@@ -659,9 +661,9 @@ ssgd_status ssgd_create(const ssgd_model* model, int32_t P, int32_t K, int32_t m
         c->resident_groups = linear_max_resident_groups(c->nbw, c->lds_bytes);
         if (c->resident_groups < c->G) return bail(SSGD_EINVAL, "d is too large for a co-resident cluster of workgroups");
         { hipDeviceProp_t prop; HIP_C(hipGetDeviceProperties(&prop, c->device)); c->cu_count = prop.multiProcessorCount; }
-        if (c->nbw == 4 && C <= 15 && linear_tile_lds_bytes(C, c->S, Kcap) <= 160 * 1024)
+        if ((c->nbw == 4 || c->G == 1) && C <= 15 && linear_tile_lds_bytes(C, c->S, Kcap) <= 160 * 1024)
             c->tile_resident_groups = linear_tile_resident_groups(linear_tile_lds_bytes(C, c->S, Kcap));
-        if (c->nbw == 4 && C <= 15 && variant == SSGD_K_ASYNC && c->S <= 8 && linear_defer_lds_bytes(C, c->S) <= 160 * 1024)
+        if (c->nbw == 4 && c->G > 1 && C <= 15 && variant == SSGD_K_ASYNC && c->S <= 8 && linear_defer_lds_bytes(C, c->S) <= 160 * 1024)
             c->defer_per_launch = linear_defer_replicas_per_launch(c->G, c->cu_count);
         HIP_C(c->params.alloc(sizeof(float) * R * c->nw));
         HIP_C(hipMemsetAsync(c->params.p, 0, sizeof(float) * R * c->nw, c->stream));

@@ -82,6 +82,7 @@ struct LinArgs {
     int64_t v0, nsteps;
     float* params;           // [R][nw], standard layout
     float* park;             // [R][G][S][4][threads][4] parked per-slot gradients: class own_cls + vv, 4 columns of the owner thread
+    int32_t park_threads;    // threads of the owner layout above: 64 per 64-column block of a workgroup
     float* park_small;       // [R][G][S][17]: bias gradient (16) and mean loss (1) of every slot
     float* zpart;            // [R][2][G][maxrows][16] partial logits exchanged inside a cluster
     int32_t maxrows;

@@ -98,7 +98,12 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-template <int KIND, bool PROF, bool WHOLE, bool CHUNKED, bool BATCH>
+// ONE: the cluster is one workgroup (d <= 256).  Its partial logits are the logits: they change lanes inside the wave
+// instead of going out to the exchange, and only the 64-column blocks that exist are loaded, written and contracted.
+// Bound by the chain of one step, TU -> logits -> delta -> gradient -> update, beside the chain lists -> sample ids ->
+// gather of the next tile.  (Least squares, d = 64, two mini-batches of 16, one replica: 3.0 us per update where the
+// exchange through memory of the general kernel takes 8.5.)
+template <int KIND, bool PROF, bool WHOLE, bool CHUNKED, bool BATCH, bool ONE>
 __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
     // consecutive block ids go to different XCDs: all slices of one cluster take block ids that
     // are congruent modulo 8 and share one L2
@@ -135,6 +140,7 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
     // summed over its tiles in the slot of its worker
     const int spr = (BATCH && mp > ROWS) ? (mp + ROWS - 1) / ROWS : 1;      // tiles per record
     const int mpt = (chunked || spr > 1) ? ROWS : mp;
+    const int nblk = ONE ? (d + 63) >> 6 : SL / 64;      // 64-column blocks in use
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int kc = Kcap > 32 ? KC : 32;      // places of the lists in LDS
@@ -325,12 +331,14 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
             // vector-memory operations of this wave until the tile is published.
             asm volatile("" : "+v"(row_id) : : "memory");
             __builtin_amdgcn_sched_barrier(0);
+            if (!ONE || lane < 16 * nblk) {
 #pragma unroll
             for (int i = 0; i < LLOADS; ++i) {
                 // rows without a sample read row 0; their delta is zero
                 uint32_t id = (uint32_t)__builtin_amdgcn_readlane((int)row_id, lw + 4 * i);
                 id = (id == kNoRow) ? 0u : id;
                 pref[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, goff[i & 3], (int)(id * row_bytes), kStream));
+            }
             }
         };
         // flags: bit 0 last tile of its update, bit 1 first tile of its update
@@ -344,8 +352,10 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
                     pref[i] = tail[i & 3] ? moved : r;
                 }
             }
+            if (!ONE || lane < 16 * nblk) {
 #pragma unroll
-            for (int i = 0; i < LLOADS; ++i) *reinterpret_cast<f32x4*>(my_tile + 4 * i * SL) = pref[i];
+                for (int i = 0; i < LLOADS; ++i) *reinterpret_cast<f32x4*>(my_tile + 4 * i * SL) = pref[i];
+            }
             if (lw == 0) {
                 L.rowid[lane] = row_id; L.ylab[lane] = row_lab;
                 if (lane == 0) { L.ctl[4] = n_K; L.ctl[5] = n_nrec; L.ctl[6] = n_nstale; L.ctl[7] = flags; }
@@ -450,7 +460,8 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
     // ================================= compute waves =================================
     const int64_t nw = (KIND == kLsq) ? d : (int64_t)C * d + C;
     float* params = a.params + (int64_t)rep * nw;
-    float* park = a.park + ((int64_t)rep * G + slice) * S * 16 * NTC;
+    const int nt = ONE ? a.park_threads : NTC;            // threads in the layout of the parked gradients
+    float* park = a.park + ((int64_t)rep * G + slice) * S * 16 * nt;
     float* small_g = a.park_small + ((int64_t)rep * G + slice) * S * 17;
     float* zpart = a.zpart + (int64_t)rep * 2 * G * a.maxrows * 16;
     unsigned int* arrive = a.arrive + kArriveStride * rep;   // fenced exchanges; word kArriveFast: shared-L2 exchanges
@@ -490,11 +501,11 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
     // shared-L2 exchange: three buffers of G x 64 x 16 words used in turn; a word is the sentinel until written
     const __amdgpu_buffer_rsrc_t ersrc = make_rsrc(a.zx + (int64_t)rep * 3 * G * 1024, (uint32_t)(3u * G * 4096u));
     constexpr uint32_t kSentinel = 0xFFFFFFFFu;
-    // parked gradients of this workgroup: class own_cls + vv of slot s, 4 columns: 16 bytes at ((s*4 + vv)*NTC + tid)*16
-    const __amdgpu_buffer_rsrc_t prsrc = make_rsrc(park, (uint32_t)S * 16u * NTC * 4u);
+    // parked gradients of this workgroup: class own_cls + vv of slot s, 4 columns: 16 bytes at ((s*4 + vv)*nt + tid)*16
+    const __amdgpu_buffer_rsrc_t prsrc = make_rsrc(park, (uint32_t)S * 16u * nt * 4u);
     int pk_off[4];
 #pragma unroll
-    for (int vv = 0; vv < 4; ++vv) pk_off[vv] = (own_cls + vv < C) ? (vv * NTC + tid) * 16 : kOutOfRange;
+    for (int vv = 0; vv < 4; ++vv) pk_off[vv] = (own_cls + vv < C && (!ONE || tid < nt)) ? (vv * nt + tid) * 16 : kOutOfRange;
     // forward: rows 16 wave .. 16 wave + 15; row / class index of this lane in the MFMA operands
     const int f_row = 16 * wave + (lane & 15);
     // lanes of classes that do not exist read the last class: their logits are never used
@@ -550,28 +561,58 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
         int opq = 0;
         asm volatile("" : "+s"(opq));
 
+        f32x4 own_z = {0.f, 0.f, 0.f, 0.f};       // ONE: logits of row z_row
         // ---- partial logits of rows 16 wave ..: D[class][row] += W[class][k] X[row][k] over this slice;
         //      the operands of the next k-block are read from LDS before the MFMAs of this one are issued
         {
             f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-            f32x4 wv = *reinterpret_cast<const f32x4*>(f_wa[0]);
-            f32x4 xv = *reinterpret_cast<const f32x4*>(f_xa[0]);
+            if constexpr (ONE) {
+                // the 64-column blocks in use; the four operand pairs of a block are read together
+                f32x4 wv[4], xv[4];
 #pragma unroll
-            for (int s = 0; s < SL / 16; ++s) {
-                f32x4 wn = wv, xn = xv;
-                if (s + 1 < SL / 16) {
-                    wn = *reinterpret_cast<const f32x4*>(f_wa[(s + 1) & 3] + ((s + 1) >> 2) * 64);
-                    xn = *reinterpret_cast<const f32x4*>(f_xa[(s + 1) & 3] + ((s + 1) >> 2) * 64);
+                for (int q = 0; q < 4; ++q) {
+                    wv[q] = *reinterpret_cast<const f32x4*>(f_wa[q]);
+                    xv[q] = *reinterpret_cast<const f32x4*>(f_xa[q]);
                 }
-                __builtin_amdgcn_sched_barrier(0);   // keep the reads ahead of the MFMAs
-                acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.x, xv.x, acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.y, xv.y, acc1, 0, 0, 0);
-                acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.z, xv.z, acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.w, xv.w, acc1, 0, 0, 0);
-                wv = wn; xv = xn;
+                for (int b = 0; b < nblk; ++b) {
+                    const int nx = min(b + 1, nblk - 1) * 64;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const f32x4 w1 = *reinterpret_cast<const f32x4*>(f_wa[q] + nx), x1 = *reinterpret_cast<const f32x4*>(f_xa[q] + nx);
+                        acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[q].x, xv[q].x, acc0, 0, 0, 0);
+                        acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[q].y, xv[q].y, acc1, 0, 0, 0);
+                        acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[q].z, xv[q].z, acc0, 0, 0, 0);
+                        acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[q].w, xv[q].w, acc1, 0, 0, 0);
+                        wv[q] = w1; xv[q] = x1;
+                    }
+                }
+            } else {
+                f32x4 wv = *reinterpret_cast<const f32x4*>(f_wa[0]);
+                f32x4 xv = *reinterpret_cast<const f32x4*>(f_xa[0]);
+#pragma unroll
+                for (int s = 0; s < SL / 16; ++s) {
+                    f32x4 wn = wv, xn = xv;
+                    if (s + 1 < SL / 16) {
+                        wn = *reinterpret_cast<const f32x4*>(f_wa[(s + 1) & 3] + ((s + 1) >> 2) * 64);
+                        xn = *reinterpret_cast<const f32x4*>(f_xa[(s + 1) & 3] + ((s + 1) >> 2) * 64);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);   // keep the reads ahead of the MFMAs
+                    acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.x, xv.x, acc0, 0, 0, 0);
+                    acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.y, xv.y, acc1, 0, 0, 0);
+                    acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.z, xv.z, acc0, 0, 0, 0);
+                    acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.w, xv.w, acc1, 0, 0, 0);
+                    wv = wn; xv = xn;
+                }
             }
             const f32x4 out = acc0 + acc1;   // classes 4*(lane/16)+0..3 of row f_row
             mark(8);
+            if constexpr (ONE) {
+                // thread tid takes class quad tid % 4 of row tid / 4, a row of this wave
+                const int from = ((lane & 3) * 16 + (lane >> 2)) * 4;
+#pragma unroll
+                for (int c = 0; c < (KIND == kLsq ? 1 : 4); ++c)
+                    own_z[c] = __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(out[c])));
+            } else
             // 16-byte buffer stores carry their whole offset in the vector register: with the scalar offset in a
             // register, such a store has lost data here when the next instruction rewrote its source registers
             if (fast) {
@@ -590,7 +631,7 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
         //      while the exchange stores are on their way
         auto park_load = [&](int slot, f32x4 (&pv)[4]) {
             // classes that do not exist are out of range and read as zero
-            const int soff = __builtin_amdgcn_readfirstlane(slot) * 16 * NTC * 4;
+            const int soff = __builtin_amdgcn_readfirstlane(slot) * 16 * nt * 4;
 #pragma unroll
             for (int vv = 0; vv < 4; ++vv)
                 pv[vv] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(prsrc, pk_off[vv], soff, 0));
@@ -604,7 +645,7 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
         // ---- arrival: this wave's stores are in the L2 (shared-L2 mode) or released to the device
         // ---- arrival.  Shared-L2 mode needs none: the readers poll the data words themselves.  Otherwise the
         //      wave's stores are released to the device and counted.
-        if (!fast && lane == 0) __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        if (!ONE && !fast && lane == 0) __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         mark(1);
 
         if ((tile_flags & 2) != 0) {
@@ -620,7 +661,7 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
 
         // ---- wave 0 polls the counter in the L2 (all 4 G compute waves of the cluster have arrived) and
         //      relays the result through an LDS word, which the other waves poll
-        if (!fast) {
+        if (!ONE && !fast) {
             const uint32_t target = (n_fenced + 1u) * (uint32_t)(4 * G);
             const int want = (int)(n_fenced + 1u);
             if (wave == 0) {
@@ -663,7 +704,9 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
         // ---- full logits of row z_row (sum of the G partials in slice order), then residual / softmax
         {
             f32x4 zz = {0.f, 0.f, 0.f, 0.f};
-            if (fast) {
+            if constexpr (ONE) {
+                zz = own_z;
+            } else if (fast) {
                 // Poll the partial logits themselves: a batch of slices has arrived for this wave when none of
                 // the words its lanes need is the sentinel, i.e. when the largest word read is not all ones.
                 // A round re-reads the whole batch; the slices are added in order once it is complete.
@@ -777,6 +820,8 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
         // ---- per record: the gradient slice delta^T X, in groups of four k-steps (16 rows); the operands
         //      of the next group are read from LDS before the MFMAs of this one are issued
         {
+            const bool has_cols = !ONE || wave < nblk;      // a wave without columns contracts nothing
+            const int n_own = has_cols ? n_rec : 0;
             const int kpr = mpt >> 2;              // k-steps per record
             const int ngrp = (kpr + 3) >> 2;       // groups per record
             const int b_lo = lane >> 4, b_cls = lane & 15;
@@ -812,7 +857,7 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
                     // by an earlier update or with the first tile of this one): later blocks add what is there, and
                     // only the last one goes to the aggregate if the update consumes the record itself.
                     if (((word >> 18) & 1) != 0) {
-                        const int soff = (word & 0xFFFF) * 16 * NTC * 4;
+                        const int soff = (word & 0xFFFF) * 16 * nt * 4;
 #pragma unroll
                         for (int vv = 0; vv < 4; ++vv) {
                             const f32x4 pv = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(prsrc, pk_off[vv], soff, 0));
@@ -828,7 +873,7 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
 #pragma unroll
                         for (int c = 0; c < 4; ++c) gsum[vv * 4 + c] += acc[c][vv];
                 } else {
-                    const int soff = (word & 0xFFFF) * 16 * NTC * 4;
+                    const int soff = (word & 0xFFFF) * 16 * nt * 4;
 #pragma unroll
                     for (int vv = 0; vv < 4; ++vv) {
                         const f32x4 gv = {acc[0][vv], acc[1][vv], acc[2][vv], acc[3][vv]};
@@ -876,7 +921,7 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
 #pragma unroll
                             for (int c = 0; c < 4; ++c) gsum[vv * 4 + c] += acc[c][vv];
                     } else {
-                        const int soff = (word & 0xFFFF) * 16 * NTC * 4;
+                        const int soff = (word & 0xFFFF) * 16 * nt * 4;
 #pragma unroll
                         for (int vv = 0; vv < 4; ++vv) {
                             const f32x4 gv = {acc[0][vv], acc[1][vv], acc[2][vv], acc[3][vv]};
@@ -887,7 +932,7 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
                 };
                 float da[2], db[2];
                 f32x4 xa[2], xb[2];
-                const int H = n_rec * (mpt >> 3);         // half-groups in the tile: 0, 4 or 8
+                const int H = has_cols ? n_rec * (mpt >> 3) : 0;         // half-groups in the tile: 0, 4 or 8
                 if (H > 0) {
                     fetch(0, da, xa);
                     fetch(1, db, xb);
@@ -926,15 +971,15 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
                 float dv[4];
                 f32x4 xv[4];
                 int r = opq, g = 0;
-                if (n_rec > 0) load_group(r, 0, dv, xv);
-                while (r < n_rec) {
+                if (n_own > 0) load_group(r, 0, dv, xv);
+                while (r < n_own) {
                     int rn = r, gn = g + 1;
                     if (gn == ngrp) { gn = 0; rn = r + 1; }
                     float dn[4];
                     f32x4 xn[4];
     #pragma unroll
                     for (int u = 0; u < 4; ++u) { dn[u] = dv[u]; xn[u] = xv[u]; }
-                    if (rn < n_rec) load_group(rn, gn, dn, xn);
+                    if (rn < n_own) load_group(rn, gn, dn, xn);
                     __builtin_amdgcn_sched_barrier(0);   // keep the reads ahead of the MFMAs
                     contract(g, dv, xv);
                     if (rn != r) finish(r);
@@ -999,15 +1044,21 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
     for (int q = tid; q < S * 17; q += NTC) small_g[q] = L.small[q];
 }
 
-template <int KIND, bool PROF, bool WHOLE, bool CHUNKED, bool BATCH>
-hipError_t launch_w(const LinArgs& a, size_t lds, hipStream_t s) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(linear_tile_kernel<KIND, PROF, WHOLE, CHUNKED, BATCH>),
+template <int KIND, bool PROF, bool WHOLE, bool CHUNKED, bool BATCH, bool ONE>
+hipError_t launch_o(const LinArgs& a, size_t lds, hipStream_t s) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(linear_tile_kernel<KIND, PROF, WHOLE, CHUNKED, BATCH, ONE>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     const int groups = (a.replicas + 7) / 8;
     const int blocks = a.pair_cus > 0 ? 8 * a.pair_cus * a.pair_layers : groups * 8 * a.G;
-    hipLaunchKernelGGL((linear_tile_kernel<KIND, PROF, WHOLE, CHUNKED, BATCH>), dim3(blocks), dim3(512), lds, s, a);
+    hipLaunchKernelGGL((linear_tile_kernel<KIND, PROF, WHOLE, CHUNKED, BATCH, ONE>), dim3(blocks), dim3(512), lds, s, a);
     return hipGetLastError();
+}
+
+template <int KIND, bool PROF, bool WHOLE, bool CHUNKED, bool BATCH>
+hipError_t launch_w(const LinArgs& a, size_t lds, hipStream_t s) {
+    // (no phase profile for one workgroup)
+    return a.G == 1 ? launch_o<KIND, false, WHOLE, CHUNKED, BATCH, true>(a, lds, s) : launch_o<KIND, PROF, WHOLE, CHUNKED, BATCH, false>(a, lds, s);
 }
 
 // K-async whose versions may have more records than a tile holds; version 0, at which all P workers start, is one.
@@ -1045,9 +1096,9 @@ int linear_tile_resident_groups(size_t lds_bytes) {
     int dev = 0, per_cu = 0;
     hipDeviceProp_t prop;
     if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(linear_tile_kernel<kSoftmax, false, false, false, false>),
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(linear_tile_kernel<kSoftmax, false, false, false, false, false>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, linear_tile_kernel<kSoftmax, false, false, false, false>, 512, lds_bytes) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, linear_tile_kernel<kSoftmax, false, false, false, false, false>, 512, lds_bytes) != hipSuccess) return 0;
     return per_cu * prop.multiProcessorCount;
 }
 

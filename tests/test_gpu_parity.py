@@ -873,6 +873,41 @@ def test_several_tiles_and_odd_row_lengths(ssgd, oracle, torch_cuda, monkeypatch
               classes=classes, check_steps=30)
 
 
+@pytest.mark.parametrize("kind,variant,P,K,m,d,classes", [
+    ("lsq", "k_async", 8, 2, 32, 256, 1),            # the widest single slice, whole records
+    ("softmax", "k_async", 5, 3, 20, 65, 15),        # second 64-column block one column wide; 60 of 64 rows
+    ("softmax", "k_async", 9, 4, 72, 190, 4),        # several tiles, records of two
+    ("softmax", "k_sync", 4, 3, 64, 128, 10),        # three tiles per iteration, two column blocks
+    ("lsq", "k_batch_sync", 3, 5, 12, 4, 1),         # four columns
+    ("softmax", "k_batch_async", 6, 3, 16, 192, 7),
+    ("softmax", "k_async", 3, 2, 8, 5, 2),           # the smallest odd row
+])
+def test_one_slice(ssgd, oracle, torch_cuda, monkeypatch, kind, variant, P, K, m, d, classes):
+    """Models of one slice: logits stay in the workgroup, only the column blocks that exist are worked on.  The layout of
+    the state is that of the general kernel, which goes on from it."""
+    if kind == "lsq":
+        X, y, _ = synth.lsq_data(700, d, 8)
+    else:
+        X, y = synth.mixture_data(700, d, classes, seed=8)
+    _run_pair(ssgd, oracle, torch_cuda, kind, X, y, P, K, m, variant, ("shifted_exp", 0.5, 1.0), 0.01, 80, seed=9,
+              classes=classes, check_steps=30)
+    if variant != "k_async":
+        return
+    Xd, yd = torch_cuda.from_numpy(X).cuda(), torch_cuda.from_numpy(y).cuda()
+    gd, od = dist_pair(ssgd, oracle, ("exp", 1.0))
+    ctx = ssgd.Context(kind, Xd, yd, P, K, m, variant, gd, 0.01, seed=3, classes=classes)
+    orc = oracle.Trainer(oracle.Model(kind, X, y, classes=classes), P, K, m, variant, od, 0.01, seed=3)
+    for kernel in (None, "general", None):
+        if kernel:
+            monkeypatch.setenv("SSGD_KERNEL", kernel)
+        else:
+            monkeypatch.delenv("SSGD_KERNEL", raising=False)
+        ctx.run(15)
+    orc.run(45)
+    assert_trace_equal(ctx.trace(), orc.trace())
+    assert rel(ctx.params(), orc.params()) <= FP32_PARAM_TOL
+
+
 def test_adasync_ksync_rule_with_growing_tile_count(ssgd, oracle, torch_cuda):
     """K-sync under the paper's rule for K (Appendix D): K grows from 2 to 16 during the run, so the iterations go
     from one tile to two; trace and parameters against the oracle."""
