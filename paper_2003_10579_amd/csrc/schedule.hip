@@ -65,6 +65,91 @@ __device__ __forceinline__ Best local_min(const double (&key)[NQ], uint32_t skip
     return b;
 }
 
+// Update j of a synchronous variant (K-sync, K-batch-sync): every worker starts a fresh mini-batch at t_j with w_j, so
+// the contributors do not depend on earlier updates.  One wavefront; writes the lists, returns t_{j+1} - t_j.
+template <int NQ, class Draw>
+__device__ __forceinline__ double sync_update(const Draw& draw_delay, bool batch, int P, int K, int width, int lane, int64_t j,
+                                              int32_t* sel, int32_t* tau, int32_t* order) {
+    const uint32_t ver = (uint32_t)j;
+    double key[NQ];
+    int32_t ord[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const int w = lane + 64 * q;
+        ord[q] = 0;
+        key[q] = (w < P) ? (double)draw_delay(w, 0, ver) : 0.0;
+    }
+    uint32_t taken = 0;
+    double last = 0.0;
+    for (int l = 0; l < K; ++l) {
+        const Best b = wave_min(local_min(key, taken, lane, P), width);
+        last = b.key;
+        if ((b.id & 63) == lane) {
+            const int q = b.id >> 6;
+#pragma unroll
+            for (int qq = 0; qq < NQ; ++qq) {
+                if (qq != q) continue;
+                sel[l] = b.id; tau[l] = (int32_t)j; order[l] = ord[qq];
+                if (!batch) {
+                    taken |= 1u << qq;
+                } else {
+                    // K-batch-sync: the worker starts its next mini-batch at the same w_j
+                    ord[qq] += 1;
+                    if (l + 1 < K) key[qq] = key[qq] + (double)draw_delay(b.id, ord[qq], ver);
+                }
+            }
+        }
+    }
+    return last;
+}
+
+// The updates of a synchronous segment side by side, one wavefront each; the time between updates is left in the trace
+// for sync_clock_kernel to add up.  (One wavefront per replica took them one after the other, K argmin rounds of 0.4 us
+// each; that stays for segments so short that a second launch, about 5 us, costs more.)
+constexpr int kSyncWaves = 4;
+template <int NQ, bool TABLE>
+__global__ __launch_bounds__(64 * kSyncWaves) void sync_schedule_kernel(SchedArgs a) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int64_t q = (int64_t)blockIdx.x * kSyncWaves + wave;
+    if (q >= a.count) return;
+    const int rep = a.replica0 + blockIdx.y, P = a.P, Kcap = a.tr.Kcap;
+    const int64_t row = (int64_t)rep * a.tr.cap + a.j0 + q;
+    auto draw_delay = [&](uint32_t worker, uint32_t ordinal, uint32_t version) -> float {
+        if constexpr (TABLE) return delay(a.dist, a.seed, kDelay, 0, rep, P, a.table_ord, worker, ordinal, version);
+        else return delay_from_bits(a.dist, draw(a.seed, kDelay, 0, rep, worker, ordinal, version).x);
+    };
+    int width = 1;
+    while (width < P && width < 64) width <<= 1;
+    const int K = a.ws.curK[rep];
+    int32_t *sel = a.tr.sel + row * Kcap, *tau = a.tr.tau + row * Kcap, *ord = a.tr.ord + row * Kcap;
+    for (int l = K + lane; l < Kcap; l += 64) { sel[l] = -1; tau[l] = -1; ord[l] = -1; }
+    const double dt = sync_update<NQ>(draw_delay, a.variant == kBatchSync, P, K, width, lane, a.j0 + q, sel, tau, ord);
+    if (lane == 0) { a.tr.t[row] = dt; a.tr.K[row] = K; }
+}
+
+// Clock of a synchronous segment: t_{j+1} = t_j + the difference left in the trace, in the order of the updates.
+__global__ __launch_bounds__(64) void sync_clock_kernel(SchedArgs a) {
+    const int lane = threadIdx.x, rep = a.replica0 + blockIdx.x;
+    double* t = a.tr.t + (int64_t)rep * a.tr.cap + a.j0;
+    double clock = a.ws.clock[rep];
+    double next = lane < a.count ? t[lane] : 0.0;
+    for (int64_t base = 0; base < a.count; base += 64) {
+        const long long bits = __double_as_longlong(next);
+        double mine = 0.0;
+        next = base + 64 + lane < a.count ? t[base + 64 + lane] : 0.0;
+#pragma unroll
+        for (int l = 0; l < 64; ++l) {         // past the end: + 0
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)bits, l);
+            const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((unsigned long long)bits >> 32), l);
+            clock = clock + __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+            mine = lane == l ? clock : mine;
+        }
+        if (base + lane < a.count) t[base + lane] = mine;
+    }
+    if (lane == 0) { a.ws.clock[rep] = clock; a.ws.n_done[rep] = a.count; a.ws.crossed[rep] = 0; }
+}
+
 // NQ: workers per lane (1 while P <= 64).  TABLE: delays come from a table in memory; kept out of the common
 // instantiation, whose loop then holds no load and never waits for its own trace stores.
 template <int NQ, bool TABLE>
@@ -210,35 +295,8 @@ __global__ __launch_bounds__(64) void schedule_kernel(SchedArgs a) {
         }
         double t_new = clock;
         if (a.variant == kSync || a.variant == kBatchSync) {
-            // every worker starts a fresh mini-batch at t_j with w_j
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                const int w = lane + 64 * q;
-                ord[q] = 0;
-                if (w < P) key[q] = (double)draw_delay(w, 0, ver);
-            }
-            uint32_t taken = 0;
-            double last = 0.0;
-            for (int l = 0; l < K; ++l) {
-                const Best b = wave_min(local_min(key, taken, lane, P), width);
-                last = b.key;
-                if ((b.id & 63) == lane) {
-                    const int q = b.id >> 6;
-#pragma unroll
-                    for (int qq = 0; qq < NQ; ++qq) {
-                        if (qq != q) continue;
-                        tr_sel[j * Kcap + l] = b.id; tr_tau[j * Kcap + l] = (int32_t)j; tr_ord[j * Kcap + l] = ord[qq];
-                        if (a.variant == kSync) {
-                            taken |= 1u << qq;
-                        } else {
-                            // K-batch-sync: the worker starts its next mini-batch at the same w_j
-                            ord[qq] += 1;
-                            if (l + 1 < K)
-                                key[qq] = key[qq] + (double)draw_delay(b.id, ord[qq], ver);
-                        }
-                    }
-                }
-            }
+            const double last = sync_update<NQ>(draw_delay, a.variant == kBatchSync, P, K, width, lane, j, tr_sel + j * Kcap,
+                                                tr_tau + j * Kcap, tr_ord + j * Kcap);
             t_new = clock + last;
         } else if (a.variant == kBatchAsync) {
             // K-batch-async: the K earliest mini-batches contribute, whoever computed them.  A worker that pushes
@@ -361,6 +419,19 @@ __global__ void adasync_kernel(AdaArgs a, int replicas) {
 
 void launch_schedule(const SchedArgs& a, int replicas, hipStream_t s) {
     const bool table = a.dist.kind == 3;
+    // (a segment that ends where the clock crosses an interval is found update by update; grids end at 2^31 blocks)
+    if ((a.variant == kSync || a.variant == kBatchSync) && !(a.interval_t > 0.0) && a.count * (int64_t)a.tr.Kcap >= 16 && replicas <= 65535 && a.count < (1ll << 31)) {
+        const dim3 grid((unsigned)((a.count + kSyncWaves - 1) / kSyncWaves), (unsigned)replicas), block(64 * kSyncWaves);
+        if (a.P <= 64) {
+            if (table) hipLaunchKernelGGL((sync_schedule_kernel<1, true>), grid, block, 0, s, a);
+            else hipLaunchKernelGGL((sync_schedule_kernel<1, false>), grid, block, 0, s, a);
+        } else {
+            if (table) hipLaunchKernelGGL((sync_schedule_kernel<kMaxWorkers / 64, true>), grid, block, 0, s, a);
+            else hipLaunchKernelGGL((sync_schedule_kernel<kMaxWorkers / 64, false>), grid, block, 0, s, a);
+        }
+        hipLaunchKernelGGL(sync_clock_kernel, dim3(replicas), dim3(64), 0, s, a);
+        return;
+    }
     if (a.P <= 64) {
         if (table) hipLaunchKernelGGL((schedule_kernel<1, true>), dim3(replicas), dim3(64), 0, s, a);
         else hipLaunchKernelGGL((schedule_kernel<1, false>), dim3(replicas), dim3(64), 0, s, a);
