@@ -279,7 +279,8 @@ ssgd_status launch_steps(ssgd_ctx* c, int64_t v0, int64_t n, float* agg_out, int
                          std::vector<std::pair<hipEvent_t, hipEvent_t>>* events) {
     const bool tile = mode != kGeneralKernel;
     // a cluster stays on one XCD (block ids congruent modulo 8), so the resident slots count per XCD
-    const int resident = tile ? c->tile_resident_groups : c->resident_groups;
+    // (clusters of one workgroup take a CU each: two on a CU get in each other's way and gain next to nothing)
+    const int resident = !tile ? c->resident_groups : (c->G == 1 ? std::min(c->tile_resident_groups, c->cu_count) : c->tile_resident_groups);
     const int per_launch = mode == kDeferKernel ? c->defer_per_launch : std::max(1, 8 * ((resident / 8) / c->G));
     arm_exchange(c, tile, mode == kDeferKernel);
     HIP_OK(c, hipGetLastError());
@@ -294,7 +295,7 @@ ssgd_status launch_steps(ssgd_ctx* c, int64_t v0, int64_t n, float* agg_out, int
         a.v0 = v0; a.nsteps = n;
         a.agg_out = agg_out;
         a.pair_cus = 0; a.pair_layers = 0;
-        a.shared_cus = (a.replicas * c->G > c->cu_count) ? 1 : 0;
+        a.shared_cus = ((a.replicas + 7) / 8 * 8 * c->G > c->cu_count) ? 1 : 0;      // an XCD takes an eighth of the clusters
         a.prof_wave = 0; a.prof_a = -1; a.prof_b = -1; a.prof_base = (int64_t)c->R * c->G * 20; a.prof_helper = (int64_t)c->R * c->G * 2;
         if (const char* e = getenv("SSGD_PHASE_PROFILE")) (void)sscanf(e, "%d,%d,%d", &a.prof_a, &a.prof_b, &a.prof_wave);
         a.debug_flags = 0;
@@ -333,7 +334,7 @@ ssgd_status launch_steps(ssgd_ctx* c, int64_t v0, int64_t n, float* agg_out, int
                 a.tr = c->tr;
                 a.v0 = v0; a.nsteps = n;
                 a.agg_out = agg_out;
-                a.pair_cus = 0; a.pair_layers = 0; a.shared_cus = 0;
+                a.pair_cus = 0; a.pair_layers = 0; a.shared_cus = 8 * c->G > c->cu_count ? 1 : 0;
                 a.prof_wave = 0; a.prof_a = -1; a.prof_b = -1; a.prof_base = (int64_t)c->R * c->G * 20; a.prof_helper = (int64_t)c->R * c->G * 2;
                 a.debug_flags = 0;
                 if (!linear_tile_supports(a, c->Kcap)) return fail(c, SSGD_EDEVICE, "a cluster was spread over XCDs and no other kernel takes its shape");
@@ -383,7 +384,7 @@ ssgd_status run_segment_linear(ssgd_ctx* c, int64_t v0, int64_t n, float* agg_ou
     a.chunked = 0;
     if (tile || defer) {
         if (c->variant == SSGD_K_ASYNC && v0 == 0 && a.mp * c->Kcap <= 64) { head = 1; a.v0 = 1; }
-        a.chunked = ((c->variant == SSGD_K_SYNC || c->variant == SSGD_K_BATCH_SYNC) && a.mp * c->Kcap > 64) ? 1 : 0;
+        a.chunked = (c->variant == SSGD_K_SYNC || c->variant == SSGD_K_BATCH_SYNC) ? 1 : 0;
         tile = tile && linear_tile_supports(a, c->Kcap);
         defer = defer && linear_defer_supports(a);
     }

@@ -101,10 +101,12 @@ __device__ __forceinline__ void lds_barrier() {
 // ONE: the cluster is one workgroup (d <= 256).  Its partial logits are the logits: they change lanes inside the wave
 // instead of going out to the exchange, and only the 64-column blocks that exist are loaded, written and contracted.
 // Bound by the chain of one step, TU -> logits -> delta -> gradient -> update, beside the chain lists -> sample ids ->
-// gather of the next tile.  (Least squares, d = 64, two mini-batches of 16, one replica: 3.0 us per update where the
+// gather of the next tile.  (Least squares, d = 64, two mini-batches of 16, one replica: 2.5 us per update where the
 // exchange through memory of the general kernel takes 8.5.)
-template <int KIND, bool PROF, bool WHOLE, bool CHUNKED, bool BATCH, bool ONE>
-__global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
+// ROOMY: a launch that leaves every workgroup a CU of its own.  Two waves per SIMD then have 256 registers each and
+// nothing is spilled; a spilled word that a loader wave reads back would wait for the gathers in front of it.
+template <int KIND, bool PROF, bool WHOLE, bool CHUNKED, bool BATCH, bool ONE, bool ROOMY>
+__global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs a) {
     // consecutive block ids go to different XCDs: all slices of one cluster take block ids that
     // are congruent modulo 8 and share one L2
     const int xcd = blockIdx.x & 7, slot_in_xcd = blockIdx.x >> 3;
@@ -175,10 +177,17 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
         const bool has_tail = d_rem != 0 && slice == G - 1;
         float* const my_tile = L.tile + lw * SL + lane * 4;
 
+        // A tile is described (sample ids, labels, lists: n_*) one turn before its rows are gathered, so that the gathers
+        // leave as soon as the tile in front of them is published; what is published is the description p_* of the tile
+        // whose rows are in `pref`.
         f32x4 pref[LLOADS];
-        uint32_t row_id = kNoRow;
-        float row_lab = 0.0f;
-        int n_K = 0, n_nrec = 0, n_nstale = 0, n_stale = 0, n_stale_pos = KC, n_rec_word = 0;
+#pragma unroll
+        for (int i = 0; i < LLOADS; ++i) pref[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        uint32_t row_id = kNoRow, p_row_id = kNoRow;
+        float row_lab = 0.0f, p_row_lab = 0.0f;
+        int n_K = 0, n_nrec = 0, n_nstale = 0, n_stale = 0, n_stale_pos = KC, n_rec_word = 0, n_rows = mpt, n_flags = 0;
+        int p_K = 0, p_nrec = 0, p_nstale = 0, p_stale = 0, p_stale_pos = KC, p_rec_word = 0, p_rows = mpt, p_flags = 0;
+        int64_t n_ver = 0, p_ver = 0;
         int q_sel = -1, q_tau = -1, q_ord = 0;   // lane l: entry l of the consume list of a later version, in flight
         int cur_sel = -1;                        // consume list of the version before the one being prepared
 
@@ -194,13 +203,13 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
             }
         };
 
+        // (every lane loads, on every turn: a load under a condition would be copied where the paths meet, and the copy
+        // waits for it and for the gathers in front of it; lanes past the list are masked when it is taken)
+        const int q_lane = min(lane, Kcap - 1);
         auto issue_lists = [&](int64_t ver) {
-            q_sel = -1; q_tau = -1; q_ord = 0;
-            if (lane < Kcap) {
-                q_sel = tr_sel[ver * Kcap + lane];
-                q_tau = tr_tau[ver * Kcap + lane];
-                if (!async) q_ord = tr_ord[ver * Kcap + lane];
-            }
+            q_sel = tr_sel[ver * Kcap + q_lane];
+            q_tau = tr_tau[ver * Kcap + q_lane];
+            q_ord = tr_ord[ver * Kcap + q_lane];
         };
         // The lists of version `ver` (in flight in q_*) become the description of its tiles.
         int h_worker = -1, h_ord = 0, h_nrec = 0, h_tiles = 1;
@@ -211,8 +220,8 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
         int h_rw = 0, h_ro = 0, h_rf = 0;        // lane j: worker, ordinal, consumed-by-this-update flag of restart j
         int h_csel = -1, h_ctau = -1, h_cord = 0;   // lane l: entry l of the consume list of the version
         const int rpt = spr > 1 ? 1 : ROWS / mp; // K-batch-async: whole records per tile (or one block of a record)
-        auto take_lists = [&](int64_t ver, bool more) {
-            const int l_sel = q_sel, l_tau = q_tau, l_ord = q_ord;
+        auto take_lists = [&](int64_t ver) {
+            const int l_sel = lane < Kcap ? q_sel : -1, l_tau = lane < Kcap ? q_tau : -1, l_ord = lane < Kcap ? q_ord : 0;
             const int K = __popcll(__ballot(l_sel >= 0));
             int nrec = async ? __popcll(__ballot(cur_sel >= 0)) : K;
             int rec_slot = async ? cur_sel : lane;
@@ -276,19 +285,25 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
             cur_sel = l_sel;
             asm volatile("" : "+v"(n_stale), "+v"(n_stale_pos), "+v"(n_rec_word), "+v"(cur_sel), "+v"(h_worker), "+v"(h_ord) : : "memory");
             if constexpr (BATCH) asm volatile("" : "+v"(h_rw), "+v"(h_ro), "+v"(h_rf), "+v"(h_csel), "+v"(h_ctau), "+v"(h_cord) : : "memory");
-            if (more) issue_lists(ver + 1);
         };
-        // Tile `t` of version `ver`: sample ids and labels; leaves the gathers in flight.
-        auto make_tile = [&](int64_t ver, int t) {
+        // Tile `t` of version `ver`: sample ids, lists; leaves the labels in flight.
+        auto describe_tile = [&](int64_t ver, int t) {
+            n_ver = ver;
+            n_flags = (t + 1 == h_tiles ? 1 : 0) | (t == 0 ? 2 : 0);      // bit 0 last tile of its update, bit 1 first
+            n_rows = mpt;                                                 // rows per record in this tile
             int rec = r_of, smp = s_of;
-            if (chunked) { const int q = t * ROWS + lane; rec = q / mp; smp = q - rec * mp; }
+            if (chunked) {
+                // one record; the contraction takes 32 rows at a time
+                n_rows = (min(ROWS, h_nrec * mp - t * ROWS) > 32) ? ROWS : 32;
+                if (t > 0) { const int q = t * ROWS + lane; rec = q / mp; smp = q - rec * mp; }
+            }
             int worker, ordinal;
             if constexpr (BATCH) {
                 // records t * rpt .. of the version; the parked part of the update comes with the first tile
                 const int tr0 = spr > 1 ? t / spr : t * rpt;       // first record of the tile
                 const int blk = spr > 1 ? t % spr : 0;             // which block of 64 rows of its record
                 rec = (r_of < rpt) ? tr0 + r_of : 0x7FFFFFF;
-                if (spr > 1) { rec = tr0; smp = ROWS * blk + lane; }
+                if (spr > 1) { rec = tr0; smp = ROWS * blk + lane; n_rows = WHOLE ? ROWS : min(ROWS, mp - ROWS * blk); }
                 n_nrec = spr > 1 ? 1 : min(rpt, h_nrec - t * rpt);
                 n_nstale = (t == 0) ? h_nstale : 0;
                 // worker, ordinal and consumed-by-this-update flag of record q
@@ -319,30 +334,40 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
                 worker = __shfl(h_worker, min(rec, 63), 64);
                 ordinal = __shfl(h_ord, min(rec, 63), 64);
             }
-            row_id = kNoRow;
-            row_lab = 0.0f;
-            if (smp < m && rec < h_nrec) {
-                row_id = batch_index(a.seed, (uint32_t)rep, (uint32_t)worker, (uint32_t)ordinal, (uint32_t)ver,
-                                     (uint32_t)smp, a.N);
-                row_lab = (KIND == kLsq) ? reinterpret_cast<const float*>(a.y)[row_id]
-                                         : __int_as_float(reinterpret_cast<const int32_t*>(a.y)[row_id]);
-            }
-            // The lists are consumed before the gathers are issued: the gathers are the youngest
-            // vector-memory operations of this wave until the tile is published.
-            asm volatile("" : "+v"(row_id) : : "memory");
+            uint32_t seed_lo = (uint32_t)a.seed, seed_hi = (uint32_t)(a.seed >> 32);
+            asm volatile("" : "+s"(seed_lo), "+s"(seed_hi));      // the round keys are rebuilt here: kept across the loop they are spilled
+            const uint32_t id = batch_index(((uint64_t)seed_hi << 32) | seed_lo, (uint32_t)rep, (uint32_t)worker, (uint32_t)ordinal, (uint32_t)ver,
+                                            (uint32_t)smp, a.N);
+            row_lab = reinterpret_cast<const float*>(a.y)[id];    // fp32 or int32: the word as it is
+            row_id = (smp < m && rec < h_nrec) ? id : kNoRow;
+        };
+        // The gathers of the tile described last.  Nothing of this wave is in flight here (`publish` has waited for it): a
+        // wave's loads return in order, so what is asked for afterwards must not be needed before the rows are.
+        auto gather = [&]() {
+            p_row_id = row_id; p_row_lab = row_lab;
+            p_K = n_K; p_nrec = n_nrec; p_nstale = n_nstale; p_stale = n_stale; p_stale_pos = n_stale_pos; p_rec_word = n_rec_word;
+            p_rows = n_rows; p_flags = n_flags; p_ver = n_ver;
+            int olw = lw;
+            asm volatile("" : "+s"(olw));
+            asm volatile("" : "+v"(p_row_id), "+v"(p_row_lab), "+v"(p_stale), "+v"(p_stale_pos), "+v"(p_rec_word) : : "memory");
+            const int used = p_nrec * p_rows;      // a CU takes in about 16 bytes of gathers per cycle: rows past the records are left out
             __builtin_amdgcn_sched_barrier(0);
             if (!ONE || lane < 16 * nblk) {
 #pragma unroll
-            for (int i = 0; i < LLOADS; ++i) {
-                // rows without a sample read row 0; their delta is zero
-                uint32_t id = (uint32_t)__builtin_amdgcn_readlane((int)row_id, lw + 4 * i);
-                id = (id == kNoRow) ? 0u : id;
-                pref[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, goff[i & 3], (int)(id * row_bytes), kStream));
+                for (int i0 = 0; i0 < LLOADS; i0 += 4) {
+                    if (4 * i0 >= used) break;
+#pragma unroll
+                    for (int i = i0; i < i0 + 4; ++i) {
+                        // rows without a sample read row 0; their delta is zero
+                        uint32_t id = (uint32_t)__builtin_amdgcn_readlane((int)p_row_id, olw + 4 * i);
+                        id = (id == kNoRow) ? 0u : id;
+                        pref[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, goff[i & 3], (int)(id * row_bytes), kStream));
+                    }
+                }
             }
-            }
+            __builtin_amdgcn_sched_barrier(0);
         };
-        // flags: bit 0 last tile of its update, bit 1 first tile of its update
-        auto publish = [&](int flags) {
+        auto publish = [&]() {
             if (has_tail) {
 #pragma unroll
                 for (int i = 0; i < LLOADS; ++i) {
@@ -357,11 +382,12 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
                 for (int i = 0; i < LLOADS; ++i) *reinterpret_cast<f32x4*>(my_tile + 4 * i * SL) = pref[i];
             }
             if (lw == 0) {
-                L.rowid[lane] = row_id; L.ylab[lane] = row_lab;
-                if (lane == 0) { L.ctl[4] = n_K; L.ctl[5] = n_nrec; L.ctl[6] = n_nstale; L.ctl[7] = flags; }
-                if (n_stale_pos < kc) L.s_stale[n_stale_pos] = n_stale;
-                if (lane < kc) L.s_rec[lane] = n_rec_word;
+                L.rowid[lane] = p_row_id; L.ylab[lane] = p_row_lab;
+                if (lane == 0) { L.ctl[4] = p_K; L.ctl[5] = p_nrec; L.ctl[6] = p_nstale; L.ctl[7] = p_flags | (p_rows << 8); }
+                if (p_stale_pos < kc) L.s_stale[p_stale_pos] = p_stale;
+                if (lane < kc) L.s_rec[lane] = p_rec_word;
             }
+            asm volatile("" : "+v"(q_sel), "+v"(q_tau), "+v"(q_ord), "+v"(row_lab) : : "memory");     // lists and labels asked for behind the rows
         };
 
         // Loader wave 0, between D and B: the column sums of the delta tile per record, i.e. the bias
@@ -372,6 +398,8 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
             const int Kv = __builtin_amdgcn_readfirstlane(L.ctl[4]);
             const int n_rec = __builtin_amdgcn_readfirstlane(L.ctl[5]);
             const int n_st = __builtin_amdgcn_readfirstlane(L.ctl[6]);
+            // (a tile of one record that the update consumes: four parts, so that no lane idles)
+            const int parts = chunked ? 4 : n_rec, rows = chunked ? flags >> 10 : flags >> 8;
             // lane = class + 16 * (record within a batch of four records)
             const int c = lane & 15, grp = lane >> 4;
             const int sidx = (c == 15) ? 16 : c;          // the slot record keeps the loss in word 16
@@ -380,20 +408,20 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
                 const float was = L.small[__builtin_amdgcn_readfirstlane(L.s_stale[i]) * 17 + sidx];
                 if (grp == 0) tot += was;
             }
-            for (int r0 = 0; r0 < n_rec; r0 += 4) {
+            for (int r0 = 0; r0 < parts; r0 += 4) {
                 const int r = r0 + grp;
-                const bool have = r < n_rec;
-                const float* zp = L.zbuf + (have ? r : 0) * mpt * 16 + c;
+                const bool have = r < parts;
+                const float* zp = L.zbuf + (have ? r : 0) * rows * 16 + c;
                 float p0 = 0.0f, p1 = 0.0f;
                 int i0 = 0;
-                for (; i0 + 16 <= mpt; i0 += 16) {     // sixteen rows in flight
+                for (; i0 + 16 <= rows; i0 += 16) {     // sixteen rows in flight
                     float t[16];
 #pragma unroll
                     for (int i = 0; i < 16; ++i) t[i] = zp[(i0 + i) * 16];
 #pragma unroll
                     for (int i = 0; i < 16; i += 2) { p0 += t[i]; p1 += t[i + 1]; }
                 }
-                for (; i0 < mpt; i0 += 4) {
+                for (; i0 < rows; i0 += 4) {
                     float t[4];
 #pragma unroll
                     for (int i = 0; i < 4; ++i) t[i] = zp[(i0 + i) * 16];
@@ -401,7 +429,7 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
                     p1 += t[1] + t[3];
                 }
                 const float part = p0 + p1;
-                const int word = have ? L.s_rec[r] : 0;
+                const int word = have ? (chunked ? 1 << 16 : L.s_rec[r]) : 0;
                 if (have) {
                     if (((word >> 16) & 1) != 0) tot += part;
                     else if (((word >> 18) & 1) != 0) L.small[(word & 0xFFFF) * 17 + sidx] += part;    // a later block of its record
@@ -424,31 +452,52 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
         lds_barrier();                               // the compute waves have set up the control words
         if (L.ctl[0] != 0) return;
         if ((async || BATCH) && a.v0 >= 1 && lane < Kcap) cur_sel = tr_sel[(a.v0 - 1) * Kcap + lane];
+        int64_t at = 0;                              // update and tile described last
+        int at_tile = 0;
         issue_lists(a.v0);
-        take_lists(a.v0, a.nsteps > 1);
-        make_tile(a.v0, 0);
-        for (int64_t step = 0; step < a.nsteps; ++step) {
-            const int tiles = h_tiles;               // of update a.v0 + step
-            for (int t = 0; t < tiles; ++t) {
-                lmark(4);
-                const int flags = (t + 1 == tiles ? 1 : 0) | (t == 0 ? 2 : 0);
-                publish(flags);
-                lmark(0);
-                lds_barrier();                       // TU
-                if (t + 1 < tiles) {
-                    make_tile(a.v0 + step, t + 1);
-                } else if (step + 1 < a.nsteps) {
-                    take_lists(a.v0 + step + 1, step + 2 < a.nsteps);
-                    make_tile(a.v0 + step + 1, 0);
-                }
-                lmark(1);
-                lds_barrier();                       // D
-                if (L.ctl[0] != 0) return;
-                if (lw == 0) bias_and_loss(a.v0 + step, flags);
-                lmark(2);
-                lds_barrier();                       // B
-                lmark(3);
+        take_lists(a.v0);
+        issue_lists(a.v0 + min((int64_t)1, a.nsteps - 1));
+        describe_tile(a.v0, 0);
+        asm volatile("" : "+v"(q_sel), "+v"(q_tau), "+v"(q_ord), "+v"(row_lab) : : "memory");
+        bool more = true;                            // the tile described last is still to be gathered
+        auto turn = [&]() {
+            gather();
+            if (at_tile + 1 < h_tiles) {
+                ++at_tile;
+            } else if (at + 1 < a.nsteps) {
+                ++at; at_tile = 0;
+                take_lists(a.v0 + at);
+            } else {
+                more = false;
             }
+            issue_lists(a.v0 + min(at + 1, a.nsteps - 1));
+            describe_tile(a.v0 + at, at_tile);       // past the last tile: that tile again, never gathered
+        };
+        // the rest of the tile that the compute waves work on; false: the launch is aborted
+        auto rest = [&](int64_t v, int flags) -> bool {
+            lmark(1);
+            lds_barrier();                           // D
+            if (L.ctl[0] != 0) return false;
+            if (lw == 0) bias_and_loss(v, flags);
+            lmark(2);
+            lds_barrier();                           // B
+            lmark(3);
+            return true;
+        };
+        turn();
+        for (;;) {
+            lmark(4);
+            publish();
+            lmark(0);
+            const int64_t v = p_ver;
+            const int flags = p_flags | (p_rows << 8);
+            lds_barrier();                           // TU
+            if (!more) {
+                if (!rest(v, flags)) return;
+                break;
+            }
+            turn();
+            if (!rest(v, flags)) return;
         }
         if constexpr (PROF) {
             if (lprof && lane == 0) a.prof[(int64_t)a.prof_base + ((int64_t)rep * G + slice) * 2 + 1] += lp_acc;
@@ -554,6 +603,7 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
         const int n_rec = __builtin_amdgcn_readfirstlane(ctl4.y);
         const int n_stale = __builtin_amdgcn_readfirstlane(ctl4.z);
         const int tile_flags = __builtin_amdgcn_readfirstlane(ctl4.w);
+        const int rows = tile_flags >> 8;                   // per record
         last_tile = (tile_flags & 1) != 0;
         const int par = (int)(n_fenced & 1u);               // buffer of a fenced exchange: a step may have several of them
         // An opaque zero: addresses built from it are recomputed every step instead of being kept in
@@ -566,43 +616,22 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
         //      the operands of the next k-block are read from LDS before the MFMAs of this one are issued
         {
             f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-            if constexpr (ONE) {
-                // the 64-column blocks in use; the four operand pairs of a block are read together
-                f32x4 wv[4], xv[4];
+            f32x4 wv = *reinterpret_cast<const f32x4*>(f_wa[0]);
+            f32x4 xv = *reinterpret_cast<const f32x4*>(f_xa[0]);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    wv[q] = *reinterpret_cast<const f32x4*>(f_wa[q]);
-                    xv[q] = *reinterpret_cast<const f32x4*>(f_xa[q]);
+            for (int s = 0; s < SL / 16; ++s) {
+                if (ONE && s > 0 && (s & 3) == 0 && s >= 4 * nblk) break;
+                f32x4 wn = wv, xn = xv;
+                if (s + 1 < SL / 16) {
+                    wn = *reinterpret_cast<const f32x4*>(f_wa[(s + 1) & 3] + ((s + 1) >> 2) * 64);
+                    xn = *reinterpret_cast<const f32x4*>(f_xa[(s + 1) & 3] + ((s + 1) >> 2) * 64);
                 }
-                for (int b = 0; b < nblk; ++b) {
-                    const int nx = min(b + 1, nblk - 1) * 64;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const f32x4 w1 = *reinterpret_cast<const f32x4*>(f_wa[q] + nx), x1 = *reinterpret_cast<const f32x4*>(f_xa[q] + nx);
-                        acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[q].x, xv[q].x, acc0, 0, 0, 0);
-                        acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[q].y, xv[q].y, acc1, 0, 0, 0);
-                        acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[q].z, xv[q].z, acc0, 0, 0, 0);
-                        acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[q].w, xv[q].w, acc1, 0, 0, 0);
-                        wv[q] = w1; xv[q] = x1;
-                    }
-                }
-            } else {
-                f32x4 wv = *reinterpret_cast<const f32x4*>(f_wa[0]);
-                f32x4 xv = *reinterpret_cast<const f32x4*>(f_xa[0]);
-#pragma unroll
-                for (int s = 0; s < SL / 16; ++s) {
-                    f32x4 wn = wv, xn = xv;
-                    if (s + 1 < SL / 16) {
-                        wn = *reinterpret_cast<const f32x4*>(f_wa[(s + 1) & 3] + ((s + 1) >> 2) * 64);
-                        xn = *reinterpret_cast<const f32x4*>(f_xa[(s + 1) & 3] + ((s + 1) >> 2) * 64);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);   // keep the reads ahead of the MFMAs
-                    acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.x, xv.x, acc0, 0, 0, 0);
-                    acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.y, xv.y, acc1, 0, 0, 0);
-                    acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.z, xv.z, acc0, 0, 0, 0);
-                    acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.w, xv.w, acc1, 0, 0, 0);
-                    wv = wn; xv = xn;
-                }
+                __builtin_amdgcn_sched_barrier(0);   // keep the reads ahead of the MFMAs
+                acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.x, xv.x, acc0, 0, 0, 0);
+                acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.y, xv.y, acc1, 0, 0, 0);
+                acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.z, xv.z, acc0, 0, 0, 0);
+                acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.w, xv.w, acc1, 0, 0, 0);
+                wv = wn; xv = xn;
             }
             const f32x4 out = acc0 + acc1;   // classes 4*(lane/16)+0..3 of row f_row
             mark(8);
@@ -817,36 +846,14 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
         if (L.ctl[0] != 0) return;   // uniform: every thread reads the same LDS word
         mark(5);
 
-        // ---- per record: the gradient slice delta^T X, in groups of four k-steps (16 rows); the operands
-        //      of the next group are read from LDS before the MFMAs of this one are issued
+        // ---- per record: the gradient slice delta^T X, in k-steps of four rows
         {
             const bool has_cols = !ONE || wave < nblk;      // a wave without columns contracts nothing
             const int n_own = has_cols ? n_rec : 0;
-            const int kpr = mpt >> 2;              // k-steps per record
-            const int ngrp = (kpr + 3) >> 2;       // groups per record
             const int b_lo = lane >> 4, b_cls = lane & 15;
-            auto load_group = [&](int r, int g, float (&dv)[4], f32x4 (&xv)[4]) {
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int k = 4 * g + u;
-                    const int row = r * mpt + 4 * min(k, kpr - 1) + b_lo;
-                    dv[u] = L.zbuf[row * 16 + b_cls];   // k-steps past the record are masked when they are used
-                    xv[u] = *reinterpret_cast<const f32x4*>(L.tile + row * SL + ((own_ch ^ (row & 15)) << 2));
-                }
-            };
             f32x4 acc[4];
 #pragma unroll
             for (int c = 0; c < 4; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-            auto contract = [&](int g, const float (&dv)[4], const f32x4 (&xv)[4]) {
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const float da = (4 * g + u < kpr) ? dv[u] : 0.0f;   // k-steps past the record contribute nothing
-                    acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(da, xv[u].x, acc[0], 0, 0, 0);
-                    acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(da, xv[u].y, acc[1], 0, 0, 0);
-                    acc[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(da, xv[u].z, acc[2], 0, 0, 0);
-                    acc[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(da, xv[u].w, acc[3], 0, 0, 0);
-                }
-            };
             // record r is complete: add it to the aggregate of update v, or park it in its slot
             auto finish = [&](int r) {
                 if constexpr (PROF) { asm volatile("" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])); mark(11); }
@@ -884,16 +891,16 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
                 for (int c = 0; c < 4; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
                 mark(12);
             };
+            // The tile and delta addresses are four base addresses (one per k-step of 16 rows, carrying the swizzle key of
+            // its rows) plus constants.
+                            int olo = b_lo, och = own_ch, ocl = b_cls;
+                            asm volatile("" : "+v"(olo), "+v"(och), "+v"(ocl));   // rebuilt every step, not kept across the loop
+                            const float* bx[4];
+            #pragma unroll
+                            for (int u = 0; u < 4; ++u) bx[u] = L.tile + (4 * u + olo) * SL + ((och ^ (4 * u + olo)) << 2);
+                            const float* bz = L.zbuf + olo * 16 + ocl;
             if constexpr (WHOLE) {
-                // Whole groups of 16 rows only, at most four of them: the tile and delta addresses are four base
-                // addresses (one per k-step of a group, carrying the swizzle key of its rows) plus constants, and
-                // two register sets take turns, one being read from LDS while the MFMAs of the other are issued.
-                int olo = b_lo, och = own_ch, ocl = b_cls;
-                asm volatile("" : "+v"(olo), "+v"(och), "+v"(ocl));   // rebuilt every step, not kept across the loop
-                const float* bx[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) bx[u] = L.tile + (4 * u + olo) * SL + ((och ^ (4 * u + olo)) << 2);
-                const float* bz = L.zbuf + olo * 16 + ocl;
+                // Whole groups of 16 rows only, at most four of them: two register sets take turns, one being read from LDS while the MFMAs of the other are issued.
                 // half-group h: k-steps 2 h and 2 h + 1, i.e. rows 8 h .. 8 h + 7
                 auto fetch = [&](int h, float (&dv)[2], f32x4 (&xv)[2]) {
 #pragma unroll
@@ -932,7 +939,7 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
                 };
                 float da[2], db[2];
                 f32x4 xa[2], xb[2];
-                const int H = has_cols ? n_rec * (mpt >> 3) : 0;         // half-groups in the tile: 0, 4 or 8
+                const int H = n_own * (rows >> 3);         // half-groups in the tile: 0, 4 or 8
                 if (H > 0) {
                     fetch(0, da, xa);
                     fetch(1, db, xb);
@@ -948,7 +955,7 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
                     __builtin_amdgcn_sched_barrier(0);
                     mac(false, db, xb);
                     if (H > 4) {
-                        const bool two = mpt == 32;         // the second record starts with half-group 4
+                        const bool two = rows == 32;         // the second record starts with half-group 4
                         if (two) done(0);
                         fetch(5, db, xb);
                         __builtin_amdgcn_sched_barrier(0);
@@ -967,25 +974,26 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
                     }
                 }
             } else {
-                // the operands of the next group are read into a second register set before the MFMAs of this one
+                // Records of any multiple of four rows, one behind the other, 16 rows a turn: a record ends where its rows do.
+                // Four register sets, each read again for the next turn as soon as its MFMAs are issued.
+                const int kpr = rows >> 2, steps = n_own * kpr;
                 float dv[4];
                 f32x4 xv[4];
-                int r = opq, g = 0;
-                if (n_own > 0) load_group(r, 0, dv, xv);
-                while (r < n_own) {
-                    int rn = r, gn = g + 1;
-                    if (gn == ngrp) { gn = 0; rn = r + 1; }
-                    float dn[4];
-                    f32x4 xn[4];
-    #pragma unroll
-                    for (int u = 0; u < 4; ++u) { dn[u] = dv[u]; xn[u] = xv[u]; }
-                    if (rn < n_own) load_group(rn, gn, dn, xn);
-                    __builtin_amdgcn_sched_barrier(0);   // keep the reads ahead of the MFMAs
-                    contract(g, dv, xv);
-                    if (rn != r) finish(r);
-    #pragma unroll
-                    for (int u = 0; u < 4; ++u) { dv[u] = dn[u]; xv[u] = xn[u]; }
-                    r = rn; g = gn;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) { dv[u] = bz[4 * u * 16]; xv[u] = *reinterpret_cast<const f32x4*>(bx[u]); }
+                int r = opq, end = kpr;
+                for (int g0 = 0; g0 < steps; g0 += 4) {
+                    const int nx = min(g0 + 4, ROWS / 4 - 4);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        if (g0 + u < steps) {
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(dv[u], xv[u][c], acc[c], 0, 0, 0);
+                            if (g0 + u + 1 == end) { finish(r); ++r; end += kpr; }
+                        }
+                        dv[u] = bz[4 * (nx + u) * 16];
+                        xv[u] = *reinterpret_cast<const f32x4*>(bx[u] + 4 * nx * SL);
+                    }
                 }
             }
         }
@@ -1044,21 +1052,22 @@ __global__ __launch_bounds__(512, 4) void linear_tile_kernel(LinArgs a) {
     for (int q = tid; q < S * 17; q += NTC) small_g[q] = L.small[q];
 }
 
-template <int KIND, bool PROF, bool WHOLE, bool CHUNKED, bool BATCH, bool ONE>
-hipError_t launch_o(const LinArgs& a, size_t lds, hipStream_t s) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(linear_tile_kernel<KIND, PROF, WHOLE, CHUNKED, BATCH, ONE>),
+template <int KIND, bool PROF, bool WHOLE, bool CHUNKED, bool BATCH, bool ONE, bool ROOMY>
+hipError_t launch_r(const LinArgs& a, size_t lds, hipStream_t s) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(linear_tile_kernel<KIND, PROF, WHOLE, CHUNKED, BATCH, ONE, ROOMY>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     const int groups = (a.replicas + 7) / 8;
     const int blocks = a.pair_cus > 0 ? 8 * a.pair_cus * a.pair_layers : groups * 8 * a.G;
-    hipLaunchKernelGGL((linear_tile_kernel<KIND, PROF, WHOLE, CHUNKED, BATCH, ONE>), dim3(blocks), dim3(512), lds, s, a);
+    hipLaunchKernelGGL((linear_tile_kernel<KIND, PROF, WHOLE, CHUNKED, BATCH, ONE, ROOMY>), dim3(blocks), dim3(512), lds, s, a);
     return hipGetLastError();
 }
 
+// (no phase profile for one workgroup, and for workgroups that share CUs only with a profile of their own)
 template <int KIND, bool PROF, bool WHOLE, bool CHUNKED, bool BATCH>
 hipError_t launch_w(const LinArgs& a, size_t lds, hipStream_t s) {
-    // (no phase profile for one workgroup)
-    return a.G == 1 ? launch_o<KIND, false, WHOLE, CHUNKED, BATCH, true>(a, lds, s) : launch_o<KIND, PROF, WHOLE, CHUNKED, BATCH, false>(a, lds, s);
+    if (a.shared_cus) return launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, false, false>(a, lds, s);
+    return a.G == 1 ? launch_r<KIND, false, WHOLE, CHUNKED, BATCH, true, true>(a, lds, s) : launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, false, true>(a, lds, s);
 }
 
 // K-async whose versions may have more records than a tile holds; version 0, at which all P workers start, is one.
@@ -1096,9 +1105,9 @@ int linear_tile_resident_groups(size_t lds_bytes) {
     int dev = 0, per_cu = 0;
     hipDeviceProp_t prop;
     if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(linear_tile_kernel<kSoftmax, false, false, false, false, false>),
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(linear_tile_kernel<kSoftmax, false, false, false, false, false, false>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, linear_tile_kernel<kSoftmax, false, false, false, false, false>, 512, lds_bytes) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, linear_tile_kernel<kSoftmax, false, false, false, false, false, false>, 512, lds_bytes) != hipSuccess) return 0;
     return per_cu * prop.multiProcessorCount;
 }
 
