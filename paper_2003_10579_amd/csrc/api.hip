@@ -420,13 +420,19 @@ ssgd_status run_updates(ssgd_ctx* c, int64_t J, float* agg_out) {
         // The schedule does not depend on the numerics (K changes only between segments here), so it is written piece by
         // piece on a second stream while the gradient kernels of the piece before run: one wavefront per replica beside
         // kernels that leave it room (the network's updates are separate launches; the steady-state kernel of K-async
-        // on the linear models leaves CUs free).  The pieces of the linear models are long: every piece is a launch of
-        // its own, which reads the gradients in flight from HBM and writes them back.
-        const bool linear_pipe = c->model.kind != SSGD_MLP2 && c->variant == SSGD_K_ASYNC && c->defer_per_launch >= 1 && agg_out == nullptr;
+        // on the linear models leaves CUs free, and the tile kernel leaves registers free where no two of its workgroups
+        // share a CU).  The pieces of the linear models are long, since every piece is a launch of its own (20 to 40 us)
+        // that reads the gradients in flight from HBM and writes them back; the first one is short, since nothing hides
+        // its schedule, and each of the next is three times the one before, since an update's schedule takes at most a
+        // third of its gradients (0.6 of 4.0 us at P = 8; K-batch-async with 8 workers 1.4 of 4.2, P = 20, K = 5 2 of 20).
+        const bool linear_async = c->model.kind != SSGD_MLP2 && (c->variant == SSGD_K_ASYNC || c->variant == SSGD_K_BATCH_ASYNC);
+        const bool leaves_room = c->defer_per_launch >= 1 || (c->tile_resident_groups >= c->G && ((c->R + 7) / 8 * 8 * c->G <= c->cu_count));
+        const bool linear_pipe = linear_async && leaves_room && agg_out == nullptr;
         // (one replica of the network takes the rows of a piece as they come: short pieces, so that the first one of a
         // segment, whose schedule nothing hides, is soon there)
-        const int64_t kPiece = c->model.kind == SSGD_MLP2 ? (c->R == 1 ? 16 : 64) : 1024;
-        const bool pipelined = (c->model.kind == SSGD_MLP2 || linear_pipe) && c->ada.mode < 2 && seg > kPiece;
+        const int64_t kPiece = c->model.kind == SSGD_MLP2 ? (c->R == 1 ? 16 : 64) : 64;
+        const int64_t kLongest = c->model.kind == SSGD_MLP2 ? kPiece : 1024;
+        const bool pipelined = (c->model.kind == SSGD_MLP2 || linear_pipe) && c->ada.mode < 2 && seg > (linear_pipe ? 2 * kPiece : kPiece);
         if (pipelined) {
             if (!c->side) HIP_OK(c, hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
             hipEvent_t before = nullptr;
@@ -452,8 +458,12 @@ ssgd_status run_updates(ssgd_ctx* c, int64_t J, float* agg_out) {
                 if (e == hipSuccess && c->j > 0)
                     e = hipMemcpyAsync(hsel, c->tr.sel + (size_t)(c->j - 1) * W, sizeof(int32_t) * W, hipMemcpyDeviceToHost, c->side);
             }
-            for (int64_t off = 0; off < seg && e == hipSuccess; off += kPiece) {
-                sa.j0 = c->j + off; sa.count = std::min(kPiece, seg - off);
+            std::vector<int64_t> lengths;        // of the pieces
+            for (int64_t off = 0, len = kPiece; off < seg; off += lengths.back(), len = std::min(3 * len, kLongest)) lengths.push_back(std::min(len, seg - off));
+            int64_t sched_off = 0;
+            for (size_t q = 0; q < lengths.size() && e == hipSuccess; sched_off += lengths[q], ++q) {
+                const int64_t off = sched_off;
+                sa.j0 = c->j + off; sa.count = lengths[q];
                 launch_schedule(sa, c->R, c->side);
                 if (one_call) {
                     const size_t cnt = (size_t)sa.count;
@@ -474,14 +484,14 @@ ssgd_status run_updates(ssgd_ctx* c, int64_t J, float* agg_out) {
                 MlpPieces pc{written.data(), (int)written.size(), kPiece, hK, htau, hsel};
                 e = mlp_run_segment(c->mlp.data(), c->R, c->tr, c->ws, c->j, seg, agg_out, c->stream, &c->last_ms, &c->last_launches, &msg, &pc);
             }
-            for (int64_t off = 0; off < seg && e == hipSuccess && lin_st == SSGD_OK && !one_call; off += kPiece, ++k) {
+            for (int64_t off = 0; off < seg && e == hipSuccess && lin_st == SSGD_OK && !one_call; off += lengths[k], ++k) {
                 e = hipStreamWaitEvent(c->stream, written[k], 0);
                 if (e != hipSuccess) break;
                 if (c->model.kind == SSGD_MLP2)
-                    e = mlp_run_segment(c->mlp.data(), c->R, c->tr, c->ws, c->j + off, std::min(kPiece, seg - off), agg_out, c->stream,
+                    e = mlp_run_segment(c->mlp.data(), c->R, c->tr, c->ws, c->j + off, lengths[k], agg_out, c->stream,
                                         &c->last_ms, &c->last_launches, &msg);
                 else
-                    lin_st = run_segment_linear(c, c->j + off, std::min(kPiece, seg - off), agg_out, &events);
+                    lin_st = run_segment_linear(c, c->j + off, lengths[k], agg_out, &events);
             }
             if (lin_st != SSGD_OK) {
                 (void)hipStreamSynchronize(c->side);

@@ -187,8 +187,8 @@ __global__ __launch_bounds__(64) void schedule_kernel(SchedArgs a) {
 
     int64_t done = 0;
     int crossed = 0;
-    if (NQ == 1 && !TABLE && a.variant == kAsync && P <= 16 && !(a.interval_t > 0.0)) {
-        // K-async with few workers, in a loop of its own: every lane ranks its worker's finish time against all
+    if (NQ == 1 && !TABLE && a.variant == kAsync && !(a.interval_t > 0.0)) {
+        // K-async with a worker per lane, in a loop of its own: every lane ranks its worker's finish time against all
         // P of them, which gives the K earliest in consume-list order at once.  The delay a worker would draw if
         // it restarted now depends on (worker, version) only: the 64 lanes draw it for 64 / width versions in one go.
         const int wmask = width - 1, per = 64 / width;
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(64) void schedule_kernel(SchedArgs a) {
         }
         key[0] = mine; tau[0] = mytau;
     }
-    if (!TABLE && a.variant == kAsync && K >= 8 && 18 * K >= P * NQ && (NQ > 1 || P > 16) && !(a.interval_t > 0.0)) {
+    if (!TABLE && a.variant == kAsync && NQ > 1 && K >= 8 && 18 * K >= P * NQ && !(a.interval_t > 0.0)) {
         // K-async with many contributors per update: K rounds of a wave-wide argmin (0.4 us each) cost more than
         // ranking every worker's finish time against all P of them (one pass over the workers, whatever K is: 22 us
         // at P = 256), which also gives the K earliest in consume-list order.
