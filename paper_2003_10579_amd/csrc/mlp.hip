@@ -5,15 +5,15 @@
 //
 // A worker's gradient is linear in two small factors, so what is kept per worker
 // from the moment it starts (at the parameters it read) until an update consumes
-// it is: its mini-batch rows in bf16, in both orientations; delta1 = back-propagated
-// error of the hidden layer, scaled by 1/m and rounded to bf16, transposed; and
-// the small second-layer gradients.  The first-layer gradient of an update,
+// it is: delta1 = back-propagated error of the hidden layer, scaled by 1/m and
+// rounded to bf16, transposed; and the small second-layer gradients.  The mini-batch
+// rows are not kept: who drew them, when and as the how-manieth mini-batch is in the
+// trace, and the contraction draws the sample ids again.  The first-layer gradient of an update,
 //     sum over the K consumed workers of  delta1_l^T X_l    (hidden x d),
 // is then one bf16 MFMA contraction over K*m rows whose epilogue applies it to the
 // fp32 master weights and refreshes their bf16 copy; no first-layer gradient is ever
 // stored.  Per update v:
-//   gather    rows of the workers that start at version v -> bf16 (row-major and transposed)
-//   forward   Z1 = X W1^T + b1 on the MFMA units (bf16 in, fp32 accumulate), H = relu(Z1) in fp32
+//   forward   Z1 = X W1^T + b1 of the workers that start at version v, rows gathered from a bf16 copy of X, on the MFMA units (bf16 in, fp32 accumulate), H = relu(Z1) in fp32
 //   layer 2   Z2 = H W2^T + b2, softmax, delta2, loss, delta1 = (W2^T delta2) * [H > 0] in fp32
 //   consume   W1 -= lr/K * sum_l delta1_l^T X_l (MFMA), then b1, W2, b2 and the loss record
 #include "mlp.hpp"
@@ -40,6 +40,7 @@ typedef float f32x8 __attribute__((ext_vector_type(8)));
 constexpr int MP = 64;         // rows kept per worker (m <= 64; the rest is zero)
 constexpr int KT = 64;         // contraction depth per stage
 constexpr int LDT = KT + 8;    // padded LDS row (bf16 elements): 144 bytes, keeps 16-byte reads conflict-poor
+constexpr int kShareSlots = 64; // most consumed slots per workgroup of the gradient contraction
 constexpr int kSmallRec = 32;  // most records per update that take the few-record path
 
 // round to nearest even, as a 16-bit pattern; infinities and NaNs are truncated
@@ -71,10 +72,10 @@ struct MlpArgs {
     int32_t n_rec_inline;      // > 0: rec_inline holds the workers of the nrec mini-batches that start (K-async)
     int16_t cons_inline[32];
     int16_t rec_inline[32];
+    int32_t cons_tau[32];      // versions of the gradients in cons_inline
     float* b1r;                // nullable: a copy of b1 (read by the layer-2 kernel, written by the small update) ...
     float* b2r;                // ... and of b2, when updates overlap and every version of the parameters has copies of its own
-    unsigned short* xb;        // [S][MP][d]   bf16 rows of the slot's mini-batch
-    unsigned short* xbt;       // [S][d][MP]   the same, transposed
+    unsigned short* xb;        // [S][MP][d]   bf16 rows of the slot's samples (evaluation of the objective)
     float* hbuf;               // [S][MP][H]   hidden activations
     unsigned short* d1t;       // [S][H][MP]   delta1 / m in bf16, transposed
     // The second-layer gradients and the loss have room for one record per quarter of the mini-batch (rows 16 q ..
@@ -141,6 +142,31 @@ __device__ __forceinline__ int consumed_slot(const MlpArgs& a, int l) {
     return a.variant == kAsync ? a.tr.sel[a.v * a.tr.Kcap + l] : l;
 }
 
+// Four sample ids of entry l of the consume list: rows 4 quad .. + 3 of its mini-batch; a row without a sample is row N
+// of the bf16 copy of the sample matrix, which is zero.
+__device__ __forceinline__ uint4 consumed_ids(const MlpArgs& a, int l, int quad) {
+    uint32_t id[4];
+    if (a.eval_base >= 0) {
+        const int64_t first = a.eval_base + (int64_t)l * MP + 4 * quad;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) id[e] = (4 * quad + e < a.m && first + e < (int64_t)a.N) ? (uint32_t)(first + e) : a.N;
+    } else {
+        const int64_t at = a.v * a.tr.Kcap + l;
+        int worker, ordinal = 0, version;
+        if (a.n_cons_inline > 0) {
+            worker = (int)a.cons_inline[l]; version = a.cons_tau[l];
+        } else {
+            worker = a.tr.sel[at]; version = a.tr.tau[at];
+            if (a.variant != kAsync) ordinal = a.tr.ord[at];
+        }
+        const u32x4 b = draw(a.seed, kBatch, (uint32_t)quad, a.rep, (uint32_t)worker, (uint32_t)ordinal, (uint32_t)version);
+        const uint32_t bits[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) id[e] = 4 * quad + e < a.m ? __umulhi(bits[e], a.N) : a.N;
+    }
+    return make_uint4(id[0], id[1], id[2], id[3]);
+}
+
 // ---- K-batch-async: the lists of update v from its trace row (Sec. 2.2: the K earliest mini-batches, whoever
 // computed them).  Mini-batches that start at version v: at v = 0 every worker's first one, later the one of the
 // worker whose push triggered update v - 1; then, for each of the first K - 1 pushes of update v, the next mini-batch
@@ -182,7 +208,6 @@ __global__ void mlp_batch_plan_kernel(MlpArgs a) {
 
 // ---- gather: one workgroup per (record, block of 128 columns) ---------------------------------
 __global__ __launch_bounds__(256) void mlp_gather_kernel(MlpArgs a) {
-    __shared__ unsigned short tr_tile[128][MP + 2];
     __shared__ uint32_t ids[MP];
     const int r = blockIdx.x, cb = blockIdx.y, tid = threadIdx.x;
     int worker, ordinal, slot;
@@ -208,32 +233,17 @@ __global__ __launch_bounds__(256) void mlp_gather_kernel(MlpArgs a) {
         unsigned short b[4] = {bf16_bits(v.x), bf16_bits(v.y), bf16_bits(v.z), bf16_bits(v.w)};
         unsigned short* dst = a.xb + ((int64_t)slot * MP + s) * a.d + cb * 128 + 4 * c4;
         *reinterpret_cast<uint2*>(dst) = make_uint2((uint32_t)b[0] | ((uint32_t)b[1] << 16), (uint32_t)b[2] | ((uint32_t)b[3] << 16));
-#pragma unroll
-        for (int q = 0; q < 4; ++q) tr_tile[4 * c4 + q][s] = b[q];
-    }
-    __syncthreads();
-    if (a.xbt == nullptr) return;       // objective evaluation: no gradient contraction follows
-    // transposed copy: column c of the block, 64 samples = 128 bytes; 8 threads per column, 16 bytes each
-    for (int q = tid; q < 128 * 8; q += 256) {
-        const int c = q >> 3, part = q & 7;
-        u16x8 v;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = tr_tile[c][8 * part + e];
-        *reinterpret_cast<u16x8*>(a.xbt + ((int64_t)slot * a.d + cb * 128 + c) * MP + 8 * part) = v;
     }
 }
 
 template <int G>
 __device__ __forceinline__ void small_update_body(const MlpArgs& a, int block, int nblocks);
 
-// ---- contraction: C[M x N] = sum over stages of A_stage[M x 64] B_stage[N x 64]^T, bf16 MFMA ----
-// FWD: rows = (record, sample) of the compute list, columns = hidden units, depth = d.
-// BWD: rows = hidden units, columns = input features, depth = 64 samples of every consumed slot.
+// ---- forward contraction of the evaluation: Z1 of the gathered rows, NT form with bf16 MFMA ----
+// rows = (record, sample), columns = hidden units, depth = d.
 // BT x BT output tile per workgroup (128: four waves of 64 x 64; 64: four waves of 32 x 32, for launches
 // that would otherwise leave most CUs idle).
-// SPLIT (gradient contraction only): blockIdx.z takes a share of the consumed slots and leaves its partial sum in
-// dw_part; mlp_w1_update_kernel adds the shares in order and applies the update.
-template <bool FWD, int BT, bool SPLIT = false>
+template <int BT>
 __global__ __launch_bounds__(256, 2) void mlp_contract_kernel(MlpArgs a) {
     constexpr int WT = BT / 2;          // rows and columns per wave
     constexpr int NF = WT / 32;         // 32 x 32 MFMA tiles per wave and dimension
@@ -243,77 +253,29 @@ __global__ __launch_bounds__(256, 2) void mlp_contract_kernel(MlpArgs a) {
     unsigned short* Bs = lds + 2 * BT * LDT;        // [2][BT][LDT]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int d = a.d, H = a.H;
-    int bm = blockIdx.x, bn = blockIdx.y, bz = blockIdx.z;
-    if constexpr (!FWD && SPLIT) {
-        // One-dimensional launch.  Consecutive block ids go to different XCDs; the H / BT workgroups that read the same
-        // columns of the same slots (the large operand) take consecutive places on one XCD, so that they run together
-        // and those columns come from HBM once.
-        const int nbm = H / BT, nbn = d / BT;
-        const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
-        const int group = (idx / nbm) * 8 + xcd;          // (column tile, share)
-        bm = idx % nbm;
-        if (group >= nbn * a.nsplit) return;
-        bn = group % nbn;
-        bz = group / nbn;
-    }
-    if constexpr (!FWD && !SPLIT) {
-        // a launch with one more row of workgroups than there are column tiles: that row takes the small parameters of
-        // the update (they do not depend on the contraction), which saves a launch per update
-        if ((int)blockIdx.y == d / BT) { small_update_body<1>(a, blockIdx.x, gridDim.x); return; }
-    }
-    // the fused update reads its tile of the fp32 parameters now, not after the contraction that it does not depend on
+    const int bm = blockIdx.x, bn = blockIdx.y;
+    const int stages = d / KT;
     constexpr int C4 = BT / 4;           // float4 groups per row
-    constexpr int NPRE = (!FWD && !SPLIT) ? BT * C4 / 256 : 1;
-    f32x4 wpre[NPRE];
-    if constexpr (!FWD && !SPLIT) {
-#pragma unroll
-        for (int j = 0; j < NPRE; ++j) {
-            const int q = tid + 256 * j, row = q / C4, c4 = q % C4;
-            wpre[j] = *reinterpret_cast<const f32x4*>(a.params + (int64_t)(bm * BT + row) * d + bn * BT + 4 * c4);
-        }
-    }
-    // gradient contraction: the slots of the consumed gradients are read once, not once per stage in front of the
-    // operand loads that depend on them
-    __shared__ int slot_list[FWD ? 1 : 256];
-    if constexpr (!FWD) {
-        for (int l = tid; l < a.Kv; l += 256) slot_list[l] = consumed_slot(a, l);
-        __syncthreads();
-    }
-    int stage0 = 0, stages = FWD ? d / KT : a.Kv;
-    if constexpr (SPLIT) {
-        static_assert(!FWD, "only the gradient contraction is split here");
-        const int total = a.Kv, shares = a.nsplit;
-        const int per = (total + shares - 1) / shares;
-        stage0 = bz * per;
-        stages = max(0, min(per, total - stage0));
-    }
 
     // global -> LDS: BT rows x 8 chunks of 16 bytes per operand; thread -> chunk tid % 8 of rows tid / 8 + 32 i
     const int lchunk = tid & 7, lrow = tid >> 3;
-    constexpr int RPT = BT / MP;        // records per row tile (FWD)
+    constexpr int RPT = BT / MP;        // records per row tile
     int slot_of[RPT];
-    if (FWD) {
 #pragma unroll
-        for (int q = 0; q < RPT; ++q) {
-            const int r = RPT * bm + q;
-            int worker = 0, ordinal = 0, slot = 0;
-            if (r < a.nrec) record_of(a, r, worker, ordinal, slot);
-            slot_of[q] = slot;
-        }
+    for (int q = 0; q < RPT; ++q) {
+        const int r = RPT * bm + q;
+        int worker = 0, ordinal = 0, slot = 0;
+        if (r < a.nrec) record_of(a, r, worker, ordinal, slot);
+        slot_of[q] = slot;
     }
     auto a_ptr = [&](int row, int stage) -> const unsigned short* {
-        if (FWD) return a.xb + ((int64_t)slot_of[row / MP] * MP + (row % MP)) * d + stage * KT;
-        return a.d1t + ((int64_t)slot_list[FWD ? 0 : stage] * H + bm * BT + row) * MP;
+        return a.xb + ((int64_t)slot_of[row / MP] * MP + (row % MP)) * d + stage * KT;
     };
-    auto b_ptr = [&](int row, int stage) -> const unsigned short* {
-        if (FWD) return a.w1r + (int64_t)(bn * BT + row) * d + stage * KT;
-        return a.xbt + ((int64_t)slot_list[FWD ? 0 : stage] * d + bn * BT + row) * MP;
-    };
+    auto b_ptr = [&](int row, int stage) -> const unsigned short* { return a.w1r + (int64_t)(bn * BT + row) * d + stage * KT; };
     // Operand stages travel global -> registers -> LDS.  A ring of PF register sets holds the stages that have been
     // asked for and not yet stored to LDS, so that PF stages (PF x BT x 256 bytes) are in flight per workgroup: with one
     // stage in flight a workgroup is bound by the latency of its loads, whatever the tile size.
     constexpr int PF = 3;
-    constexpr bool kAlways = FWD || SPLIT;   // the loops of these are long (d / 64 stages, or a share of many slots)
     u16x8 ra[PF][LP], rb[PF][LP];
     auto fetch = [&](auto slot, int stage) {
         constexpr int Q = decltype(slot)::value;
@@ -346,22 +308,20 @@ __global__ __launch_bounds__(256, 2) void mlp_contract_kernel(MlpArgs a) {
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, 2>;
-    if (stages > 0) fetch(I0{}, stage0);
-    if (stages > 1) fetch(I1{}, stage0 + 1);
-    if (stages > 2) fetch(I2{}, stage0 + 2);
-    if (stages > 0) stash(I0{}, 0);
+    fetch(I0{}, 0);
+    if (stages > 1) fetch(I1{}, 1);
+    if (stages > 2) fetch(I2{}, 2);
+    stash(I0{}, 0);
     __syncthreads();
     // stage st is in LDS buffer st & 1 and came from ring slot st % PF, which is free again
     auto one_stage = [&](auto cur, auto nxt, int st) {
         const int buf = st & 1;
         // (long loops: always issued, the last stages over again at the end.  Behind a branch the compiler no longer knows
         // how many loads are in flight and makes the stores to LDS below wait for all of them, these new ones included.)
-        if constexpr (kAlways) {
-            fetch(cur, stage0 + min(st + PF, stages - 1));
-            // the loads go out before anything else of the stage: moved down between the MFMAs, their registers get
-            // shared with the operand fragments, and every stage then starts by waiting for all loads in flight
-            __builtin_amdgcn_sched_barrier(0);
-        } else if (st + PF < stages) fetch(cur, stage0 + st + PF);
+        fetch(cur, min(st + PF, stages - 1));
+        // the loads go out before anything else of the stage: moved down between the MFMAs, their registers get
+        // shared with the operand fragments, and every stage then starts by waiting for all loads in flight
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int kk = 0; kk < KT / 16; ++kk) {
             bf16x8 fa[NF], fb[NF];
@@ -379,11 +339,10 @@ __global__ __launch_bounds__(256, 2) void mlp_contract_kernel(MlpArgs a) {
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
         }
         // (long loops: also after the last stage, whose other buffer nobody reads any more -- no branch, see above)
-        if constexpr (kAlways) stash(nxt, buf ^ 1);
-        else if (st + 1 < stages) stash(nxt, buf ^ 1);
+        stash(nxt, buf ^ 1);
         __syncthreads();
     };
-    if constexpr (kAlways) {
+    {
         // whole rounds of the ring without a branch inside, then what is left
         int st = 0;
         for (; st + PF <= stages; st += PF) {
@@ -393,12 +352,6 @@ __global__ __launch_bounds__(256, 2) void mlp_contract_kernel(MlpArgs a) {
         }
         if (st < stages) one_stage(I0{}, I1{}, st);
         if (st + 1 < stages) one_stage(I1{}, I2{}, st + 1);
-    } else {
-        for (int st = 0; st < stages; st += PF) {
-            one_stage(I0{}, I1{}, st);
-            if (st + 1 < stages) one_stage(I1{}, I2{}, st + 1);
-            if (st + 2 < stages) one_stage(I2{}, I0{}, st + 2);
-        }
     }
 
     // The result goes through LDS so that the global accesses of the epilogue run along rows.
@@ -416,27 +369,224 @@ __global__ __launch_bounds__(256, 2) void mlp_contract_kernel(MlpArgs a) {
                 Cs[row * LDC + col] = acc[i][j][e];
             }
     __syncthreads();
+#pragma unroll
+    for (int j = 0; j < BT * C4 / 256; ++j) {
+        const int q = tid + 256 * j;
+        const int row = q / C4, c4 = q % C4;
+        const f32x4 v = *reinterpret_cast<const f32x4*>(Cs + row * LDC + 4 * c4);
+        const int r = RPT * bm + row / MP;
+        if (r < a.nrec) {
+            const int n = bn * BT + 4 * c4;
+            const f32x4 b1 = *reinterpret_cast<const f32x4*>(a.params + (int64_t)H * d + n);
+            f32x4 h;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) { const float z = v[c] + b1[c]; h[c] = z > 0.0f ? z : 0.0f; }
+            *reinterpret_cast<f32x4*>(a.hbuf + ((int64_t)slot_of[row / MP] * MP + (row % MP)) * H + n) = h;
+        }
+    }
+}
+
+// ---- first-layer gradient: dW1[H x d] = sum over the consumed slots of delta1_l^T X_l, bf16 MFMA, 64 samples a stage ----
+// delta1 is kept transposed ([hidden][sample]), the layout of its operand.  The rows come from the bf16 copy of the sample
+// matrix by their sample ids, drawn again at the start, and stay row-major in LDS; the operand wants eight samples of a
+// feature per lane, which two transposing 64-bit LDS reads give (sixteen lanes pass the addresses of a block of 4 samples x
+// 16 features, lane r that of sample r / 4, features 4 (r % 4) .. + 3, and lane r receives feature r of the four samples).
+// So the forward pass writes no transposed copy of its rows (50 MB per update at K = 128, d = 3072, by one tile column of
+// its workgroups, for which the others had to wait) and nothing is kept per slot for it.
+// The 16-byte chunks of both tiles are permuted by row so that the lanes of a read hit different banks: unpadded, the two
+// stages and the ids of a share leave room for two workgroups per CU.
+// BT x BT output tile per workgroup; the two halves of a launch that differ:
+// SPLIT: a share of the consumed slots per workgroup, partial sums left in dw_part, which mlp_w1_update_kernel adds in
+// order; otherwise the epilogue applies the update.
+template <int BT> __device__ __forceinline__ int row_key(int s) { return BT == 128 ? 4 * (s & 3) : 4 * ((s >> 1) & 1); }
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+template <int BT, bool SPLIT>
+__global__ __launch_bounds__(256, 2) void mlp_grad_kernel(MlpArgs a) {
+    constexpr int WT = BT / 2;          // rows and columns per wave
+    constexpr int NF = WT / 32;         // 32 x 32 MFMA tiles per wave and dimension
+    constexpr int LP = BT / 32;         // 16-byte loads per thread, operand and stage
+    constexpr int CB = BT / 8;          // 16-byte chunks of a sample's part
+    constexpr int RB = 256 / CB;        // samples per load of the workgroup
+    extern __shared__ __attribute__((aligned(16))) unsigned short lds[];
+    unsigned short* As = lds;                       // [2][BT][64]  hidden unit, sample
+    unsigned short* Bs = lds + 2 * BT * KT;         // [2][64][BT]  sample, feature
+    uint32_t* ids = reinterpret_cast<uint32_t*>(lds + 4 * BT * KT);      // [slots of the share][64]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int d = a.d, H = a.H;
+    int bm = blockIdx.x, bn = blockIdx.y, bz = 0;
+    if constexpr (SPLIT) {
+        // One-dimensional launch.  Consecutive block ids go to different XCDs; the H / BT workgroups that read the same
+        // columns of the same slots (the large operand) take consecutive places on one XCD, so that they run together
+        // and those columns come from HBM once.
+        const int nbm = H / BT, nbn = d / BT;
+        const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
+        const int group = (idx / nbm) * 8 + xcd;          // (column tile, share)
+        bm = idx % nbm;
+        if (group >= nbn * a.nsplit) return;
+        bn = group % nbn;
+        bz = group / nbn;
+    } else {
+        // a launch with one more row of workgroups than there are column tiles: that row takes the small parameters of
+        // the update (they do not depend on the contraction), which saves a launch per update
+        if ((int)blockIdx.y == d / BT) { small_update_body<1>(a, blockIdx.x, gridDim.x); return; }
+    }
+    int stage0 = 0, stages = a.Kv;
+    if constexpr (SPLIT) {
+        const int per = (a.Kv + a.nsplit - 1) / a.nsplit;
+        stage0 = bz * per;
+        stages = max(0, min(per, a.Kv - stage0));
+    }
+    // the fused update reads its tile of the fp32 parameters now, not after the contraction that it does not depend on
+    constexpr int C4 = BT / 4;           // float4 groups per row
+    constexpr int NPRE = SPLIT ? 1 : BT * C4 / 256;
+    f32x4 wpre[NPRE];
+    if constexpr (!SPLIT) {
+#pragma unroll
+        for (int j = 0; j < NPRE; ++j) {
+            const int q = tid + 256 * j, row = q / C4, c4 = q % C4;
+            wpre[j] = *reinterpret_cast<const f32x4*>(a.params + (int64_t)(bm * BT + row) * d + bn * BT + 4 * c4);
+        }
+    }
+    // slots and sample ids of the share, once
+    __shared__ int slot_list[kShareSlots];
+    for (int l = tid; l < stages; l += 256) slot_list[l] = consumed_slot(a, stage0 + l);
+    for (int q = tid; q < stages * (MP / 4); q += 256)
+        *reinterpret_cast<uint4*>(ids + 4 * q) = consumed_ids(a, stage0 + q / (MP / 4), q % (MP / 4));
+    __syncthreads();
+
+    // delta1: chunk tid % 8 of hidden units tid / 8 + 32 i; rows: chunk tid % CB of samples tid / CB + RB i
+    const int lchunk = tid & 7, lrow = tid >> 3, bchunk = tid % CB, brow = tid / CB;
+    const unsigned short* const a_base = a.d1t + (int64_t)(bm * BT + lrow) * MP + 8 * lchunk;
+    const unsigned short* const b_base = a.Xb + bn * BT + 8 * bchunk;
+    // Operand stages travel global -> registers -> LDS.  A ring of PF register sets holds the stages that have been
+    // asked for and not yet stored to LDS, so that PF stages (PF x BT x 256 bytes) are in flight per workgroup: with one
+    // stage in flight a workgroup is bound by the latency of its loads, whatever the tile size.
+    constexpr int PF = 3;
+    u16x8 ra[PF][LP], rb[PF][LP];
+    uint32_t next_id[LP];                // of the stage that is asked for next
+    int next_slot = 0;
+    auto look_up = [&](int stage) {
+        const int st = min(stage, stages - 1);
+        next_slot = slot_list[st];
+#pragma unroll
+        for (int i = 0; i < LP; ++i) next_id[i] = ids[st * MP + brow + RB * i];
+    };
+    auto fetch = [&](auto slot) {
+        constexpr int Q = decltype(slot)::value;
+        const int64_t at = (int64_t)__builtin_amdgcn_readfirstlane(next_slot) * H * MP;
+#pragma unroll
+        for (int i = 0; i < LP; ++i) {
+            ra[Q][i] = *reinterpret_cast<const u16x8*>(a_base + at + 32 * i * MP);
+            rb[Q][i] = *reinterpret_cast<const u16x8*>(b_base + (uint64_t)next_id[i] * (uint32_t)d);
+        }
+    };
+    auto stash = [&](auto slot, int buf) {
+        constexpr int Q = decltype(slot)::value;
+#pragma unroll
+        for (int i = 0; i < LP; ++i) {
+            const int row = lrow + 32 * i, s = brow + RB * i;
+            *reinterpret_cast<u16x8*>(As + (buf * BT + row) * KT + 8 * (lchunk ^ (row & 7))) = ra[Q][i];
+            *reinterpret_cast<u16x8*>(Bs + (buf * KT + s) * BT + 8 * (bchunk ^ row_key<BT>(s))) = rb[Q][i];
+        }
+    };
+
+    const int wm = wave >> 1, wn = wave & 1;
+    f32x16 acc[NF][NF];
+#pragma unroll
+    for (int i = 0; i < NF; ++i)
+#pragma unroll
+        for (int j = 0; j < NF; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    if (stages > 0) {
+        look_up(0); fetch(I0{});
+        look_up(1); fetch(I1{});         // (a share of fewer stages asks for its last one again)
+        look_up(2); fetch(I2{});
+        look_up(3);
+        stash(I0{}, 0);
+    }
+    __syncthreads();
+    // transposing read: group of 16 lanes lane / 16, features 16 (group % 2), samples 8 (group / 2) of a 16-sample step
+    const int tr_s = 8 * (lane >> 5) + ((lane >> 2) & 3), tr_f = wn * WT + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+    auto transposed = [&](int buf, int s, int f) -> s16x4 {
+        const unsigned short* p = Bs + (buf * KT + s) * BT + 8 * ((f >> 3) ^ row_key<BT>(s)) + (f & 7);
+        return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(p));
+    };
+    // stage st is in LDS buffer st & 1 and came from ring slot st % PF, which is free again
+    auto one_stage = [&](auto cur, auto nxt, int st) {
+        const int buf = st & 1;
+        // Always issued, the last stage over again at the end.  Behind a branch the compiler no longer knows how many
+        // loads are in flight and makes the stores to LDS below wait for all of them, these new ones included.
+        fetch(cur);
+        // the loads go out before anything else of the stage: moved down between the MFMAs, their registers get
+        // shared with the operand fragments, and every stage then starts by waiting for all loads in flight
+        __builtin_amdgcn_sched_barrier(0);
+        look_up(st + PF + 1);
+#pragma unroll
+        for (int kk = 0; kk < KT / 16; ++kk) {
+            bf16x8 fa[NF], fb[NF];
+            // operand layout of the 32x32x16 MFMA: lane -> row lane % 32, depth 8 (lane / 32) .. + 7
+#pragma unroll
+            for (int i = 0; i < NF; ++i) {
+                const int row = wm * WT + i * 32 + (lane & 31);
+                fa[i] = *reinterpret_cast<const bf16x8*>(As + (buf * BT + row) * KT + 8 * ((2 * kk + (lane >> 5)) ^ (row & 7)));
+            }
+#pragma unroll
+            for (int j = 0; j < NF; ++j) {
+                const s16x4 lo = transposed(buf, 16 * kk + tr_s, tr_f + 32 * j), hi = transposed(buf, 16 * kk + tr_s + 4, tr_f + 32 * j);
+                fb[j] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+            }
+#pragma unroll
+            for (int i = 0; i < NF; ++i)
+#pragma unroll
+                for (int j = 0; j < NF; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+        }
+        // (also after the last stage, whose other buffer nobody reads any more: no branch, see above)
+        stash(nxt, buf ^ 1);
+        __syncthreads();
+    };
+    {
+        // whole rounds of the ring without a branch inside, then what is left
+        int st = 0;
+        for (; st + PF <= stages; st += PF) {
+            one_stage(I0{}, I1{}, st);
+            one_stage(I1{}, I2{}, st + 1);
+            one_stage(I2{}, I0{}, st + 2);
+        }
+        if (st < stages) one_stage(I0{}, I1{}, st);
+        if (st + 1 < stages) one_stage(I1{}, I2{}, st + 1);
+    }
+
+    // The result goes through LDS so that the global accesses of the epilogue run along rows.
+    // result layout: element e of lane -> row 8 (e / 4) + 4 (lane / 32) + e % 4, column lane % 32
+    constexpr int LDC = BT + 4;
+    float* Cs = reinterpret_cast<float*>(lds);      // [BT][LDC], over the operand buffers and ids
+#pragma unroll
+    for (int i = 0; i < NF; ++i)
+#pragma unroll
+        for (int j = 0; j < NF; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int row = wm * WT + i * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+                const int col = wn * WT + j * 32 + (lane & 31);
+                Cs[row * LDC + col] = acc[i][j][e];
+            }
+    __syncthreads();
     const float scale = a.lr / (float)a.Kv, invK = 1.0f / (float)a.Kv;
 #pragma unroll
     for (int j = 0; j < BT * C4 / 256; ++j) {
         const int q = tid + 256 * j;
         const int row = q / C4, c4 = q % C4;
         const f32x4 v = *reinterpret_cast<const f32x4*>(Cs + row * LDC + 4 * c4);
-        if (FWD) {
-            const int r = RPT * bm + row / MP;
-            if (r < a.nrec) {
-                const int n = bn * BT + 4 * c4;
-                const f32x4 b1 = *reinterpret_cast<const f32x4*>(a.params + (int64_t)H * d + n);
-                f32x4 h;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) { const float z = v[c] + b1[c]; h[c] = z > 0.0f ? z : 0.0f; }
-                *reinterpret_cast<f32x4*>(a.hbuf + ((int64_t)slot_of[row / MP] * MP + (row % MP)) * H + n) = h;
-            }
-        } else if constexpr (SPLIT) {
-            const int64_t p = (int64_t)(bm * BT + row) * d + bn * BT + 4 * c4;
+        const int64_t p = (int64_t)(bm * BT + row) * d + bn * BT + 4 * c4;
+        if constexpr (SPLIT) {
             *reinterpret_cast<f32x4*>(a.dw_part + (int64_t)bz * H * d + p) = v;
         } else {
-            const int64_t p = (int64_t)(bm * BT + row) * d + bn * BT + 4 * c4;
             f32x4 w = wpre[NPRE == 1 ? 0 : j];
             unsigned short wb[4];
 #pragma unroll
@@ -451,9 +601,7 @@ __global__ __launch_bounds__(256, 2) void mlp_contract_kernel(MlpArgs a) {
 // ---- Few records (small K): the forward pass straight from the sample matrix --------------------------------
 // One launch does what the gather kernel, the split forward contraction and its finishing kernel do otherwise:
 // workgroup (record r, 64 hidden units bn, share z of the depth d) draws the sample ids of the record, reads its rows
-// from the bf16 copy of X and leaves its partial sums of Z1 in dw_part; the workgroups
-// with bn = 0 also write the rows' transposed bf16 copy, which the first-layer gradient contraction of a later update
-// reads.  (Workgroups of one launch do not hand results to each other: making one workgroup's stores visible to
+// from the bf16 copy of X and leaves its partial sums of Z1 in dw_part.  (Workgroups of one launch do not hand results to each other: making one workgroup's stores visible to
 // another on a different XCD costs a write-back of the L2, far more than the launch it would save.)  A launch of this
 // kind is a chain of load latencies, so three stages per operand are in flight in registers.
 template <int BT, bool SPLIT>
@@ -526,10 +674,6 @@ __global__ __launch_bounds__(256, 2) void mlp_fwd_gather_kernel(MlpArgs a) {
         for (int j = 0; j < NF; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-    // The transposed bf16 copy of the rows (read by the gradient contraction of a later update) is written by the
-    // workgroups with bn = 0.  (Sharing it out between the workgroups that read the same rows was measured slower: the
-    // 2-byte LDS reads of the transposition then delay the operand reads of every workgroup, not of a quarter of them.
-    // Likewise the thread mapping below: eight samples per thread instead of sixteen was slower by a third.)
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, PF == 3 ? 2 : 0>;
@@ -562,25 +706,6 @@ __global__ __launch_bounds__(256, 2) void mlp_fwd_gather_kernel(MlpArgs a) {
 #pragma unroll
                 for (int j = 0; j < NF; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
-        }
-        if (bn == 0) {
-            // transposed copy of this stage's rows: thread -> feature tid / 4, samples 16 (tid % 4) .. + 15 of every record
-            const int k = tid >> 2, part = tid & 3;
-#pragma unroll
-            for (int q = 0; q < RPT; ++q) {
-                const int slot = slot_s[q];
-                if (slot >= 0) {
-                    u16x8 v0, v1;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        v0[e] = As[(buf * BT + q * MP + 16 * part + e) * LDT + k];
-                        v1[e] = As[(buf * BT + q * MP + 16 * part + 8 + e) * LDT + k];
-                    }
-                    unsigned short* dst = a.xbt + ((int64_t)slot * d + (int64_t)(stage0 + st) * KT + k) * MP + 16 * part;
-                    *reinterpret_cast<u16x8*>(dst) = v0;
-                    *reinterpret_cast<u16x8*>(dst + 8) = v1;
-                }
-            }
         }
         // (long loops: also after the last stage, whose other buffer nobody reads any more -- no branch, see above)
         if constexpr (kAlways) stash(nxt, buf ^ 1);
@@ -1074,6 +1199,8 @@ __global__ void mlp_init_kernel(float* params, uint64_t seed, int64_t nw, int64_
 
 // operand double buffer; the epilogue's fp32 tile [BT][BT + 4] fits inside it
 size_t contract_lds(int bt) { return (size_t)4 * bt * LDT * 2; }
+// gradient contraction: unpadded double buffer and the sample ids of `slots` slots, or the epilogue's tile
+size_t grad_lds(int bt, int slots) { return std::max((size_t)4 * bt * KT * 2 + (size_t)slots * MP * 4, sizeof(float) * (size_t)bt * (bt + 4)); }
 // Forward streams of the overlapped updates.  With the caller's stream and the stream of the schedule they are four:
 // a process has four hardware queues here, and streams that share one run their kernels one after the other (a long
 // schedule kernel in front of a forward kernel, say).
@@ -1104,7 +1231,8 @@ struct MlpState {
     DevMem w1v, w2v, b1v, b2v, fwd_part;   // allocated by the first segment that overlaps
     hipStream_t fwd_stream[kFwdStreams] = {};
     std::vector<hipEvent_t> ev_pool;
-    DevMem params, w1r, w2r, xb, xbt, hbuf, d1t, gb1, gw2, gb2, d2, loss, ylab, dw_part, plan, quartered;
+    size_t gap_bytes = 0;        // of a buffer that snapshots hold a place for
+    DevMem params, w1r, w2r, xb, hbuf, d1t, gb1, gw2, gb2, d2, loss, ylab, dw_part, plan, quartered;
     hipStream_t stream = nullptr;
 };
 
@@ -1133,7 +1261,7 @@ hipError_t mlp_create(MlpState** out, const ssgd_model& model, int P, int m, int
     TRY(s->w1r.alloc(2 * (size_t)n1));
     TRY(s->w2r.alloc(sizeof(float) * n2));
     TRY(s->xb.alloc(2 * S * MP * a.d));
-    TRY(s->xbt.alloc(2 * S * MP * a.d));
+    s->gap_bytes = 2 * S * MP * a.d;
     TRY(s->hbuf.alloc(sizeof(float) * S * MP * a.H));
     TRY(s->d1t.alloc(2 * S * MP * a.H));
     TRY(s->gb1.alloc(sizeof(float) * S * 4 * a.H));
@@ -1166,7 +1294,6 @@ hipError_t mlp_create(MlpState** out, const ssgd_model& model, int P, int m, int
         a.plan = (int32_t*)s->plan.p;
     }
     TRY(hipMemsetAsync(s->xb.p, 0, 2 * S * MP * a.d, stream));
-    TRY(hipMemsetAsync(s->xbt.p, 0, 2 * S * MP * a.d, stream));
     TRY(hipMemsetAsync(s->hbuf.p, 0, sizeof(float) * S * MP * a.H, stream));
     TRY(hipMemsetAsync(s->d1t.p, 0, 2 * S * MP * a.H, stream));
     TRY(hipMemsetAsync(s->gb1.p, 0, sizeof(float) * S * 4 * a.H, stream));
@@ -1175,7 +1302,7 @@ hipError_t mlp_create(MlpState** out, const ssgd_model& model, int P, int m, int
     TRY(hipMemsetAsync(s->loss.p, 0, sizeof(float) * S * 4, stream));
     TRY(hipMemsetAsync(s->ylab.p, 0xFF, sizeof(int32_t) * S * MP, stream));
     a.params = (float*)s->params.p; a.w1r = (unsigned short*)s->w1r.p; a.w2r = (float*)s->w2r.p;
-    a.xb = (unsigned short*)s->xb.p; a.xbt = (unsigned short*)s->xbt.p; a.hbuf = (float*)s->hbuf.p;
+    a.xb = (unsigned short*)s->xb.p; a.hbuf = (float*)s->hbuf.p;
     a.d1t = (unsigned short*)s->d1t.p; a.gb1 = (float*)s->gb1.p; a.gw2 = (float*)s->gw2.p; a.gb2 = (float*)s->gb2.p;
     a.loss = (float*)s->loss.p; a.ylab = (int32_t*)s->ylab.p; a.d2 = (float*)s->d2.p; a.quartered = (int32_t*)s->quartered.p;
     a.dw_part = (float*)s->dw_part.p; a.nsplit = 1; a.fsplit = 1; a.eval_base = -1;
@@ -1184,10 +1311,10 @@ hipError_t mlp_create(MlpState** out, const ssgd_model& model, int P, int m, int
     const float bound1 = (float)(1.0 / sqrt((double)a.d)), bound2 = (float)(1.0 / sqrt((double)a.H));
     hipLaunchKernelGGL(mlp_init_kernel, dim3(1024), dim3(256), 0, stream, a.params, seed, s->nw, n1, off2, n2, bound1, bound2);
     TRY(hipGetLastError());
-    TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_contract_kernel<true, 128>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)contract_lds(128)));
-    TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_contract_kernel<true, 64>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)contract_lds(64)));
-    TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_contract_kernel<false, 64>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)contract_lds(64)));
-    TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_contract_kernel<false, 128, true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)contract_lds(128)));
+    TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_contract_kernel<128>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)contract_lds(128)));
+    TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_contract_kernel<64>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)contract_lds(64)));
+    TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_grad_kernel<64, false>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)grad_lds(64, 32)));
+    TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_grad_kernel<128, true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)grad_lds(128, kShareSlots)));
     TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_mid_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)mid_lds_bytes(1024)));
     TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_fwd_gather_kernel<128, false>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)contract_lds(128)));
     TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_fwd_gather_kernel<64, true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)contract_lds(64)));
@@ -1242,15 +1369,16 @@ void launch_backward(MlpArgs& a, hipStream_t stream, hipEvent_t done = nullptr) 
         // many slots: 128 x 128 tiles (half the operand traffic of the small ones), the slots split into shares so
         // that the chip is still full; the shares are added, in order, by the update kernel
         // (as many shares as keep all workgroups resident at once, two per CU on 256 CUs: a second, partial round of
-        // workgroups costs more than the shorter shares gain)
+        // workgroups costs more than the shorter shares gain; more only where a share would be longer than its id list)
         const int tiles = (a.H / 128) * (a.d / 128);
-        a.nsplit = std::max(1, std::min({kMaxSplit, a.Kv / 8, 512 / tiles}));
-        hipLaunchKernelGGL((mlp_contract_kernel<false, 128, true>), dim3((a.H / 128) * 8 * (((a.d / 128) * a.nsplit + 7) / 8)), dim3(256), contract_lds(128), stream, a);
+        a.nsplit = std::max({1, std::min({kMaxSplit, a.Kv / 8, 512 / tiles}), (a.Kv + kShareSlots - 1) / kShareSlots});
+        hipLaunchKernelGGL((mlp_grad_kernel<128, true>), dim3((a.H / 128) * 8 * (((a.d / 128) * a.nsplit + 7) / 8)), dim3(256),
+                           grad_lds(128, (a.Kv + a.nsplit - 1) / a.nsplit), stream, a);
         hipExtLaunchKernelGGL(mlp_w1_update_kernel, dim3(kW1Blocks + kSmallBlocks16), dim3(256), 0, stream, nullptr, done, 0, a);
     } else {
         // small tiles: 384 workgroups instead of 96 matter more than the reuse inside a larger tile; one more row of
         // workgroups takes the small parameters
-        hipExtLaunchKernelGGL((mlp_contract_kernel<false, 64>), dim3(a.H / 64, a.d / 64 + 1), dim3(256), contract_lds(64), stream, nullptr, done, 0, a);
+        hipExtLaunchKernelGGL((mlp_grad_kernel<64, false>), dim3(a.H / 64, a.d / 64 + 1), dim3(256), grad_lds(64, a.Kv), stream, nullptr, done, 0, a);
     }
 }
 void launch_update(MlpArgs& a, hipStream_t stream) {
@@ -1440,6 +1568,7 @@ hipError_t mlp_run_segment(MlpState* const* states, int R, const Trace& tr, cons
             a.n_cons_inline = 0; a.n_rec_inline = 0;
             if (Kv <= 32) {
                 a.n_cons_inline = Kv;
+                for (int l = 0; l < Kv; ++l) a.cons_tau[l] = tau_host[(size_t)((v - v0) * tr.Kcap + l)];
                 for (int l = 0; l < Kv; ++l) a.cons_inline[l] = (int16_t)sel_host[(size_t)((v - sel_first) * tr.Kcap + l)];
             }
             if (v >= 1 && nrec <= 32) {
@@ -1613,7 +1742,7 @@ hipError_t mlp_full_loss(MlpState* s, double* out, hipStream_t stream, std::stri
     if (e == hipSuccess) e = loss.alloc(sizeof(float) * (size_t)E * 4);
     if (e == hipSuccess) e = ylab.alloc(sizeof(int32_t) * (size_t)E * MP);
     if (e != hipSuccess) { release(); return fail(e, "allocating the evaluation buffers"); }
-    a.xb = (unsigned short*)xb.p; a.xbt = nullptr; a.hbuf = (float*)hbuf.p; a.d2 = (float*)d2.p;
+    a.xb = (unsigned short*)xb.p; a.hbuf = (float*)hbuf.p; a.d2 = (float*)d2.p;
     a.loss = (float*)loss.p; a.ylab = (int32_t*)ylab.p;
     a.d1t = nullptr; a.gb1 = nullptr; a.gw2 = nullptr; a.gb2 = nullptr; a.agg_out = nullptr;
     a.m = MP; a.v = 0; a.Kv = 1;
@@ -1626,9 +1755,9 @@ hipError_t mlp_full_loss(MlpState* s, double* out, hipStream_t stream, std::stri
         a.nrec = (int)std::min<int64_t>(E, nslot - s0);
         hipLaunchKernelGGL(mlp_gather_kernel, dim3(a.nrec, a.d / 128), dim3(256), 0, stream, a);
         if (((a.nrec + 1) / 2) * (a.H / 128) >= 192)
-            hipLaunchKernelGGL((mlp_contract_kernel<true, 128>), dim3((a.nrec + 1) / 2, a.H / 128), dim3(256), contract_lds(128), stream, a);
+            hipLaunchKernelGGL((mlp_contract_kernel<128>), dim3((a.nrec + 1) / 2, a.H / 128), dim3(256), contract_lds(128), stream, a);
         else
-            hipLaunchKernelGGL((mlp_contract_kernel<true, 64>), dim3(a.nrec, a.H / 64), dim3(256), contract_lds(64), stream, a);
+            hipLaunchKernelGGL((mlp_contract_kernel<64>), dim3(a.nrec, a.H / 64), dim3(256), contract_lds(64), stream, a);
         hipLaunchKernelGGL(mlp_output_kernel, dim3(a.nrec), dim3(256), 0, stream, a);
         e = hipGetLastError();
         if (e == hipSuccess) e = hipMemcpyAsync(h.data(), a.loss, sizeof(float) * a.nrec * 4, hipMemcpyDeviceToHost, stream);
@@ -1653,17 +1782,17 @@ hipError_t mlp_full_gradient(MlpState* s, float* grad_out_host, hipStream_t stre
     MlpArgs a = s->a;
     const int64_t N = (int64_t)a.N, nslot = (N + MP - 1) / MP;
     const size_t E = (size_t)std::min<int64_t>(nslot, 256);
-    DevMem xb, xbt, hbuf, d1t, gb1, gw2, gb2, d2, loss, ylab, quart, agg, tloss;
-    DevMem* all[] = {&xb, &xbt, &hbuf, &d1t, &gb1, &gw2, &gb2, &d2, &loss, &ylab, &quart, &agg, &tloss};
+    DevMem xb, hbuf, d1t, gb1, gw2, gb2, d2, loss, ylab, quart, agg, tloss;
+    DevMem* all[] = {&xb, &hbuf, &d1t, &gb1, &gw2, &gb2, &d2, &loss, &ylab, &quart, &agg, &tloss};
     auto release = [&]() { for (DevMem* b : all) b->release(); };
-    const size_t sizes[] = {2 * E * MP * a.d, 2 * E * MP * a.d, sizeof(float) * E * MP * a.H, 2 * E * MP * a.H,
+    const size_t sizes[] = {2 * E * MP * a.d, sizeof(float) * E * MP * a.H, 2 * E * MP * a.H,
                             sizeof(float) * E * 4 * a.H, sizeof(float) * E * 4 * a.C * a.H, sizeof(float) * E * 4 * 16,
                             sizeof(float) * E * MP * 16, sizeof(float) * E * 4, sizeof(int32_t) * E * MP, sizeof(int32_t) * E,
                             sizeof(float) * (size_t)s->nw, sizeof(float) * 16};
     hipError_t e = hipSuccess;
     for (size_t q = 0; q < sizeof(all) / sizeof(all[0]) && e == hipSuccess; ++q) e = all[q]->alloc(sizes[q]);
     if (e != hipSuccess) { release(); return fail(e, "allocating the evaluation buffers"); }
-    a.xb = (unsigned short*)xb.p; a.xbt = (unsigned short*)xbt.p; a.hbuf = (float*)hbuf.p; a.d1t = (unsigned short*)d1t.p;
+    a.xb = (unsigned short*)xb.p; a.hbuf = (float*)hbuf.p; a.d1t = (unsigned short*)d1t.p;
     a.gb1 = (float*)gb1.p; a.gw2 = (float*)gw2.p; a.gb2 = (float*)gb2.p; a.d2 = (float*)d2.p; a.loss = (float*)loss.p;
     a.ylab = (int32_t*)ylab.p; a.quartered = (int32_t*)quart.p; a.agg_out = (float*)agg.p;
     a.tr.loss = (float*)tloss.p;       // the loss record of the pretended update goes nowhere
@@ -1687,19 +1816,12 @@ hipError_t mlp_full_gradient(MlpState* s, float* grad_out_host, hipStream_t stre
         a.Kv = a.nrec;
         hipLaunchKernelGGL(mlp_gather_kernel, dim3(a.nrec, a.d / 128), dim3(256), 0, stream, a);
         if (((a.nrec + 1) / 2) * (a.H / 128) >= 192)
-            hipLaunchKernelGGL((mlp_contract_kernel<true, 128>), dim3((a.nrec + 1) / 2, a.H / 128), dim3(256), contract_lds(128), stream, a);
+            hipLaunchKernelGGL((mlp_contract_kernel<128>), dim3((a.nrec + 1) / 2, a.H / 128), dim3(256), contract_lds(128), stream, a);
         else
-            hipLaunchKernelGGL((mlp_contract_kernel<true, 64>), dim3(a.nrec, a.H / 64), dim3(256), contract_lds(64), stream, a);
+            hipLaunchKernelGGL((mlp_contract_kernel<64>), dim3(a.nrec, a.H / 64), dim3(256), contract_lds(64), stream, a);
         hipLaunchKernelGGL(mlp_output_kernel, dim3(a.nrec), dim3(256), 0, stream, a);
         hipLaunchKernelGGL(mlp_delta1_kernel, dim3(a.nrec, a.H / 64), dim3(256), 0, stream, a);
-        if (a.Kv >= 32) {
-            const int tiles = (a.H / 128) * (a.d / 128);
-            a.nsplit = std::max(1, std::min({kMaxSplit, a.Kv / 8, 512 / tiles}));
-            hipLaunchKernelGGL((mlp_contract_kernel<false, 128, true>), dim3((a.H / 128) * 8 * (((a.d / 128) * a.nsplit + 7) / 8)), dim3(256), contract_lds(128), stream, a);
-            hipLaunchKernelGGL(mlp_w1_update_kernel, dim3(kW1Blocks + kSmallBlocks16), dim3(256), 0, stream, a);
-        } else {
-            hipLaunchKernelGGL((mlp_contract_kernel<false, 64>), dim3(a.H / 64, a.d / 64 + 1), dim3(256), contract_lds(64), stream, a);
-        }
+        launch_backward(a, stream);
         e = hipGetLastError();
         if (e == hipSuccess) e = hipMemcpyAsync(h.data(), a.agg_out, sizeof(float) * (size_t)s->nw, hipMemcpyDeviceToHost, stream);
         if (e == hipSuccess) e = hipStreamSynchronize(stream);
@@ -1714,15 +1836,16 @@ hipError_t mlp_full_gradient(MlpState* s, float* grad_out_host, hipStream_t stre
 }
 
 // Everything a later update depends on: parameters (fp32 master and operand copies) and the factors of the
-// mini-batches in flight, slot by slot.
+// mini-batches in flight, slot by slot.  The null stands for a copy of their rows that snapshots used to hold: its place
+// is kept, so that they keep their layout, and filled with zeros.
 static std::vector<DevMem*> mlp_state_buffers(MlpState* s) {
-    return {&s->params, &s->w1r, &s->w2r, &s->xb, &s->xbt, &s->hbuf, &s->d1t, &s->gb1, &s->gw2, &s->gb2, &s->d2, &s->loss,
+    return {&s->params, &s->w1r, &s->w2r, &s->xb, nullptr, &s->hbuf, &s->d1t, &s->gb1, &s->gw2, &s->gb2, &s->d2, &s->loss,
             &s->ylab, &s->plan, &s->quartered};
 }
 
 int64_t mlp_state_bytes(MlpState* s) {
     int64_t n = 8;
-    for (DevMem* b : mlp_state_buffers(s)) n += (int64_t)b->bytes;
+    for (DevMem* b : mlp_state_buffers(s)) n += (int64_t)(b ? b->bytes : s->gap_bytes);
     return n;
 }
 
@@ -1731,6 +1854,7 @@ hipError_t mlp_get_state(MlpState* s, unsigned char* host) {
     memcpy(host, &k, 8);
     size_t off = 8;
     for (DevMem* b : mlp_state_buffers(s)) {
+        if (!b) { memset(host + off, 0, s->gap_bytes); off += s->gap_bytes; continue; }
         hipError_t e = hipMemcpy(host + off, b->p, b->bytes, hipMemcpyDeviceToHost);
         if (e != hipSuccess) return e;
         off += b->bytes;
@@ -1744,6 +1868,7 @@ hipError_t mlp_set_state(MlpState* s, const unsigned char* host) {
     s->prevK = (int)k;
     size_t off = 8;
     for (DevMem* b : mlp_state_buffers(s)) {
+        if (!b) { off += s->gap_bytes; continue; }
         hipError_t e = hipMemcpy(b->p, host + off, b->bytes, hipMemcpyHostToDevice);
         if (e != hipSuccess) return e;
         off += b->bytes;
@@ -1758,7 +1883,7 @@ void mlp_destroy(MlpState* s) {
     if (s->own) { (void)hipStreamSynchronize(s->own); (void)hipStreamDestroy(s->own); }
     for (hipStream_t& f : s->fwd_stream) if (f) { (void)hipStreamSynchronize(f); (void)hipStreamDestroy(f); }
     for (hipEvent_t ev : s->ev_pool) (void)hipEventDestroy(ev);
-    DevMem* bufs[] = {&s->params, &s->w1r, &s->w2r, &s->xb, &s->xbt, &s->hbuf, &s->d1t, &s->gb1, &s->gw2, &s->gb2, &s->d2, &s->loss, &s->ylab,
+    DevMem* bufs[] = {&s->params, &s->w1r, &s->w2r, &s->xb, &s->hbuf, &s->d1t, &s->gb1, &s->gw2, &s->gb2, &s->d2, &s->loss, &s->ylab,
                       &s->dw_part, &s->plan, &s->quartered, &s->w1v, &s->w2v, &s->b1v, &s->b2v, &s->fwd_part, &s->xb16};
     for (DevMem* b : bufs) b->release();
     delete s;
