@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -17,6 +18,42 @@ using namespace ssgd;
 namespace {
 
 thread_local std::string g_err;
+
+// Pinned host memory outlives the context that asked for it: taking a block and giving it back cost 30 and 50 us, more
+// than anything else in making and destroying a small context.  At most kMaxSpare blocks of at most kSpareBytes are kept,
+// per device, for whoever asks next; a block is given back when nothing queued can write to it any more.
+struct PinnedPool {
+    static constexpr size_t kMaxSpare = 8, kSpareBytes = 4 << 20, kLeastBytes = 64 << 10;
+    struct Block { void* p; size_t bytes; int device; };
+    std::mutex mutex;
+    std::vector<Block> spare;
+    hipError_t take(size_t bytes, int device, void** p, size_t* got) {
+        bytes = std::max(bytes, kLeastBytes);
+        {
+            std::lock_guard<std::mutex> lock(mutex);
+            for (size_t q = 0; q < spare.size(); ++q)
+                if (spare[q].device == device && spare[q].bytes >= bytes) {
+                    *p = spare[q].p; *got = spare[q].bytes;
+                    spare.erase(spare.begin() + (ptrdiff_t)q);
+                    return hipSuccess;
+                }
+        }
+        const hipError_t e = hipHostMalloc(p, bytes, hipHostMallocDefault);
+        if (e == hipSuccess) *got = bytes; else *p = nullptr;
+        return e;
+    }
+    void give(void* p, size_t bytes, int device) {
+        if (!p) return;
+        {
+            std::lock_guard<std::mutex> lock(mutex);
+            if (spare.size() < kMaxSpare && bytes <= kSpareBytes && spare.capacity() > spare.size()) { spare.push_back({p, bytes, device}); return; }
+        }
+        (void)hipHostFree(p);
+    }
+    PinnedPool() { spare.reserve(kMaxSpare); }
+};
+// (never destroyed: the runtime may be gone by the time static objects are)
+PinnedPool& pinned_pool() { static PinnedPool* pool = new PinnedPool; return *pool; }
 
 struct DevBuf {
     void* p = nullptr;
@@ -45,6 +82,7 @@ struct ssgd_ctx {
     size_t host_rows_words = 0;
     void* host_out = nullptr;       // pinned: kernels leave results here that a call hands to the caller (host_out_room)
     size_t host_out_bytes = 0;
+    size_t host_flags_bytes = 0;
     int32_t* host_flags = nullptr;  // pinned: abort flag and one fall-back flag per replica, written by flags_kernel behind the kernels that raise them
     bool flags_seen = false;        // host_flags holds the flags of everything queued so far (the stream has been waited for)
     DevBuf fg_work;                 // partial gradients of ssgd_full_gradient, kept from its first call on
@@ -93,11 +131,9 @@ ssgd_status fail(ssgd_ctx* c, ssgd_status st, const std::string& msg) {
 // saves the copy command and its staging.
 hipError_t host_out_room(ssgd_ctx* c, size_t bytes) {
     if (c->host_out_bytes >= bytes) return hipSuccess;
-    if (c->host_out) (void)hipHostFree(c->host_out);
+    pinned_pool().give(c->host_out, c->host_out_bytes, c->device);     // every writer has been waited for by the call that launched it
     c->host_out = nullptr; c->host_out_bytes = 0;
-    const hipError_t e = hipHostMalloc(&c->host_out, bytes, hipHostMallocDefault);
-    if (e == hipSuccess) c->host_out_bytes = bytes;
-    return e;
+    return pinned_pool().take(bytes, c->device, &c->host_out, &c->host_out_bytes);
 }
 
 // Rows of several device arrays, one behind the other, to memory that the host reads: one launch and one wait where a
@@ -639,7 +675,7 @@ ssgd_status ssgd_create(const ssgd_model* model, int32_t P, int32_t K, int32_t m
     }
     c->tr.Kcap = Kcap; c->tr.cap = 0;
     HIP_C(c->abort_flag.alloc(sizeof(int32_t)));
-    HIP_C(hipHostMalloc((void**)&c->host_flags, sizeof(int32_t) * (size_t)(1 + R), hipHostMallocDefault));
+    HIP_C(pinned_pool().take(sizeof(int32_t) * (size_t)(1 + R), c->device, (void**)&c->host_flags, &c->host_flags_bytes));
     HIP_C(hipMemsetAsync(c->abort_flag.p, 0, sizeof(int32_t), c->stream));
 
     if (model->kind == SSGD_MLP2) {
@@ -1142,8 +1178,8 @@ void ssgd_destroy(ssgd_ctx* c) {
     for (size_t r = c->mlp.size(); r-- > 0;) mlp_destroy(c->mlp[r]);   // the first one owns what the others share
     if (c->side) (void)hipStreamDestroy(c->side);
     if (c->host_rows) (void)hipHostFree(c->host_rows);
-    if (c->host_out) (void)hipHostFree(c->host_out);
-    if (c->host_flags) (void)hipHostFree(c->host_flags);
+    pinned_pool().give(c->host_out, c->host_out_bytes, c->device);
+    pinned_pool().give(c->host_flags, c->host_flags_bytes, c->device);
     DevBuf* bufs[] = {&c->table, &c->tr_t, &c->tr_loss, &c->tr_K, &c->tr_sel, &c->tr_tau, &c->tr_ord, &c->ws_finish,
                       &c->ws_tau, &c->ws_ord, &c->ws_clock, &c->ws_curK, &c->ws_winprev, &c->ws_winidx, &c->ws_F0,
                       &c->ws_intstart, &c->ws_crossed, &c->ws_ndone, &c->params, &c->park, &c->park_small, &c->zpart, &c->zx, &c->dx, &c->fallback,

@@ -908,6 +908,31 @@ def test_one_slice(ssgd, oracle, torch_cuda, monkeypatch, kind, variant, P, K, m
     assert rel(ctx.params(), orc.params()) <= FP32_PARAM_TOL
 
 
+def test_contexts_one_after_the_other_and_side_by_side_share_no_results(ssgd, torch_cuda):
+    """Pinned blocks go from a destroyed context to the next one: what a context hands out is its own, whatever the
+    others are doing, from several threads too."""
+    import threading
+    X, y, _ = synth.lsq_data(600, 32, 3)
+    Xd, yd = torch_cuda.from_numpy(X).cuda(), torch_cuda.from_numpy(y).cuda()
+
+    def once(seed):
+        ctx = ssgd.Context("lsq", Xd, yd, 4, 2, 8, "k_async", ssgd.delay_dist("exp", 1.0), 0.01, seed=seed, replicas=2)
+        ctx.run(20)
+        out = (ctx.trace(1)["t"].tobytes(), ctx.params(1).tobytes(), ctx.full_gradient(1).tobytes())
+        ctx.close()
+        return out
+
+    alone = [once(s) for s in range(4)]
+    got = [[] for _ in range(4)]
+    threads = [threading.Thread(target=lambda s=s: got[s].extend(once(s) for _ in range(6))) for s in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for s in range(4):
+        assert len(got[s]) == 6 and all(g == alone[s] for g in got[s])
+
+
 def test_adasync_ksync_rule_with_growing_tile_count(ssgd, oracle, torch_cuda):
     """K-sync under the paper's rule for K (Appendix D): K grows from 2 to 16 during the run, so the iterations go
     from one tile to two; trace and parameters against the oracle."""
