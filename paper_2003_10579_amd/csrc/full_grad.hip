@@ -14,7 +14,7 @@
 // and CU, below the 23 000 cycles that the rows take to arrive.
 // full_grad_reduce_kernel adds the workgroups' partial gradients in order in fp64.
 // N = 50000, d = 3072, 10 classes: 199 us (3.1 TB/s) + 10 us for the reduction, where the two passes below took 518 +
-// 297 + 35; N = 4096, d = 256, least squares: 5 + 5 us where they took 5 + 40 + 6 (32 workgroups in the second pass).
+// 297 + 35; N = 4096, d = 256, least squares: 5 + 3 us where they took 5 + 40 + 6 (32 workgroups in the second pass).
 //
 // Shapes whose weights do not fit the LDS beside that (more than about 11 classes at d = 3072, or d > 3072) take two
 // passes: deltas to memory (16 floats per sample), then G[c][col] = sum_n delta[n][c] X[n][col] with a thread per column.
@@ -287,14 +287,17 @@ __global__ __launch_bounds__(256) void full_grad_partial_kernel(FullGradArgs a) 
         for (int c = 0; c < C; ++c) a.partial[((int64_t)blockIdx.y * C + c) * (d + 1) + col] = acc[c];
 }
 
-// 64 outputs per workgroup; each of the four waves adds a quarter of the partial gradients (fp64, in order), the quarters
-// are added in order.  A wave keeps eight loads in flight: the partial gradients are what it waits for.
-__global__ __launch_bounds__(256) void full_grad_reduce_kernel(FullGradArgs a) {
-    __shared__ double quarters[4][64];
+// 64 outputs per workgroup; each of the sixteen waves adds a sixteenth of the partial gradients (fp64, in order), their sums
+// are added in order.  What bounds it is the chain of loads of a wave, eight in flight at a time: with four waves and 256
+// partial gradients it was eight round trips to memory deep, now it is two (256 partial gradients of 4096 x 256 least
+// squares: 5.3 -> 3.3 us; those of d = 3072, 10 classes, 31 MB: 10 us either way).
+constexpr int kReduceWaves = 16;
+__global__ __launch_bounds__(64 * kReduceWaves) void full_grad_reduce_kernel(FullGradArgs a) {
+    __shared__ double parts[kReduceWaves][64];
     const int d = a.d, C = a.C, lane = threadIdx.x & 63, part = threadIdx.x >> 6;
     const int total = C * (d + 1);
     const int q = blockIdx.x * 64 + lane;
-    const int per = (a.chunks + 3) / 4, ch0 = part * per, ch1 = min(a.chunks, ch0 + per);
+    const int per = (a.chunks + kReduceWaves - 1) / kReduceWaves, ch0 = part * per, ch1 = min(a.chunks, ch0 + per);
     double sum = 0.0;
     if (q < total) {
         const float* src = a.partial + q;
@@ -308,10 +311,12 @@ __global__ __launch_bounds__(256) void full_grad_reduce_kernel(FullGradArgs a) {
         }
         for (; ch < ch1; ++ch) sum += (double)src[(int64_t)ch * total];
     }
-    quarters[part][lane] = sum;
+    parts[part][lane] = sum;
     __syncthreads();
     if (part == 0 && q < total) {
-        sum = ((quarters[0][lane] + quarters[1][lane]) + quarters[2][lane]) + quarters[3][lane];
+        sum = parts[0][lane];
+#pragma unroll
+        for (int p = 1; p < kReduceWaves; ++p) sum += parts[p][lane];
         const int c = q / (d + 1), col = q - c * (d + 1);
         const float gr = (float)(sum / (double)a.N);
         if (col < d) a.out[(int64_t)c * d + col] = gr;
@@ -427,7 +432,7 @@ hipError_t launch_full_grad(int kind, const float* X, const void* y, int64_t N, 
         else hipLaunchKernelGGL(full_grad_delta_kernel<kSoftmax>, dim3(blocks), dim3(256), 0, s, a);
         hipLaunchKernelGGL(full_grad_partial_kernel, dim3((d + 1 + 255) / 256, a.chunks), dim3(256), 0, s, a);
     }
-    hipLaunchKernelGGL(full_grad_reduce_kernel, dim3((C * (d + 1) + 63) / 64), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(full_grad_reduce_kernel, dim3((C * (d + 1) + 63) / 64), dim3(64 * kReduceWaves), 0, s, a);
     return hipGetLastError();
 }
 
