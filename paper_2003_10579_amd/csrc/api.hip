@@ -464,8 +464,8 @@ ssgd_status run_updates(ssgd_ctx* c, int64_t J, float* agg_out) {
         const bool linear_async = c->model.kind != SSGD_MLP2 && (c->variant == SSGD_K_ASYNC || c->variant == SSGD_K_BATCH_ASYNC);
         const bool leaves_room = c->defer_per_launch >= 1 || (c->tile_resident_groups >= c->G && ((c->R + 7) / 8 * 8 * c->G <= c->cu_count));
         const bool linear_pipe = linear_async && leaves_room && agg_out == nullptr;
-        // (one replica of the network takes the rows of a piece as they come: short pieces, so that the first one of a
-        // segment, whose schedule nothing hides, is soon there)
+        // (one replica of the network takes the rows of a piece as they come: short pieces, the first one shorter still,
+        // since nothing hides its schedule: 10 us per update at P = 256, K = 8, 26 at K = 128)
         const int64_t kPiece = c->model.kind == SSGD_MLP2 ? (c->R == 1 ? 16 : 64) : 64;
         const int64_t kLongest = c->model.kind == SSGD_MLP2 ? kPiece : 1024;
         const bool pipelined = (c->model.kind == SSGD_MLP2 || linear_pipe) && c->ada.mode < 2 && seg > (linear_pipe ? 2 * kPiece : kPiece);
@@ -495,7 +495,12 @@ ssgd_status run_updates(ssgd_ctx* c, int64_t J, float* agg_out) {
                     e = hipMemcpyAsync(hsel, c->tr.sel + (size_t)(c->j - 1) * W, sizeof(int32_t) * W, hipMemcpyDeviceToHost, c->side);
             }
             std::vector<int64_t> lengths;        // of the pieces
-            for (int64_t off = 0, len = kPiece; off < seg; off += lengths.back(), len = std::min(3 * len, kLongest)) lengths.push_back(std::min(len, seg - off));
+            std::vector<int64_t> firsts;         // where they begin, and the end of the last one
+            for (int64_t off = 0, len = one_call ? kPiece / 4 : kPiece; off < seg; off += lengths.back(), len = one_call ? kPiece : std::min(3 * len, kLongest)) {
+                firsts.push_back(off);
+                lengths.push_back(std::min(len, seg - off));
+            }
+            firsts.push_back(seg);
             int64_t sched_off = 0;
             for (size_t q = 0; q < lengths.size() && e == hipSuccess; sched_off += lengths[q], ++q) {
                 const int64_t off = sched_off;
@@ -517,7 +522,7 @@ ssgd_status run_updates(ssgd_ctx* c, int64_t J, float* agg_out) {
             ssgd_status lin_st = SSGD_OK;
             if (one_call && e == hipSuccess) {
                 // (the kernels are launched after the host has seen a piece's event: no stream has to wait for it)
-                MlpPieces pc{written.data(), (int)written.size(), kPiece, hK, htau, hsel};
+                MlpPieces pc{written.data(), (int)written.size(), firsts.data(), hK, htau, hsel};
                 e = mlp_run_segment(c->mlp.data(), c->R, c->tr, c->ws, c->j, seg, agg_out, c->stream, &c->last_ms, &c->last_launches, &msg, &pc);
             }
             for (int64_t off = 0; off < seg && e == hipSuccess && lin_st == SSGD_OK && !one_call; off += lengths[k], ++k) {

@@ -1395,7 +1395,7 @@ hipError_t mlp_run_segment(MlpState* const* states, int R, const Trace& tr, cons
                            float* agg_out, hipStream_t stream, double* ms_accum, int64_t* launches, std::string* msg,
                            const MlpPieces* pieces) {
     auto fail = [&](hipError_t e, const char* what) { if (msg) *msg = what; return e; };
-    if (pieces != nullptr && (R != 1 || pieces->count < 1 || pieces->len < 1 || pieces->count * pieces->len < n))
+    if (pieces != nullptr && (R != 1 || pieces->count < 1 || pieces->first[0] != 0 || pieces->first[pieces->count] != n))
         return fail(hipErrorInvalidValue, "pieces of a segment: one replica, and they cover the segment");
     std::vector<MlpArgs> args((size_t)R);
     std::vector<std::vector<int32_t>> Ks((size_t)R, std::vector<int32_t>((size_t)n));
@@ -1463,7 +1463,7 @@ hipError_t mlp_run_segment(MlpState* const* states, int R, const Trace& tr, cons
         const int k = pieces_taken;
         const hipError_t pe = hipEventSynchronize(pieces->ready[k]);
         if (pe != hipSuccess) return pe;
-        const int64_t qa = (int64_t)k * pieces->len, qb = std::min<int64_t>(n, qa + pieces->len);
+        const int64_t qa = pieces->first[k], qb = pieces->first[k + 1];
         const size_t W = (size_t)tr.Kcap;
         std::memcpy(Ks[0].data() + qa, pieces->K + qa, sizeof(int32_t) * (size_t)(qb - qa));
         std::memcpy(tau_host.data() + (size_t)qa * W, pieces->tau + (size_t)qa * W, sizeof(int32_t) * (size_t)(qb - qa) * W);
@@ -1506,11 +1506,20 @@ hipError_t mlp_run_segment(MlpState* const* states, int R, const Trace& tr, cons
     // (worth it where at most a quarter of the lists of the segment name their own version)
     int64_t q0 = n;
     if (tau_host.size() == (size_t)(n * tr.Kcap) && n >= 4 && args[0].variant == kAsync && agg_out == nullptr) {
-        int64_t own = 0;
-        for (int64_t q = 0; q < avail; ++q) {
-            bool names_itself = false;
-            for (int l = 0; l < Ks[0][(size_t)q]; ++l) names_itself |= tau_host[(size_t)(q * tr.Kcap + l)] >= (int32_t)(v0 + q);
-            own += names_itself ? 1 : 0;
+        int64_t own = 0, counted = 0;
+        auto count_own = [&]() {
+            for (; counted < avail; ++counted) {
+                bool names_itself = false;
+                for (int l = 0; l < Ks[0][(size_t)counted]; ++l) names_itself |= tau_host[(size_t)(counted * tr.Kcap + l)] >= (int32_t)(v0 + counted);
+                own += names_itself ? 1 : 0;
+            }
+        };
+        count_own();
+        // (the first piece is too short to tell unless its lists agree)
+        if (pieces != nullptr && pieces_taken < pieces->count && own > 0 && 4 * own < 3 * avail) {
+            const hipError_t pe = take_piece();
+            if (pe != hipSuccess) { drop(); return fail(pe, "the second piece of the schedule"); }
+            count_own();
         }
         if (4 * own <= avail) q0 = 0;
     }
