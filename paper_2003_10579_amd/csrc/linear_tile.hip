@@ -358,10 +358,11 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                     if (4 * i0 >= used) break;
 #pragma unroll
                     for (int i = i0; i < i0 + 4; ++i) {
-                        // rows without a sample read row 0; their delta is zero
-                        uint32_t id = (uint32_t)__builtin_amdgcn_readlane((int)p_row_id, olw + 4 * i);
-                        id = (id == kNoRow) ? 0u : id;
-                        pref[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, goff[i & 3], (int)(id * row_bytes), kStream));
+                        // rows without a sample are zero: their delta is, but zero times an infinity is not
+                        const uint32_t id = (uint32_t)__builtin_amdgcn_readlane((int)p_row_id, olw + 4 * i);
+                        const bool none = id == kNoRow;
+                        pref[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, none ? kOutOfRange : goff[i & 3],
+                                                                                                  none ? 0 : (int)(id * row_bytes), kStream));
                     }
                 }
             }

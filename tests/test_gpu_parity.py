@@ -908,6 +908,32 @@ def test_one_slice(ssgd, oracle, torch_cuda, monkeypatch, kind, variant, P, K, m
     assert rel(ctx.params(), orc.params()) <= FP32_PARAM_TOL
 
 
+@pytest.mark.parametrize("kind,variant,P,K,m,d,classes", [
+    ("softmax", "k_async", 6, 3, 25, 261, 3),       # several tiles, rows of odd length, padded records
+    ("lsq", "k_sync", 4, 2, 5, 64, 1),              # one slice, a record of 32 rows of which 16 are there
+    ("softmax", "k_batch_sync", 3, 3, 22, 516, 4),  # the last tile half empty
+    ("lsq", "k_async", 5, 2, 7, 35, 1),
+    ("softmax", "k_batch_async", 4, 2, 70, 260, 3), # records of a full tile and one of 8 rows
+])
+def test_rows_that_no_sample_names_do_not_matter(ssgd, oracle, torch_cuda, kind, variant, P, K, m, d, classes):
+    """The places of a tile that hold no sample contribute nothing, also where the data set holds infinities and NaN in rows
+    that were not drawn."""
+    X, y = synth.lsq_data(3000, d, 8)[:2] if kind == "lsq" else synth.mixture_data(3000, d, classes, seed=8)
+    gd, od = dist_pair(ssgd, oracle, ("exp", 1.0))
+    for seed in range(50):
+        bad = X.copy()
+        bad[0], bad[1] = np.inf, np.nan
+        orc = oracle.Trainer(oracle.Model(kind, bad, y, classes=classes), P, K, m, variant, od, 0.01, seed=seed)
+        orc.run(5)
+        if np.all(np.isfinite(orc.params())):
+            break
+    assert np.all(np.isfinite(orc.params()))
+    ctx = ssgd.Context(kind, torch_cuda.from_numpy(bad).cuda(), torch_cuda.from_numpy(y).cuda(), P, K, m, variant, gd, 0.01, seed=seed,
+                       classes=classes)
+    ctx.run(5)
+    assert rel(ctx.params(), orc.params()) <= FP32_PARAM_TOL
+
+
 def test_contexts_one_after_the_other_and_side_by_side_share_no_results(ssgd, torch_cuda):
     """Pinned blocks go from a destroyed context to the next one: what a context hands out is its own, whatever the
     others are doing, from several threads too."""
