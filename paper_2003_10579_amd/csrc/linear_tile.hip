@@ -101,7 +101,7 @@ __device__ __forceinline__ void lds_barrier() {
 // ONE: the cluster is one workgroup (d <= 256).  Its partial logits are the logits: they change lanes inside the wave
 // instead of going out to the exchange, and only the 64-column blocks that exist are loaded, written and contracted.
 // Bound by the chain of one step, TU -> logits -> delta -> gradient -> update, beside the chain lists -> sample ids ->
-// gather of the next tile.  (Least squares, d = 64, two mini-batches of 16, one replica: 2.5 us per update where the
+// gather of the next tile.  (Least squares, d = 64, two mini-batches of 16, one replica: 2.2 us per update where the
 // exchange through memory of the general kernel takes 8.5.)
 // ROOMY: a launch that leaves every workgroup a CU of its own.  Two waves per SIMD then have 256 registers each and
 // nothing is spilled; a spilled word that a loader wave reads back would wait for the gathers in front of it.
@@ -134,9 +134,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
     const bool async = a.variant == kAsync;
     // A tile holds whole records of mp rows; when an iteration spans several tiles, a tile is one block of 64 rows
     // of the iteration's mini-batches, all of them part of the update.
-    // (read from the arguments where it is possible at all: as a compile-time constant it led the compiler to keep
-    // two tiles of gathered rows alive and spill them)
-    const bool chunked = CHUNKED && a.chunked != 0;
+    constexpr bool chunked = CHUNKED;
     // Records described one by one (BATCH: K-batch-async, and K-async when a version may have more records than a tile
     // holds), mini-batches of more than 64 rows: a tile is one block of 64 rows of one record; the record's gradient is
     // summed over its tiles in the slot of its worker
@@ -283,7 +281,8 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                 h_tiles = spr > 1 ? max(1, nrec * spr) : max(1, (nrec + rpt - 1) / rpt);
             }
             cur_sel = l_sel;
-            asm volatile("" : "+v"(n_stale), "+v"(n_stale_pos), "+v"(n_rec_word), "+v"(cur_sel), "+v"(h_worker), "+v"(h_ord) : : "memory");
+            if constexpr (chunked) asm volatile("" : "+v"(h_worker), "+v"(h_ord) : : "memory");
+            else asm volatile("" : "+v"(n_stale), "+v"(n_stale_pos), "+v"(n_rec_word), "+v"(cur_sel), "+v"(h_worker), "+v"(h_ord) : : "memory");
             if constexpr (BATCH) asm volatile("" : "+v"(h_rw), "+v"(h_ro), "+v"(h_rf), "+v"(h_csel), "+v"(h_ctau), "+v"(h_cord) : : "memory");
         };
         // Tile `t` of version `ver`: sample ids, lists; leaves the labels in flight.
@@ -349,7 +348,8 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
             p_rows = n_rows; p_flags = n_flags; p_ver = n_ver;
             int olw = lw;
             asm volatile("" : "+s"(olw));
-            asm volatile("" : "+v"(p_row_id), "+v"(p_row_lab), "+v"(p_stale), "+v"(p_stale_pos), "+v"(p_rec_word) : : "memory");
+            if constexpr (chunked) asm volatile("" : "+v"(p_row_id), "+v"(p_row_lab) : : "memory");
+            else asm volatile("" : "+v"(p_row_id), "+v"(p_row_lab), "+v"(p_stale), "+v"(p_stale_pos), "+v"(p_rec_word) : : "memory");
             const int used = p_nrec * p_rows;      // a CU takes in about 16 bytes of gathers per cycle: rows past the records are left out
             __builtin_amdgcn_sched_barrier(0);
             if (!ONE || lane < 16 * nblk) {
@@ -385,8 +385,8 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
             if (lw == 0) {
                 L.rowid[lane] = p_row_id; L.ylab[lane] = p_row_lab;
                 if (lane == 0) { L.ctl[4] = p_K; L.ctl[5] = p_nrec; L.ctl[6] = p_nstale; L.ctl[7] = p_flags | (p_rows << 8); }
-                if (p_stale_pos < kc) L.s_stale[p_stale_pos] = p_stale;
-                if (lane < kc) L.s_rec[lane] = p_rec_word;
+                if (!chunked && p_stale_pos < kc) L.s_stale[p_stale_pos] = p_stale;
+                if (lane < kc) L.s_rec[lane] = chunked ? 1 << 16 : p_rec_word;       // (only the first entry is read)
             }
             asm volatile("" : "+v"(q_sel), "+v"(q_tau), "+v"(q_ord), "+v"(row_lab) : : "memory");     // lists and labels asked for behind the rows
         };
@@ -669,8 +669,8 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         f32x4 pva[4], pvb[4];
 #pragma unroll
         for (int vv = 0; vv < 4; ++vv) { pva[vv] = f32x4{0.f, 0.f, 0.f, 0.f}; pvb[vv] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-        if (n_stale > 0) park_load(st01.x, pva);
-        if (n_stale > 1) park_load(st01.y, pvb);
+        if (!chunked && n_stale > 0) park_load(st01.x, pva);
+        if (!chunked && n_stale > 1) park_load(st01.y, pvb);
         mark(9);
         // ---- arrival: this wave's stores are in the L2 (shared-L2 mode) or released to the device
         // ---- arrival.  Shared-L2 mode needs none: the readers poll the data words themselves.  Otherwise the
@@ -682,7 +682,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
 #pragma unroll
             for (int e = 0; e < 16; ++e) gsum[e] = pva[e >> 2][e & 3] + pvb[e >> 2][e & 3];
         }
-        for (int i = 2; i < n_stale; ++i) {     // further parked gradients (K > 2)
+        for (int i = 2; !chunked && i < n_stale; ++i) {     // further parked gradients (K > 2)
             park_load(L.s_stale[i], pva);
 #pragma unroll
             for (int e = 0; e < 16; ++e) gsum[e] += pva[e >> 2][e & 3];
@@ -1096,8 +1096,7 @@ bool linear_tile_supports(const LinArgs& a, int max_records) {
     // the consume list and the restarts of an update sit in one lane each; the last chunk of a row is read as its last four columns
     if (a.C > 15 || a.d < 4 || a.tr.Kcap > KC || max_records > KC) return false;
     const bool synchronous = a.variant == kSync || a.variant == kBatchSync;
-    if (synchronous && a.mp * max_records > ROWS && !a.chunked) return false;
-    if (!synchronous && a.chunked) return false;
+    if (synchronous != (a.chunked != 0)) return false;
     if ((uint64_t)a.N * (uint64_t)a.d * 4u >= (1ull << 32)) return false;   // one buffer descriptor spans the sample matrix
     return linear_tile_lds_bytes(a.C, a.S, a.tr.Kcap) <= 160 * 1024;
 }
