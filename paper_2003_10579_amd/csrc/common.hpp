@@ -108,9 +108,9 @@ struct LinArgs {
     int32_t debug_flags;                 // test switches set by the host (SSGD_DEBUG_FLAGS): bit 1 makes the odd replicas take the path of a cluster spread over XCDs
     int64_t prof_base;                   // first word of the steady-state kernel's part of prof
     int64_t prof_helper;                 // offset, from prof_base, of the helper workgroups' words (one per replica)
-    // Steady-state kernel: 1 for a synchronous variant whose iteration does not fit one 64-row tile.  The rows of the
-    // K mini-batches are then taken 64 at a time, each tile through the whole forward / exchange / backward schedule,
-    // the gradient summed over the tiles and the update applied after the last one.
+    // Steady-state kernel: 1 for a synchronous variant.  The rows of the K mini-batches are then taken 64 at a time, each
+    // tile through the whole forward / exchange / backward schedule, the gradient summed over the tiles and the update
+    // applied after the last one.
     int32_t chunked;
     unsigned long long* prof;   // nullable diagnostics: [R][G][20] cycles per phase (general kernel), then [R][G][2] cycles of the profiled interval (steady-state kernel: compute wave, loader wave)
 };

@@ -131,7 +131,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
     const int Kcap = a.tr.Kcap;
     const int64_t cap = a.tr.cap;
     const int col0 = slice * SL;
-    const bool async = a.variant == kAsync;
+    const bool async = !CHUNKED && (!BATCH || a.variant == kAsync);      // K-async
     // A tile holds whole records of mp rows; when an iteration spans several tiles, a tile is one block of 64 rows
     // of the iteration's mini-batches, all of them part of the update.
     constexpr bool chunked = CHUNKED;
@@ -1075,10 +1075,10 @@ hipError_t launch_w(const LinArgs& a, size_t lds, hipStream_t s) {
 bool records_one_by_one(const LinArgs& a) { return a.variant == kBatchAsync || (a.variant == kAsync && (a.v0 < 1 || a.mp * a.tr.Kcap > ROWS)); }
 
 // WHOLE: every record is a whole number of 32-row blocks, so the gradient contraction is fully unrolled;
-// CHUNKED: an iteration of a synchronous variant spans several tiles; BATCH: records described one by one
+// CHUNKED: a synchronous variant, one record per tile; BATCH: records described one by one; neither: K-async, one tile
 template <int KIND, bool PROF>
 hipError_t launch_k(const LinArgs& a, size_t lds, hipStream_t s) {
-    if (a.chunked) return launch_w<KIND, PROF, true, true, false>(a, lds, s);      // tiles of one 64-row record
+    if (a.chunked) return launch_w<KIND, PROF, true, true, false>(a, lds, s);
     const bool whole = a.mp == 32 || a.mp == 64;
     if (records_one_by_one(a))           // (no phase profile for this form)
         return whole ? launch_w<KIND, false, true, false, true>(a, lds, s) : launch_w<KIND, false, false, false, true>(a, lds, s);
