@@ -5,6 +5,7 @@
 
 #include <string>
 
+#include "limits.hpp"
 #include "rng.hpp"
 
 namespace ssgd {

@@ -49,7 +49,7 @@ constexpr int kAgentLoad = 16;  // cache policy: served by the L2, never by a CU
 constexpr int kStream = 2;      // cache policy: non-temporal
 constexpr uint32_t kNoRow = 0xFFFFFFFFu;
 constexpr uint32_t kSentinel = 0xFFFFFFFFu;    // an exchange word that has not been written yet
-constexpr int kOutOfRange = (int)0x80000000;   // buffer offset past any buffer: loads give 0, stores are dropped
+constexpr int kOutOfRange = (int)0x80000000;   // offset past any buffer of exchanged words: loads give 0, stores are dropped
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
@@ -480,7 +480,7 @@ __device__ __forceinline__ void slice_role(const LinArgs& a, int rep, int slice,
         for (int q = 0; q < 4; ++q) {
             const int key = (lw + 4 * q) & 15;
             const int col = col0 + 4 * (lane ^ key);
-            goff[q] = (col < d) ? col * 4 : kOutOfRange;    // past the end of the row: zeros
+            goff[q] = (col < d) ? col * 4 : (int)kPastMatrix;    // past the end of the row: zeros
         }
         float* const my_tile = L.tile + lw * SL + lane * 4;
 
@@ -974,7 +974,7 @@ bool linear_defer_supports(const LinArgs& a) {
     if (a.variant != kAsync || a.v0 < 1 || a.chunked || !a.allow_fast) return false;     // step 0 of K-async starts all P workers
     if (a.C > 15 || (a.d % 4) != 0 || (a.mp % 16) != 0 || a.mp > ROWS) return false;
     if (a.S > SMAX || a.P > SMAX || a.tr.Kcap > SMAX || a.tr.Kcap * a.mp > ROWS) return false;
-    if ((uint64_t)a.N * (uint64_t)a.d * 4u >= (1ull << 32)) return false;   // one buffer descriptor spans the sample matrix
+    if (!one_descriptor_spans(a.N, (uint64_t)a.d)) return false;
     return linear_defer_lds_bytes(a.C, a.S) <= 160 * 1024;
 }
 

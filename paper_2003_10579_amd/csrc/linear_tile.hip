@@ -44,7 +44,7 @@ constexpr int KC = 64;          // list entries per step (one lane of a wave eac
 constexpr int kAgentLoad = 16;  // cache policy: served by the L2, never by a CU's L1
 constexpr int kStream = 2;      // cache policy: non-temporal
 constexpr uint32_t kNoRow = 0xFFFFFFFFu;
-constexpr int kOutOfRange = (int)0x80000000;   // buffer offset past any buffer: loads give 0, stores are dropped
+constexpr int kOutOfRange = (int)0x80000000;   // offset past any buffer of exchanged words or parked gradients: loads give 0, stores are dropped
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
@@ -169,7 +169,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
             const int key = (lw + 4 * q) & 15;
             const int col = col0 + 4 * (lane ^ key);
             tail[q] = col < d && col + 4 > d;
-            goff[q] = (col < d) ? min(col, d - 4) * 4 : kOutOfRange;    // past the end of the row: zeros
+            goff[q] = (col < d) ? min(col, d - 4) * 4 : (int)kPastMatrix;    // past the end of the row: zeros
         }
         const int d_rem = d & 3;
         const bool has_tail = d_rem != 0 && slice == G - 1;
@@ -361,7 +361,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                         // rows without a sample are zero: their delta is, but zero times an infinity is not
                         const uint32_t id = (uint32_t)__builtin_amdgcn_readlane((int)p_row_id, olw + 4 * i);
                         const bool none = id == kNoRow;
-                        pref[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, none ? kOutOfRange : goff[i & 3],
+                        pref[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, none ? (int)kPastMatrix : goff[i & 3],
                                                                                                   none ? 0 : (int)(id * row_bytes), kStream));
                     }
                 }
@@ -1097,7 +1097,7 @@ bool linear_tile_supports(const LinArgs& a, int max_records) {
     if (a.C > 15 || a.d < 4 || a.tr.Kcap > KC || max_records > KC) return false;
     const bool synchronous = a.variant == kSync || a.variant == kBatchSync;
     if (synchronous != (a.chunked != 0)) return false;
-    if ((uint64_t)a.N * (uint64_t)a.d * 4u >= (1ull << 32)) return false;   // one buffer descriptor spans the sample matrix
+    if (!one_descriptor_spans(a.N, (uint64_t)a.d)) return false;
     return linear_tile_lds_bytes(a.C, a.S, a.tr.Kcap) <= 160 * 1024;
 }
 

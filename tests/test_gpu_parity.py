@@ -934,6 +934,32 @@ def test_rows_that_no_sample_names_do_not_matter(ssgd, oracle, torch_cuda, kind,
     assert rel(ctx.params(), orc.params()) <= FP32_PARAM_TOL
 
 
+@pytest.mark.parametrize("kind,variant,P,K,m,N,d,classes", [
+    ("lsq", "k_sync", 4, 2, 14, 6_000_000, 100, 1),          # one slice; 2 of 16 places of a record without a sample
+    ("softmax", "k_async", 6, 3, 25, 700_000, 785, 3),       # several tiles, one column in the last chunk
+    ("softmax", "k_batch_async", 4, 2, 16, 720_000, 772, 3), # one slice of four that is four columns wide
+    ("softmax", "k_async", 5, 2, 32, 1_050_000, 516, 3),     # the kernel that keeps gradients in flight in LDS
+])
+def test_sample_matrices_above_two_gib(ssgd, oracle, torch_cuda, kind, variant, P, K, m, N, d, classes):
+    """Columns past the end of a row and places without a sample read zeros, whatever lies 2 GiB behind the row.  The row at
+    byte 2^31 holds infinities and is not drawn."""
+    torch = torch_cuda
+    g = torch.Generator(device="cuda").manual_seed(5)
+    Xd = torch.randn(N, d, generator=g, device="cuda")
+    yd = Xd[:, :16].sum(1) if kind == "lsq" else torch.randint(0, classes, (N,), generator=g, device="cuda", dtype=torch.int32)
+    assert 2 ** 31 < 4 * N * d < 2 ** 32
+    Xd[2 ** 31 // (4 * d)] = float("inf")
+    X, y = Xd.cpu().numpy(), yd.cpu().numpy()
+    gd, od = dist_pair(ssgd, oracle, ("exp", 1.0))
+    ctx = ssgd.Context(kind, Xd, yd, P, K, m, variant, gd, 0.002, seed=3, classes=classes)
+    orc = oracle.Trainer(oracle.Model(kind, X, y, classes=classes), P, K, m, variant, od, 0.002, seed=3)
+    ctx.run(60)
+    orc.run(60)
+    assert_trace_equal(ctx.trace(), orc.trace())
+    assert np.all(np.isfinite(orc.params())) and rel(ctx.params(), orc.params()) <= FP32_PARAM_TOL
+    ctx.close()
+
+
 def test_contexts_one_after_the_other_and_side_by_side_share_no_results(ssgd, torch_cuda):
     """Pinned blocks go from a destroyed context to the next one: what a context hands out is its own, whatever the
     others are doing, from several threads too."""

@@ -1,0 +1,35 @@
+"""The address limits of `csrc/limits.hpp`, compiled by themselves with the host compiler (no GPU)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2003_10579_amd", "csrc")
+
+
+def _evaluate(tmp_path, body):
+    """Runs `body`, C++ statements that print numbers, against the header."""
+    if shutil.which("g++") is None:
+        pytest.skip("g++ not available")
+    src, exe = tmp_path / "limits.cpp", tmp_path / "limits"
+    src.write_text('#include <cstdio>\n#include "limits.hpp"\nusing namespace ssgd;\nint main() {\n' + body + "\nreturn 0;\n}\n")
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    out = subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout
+    return [int(v) for v in out.split()]
+
+
+def test_lanes_that_read_zeros_are_past_every_accepted_matrix(tmp_path):
+    """A raw buffer load is out of range from vector offset >= size - scalar offset on.  Sizes on both sides of 2 GiB and of
+    the limit; the scalar offset is that of any row, so the first row (offset 0) is the one that asks for most."""
+    sizes = [(4096, 64), (700_000, 785), (6_000_000, 100), (536_870_912, 1), (536_870_913, 1), (1_073_741_820, 1), (1_073_741_821, 1),
+             (268_435_455, 4), (268_435_456, 4), (2 ** 32 - 1, 3)]
+    body = 'printf("%u\\n", kPastMatrix);\n' + "".join(f'printf("%d\\n", (int)one_descriptor_spans({n}ull, {d}ull));\n' for n, d in sizes)
+    past, *spans = _evaluate(tmp_path, body)
+    assert past % 4 == 0 and past + 16 <= 2 ** 32       # the four words of a load do not wrap
+    for (n, d), ok in zip(sizes, spans):
+        assert ok == (4 * n * d <= past), (n, d)
+        if ok:
+            assert past >= 4 * n * d                    # out of range beside row 0, hence beside every row
+    assert spans == [1, 1, 1, 1, 1, 1, 0, 1, 0, 0]
