@@ -214,7 +214,8 @@ ssgd_status ssgd_set_state(ssgd_ctx *ctx, const void *host_buf, int64_t bytes);
  * fresh start and T_l (l = 1..chain_len) is recorded; for SSGD_K_BATCH_ASYNC (Lemma 5)
  * the pushes of all workers form one sequence for every K and update l is push l K.
  * P <= 256, chain_len <= 4096, for SSGD_K_BATCH_ASYNC chain_len * Kmax <= 7500 (else
- * SSGD_EINVAL).  Outputs are HOST arrays of
+ * SSGD_EINVAL); a rate, alpha or scale that is not above zero and a parameter that is no number give
+ * SSGD_EINVAL too.  Outputs are HOST arrays of
  * (Kmax-Kmin+1) x chain_len entries: mean and unbiased variance of T_l, and
  * (nullable) the raw sums `sum` and `sumsq`; per_trial (HOST, nullable,
  * trials x (Kmax-Kmin+1) x chain_len fp64) receives every trial's T_l. */

@@ -453,6 +453,9 @@ def test_mc_ten_thousand_trials_bit_exact(ssgd, oracle, torch_cuda, variant):
     ("k_batch_async", 1, 1, 4, 5, 20, ("exp", 1.0)), ("k_batch_async", 200, 1, 200, 6, 5, ("shifted_exp", 5.0, 50.0)),
     ("k_batch_async", 70, 64, 64, 8, 10, ("pareto", 0.3, 1.0)), ("k_batch_async", 2, 300, 300, 20, 3, ("exp", 1.0)),
     ("k_batch_async", 4, 700, 700, 1, 3, ("pareto", 0.02, 1.0)),       # delays up to infinity
+    ("k_async", 70, 1, 70, 4, 10, ("pareto", 0.02, 1.0)), ("k_async", 200, 150, 150, 4, 10, ("pareto", 0.02, 1.0)),
+    ("k_sync", 70, 1, 70, 4, 10, ("pareto", 0.02, 1.0)), ("k_sync", 130, 129, 130, 4, 10, ("pareto", 0.02, 1.0)),
+    ("k_batch_sync", 70, 60, 72, 4, 10, ("pareto", 0.02, 1.0)), ("k_batch_async", 70, 1, 8, 3, 10, ("pareto", 0.02, 1.0)),
 ])
 def test_mc_trials_at_the_edges_of_the_shapes(ssgd, oracle, torch_cuda, variant, P, Kmin, Kmax, L, trials, spec):
     """Every trial's T_l bit for bit where registers, windows and lists are just full or just exceeded."""

@@ -95,6 +95,19 @@ def test_runtime_mc_rejects_invalid_arguments(L):
         assert L.ssgd_runtime_mc(*args(**bad)) == ssgd.EINVAL
 
 
+@pytest.mark.parametrize("spec", [("exp", float("nan")), ("shifted_exp", 0.5, float("nan")), ("shifted_exp", float("nan"), 1.0),
+                                  ("pareto", float("nan"), 1.0), ("pareto", 2.0, float("nan")), ("exp", -1.0)])
+def test_distribution_parameters_that_are_no_numbers_are_refused(L, spec):
+    """By every entry point that takes a distribution, before it looks for a device."""
+    d, md, h = ssgd.delay_dist(*spec), _model(), C.c_void_p(0x1234)
+    bits, out = (C.c_uint32 * 4)(), (C.c_float * 4)()
+    for variant in range(4):
+        assert L.ssgd_runtime_mc(variant, 8, 1, 4, C.byref(d), 0, 10, 2, 0, None, None, None, None, None, None) == ssgd.EINVAL
+        assert b"distribution" in L.ssgd_last_error(None)
+        assert L.ssgd_create(C.byref(md), 4, 2, 4, variant, C.byref(d), 0.1, 0, 1, None, None, C.byref(h)) == ssgd.EINVAL
+    assert L.ssgd_debug_delays(C.byref(d), bits, 4, out) == ssgd.EINVAL
+
+
 def test_state_entry_points_reject_null_arguments(L):
     n = C.c_int64(0)
     buf = (C.c_ubyte * 16)()
