@@ -39,6 +39,7 @@ struct McArgs {
     int32_t variant, P, Kmin, Kmax, chain_len;
     int32_t nslices;     // block b takes the values K = Kmin + b % nslices, + nslices, ...: small accumulators, many waves per CU
     int64_t trial0, trials;
+    int32_t one_by_one;  // K-batch-async: delays may be below zero, so that a push can be earlier than the one before it
     double mean_delay;   // a rough value: first guess of a selection, size of the K-batch-async lists
     double* partial;     // [blocks][nK*chain_len][2]
     double* per_trial;   // nullable
@@ -344,7 +345,7 @@ __global__ __launch_bounds__(64, VARIANT == kBatchAsync ? 4 : 8) void mc_kernel(
                 started[q] = 0;
             }
             if (lane == 0) push[0] = 0.0;
-            int n = 0, halvings = 0;
+            int n = 0, halvings = a.one_by_one ? 40 : 0;
             double t = 0.0, span = 0.0;
             while (n < npush && halvings < 40) {
                 // renewals up to t + span, meant to be the ones still needed or the 300 next
@@ -395,7 +396,7 @@ __global__ __launch_bounds__(64, VARIANT == kBatchAsync ? 4 : 8) void mc_kernel(
                 n += keep;
                 wave_fence();
             }
-            for (; n < npush; ++n) {           // more pushes at one instant than a list holds: one by one
+            for (; n < npush; ++n) {           // more pushes at one instant than a list holds, or no lists: one by one
                 const Best b = wave_argmin<NQ>(key, lane);
                 if (lane == 0) push[n + 1] = b.key;
                 if ((b.id & 63) == lane) {
@@ -678,6 +679,7 @@ extern "C" __attribute__((visibility("default"))) ssgd_status ssgd_runtime_mc(in
     case SSGD_SHIFTED_EXP: a.mean_delay = dist->shift + 1.0 / dist->rate; break;
     default: a.mean_delay = dist->alpha > 1.5 ? dist->scale * dist->alpha / (dist->alpha - 1.0) : 3.0 * dist->scale; break;
     }
+    a.one_by_one = dist->kind == SSGD_SHIFTED_EXP && dist->shift < 0.0 ? 1 : 0;
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) { mc_fail("no device"); return SSGD_EDEVICE; }
     const int64_t groups = std::max<int64_t>(1, std::min<int64_t>(trials, (int64_t)cus * 32 / nslices));

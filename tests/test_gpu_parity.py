@@ -474,6 +474,19 @@ def test_mc_with_tied_finish_times(ssgd, oracle, torch_cuda):
         assert np.array_equal(g["per_trial"], o["per_trial"]), variant
 
 
+@pytest.mark.parametrize("shift", [-0.6, -3.0])
+def test_mc_with_delays_below_zero(ssgd, oracle, torch_cuda, shift):
+    """A shift below zero is accepted: the events are taken in the order in which the process finds them, a push of
+    K-batch-async that is earlier than the one before it included."""
+    gd, od = dist_pair(ssgd, oracle, ("shifted_exp", shift, 1.0))
+    for variant, P, K0, K1 in (("k_async", 70, 1, 70), ("k_sync", 70, 1, 70), ("k_batch_sync", 9, 1, 12), ("k_batch_async", 70, 1, 9), ("k_batch_async", 5, 3, 3)):
+        g = ssgd.runtime_mc(variant, P, K0, K1, gd, 12, 4, seed=8, per_trial=True)
+        o = oracle.runtime_mc(variant, P, K0, K1, od, 12, 4, seed=8, per_trial=True)
+        assert np.array_equal(g["per_trial"], o["per_trial"]), variant
+        if variant == "k_batch_async":
+            assert (o["per_trial"] < 0).any()          # a sorted list of pushes has none
+
+
 def test_mc_closed_forms_at_scale(ssgd, torch_cuda):
     """2e5 trials, P=128, all K: Exp(1) order statistics (App. B.1) for every update of the K-async chain
     (App. B.3); shifted exponential first update = shift + harmonic form; K-async <= K-sync afterwards."""
