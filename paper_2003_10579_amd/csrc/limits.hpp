@@ -1,4 +1,4 @@
-// Limits of addresses that the kernels share, as plain host arithmetic (no HIP), so that a test can compile it by itself.
+// Limits of addresses and launches, as plain host arithmetic (no HIP), so that a test can compile it by itself.
 #pragma once
 #include <stdint.h>
 
@@ -11,5 +11,11 @@ namespace ssgd {
 // on.)  The last of the four words of the load does not wrap either.
 constexpr uint32_t kPastMatrix = 0xFFFFFFF0u;
 inline bool one_descriptor_spans(uint64_t N, uint64_t d) { return N * d * 4u <= kPastMatrix; }
+
+// Schedule of the synchronous variants: updates (one wavefront each) of one launch.  A launch ends at 2^32 threads in one
+// dimension, that is at 2^26 updates; longer segments take several launches, of far fewer updates, so that a test gets there.
+constexpr int kSyncWaves = 4;
+constexpr int64_t kSyncUpdatesPerLaunch = 1 << 16;
+inline uint32_t sync_schedule_blocks(int64_t updates) { return (uint32_t)((updates + kSyncWaves - 1) / kSyncWaves); }
 
 }  // namespace ssgd

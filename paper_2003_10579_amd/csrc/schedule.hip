@@ -4,6 +4,8 @@
 // One wavefront simulates one replica; each lane owns up to four of the P <= 256
 // workers.  The delays do not depend on the data, so a whole segment of updates is
 // scheduled before any gradient is taken; the gradient kernels then read the trace.
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace ssgd {
@@ -106,7 +108,6 @@ __device__ __forceinline__ double sync_update(const Draw& draw_delay, bool batch
 // The updates of a synchronous segment side by side, one wavefront each; the time between updates is left in the trace
 // for sync_clock_kernel to add up.  (One wavefront per replica took them one after the other, K argmin rounds of 0.4 us
 // each; that stays for segments so short that a second launch, about 5 us, costs more.)
-constexpr int kSyncWaves = 4;
 template <int NQ, bool TABLE>
 __global__ __launch_bounds__(64 * kSyncWaves) void sync_schedule_kernel(SchedArgs a) {
     const int lane = threadIdx.x & 63;
@@ -419,15 +420,19 @@ __global__ void adasync_kernel(AdaArgs a, int replicas) {
 
 void launch_schedule(const SchedArgs& a, int replicas, hipStream_t s) {
     const bool table = a.dist.kind == 3;
-    // (a segment that ends where the clock crosses an interval is found update by update; grids end at 2^31 blocks)
-    if ((a.variant == kSync || a.variant == kBatchSync) && !(a.interval_t > 0.0) && a.count * (int64_t)a.tr.Kcap >= 16 && replicas <= 65535 && a.count < (1ll << 31)) {
-        const dim3 grid((unsigned)((a.count + kSyncWaves - 1) / kSyncWaves), (unsigned)replicas), block(64 * kSyncWaves);
-        if (a.P <= 64) {
-            if (table) hipLaunchKernelGGL((sync_schedule_kernel<1, true>), grid, block, 0, s, a);
-            else hipLaunchKernelGGL((sync_schedule_kernel<1, false>), grid, block, 0, s, a);
-        } else {
-            if (table) hipLaunchKernelGGL((sync_schedule_kernel<kMaxWorkers / 64, true>), grid, block, 0, s, a);
-            else hipLaunchKernelGGL((sync_schedule_kernel<kMaxWorkers / 64, false>), grid, block, 0, s, a);
+    // (a segment that ends where the clock crosses an interval is found update by update; a grid has 65535 rows)
+    if ((a.variant == kSync || a.variant == kBatchSync) && !(a.interval_t > 0.0) && a.count * (int64_t)a.tr.Kcap >= 16 && replicas <= 65535) {
+        for (int64_t off = 0; off < a.count; off += kSyncUpdatesPerLaunch) {
+            SchedArgs b = a;
+            b.j0 = a.j0 + off; b.count = std::min(kSyncUpdatesPerLaunch, a.count - off);
+            const dim3 grid(sync_schedule_blocks(b.count), (unsigned)replicas), block(64 * kSyncWaves);
+            if (a.P <= 64) {
+                if (table) hipLaunchKernelGGL((sync_schedule_kernel<1, true>), grid, block, 0, s, b);
+                else hipLaunchKernelGGL((sync_schedule_kernel<1, false>), grid, block, 0, s, b);
+            } else {
+                if (table) hipLaunchKernelGGL((sync_schedule_kernel<kMaxWorkers / 64, true>), grid, block, 0, s, b);
+                else hipLaunchKernelGGL((sync_schedule_kernel<kMaxWorkers / 64, false>), grid, block, 0, s, b);
+            }
         }
         hipLaunchKernelGGL(sync_clock_kernel, dim3(replicas), dim3(64), 0, s, a);
         return;

@@ -950,6 +950,23 @@ def test_rows_that_no_sample_names_do_not_matter(ssgd, oracle, torch_cuda, kind,
     assert rel(ctx.params(), orc.params()) <= FP32_PARAM_TOL
 
 
+@pytest.mark.parametrize("variant", ["k_sync", "k_batch_sync"])
+def test_schedule_of_several_launches(ssgd, oracle, torch_cuda, variant):
+    """A synchronous segment of more updates than one launch of its schedule takes."""
+    X, y, _ = synth.lsq_data(300, 8, 3)
+    Xd, yd = torch_cuda.from_numpy(X).cuda(), torch_cuda.from_numpy(y).cuda()
+    gd, od = dist_pair(ssgd, oracle, ("exp", 1.0))
+    J = 2 ** 16 + 1003
+    ctx = ssgd.Context("lsq", Xd, yd, 3, 2, 4, variant, gd, 0.01, seed=5, replicas=2)
+    ctx.run(J)
+    for r in range(2):
+        orc = oracle.Trainer(oracle.Model("lsq", X, y), 3, 2, 4, variant, od, 0.01, seed=5, replica=r)
+        orc.run(J)
+        assert_trace_equal(ctx.trace(r), orc.trace())
+        assert rel(ctx.params(r), orc.params()) <= FP32_PARAM_TOL
+    ctx.close()
+
+
 @pytest.mark.parametrize("kind,variant,P,K,m,N,d,classes", [
     ("lsq", "k_sync", 4, 2, 14, 6_000_000, 100, 1),          # one slice; 2 of 16 places of a record without a sample
     ("softmax", "k_async", 6, 3, 25, 700_000, 785, 3),       # several tiles, one column in the last chunk

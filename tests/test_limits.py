@@ -1,4 +1,4 @@
-"""The address limits of `csrc/limits.hpp`, compiled by themselves with the host compiler (no GPU)."""
+"""The limits of `csrc/limits.hpp`, compiled by themselves with the host compiler (no GPU)."""
 import os
 import shutil
 import subprocess
@@ -33,3 +33,9 @@ def test_lanes_that_read_zeros_are_past_every_accepted_matrix(tmp_path):
         if ok:
             assert past >= 4 * n * d                    # out of range beside row 0, hence beside every row
     assert spans == [1, 1, 1, 1, 1, 1, 0, 1, 0, 0]
+
+
+def test_schedule_launches_stay_below_the_largest_grid(tmp_path):
+    """Work items of one dimension of a launch are counted in 32 bits."""
+    per, blocks, block = _evaluate(tmp_path, 'printf("%lld %u %d\\n", (long long)kSyncUpdatesPerLaunch, sync_schedule_blocks(kSyncUpdatesPerLaunch), 64 * kSyncWaves);')
+    assert 0 < blocks * block < 2 ** 32 and blocks * block >= 64 * per
