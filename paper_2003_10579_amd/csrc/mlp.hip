@@ -75,7 +75,7 @@ struct MlpArgs {
     int32_t cons_tau[32];      // versions of the gradients in cons_inline
     float* b1r;                // nullable: a copy of b1 (read by the layer-2 kernel, written by the small update) ...
     float* b2r;                // ... and of b2, when updates overlap and every version of the parameters has copies of its own
-    unsigned short* xb;        // [S][MP][d]   bf16 rows of the slot's samples (evaluation of the objective)
+    unsigned short* xb;        // [slots][MP][d]  bf16 rows gathered by the evaluation of the objective, which brings the buffer (null in training)
     float* hbuf;               // [S][MP][H]   hidden activations
     unsigned short* d1t;       // [S][H][MP]   delta1 / m in bf16, transposed
     // The second-layer gradients and the loss have room for one record per quarter of the mini-batch (rows 16 q ..
@@ -1232,8 +1232,8 @@ struct MlpState {
     DevMem w1v, w2v, b1v, b2v, fwd_part;   // allocated by the first segment that overlaps
     hipStream_t fwd_stream[kFwdStreams] = {};
     std::vector<hipEvent_t> ev_pool;
-    size_t gap_bytes = 0;        // of a buffer that snapshots hold a place for
-    DevMem params, w1r, w2r, xb, hbuf, d1t, gb1, gw2, gb2, d2, loss, ylab, dw_part, plan, quartered;
+    size_t gap_bytes = 0;        // of each of two buffers that snapshots hold a place for
+    DevMem params, w1r, w2r, hbuf, d1t, gb1, gw2, gb2, d2, loss, ylab, dw_part, plan, quartered;
     hipStream_t stream = nullptr;
 };
 
@@ -1261,7 +1261,6 @@ hipError_t mlp_create(MlpState** out, const ssgd_model& model, int P, int m, int
     TRY(s->params.alloc(sizeof(float) * s->nw));
     TRY(s->w1r.alloc(2 * (size_t)n1));
     TRY(s->w2r.alloc(sizeof(float) * n2));
-    TRY(s->xb.alloc(2 * S * MP * a.d));
     s->gap_bytes = 2 * S * MP * a.d;
     TRY(s->hbuf.alloc(sizeof(float) * S * MP * a.H));
     TRY(s->d1t.alloc(2 * S * MP * a.H));
@@ -1294,7 +1293,6 @@ hipError_t mlp_create(MlpState** out, const ssgd_model& model, int P, int m, int
         TRY(hipMemcpy(s->plan.p, h.data(), sizeof(int32_t) * h.size(), hipMemcpyHostToDevice));
         a.plan = (int32_t*)s->plan.p;
     }
-    TRY(hipMemsetAsync(s->xb.p, 0, 2 * S * MP * a.d, stream));
     TRY(hipMemsetAsync(s->hbuf.p, 0, sizeof(float) * S * MP * a.H, stream));
     TRY(hipMemsetAsync(s->d1t.p, 0, 2 * S * MP * a.H, stream));
     TRY(hipMemsetAsync(s->gb1.p, 0, sizeof(float) * S * 4 * a.H, stream));
@@ -1303,7 +1301,7 @@ hipError_t mlp_create(MlpState** out, const ssgd_model& model, int P, int m, int
     TRY(hipMemsetAsync(s->loss.p, 0, sizeof(float) * S * 4, stream));
     TRY(hipMemsetAsync(s->ylab.p, 0xFF, sizeof(int32_t) * S * MP, stream));
     a.params = (float*)s->params.p; a.w1r = (unsigned short*)s->w1r.p; a.w2r = (float*)s->w2r.p;
-    a.xb = (unsigned short*)s->xb.p; a.hbuf = (float*)s->hbuf.p;
+    a.hbuf = (float*)s->hbuf.p;
     a.d1t = (unsigned short*)s->d1t.p; a.gb1 = (float*)s->gb1.p; a.gw2 = (float*)s->gw2.p; a.gb2 = (float*)s->gb2.p;
     a.loss = (float*)s->loss.p; a.ylab = (int32_t*)s->ylab.p; a.d2 = (float*)s->d2.p; a.quartered = (int32_t*)s->quartered.p;
     a.dw_part = (float*)s->dw_part.p; a.nsplit = 1; a.fsplit = 1; a.eval_base = -1;
@@ -1846,10 +1844,10 @@ hipError_t mlp_full_gradient(MlpState* s, float* grad_out_host, hipStream_t stre
 }
 
 // Everything a later update depends on: parameters (fp32 master and operand copies) and the factors of the
-// mini-batches in flight, slot by slot.  The null stands for a copy of their rows that snapshots used to hold: its place
-// is kept, so that they keep their layout, and filled with zeros.
+// mini-batches in flight, slot by slot.  The nulls stand for the two copies of their rows that snapshots used to hold:
+// their places are kept, so that snapshots keep their layout, and filled with zeros.
 static std::vector<DevMem*> mlp_state_buffers(MlpState* s) {
-    return {&s->params, &s->w1r, &s->w2r, &s->xb, nullptr, &s->hbuf, &s->d1t, &s->gb1, &s->gw2, &s->gb2, &s->d2, &s->loss,
+    return {&s->params, &s->w1r, &s->w2r, nullptr, nullptr, &s->hbuf, &s->d1t, &s->gb1, &s->gw2, &s->gb2, &s->d2, &s->loss,
             &s->ylab, &s->plan, &s->quartered};
 }
 
@@ -1893,7 +1891,7 @@ void mlp_destroy(MlpState* s) {
     if (s->own) { (void)hipStreamSynchronize(s->own); (void)hipStreamDestroy(s->own); }
     for (hipStream_t& f : s->fwd_stream) if (f) { (void)hipStreamSynchronize(f); (void)hipStreamDestroy(f); }
     for (hipEvent_t ev : s->ev_pool) (void)hipEventDestroy(ev);
-    DevMem* bufs[] = {&s->params, &s->w1r, &s->w2r, &s->xb, &s->hbuf, &s->d1t, &s->gb1, &s->gw2, &s->gb2, &s->d2, &s->loss, &s->ylab,
+    DevMem* bufs[] = {&s->params, &s->w1r, &s->w2r, &s->hbuf, &s->d1t, &s->gb1, &s->gw2, &s->gb2, &s->d2, &s->loss, &s->ylab,
                       &s->dw_part, &s->plan, &s->quartered, &s->w1v, &s->w2v, &s->b1v, &s->b2v, &s->fwd_part, &s->xb16};
     for (DevMem* b : bufs) b->release();
     delete s;

@@ -1104,6 +1104,32 @@ def test_snapshot_resume_continues_the_same_run(ssgd, oracle, torch_cuda, kind, 
         c.close()
 
 
+def test_network_context_holds_no_copies_of_rows(ssgd, torch_cuda):
+    """Device memory of a context with 256 slots at d = 3072: the bf16 rows of the slots' mini-batches would be 100 MB by
+    themselves.  A snapshot keeps the places of two such copies, whatever they hold."""
+    torch = torch_cuda
+    X, y = synth.mixture_data(300, 3072, 4, seed=2)
+    Xd, yd = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
+    mk = lambda: ssgd.Context("mlp2", Xd, yd, 256, 8, 64, "k_async", ssgd.delay_dist("exp", 1.0), 0.01, seed=1, classes=4, hidden=128, bf16=1)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    a = mk()
+    rows = 2 * 256 * 64 * 3072
+    assert before - torch.cuda.mem_get_info()[0] < rows
+    a.run(12)
+    blob = a.get_state()
+    a.run(20)
+    zeros = np.flatnonzero(np.diff(np.concatenate(([1], (blob != 0).view(np.int8), [1]))))
+    start, length = max(((s, e - s) for s, e in zip(zeros[::2], zeros[1::2])), key=lambda p: p[1])
+    assert length >= 2 * rows                            # the longest run of zero bytes (the activations behind it may begin with zeros)
+    blob[start + 4096:start + 2 * rows - 4096] = 0xFF
+    b = mk()
+    b.set_state(blob)
+    b.run(20)
+    assert np.array_equal(a.params(), b.params())
+    a.close(); b.close()
+
+
 def test_malformed_snapshots_leave_the_context_unchanged(ssgd, oracle, torch_cuda):
     """A truncated buffer, a header that claims more updates than the buffer holds, or one whose size does not
     fit this configuration is refused with SSGD_EINVAL before the context is touched: the run goes on as if
