@@ -40,7 +40,7 @@ typedef float f32x8 __attribute__((ext_vector_type(8)));
 constexpr int MP = 64;         // rows kept per worker (m <= 64; the rest is zero)
 constexpr int KT = 64;         // contraction depth per stage
 constexpr int LDT = KT + 8;    // padded LDS row (bf16 elements): 144 bytes, keeps 16-byte reads conflict-poor
-constexpr int kShareSlots = 64; // most consumed slots per workgroup of the gradient contraction
+constexpr int kShareSlots = 64; // most consumed slots per workgroup of the gradient contraction: one per lane
 constexpr int kSmallRec = 32;  // most records per update that take the few-record path
 
 // round to nearest even, as a 16-bit pattern; infinities and NaNs are truncated
@@ -395,7 +395,9 @@ __global__ __launch_bounds__(256, 2) void mlp_contract_kernel(MlpArgs a) {
 // its workgroups, for which the others had to wait) and nothing is kept per slot for it.
 // K = 128, H = 512, d = 3072: this kernel 41 us either way (630 TFLOP/s), the forward kernel 64 -> 41 us.
 // The 16-byte chunks of both tiles are permuted by row so that the lanes of a read hit different banks: unpadded, the two
-// stages and the ids of a share leave room for two workgroups per CU.
+// stages and the ids of the longest share (64 slots) are half the LDS of a CU to the byte, so two workgroups fit; the slots
+// themselves are in registers for that reason (a list of them in LDS left one workgroup per CU where shares are full, K = 128 at
+// H = 1024).
 // BT x BT output tile per workgroup; the two halves of a launch that differ:
 // SPLIT: a share of the consumed slots per workgroup, partial sums left in dw_part, which mlp_w1_update_kernel adds in
 // order; otherwise the epilogue applies the update.
@@ -448,9 +450,8 @@ __global__ __launch_bounds__(256, 2) void mlp_grad_kernel(MlpArgs a) {
             wpre[j] = *reinterpret_cast<const f32x4*>(a.params + (int64_t)(bm * BT + row) * d + bn * BT + 4 * c4);
         }
     }
-    // slots and sample ids of the share, once
-    __shared__ int slot_list[kShareSlots];
-    for (int l = tid; l < stages; l += 256) slot_list[l] = consumed_slot(a, stage0 + l);
+    // slots (lane l of every wave: entry l) and sample ids of the share, once
+    const int slot_of_lane = lane < stages ? consumed_slot(a, stage0 + lane) : 0;
     for (int q = tid; q < stages * (MP / 4); q += 256)
         *reinterpret_cast<uint4*>(ids + 4 * q) = consumed_ids(a, stage0 + q / (MP / 4), q % (MP / 4));
     __syncthreads();
@@ -468,13 +469,13 @@ __global__ __launch_bounds__(256, 2) void mlp_grad_kernel(MlpArgs a) {
     int next_slot = 0;
     auto look_up = [&](int stage) {
         const int st = min(stage, stages - 1);
-        next_slot = slot_list[st];
+        next_slot = __builtin_amdgcn_readlane(slot_of_lane, st);
 #pragma unroll
         for (int i = 0; i < LP; ++i) next_id[i] = ids[st * MP + brow + RB * i];
     };
     auto fetch = [&](auto slot) {
         constexpr int Q = decltype(slot)::value;
-        const int64_t at = (int64_t)__builtin_amdgcn_readfirstlane(next_slot) * H * MP;
+        const int64_t at = (int64_t)next_slot * H * MP;
 #pragma unroll
         for (int i = 0; i < LP; ++i) {
             ra[Q][i] = *reinterpret_cast<const u16x8*>(a_base + at + 32 * i * MP);
@@ -1201,6 +1202,7 @@ __global__ void mlp_init_kernel(float* params, uint64_t seed, int64_t nw, int64_
 // operand double buffer; the epilogue's fp32 tile [BT][BT + 4] fits inside it
 size_t contract_lds(int bt) { return (size_t)4 * bt * LDT * 2; }
 // gradient contraction: unpadded double buffer and the sample ids of `slots` slots, or the epilogue's tile
+static_assert(2 * (4 * 128 * KT * 2 + kShareSlots * MP * 4) <= 160 * 1024, "two workgroups per CU with the longest share");
 size_t grad_lds(int bt, int slots) { return std::max((size_t)4 * bt * KT * 2 + (size_t)slots * MP * 4, sizeof(float) * (size_t)bt * (bt + 4)); }
 // Forward streams of the overlapped updates.  With the caller's stream and the stream of the schedule they are four:
 // a process has four hardware queues here, and streams that share one run their kernels one after the other (a long

@@ -767,6 +767,22 @@ def test_config4_mlp_full_size_large_K(ssgd, oracle, torch_cuda, mixture_full):
     ctx.close()
 
 
+@pytest.mark.parametrize("K", [128, 125])
+def test_mlp_gradient_contraction_with_full_shares(ssgd, oracle, torch_cuda, K):
+    """1024 x 3072 outputs leave two shares of the consumed slots: 64 of them, the most a workgroup takes, or 63 and 62."""
+    torch = torch_cuda
+    X, y = synth.mixture_data(500, 3072, 3, seed=4)
+    gd, od = dist_pair(ssgd, oracle, ("exp", 1.0))
+    ctx = ssgd.Context("mlp2", torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda(), 128, K, 2, "k_sync", gd, 0.05, seed=2,
+                       classes=3, hidden=1024, bf16=1)
+    tr = oracle.Trainer(oracle.Model("mlp2", X, y, classes=3, hidden=1024, bf16=1), 128, K, 2, "k_sync", od, 0.05, seed=2)
+    agg = torch.zeros(ctx.nw, dtype=torch.float32, device="cuda")
+    ctx.step(agg)
+    assert rel(agg.cpu().numpy(), tr.step()) <= MLP_GRAD_TOL
+    assert rel(ctx.params(), tr.params()) <= MLP_PARAM_TOL
+    ctx.close()
+
+
 def test_exchange_fallback_without_shared_l2(ssgd, oracle, torch_cuda, monkeypatch):
     """The cluster exchange has two protocols: through the L2 of one XCD (data words polled directly) and, for a
     cluster that is spread over XCDs, released stores with an arrival counter.  The second one is forced here."""
