@@ -135,6 +135,13 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
     // A tile holds whole records of mp rows; when an iteration spans several tiles, a tile is one block of 64 rows
     // of the iteration's mini-batches, all of them part of the update.
     constexpr bool chunked = CHUNKED;
+    // When a tile's rows are asked for: as soon as the tile in front of it is in LDS, or behind the description of the tile
+    // after it, some 3000 cycles later.  The gathers keep the memory path of the CU busy for 4000 cycles, and what the compute
+    // waves have to wait for meanwhile (parked gradients, partial logits and the stores in front of them) queues behind them,
+    // so they go late wherever there is an exchange: softmax, d = 3072, two mini-batches of 32, 8 replicas: K-sync 5.46 -> 4.85 us
+    // per update, K-batch-async 6.90 -> 6.05; early where nothing is waited for (one slice), and for synchronous iterations
+    // with two workgroups per CU (K-batch-sync of 16 x 128, 40 replicas: 285 early, 281 to 292 late).
+    constexpr bool kLate = !ONE && (ROOMY || !CHUNKED);
     // Records described one by one (BATCH: K-batch-async, and K-async when a version may have more records than a tile
     // holds), mini-batches of more than 64 rows: a tile is one block of 64 rows of one record; the record's gradient is
     // summed over its tiles in the slot of its worker
@@ -175,9 +182,8 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         const bool has_tail = d_rem != 0 && slice == G - 1;
         float* const my_tile = L.tile + lw * SL + lane * 4;
 
-        // A tile is described (sample ids, labels, lists: n_*) one turn before its rows are gathered, so that the gathers
-        // leave as soon as the tile in front of them is published; what is published is the description p_* of the tile
-        // whose rows are in `pref`.
+        // A tile is described (sample ids, labels, lists: n_*) one turn before its rows are gathered; what is published is the
+        // description p_* of the tile whose rows are in `pref`.
         f32x4 pref[LLOADS];
 #pragma unroll
         for (int i = 0; i < LLOADS; ++i) pref[i] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -340,16 +346,18 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
             row_lab = reinterpret_cast<const float*>(a.y)[id];    // fp32 or int32: the word as it is
             row_id = (smp < m && rec < h_nrec) ? id : kNoRow;
         };
-        // The gathers of the tile described last.  Nothing of this wave is in flight here (`publish` has waited for it): a
-        // wave's loads return in order, so what is asked for afterwards must not be needed before the rows are.
-        auto gather = [&]() {
+        // The tile described last becomes the one whose rows are gathered.
+        auto adopt = [&]() {
             p_row_id = row_id; p_row_lab = row_lab;
             p_K = n_K; p_nrec = n_nrec; p_nstale = n_nstale; p_stale = n_stale; p_stale_pos = n_stale_pos; p_rec_word = n_rec_word;
             p_rows = n_rows; p_flags = n_flags; p_ver = n_ver;
-            int olw = lw;
-            asm volatile("" : "+s"(olw));
             if constexpr (chunked) asm volatile("" : "+v"(p_row_id), "+v"(p_row_lab) : : "memory");
             else asm volatile("" : "+v"(p_row_id), "+v"(p_row_lab), "+v"(p_stale), "+v"(p_stale_pos), "+v"(p_rec_word) : : "memory");
+        };
+        // Its gathers.  A wave's loads return in order, so what is asked for afterwards must not be needed before the rows are.
+        auto gather = [&]() {
+            int olw = lw;
+            asm volatile("" : "+s"(olw));
             const int used = p_nrec * p_rows;      // a CU takes in about 16 bytes of gathers per cycle: rows past the records are left out
             __builtin_amdgcn_sched_barrier(0);
             if (!ONE || lane < 16 * nblk) {
@@ -462,7 +470,8 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         asm volatile("" : "+v"(q_sel), "+v"(q_tau), "+v"(q_ord), "+v"(row_lab) : : "memory");
         bool more = true;                            // the tile described last is still to be gathered
         auto turn = [&]() {
-            gather();
+            adopt();
+            if constexpr (!kLate) gather();
             if (at_tile + 1 < h_tiles) {
                 ++at_tile;
             } else if (at + 1 < a.nsteps) {
@@ -473,6 +482,10 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
             }
             issue_lists(a.v0 + min(at + 1, a.nsteps - 1));
             describe_tile(a.v0 + at, at_tile);       // past the last tile: that tile again, never gathered
+            if constexpr (kLate) {
+                asm volatile("" : "+v"(row_id) : : "memory");
+                gather();
+            }
         };
         // the rest of the tile that the compute waves work on; false: the launch is aborted
         auto rest = [&](int64_t v, int flags) -> bool {
@@ -678,6 +691,13 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         if (!ONE && !fast && lane == 0) __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         mark(1);
 
+        // (waited for whether this is the update's first tile or not: where the compiler takes them to be in flight still, it
+        // puts a wait for everything in front of the softmax, and that is one for the re-arming store behind the gathers: 1600
+        // cycles; K-async at the shape above 6.35 -> 5.48 us per update)
+        if constexpr (!chunked) {
+#pragma unroll
+            for (int vv = 0; vv < 4; ++vv) asm volatile("" : "+v"(pva[vv]), "+v"(pvb[vv]));
+        }
         if ((tile_flags & 2) != 0) {
 #pragma unroll
             for (int e = 0; e < 16; ++e) gsum[e] = pva[e >> 2][e & 3] + pvb[e >> 2][e & 3];
