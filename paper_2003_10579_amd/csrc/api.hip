@@ -332,6 +332,7 @@ ssgd_status launch_steps(ssgd_ctx* c, int64_t v0, int64_t n, float* agg_out, int
         a.agg_out = agg_out;
         a.pair_cus = 0; a.pair_layers = 0;
         a.shared_cus = ((a.replicas + 7) / 8 * 8 * c->G > c->cu_count) ? 1 : 0;      // an XCD takes an eighth of the clusters
+        a.whole_cus = !a.shared_cus && whole_cus(c->G, c->cu_count) ? 1 : 0;
         a.prof_wave = 0; a.prof_a = -1; a.prof_b = -1; a.prof_base = (int64_t)c->R * c->G * 20; a.prof_helper = (int64_t)c->R * c->G * 2;
         if (const char* e = getenv("SSGD_PHASE_PROFILE")) (void)sscanf(e, "%d,%d,%d", &a.prof_a, &a.prof_b, &a.prof_wave);
         a.debug_flags = 0;
@@ -371,6 +372,7 @@ ssgd_status launch_steps(ssgd_ctx* c, int64_t v0, int64_t n, float* agg_out, int
                 a.v0 = v0; a.nsteps = n;
                 a.agg_out = agg_out;
                 a.pair_cus = 0; a.pair_layers = 0; a.shared_cus = 8 * c->G > c->cu_count ? 1 : 0;
+                a.whole_cus = !a.shared_cus && whole_cus(c->G, c->cu_count) ? 1 : 0;
                 a.prof_wave = 0; a.prof_a = -1; a.prof_b = -1; a.prof_base = (int64_t)c->R * c->G * 20; a.prof_helper = (int64_t)c->R * c->G * 2;
                 a.debug_flags = 0;
                 if (!linear_tile_supports(a, c->Kcap)) return fail(c, SSGD_EDEVICE, "a cluster was spread over XCDs and no other kernel takes its shape");

@@ -105,6 +105,7 @@ struct LinArgs {
     // CUs.  Polling for the exchange then pauses longer between rounds: the re-reads of a waiting workgroup compete
     // with the memory operations of the one it shares the CU with.
     int32_t shared_cus;
+    int32_t whole_cus;                   // steady-state kernel: the form that takes a CU per workgroup
     int32_t prof_wave, prof_a, prof_b;   // diagnostics: wave and the pair of marks of the phase profile
     int32_t debug_flags;                 // test switches set by the host (SSGD_DEBUG_FLAGS): bit 1 makes the odd replicas take the path of a cluster spread over XCDs
     int64_t prof_base;                   // first word of the steady-state kernel's part of prof

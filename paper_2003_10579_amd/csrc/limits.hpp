@@ -18,4 +18,11 @@ constexpr int kSyncWaves = 4;
 constexpr int64_t kSyncUpdatesPerLaunch = 1 << 16;
 inline uint32_t sync_schedule_blocks(int64_t updates) { return (uint32_t)((updates + kSyncWaves - 1) / kSyncWaves); }
 
+// Whether the workgroups of a cluster may take a CU each for themselves.  The clusters of several launches (contexts of one
+// process run beside each other, one launch per hardware queue) can hold part of their CUs on an XCD and wait for the rest;
+// with at most G - 1 each, one of them still finds its last CU as long as the others leave one free.  Two workgroups per CU
+// leave twice the room.
+constexpr int kXcds = 8, kHardwareQueues = 4;
+inline bool whole_cus(int G, int cus) { return G == 1 || kHardwareQueues * (G - 1) < cus / kXcds; }
+
 }  // namespace ssgd

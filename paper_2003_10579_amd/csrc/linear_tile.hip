@@ -103,9 +103,16 @@ __device__ __forceinline__ void lds_barrier() {
 // Bound by the chain of one step, TU -> logits -> delta -> gradient -> update, beside the chain lists -> sample ids ->
 // gather of the next tile.  (Least squares, d = 64, two mini-batches of 16, one replica: 2.2 us per update where the
 // exchange through memory of the general kernel takes 8.5.)
-// ROOMY: a launch that leaves every workgroup a CU of its own.  Two waves per SIMD then have 256 registers each and
-// nothing is spilled; a spilled word that a loader wave reads back would wait for the gathers in front of it.
-template <int KIND, bool PROF, bool WHOLE, bool CHUNKED, bool BATCH, bool ONE, bool ROOMY>
+// ROOMY: every workgroup takes a CU for itself.  Two waves per SIMD then have 256 registers each and nothing is spilled; a
+// spilled word that a loader wave reads back would wait for the gathers in front of it.  (1 to 4 % at d = 3072.  Not for
+// clusters so wide that those of several launches could keep each other from becoming complete: LinArgs::whole_cus.)
+// LATE: when a tile's rows are asked for: as soon as the tile in front of it is in LDS, or behind the description of the tile
+// after it, some 3000 cycles later.  The gathers keep the memory path of the CU busy for 4000 cycles, and what the compute
+// waves have to wait for meanwhile (parked gradients, partial logits and the stores in front of them) queues behind them, so
+// they go late wherever there is an exchange: softmax, d = 3072, two mini-batches of 32, 8 replicas: K-sync 5.46 -> 4.85 us per
+// update, K-batch-async 6.90 -> 6.05; early where nothing is waited for (one slice), and for synchronous iterations with two
+// workgroups per CU (K-batch-sync of 16 x 128, 40 replicas: 285 early, 281 to 292 late).
+template <int KIND, bool PROF, bool WHOLE, bool CHUNKED, bool BATCH, bool ONE, bool ROOMY, bool LATE>
 __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs a) {
     // consecutive block ids go to different XCDs: all slices of one cluster take block ids that
     // are congruent modulo 8 and share one L2
@@ -135,13 +142,6 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
     // A tile holds whole records of mp rows; when an iteration spans several tiles, a tile is one block of 64 rows
     // of the iteration's mini-batches, all of them part of the update.
     constexpr bool chunked = CHUNKED;
-    // When a tile's rows are asked for: as soon as the tile in front of it is in LDS, or behind the description of the tile
-    // after it, some 3000 cycles later.  The gathers keep the memory path of the CU busy for 4000 cycles, and what the compute
-    // waves have to wait for meanwhile (parked gradients, partial logits and the stores in front of them) queues behind them,
-    // so they go late wherever there is an exchange: softmax, d = 3072, two mini-batches of 32, 8 replicas: K-sync 5.46 -> 4.85 us
-    // per update, K-batch-async 6.90 -> 6.05; early where nothing is waited for (one slice), and for synchronous iterations
-    // with two workgroups per CU (K-batch-sync of 16 x 128, 40 replicas: 285 early, 281 to 292 late).
-    constexpr bool kLate = !ONE && (ROOMY || !CHUNKED);
     // Records described one by one (BATCH: K-batch-async, and K-async when a version may have more records than a tile
     // holds), mini-batches of more than 64 rows: a tile is one block of 64 rows of one record; the record's gradient is
     // summed over its tiles in the slot of its worker
@@ -471,7 +471,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         bool more = true;                            // the tile described last is still to be gathered
         auto turn = [&]() {
             adopt();
-            if constexpr (!kLate) gather();
+            if constexpr (!LATE) gather();
             if (at_tile + 1 < h_tiles) {
                 ++at_tile;
             } else if (at + 1 < a.nsteps) {
@@ -482,7 +482,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
             }
             issue_lists(a.v0 + min(at + 1, a.nsteps - 1));
             describe_tile(a.v0 + at, at_tile);       // past the last tile: that tile again, never gathered
-            if constexpr (kLate) {
+            if constexpr (LATE) {
                 asm volatile("" : "+v"(row_id) : : "memory");
                 gather();
             }
@@ -1073,22 +1073,25 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
     for (int q = tid; q < S * 17; q += NTC) small_g[q] = L.small[q];
 }
 
-template <int KIND, bool PROF, bool WHOLE, bool CHUNKED, bool BATCH, bool ONE, bool ROOMY>
+template <int KIND, bool PROF, bool WHOLE, bool CHUNKED, bool BATCH, bool ONE, bool ROOMY, bool LATE>
 hipError_t launch_r(const LinArgs& a, size_t lds, hipStream_t s) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(linear_tile_kernel<KIND, PROF, WHOLE, CHUNKED, BATCH, ONE, ROOMY>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(linear_tile_kernel<KIND, PROF, WHOLE, CHUNKED, BATCH, ONE, ROOMY, LATE>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     const int groups = (a.replicas + 7) / 8;
     const int blocks = a.pair_cus > 0 ? 8 * a.pair_cus * a.pair_layers : groups * 8 * a.G;
-    hipLaunchKernelGGL((linear_tile_kernel<KIND, PROF, WHOLE, CHUNKED, BATCH, ONE, ROOMY>), dim3(blocks), dim3(512), lds, s, a);
+    hipLaunchKernelGGL((linear_tile_kernel<KIND, PROF, WHOLE, CHUNKED, BATCH, ONE, ROOMY, LATE>), dim3(blocks), dim3(512), lds, s, a);
     return hipGetLastError();
 }
 
 // (no phase profile for one workgroup, and for workgroups that share CUs only with a profile of their own)
 template <int KIND, bool PROF, bool WHOLE, bool CHUNKED, bool BATCH>
 hipError_t launch_w(const LinArgs& a, size_t lds, hipStream_t s) {
-    if (a.shared_cus) return launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, false, false>(a, lds, s);
-    return a.G == 1 ? launch_r<KIND, false, WHOLE, CHUNKED, BATCH, true, true>(a, lds, s) : launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, false, true>(a, lds, s);
+    if (a.G == 1) return launch_r<KIND, false, WHOLE, CHUNKED, BATCH, true, true, false>(a, lds, s);
+    if (a.whole_cus) return launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, false, true, true>(a, lds, s);
+    if constexpr (CHUNKED)
+        if (a.shared_cus) return launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, false, false, false>(a, lds, s);
+    return launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, false, false, true>(a, lds, s);
 }
 
 // K-async whose versions may have more records than a tile holds; version 0, at which all P workers start, is one.
@@ -1125,9 +1128,9 @@ int linear_tile_resident_groups(size_t lds_bytes) {
     int dev = 0, per_cu = 0;
     hipDeviceProp_t prop;
     if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(linear_tile_kernel<kSoftmax, false, false, false, false, false, false>),
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(linear_tile_kernel<kSoftmax, false, false, false, false, false, false, true>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, linear_tile_kernel<kSoftmax, false, false, false, false, false, false>, 512, lds_bytes) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, linear_tile_kernel<kSoftmax, false, false, false, false, false, false, true>, 512, lds_bytes) != hipSuccess) return 0;
     return per_cu * prop.multiProcessorCount;
 }
 

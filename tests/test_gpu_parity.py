@@ -1034,6 +1034,41 @@ def test_contexts_one_after_the_other_and_side_by_side_share_no_results(ssgd, to
         assert len(got[s]) == 6 and all(g == alone[s] for g in got[s])
 
 
+@pytest.mark.parametrize("d,variant", [(2048, "k_sync"), (3072, "k_batch_async")])
+def test_clusters_of_four_contexts_at_once(ssgd, torch_cuda, d, variant):
+    """Four contexts from four threads, each of 16 clusters of 8 and of 12 workgroups: what one computes does not depend on
+    the others, and none of them is kept waiting for CUs until it gives up."""
+    import threading
+    torch = torch_cuda
+    X, y = synth.mixture_data(600, d, 3, seed=3)
+    Xd, yd = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    torch.cuda.synchronize()
+    ctxs = [ssgd.Context("softmax", Xd, yd, 6, 2, 32, variant, ssgd.delay_dist("exp", 1.0), 0.01, seed=5, classes=3, replicas=16,
+                         stream=s.cuda_stream) for s in streams]
+    alone = ssgd.Context("softmax", Xd, yd, 6, 2, 32, variant, ssgd.delay_dist("exp", 1.0), 0.01, seed=5, classes=3, replicas=16)
+    alone.run(150)
+    errors = []
+
+    def work(c):
+        try:
+            for _ in range(3):
+                c.run(50)
+        except ssgd.SsgdError as e:
+            errors.append(str(e))
+
+    threads = [threading.Thread(target=work, args=(c,)) for c in ctxs]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    for c in ctxs:
+        assert np.array_equal(c.params(11), alone.params(11))
+        c.close()
+    alone.close()
+
+
 def test_adasync_ksync_rule_with_growing_tile_count(ssgd, oracle, torch_cuda):
     """K-sync under the paper's rule for K (Appendix D): K grows from 2 to 16 during the run, so the iterations go
     from one tile to two; trace and parameters against the oracle."""

@@ -39,3 +39,9 @@ def test_schedule_launches_stay_below_the_largest_grid(tmp_path):
     """Work items of one dimension of a launch are counted in 32 bits."""
     per, blocks, block = _evaluate(tmp_path, 'printf("%lld %u %d\\n", (long long)kSyncUpdatesPerLaunch, sync_schedule_blocks(kSyncUpdatesPerLaunch), 64 * kSyncWaves);')
     assert 0 < blocks * block < 2 ** 32 and blocks * block >= 64 * per
+
+
+def test_clusters_of_four_launches_cannot_keep_each_other_incomplete(tmp_path):
+    """Widths up to a whole XCD of 32 CUs: four launches that each hold all but one of the CUs of a cluster leave one free."""
+    ok = _evaluate(tmp_path, "".join(f'printf("%d\\n", (int)whole_cus({G}, 256));\n' for G in range(1, 33)))
+    assert ok == [1 if G == 1 or 4 * (G - 1) < 32 else 0 for G in range(1, 33)] and ok[:8] == [1] * 8 and not any(ok[8:])
