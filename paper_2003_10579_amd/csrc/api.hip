@@ -309,6 +309,8 @@ void arm_exchange(ssgd_ctx* c, bool tile, bool helper) {
                        c->dx.as<uint32_t>(), n_dx, c->fallback.as<uint32_t>(), helper ? (int64_t)c->R : (int64_t)0);
 }
 
+constexpr int64_t kShortSegment = 16;      // updates
+
 // One launch per group of co-resident replicas; `mode` selects the kernel.
 enum LinearKernel { kGeneralKernel = 0, kTileKernel = 1, kDeferKernel = 2 };
 ssgd_status launch_steps(ssgd_ctx* c, int64_t v0, int64_t n, float* agg_out, int mode,
@@ -424,7 +426,8 @@ ssgd_status run_segment_linear(ssgd_ctx* c, int64_t v0, int64_t n, float* agg_ou
         if (c->variant == SSGD_K_ASYNC && v0 == 0 && a.mp * c->Kcap <= 64) { head = 1; a.v0 = 1; }
         a.chunked = (c->variant == SSGD_K_SYNC || c->variant == SSGD_K_BATCH_SYNC) ? 1 : 0;
         tile = tile && linear_tile_supports(a, c->Kcap);
-        defer = defer && linear_defer_supports(a);
+        // (a launch of it is 5 us longer, and of one slice an update 0.5 to 1.2 us shorter)
+        defer = defer && linear_defer_supports(a) && (c->G > 1 || n - head >= kShortSegment);
     }
     if (!tile && !defer && c->variant == SSGD_K_BATCH_ASYNC) return fail(c, SSGD_EINVAL, "K-batch-async: the cluster of this shape does not fit the device");
     if (!tile && !defer) return launch_steps(c, v0, n, agg_out, kGeneralKernel, events);
@@ -458,13 +461,19 @@ ssgd_status run_updates(ssgd_ctx* c, int64_t J, float* agg_out) {
         // The schedule does not depend on the numerics (K changes only between segments here), so it is written piece by
         // piece on a second stream while the gradient kernels of the piece before run: one wavefront per replica beside
         // kernels that leave it room (the network's updates are separate launches; the steady-state kernel of K-async
-        // on the linear models leaves CUs free, and the tile kernel leaves registers free where no two of its workgroups
-        // share a CU).  The pieces of the linear models are long, since every piece is a launch of its own (20 to 40 us)
+        // on the linear models leaves CUs free as a rule, and so does the tile kernel where no two of its workgroups share a
+        // CU).  The pieces of the linear models are long, since every piece is a launch of its own (20 to 40 us)
         // that reads the gradients in flight from HBM and writes them back; the first one is short, since nothing hides
         // its schedule, and each of the next is three times the one before, since an update's schedule takes at most a
         // third of its gradients (0.6 of 4.0 us at P = 8; K-batch-async with 8 workers 1.4 of 4.2, P = 20, K = 5 2 of 20).
         const bool linear_async = c->model.kind != SSGD_MLP2 && (c->variant == SSGD_K_ASYNC || c->variant == SSGD_K_BATCH_ASYNC);
-        const bool leaves_room = c->defer_per_launch >= 1 || (c->tile_resident_groups >= c->G && ((c->R + 7) / 8 * 8 * c->G <= c->cu_count));
+        // Where the steady-state kernel of K-async fills the chip, the schedule's wavefront disturbs a cluster: worth it for one
+        // launch per piece at most (d = 768, 64 replicas, 3000 updates: 4.20 us per update piece by piece, 4.40 in one go; 200
+        // replicas in four launches: 17.0 against 16.3; one slice, 128 replicas: 4.8 against 4.4).
+        const bool defer_room = c->defer_per_launch >= 1 && ((std::min(c->R, c->defer_per_launch) + 7) / 8 * (c->G + 1) < c->cu_count / 8 ||
+                                                             (c->G > 1 && c->R <= c->defer_per_launch));
+        const bool tile_room = c->defer_per_launch < 1 && c->tile_resident_groups >= c->G && ((c->R + 7) / 8 * 8 * c->G <= c->cu_count);
+        const bool leaves_room = defer_room || tile_room;
         const bool linear_pipe = linear_async && leaves_room && agg_out == nullptr;
         // (one replica of the network takes the rows of a piece as they come: short pieces, the first one shorter still,
         // since nothing hides its schedule: 10 us per update at P = 256, K = 8, 26 at K = 128)
@@ -717,8 +726,13 @@ ssgd_status ssgd_create(const ssgd_model* model, int32_t P, int32_t K, int32_t m
         { hipDeviceProp_t prop; HIP_C(hipGetDeviceProperties(&prop, c->device)); c->cu_count = prop.multiProcessorCount; }
         if ((c->nbw == 4 || c->G == 1) && C <= 15 && linear_tile_lds_bytes(C, c->S, Kcap) <= 160 * 1024)
             c->tile_resident_groups = linear_tile_resident_groups(linear_tile_lds_bytes(C, c->S, Kcap));
-        if (c->nbw == 4 && c->G > 1 && C <= 15 && variant == SSGD_K_ASYNC && c->S <= 8 && linear_defer_lds_bytes(C, c->S) <= 160 * 1024)
+        if (c->nbw == 4 && C <= 15 && variant == SSGD_K_ASYNC && c->S <= 8 && linear_defer_lds_bytes(C, c->S) <= 160 * 1024)
             c->defer_per_launch = linear_defer_replicas_per_launch(c->G, c->cu_count);
+        // One slice has no exchange to hide, so the tile kernel, which needs no helper workgroup, is the better one where that
+        // would cost a second launch (136 replicas, d = 256: 5.6 against 8.5 us per update) and where many updates consume
+        // mini-batches of their own version (P = 4, K = 2: 4.8 against 5.4, P = 8, K = 4: 5.7 against 6.3; P = 5, K = 2: 4.85
+        // against 4.77, P = 8, K = 3: 4.95 against 4.78, P = 8, K = 2: 4.9 against 3.9).
+        if (c->G == 1 && (R > c->defer_per_launch || 5 * Kcap > 2 * P)) c->defer_per_launch = 0;
         HIP_C(c->params.alloc(sizeof(float) * R * c->nw));
         HIP_C(hipMemsetAsync(c->params.p, 0, sizeof(float) * R * c->nw, c->stream));
         const size_t park_n = (size_t)R * c->G * c->S * 16 * SL;

@@ -907,6 +907,8 @@ def test_several_tiles_and_odd_row_lengths(ssgd, oracle, torch_cuda, monkeypatch
 
 @pytest.mark.parametrize("kind,variant,P,K,m,d,classes", [
     ("lsq", "k_async", 8, 2, 32, 256, 1),            # the widest single slice, whole records
+    ("softmax", "k_async", 8, 3, 16, 132, 10),       # the most contributors of eight workers with gradients in flight in LDS
+    ("softmax", "k_async", 8, 4, 16, 132, 10),       # one more: no longer
     ("softmax", "k_async", 5, 3, 20, 65, 15),        # second 64-column block one column wide; 60 of 64 rows
     ("softmax", "k_async", 9, 4, 72, 190, 4),        # several tiles, records of two
     ("softmax", "k_sync", 4, 3, 64, 128, 10),        # three tiles per iteration, two column blocks
@@ -929,13 +931,14 @@ def test_one_slice(ssgd, oracle, torch_cuda, monkeypatch, kind, variant, P, K, m
     gd, od = dist_pair(ssgd, oracle, ("exp", 1.0))
     ctx = ssgd.Context(kind, Xd, yd, P, K, m, variant, gd, 0.01, seed=3, classes=classes)
     orc = oracle.Trainer(oracle.Model(kind, X, y, classes=classes), P, K, m, variant, od, 0.01, seed=3)
-    for kernel in (None, "general", None):
+    # (segments of 16 updates and more take the kernel that keeps gradients in flight in LDS where it has the shape)
+    for kernel, J in ((None, 20), ("general", 15), (None, 7), ("tile", 20), (None, 18)):
         if kernel:
             monkeypatch.setenv("SSGD_KERNEL", kernel)
         else:
             monkeypatch.delenv("SSGD_KERNEL", raising=False)
-        ctx.run(15)
-    orc.run(45)
+        ctx.run(J)
+    orc.run(80)
     assert_trace_equal(ctx.trace(), orc.trace())
     assert rel(ctx.params(), orc.params()) <= FP32_PARAM_TOL
 
