@@ -317,8 +317,7 @@ ssgd_status launch_steps(ssgd_ctx* c, int64_t v0, int64_t n, float* agg_out, int
                          std::vector<std::pair<hipEvent_t, hipEvent_t>>* events) {
     const bool tile = mode != kGeneralKernel;
     // a cluster stays on one XCD (block ids congruent modulo 8), so the resident slots count per XCD
-    // (clusters of one workgroup take a CU each: two on a CU get in each other's way and gain next to nothing)
-    const int resident = !tile ? c->resident_groups : (c->G == 1 ? std::min(c->tile_resident_groups, c->cu_count) : c->tile_resident_groups);
+    const int resident = tile ? c->tile_resident_groups : c->resident_groups;
     const int per_launch = mode == kDeferKernel ? c->defer_per_launch : std::max(1, 8 * ((resident / 8) / c->G));
     arm_exchange(c, tile, mode == kDeferKernel);
     HIP_OK(c, hipGetLastError());

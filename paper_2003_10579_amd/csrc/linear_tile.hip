@@ -105,7 +105,9 @@ __device__ __forceinline__ void lds_barrier() {
 // exchange through memory of the general kernel takes 8.5.)
 // ROOMY: every workgroup takes a CU for itself.  Two waves per SIMD then have 256 registers each and nothing is spilled; a
 // spilled word that a loader wave reads back would wait for the gathers in front of it.  (1 to 4 % at d = 3072.  Not for
-// clusters so wide that those of several launches could keep each other from becoming complete: LinArgs::whole_cus.)
+// clusters so wide that those of several launches could keep each other from becoming complete: LinArgs::whole_cus.  Not
+// where a launch has more workgroups than the chip has CUs: 1024 replicas of least squares, d = 64, two mini-batches of 16,
+// take 6.4 us per update with two workgroups per CU and 10.2 in rounds of one.)
 // LATE: when a tile's rows are asked for: as soon as the tile in front of it is in LDS, or behind the description of the tile
 // after it, some 3000 cycles later.  The gathers keep the memory path of the CU busy for 4000 cycles, and what the compute
 // waves have to wait for meanwhile (parked gradients, partial logits and the stores in front of them) queues behind them, so
@@ -1087,7 +1089,8 @@ hipError_t launch_r(const LinArgs& a, size_t lds, hipStream_t s) {
 // (no phase profile for one workgroup, and for workgroups that share CUs only with a profile of their own)
 template <int KIND, bool PROF, bool WHOLE, bool CHUNKED, bool BATCH>
 hipError_t launch_w(const LinArgs& a, size_t lds, hipStream_t s) {
-    if (a.G == 1) return launch_r<KIND, false, WHOLE, CHUNKED, BATCH, true, true, false>(a, lds, s);
+    if (a.G == 1) return a.shared_cus ? launch_r<KIND, false, WHOLE, CHUNKED, BATCH, true, false, false>(a, lds, s)
+                                      : launch_r<KIND, false, WHOLE, CHUNKED, BATCH, true, true, false>(a, lds, s);
     if (a.whole_cus) return launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, false, true, true>(a, lds, s);
     if constexpr (CHUNKED)
         if (a.shared_cus) return launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, false, false, false>(a, lds, s);

@@ -1037,6 +1037,23 @@ def test_contexts_one_after_the_other_and_side_by_side_share_no_results(ssgd, to
         assert len(got[s]) == 6 and all(g == alone[s] for g in got[s])
 
 
+@pytest.mark.parametrize("kind,variant,m,d,R", [("lsq", "k_sync", 8, 64, 300), ("softmax", "k_async", 16, 100, 300), ("lsq", "k_batch_async", 8, 36, 515)])
+def test_more_replicas_of_one_slice_than_cus(ssgd, oracle, torch_cuda, kind, variant, m, d, R):
+    """Two workgroups per CU, and a second launch for the replicas past two per CU."""
+    classes = 1 if kind == "lsq" else 5
+    X, y = synth.lsq_data(400, d, 8)[:2] if kind == "lsq" else synth.mixture_data(400, d, classes, seed=8)
+    gd, od = dist_pair(ssgd, oracle, ("exp", 1.0))
+    ctx = ssgd.Context(kind, torch_cuda.from_numpy(X).cuda(), torch_cuda.from_numpy(y).cuda(), 5, 2, m, variant, gd, 0.01, seed=9,
+                       classes=classes, replicas=R)
+    ctx.run(70)
+    for r in (0, 255, 256, R - 1):
+        orc = oracle.Trainer(oracle.Model(kind, X, y, classes=classes), 5, 2, m, variant, od, 0.01, seed=9, replica=r)
+        orc.run(70)
+        assert_trace_equal(ctx.trace(r), orc.trace())
+        assert rel(ctx.params(r), orc.params()) <= FP32_PARAM_TOL
+    ctx.close()
+
+
 @pytest.mark.parametrize("d,variant", [(2048, "k_sync"), (3072, "k_batch_async")])
 def test_clusters_of_four_contexts_at_once(ssgd, torch_cuda, d, variant):
     """Four contexts from four threads, each of 16 clusters of 8 and of 12 workgroups: what one computes does not depend on
