@@ -696,7 +696,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         // (waited for whether this is the update's first tile or not: where the compiler takes them to be in flight still, it
         // puts a wait for everything in front of the softmax, and that is one for the re-arming store behind the gathers: 1600
         // cycles; K-async at the shape above 6.35 -> 5.48 us per update)
-        if constexpr (!chunked) {
+        if constexpr (!chunked && !ONE) {
 #pragma unroll
             for (int vv = 0; vv < 4; ++vv) asm volatile("" : "+v"(pva[vv]), "+v"(pvb[vv]));
         }
