@@ -1086,11 +1086,10 @@ hipError_t launch_r(const LinArgs& a, size_t lds, hipStream_t s) {
     return hipGetLastError();
 }
 
-// (no phase profile for one workgroup, and for workgroups that share CUs only with a profile of their own)
 template <int KIND, bool PROF, bool WHOLE, bool CHUNKED, bool BATCH>
 hipError_t launch_w(const LinArgs& a, size_t lds, hipStream_t s) {
-    if (a.G == 1) return a.shared_cus ? launch_r<KIND, false, WHOLE, CHUNKED, BATCH, true, false, false>(a, lds, s)
-                                      : launch_r<KIND, false, WHOLE, CHUNKED, BATCH, true, true, false>(a, lds, s);
+    if (a.G == 1) return a.shared_cus ? launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, true, false, false>(a, lds, s)
+                                      : launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, true, true, false>(a, lds, s);
     if (a.whole_cus) return launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, false, true, true>(a, lds, s);
     if constexpr (CHUNKED)
         if (a.shared_cus) return launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, false, false, false>(a, lds, s);
@@ -1106,8 +1105,7 @@ template <int KIND, bool PROF>
 hipError_t launch_k(const LinArgs& a, size_t lds, hipStream_t s) {
     if (a.chunked) return launch_w<KIND, PROF, true, true, false>(a, lds, s);
     const bool whole = a.mp == 32 || a.mp == 64;
-    if (records_one_by_one(a))           // (no phase profile for this form)
-        return whole ? launch_w<KIND, false, true, false, true>(a, lds, s) : launch_w<KIND, false, false, false, true>(a, lds, s);
+    if (records_one_by_one(a)) return whole ? launch_w<KIND, PROF, true, false, true>(a, lds, s) : launch_w<KIND, PROF, false, false, true>(a, lds, s);
     return whole ? launch_w<KIND, PROF, true, false, false>(a, lds, s) : launch_w<KIND, PROF, false, false, false>(a, lds, s);
 }
 

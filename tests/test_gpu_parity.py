@@ -1037,6 +1037,24 @@ def test_contexts_one_after_the_other_and_side_by_side_share_no_results(ssgd, to
         assert len(got[s]) == 6 and all(g == alone[s] for g in got[s])
 
 
+@pytest.mark.parametrize("variant,P,K,m,d,R", [
+    ("k_sync", 4, 2, 16, 64, 1), ("k_async", 12, 2, 16, 100, 2), ("k_batch_async", 4, 2, 16, 36, 300),      # one slice
+    ("k_async", 20, 5, 25, 300, 1), ("k_batch_async", 4, 2, 16, 300, 1),                                    # records one by one
+    ("k_sync", 4, 2, 16, 300, 1), ("k_async", 6, 2, 16, 300, 1)])
+def test_phase_profile_of_every_form(ssgd, torch_cuda, monkeypatch, capfd, variant, P, K, m, d, R):
+    """SSGD_PHASE_PROFILE prints the cycles of a whole step (from one mark to its next passing) for every kernel that runs
+    the steady state."""
+    import re
+    monkeypatch.setenv("SSGD_PHASE_PROFILE", "5,6,0" if variant != "k_async" or P > 8 else "4,5,0")
+    X, y, _ = synth.lsq_data(300, d, 8)
+    ctx = ssgd.Context("lsq", torch_cuda.from_numpy(X).cuda(), torch_cuda.from_numpy(y).cuda(), P, K, m, variant,
+                       ssgd.delay_dist("exp", 1.0), 0.01, seed=9, replicas=R)
+    ctx.run(100)
+    ctx.close()
+    cycles = float(re.search(r"ssgd phase profile .*: (\d+) cycles", capfd.readouterr().err).group(1))
+    assert 100 < cycles < 1e6
+
+
 @pytest.mark.parametrize("kind,variant,m,d,R", [("lsq", "k_sync", 8, 64, 300), ("softmax", "k_async", 16, 100, 300), ("lsq", "k_batch_async", 8, 36, 515)])
 def test_more_replicas_of_one_slice_than_cus(ssgd, oracle, torch_cuda, kind, variant, m, d, R):
     """Two workgroups per CU, and a second launch for the replicas past two per CU."""
