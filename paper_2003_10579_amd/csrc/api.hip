@@ -20,21 +20,23 @@ namespace {
 thread_local std::string g_err;
 
 // Pinned host memory outlives the context that asked for it: taking a block and giving it back cost 30 and 50 us, more
-// than anything else in making and destroying a small context.  At most kMaxSpare blocks of at most kSpareBytes are kept,
-// per device, for whoever asks next; a block is given back when nothing queued can write to it any more.
+// than anything else in making and destroying a small context.  At most kMaxSpare blocks of at most kSpareBytes are kept
+// for whoever asks next on the same device; a block is given back when nothing queued can write to it any more.
 struct PinnedPool {
-    static constexpr size_t kMaxSpare = 8, kSpareBytes = 4 << 20, kLeastBytes = 64 << 10;
+    static constexpr size_t kSpareBytes = 4 << 20, kLeastBytes = 64 << 10;
+    static constexpr int kMaxSpare = 8;
     struct Block { void* p; size_t bytes; int device; };
     std::mutex mutex;
-    std::vector<Block> spare;
+    Block spare[kMaxSpare] = {};         // (no container: giving a block back cannot fail, making the pool neither)
+    int count = 0;
     hipError_t take(size_t bytes, int device, void** p, size_t* got) {
         bytes = std::max(bytes, kLeastBytes);
         {
             std::lock_guard<std::mutex> lock(mutex);
-            for (size_t q = 0; q < spare.size(); ++q)
+            for (int q = 0; q < count; ++q)
                 if (spare[q].device == device && spare[q].bytes >= bytes) {
                     *p = spare[q].p; *got = spare[q].bytes;
-                    spare.erase(spare.begin() + (ptrdiff_t)q);
+                    spare[q] = spare[--count];
                     return hipSuccess;
                 }
         }
@@ -46,14 +48,13 @@ struct PinnedPool {
         if (!p) return;
         {
             std::lock_guard<std::mutex> lock(mutex);
-            if (spare.size() < kMaxSpare && bytes <= kSpareBytes && spare.capacity() > spare.size()) { spare.push_back({p, bytes, device}); return; }
+            if (count < kMaxSpare && bytes <= kSpareBytes) { spare[count++] = {p, bytes, device}; return; }
         }
         (void)hipHostFree(p);
     }
-    PinnedPool() { spare.reserve(kMaxSpare); }
 };
-// (never destroyed: the runtime may be gone by the time static objects are)
-PinnedPool& pinned_pool() { static PinnedPool* pool = new PinnedPool; return *pool; }
+// (nothing is freed at the end of the process: the runtime may be gone by then)
+PinnedPool& pinned_pool() { static PinnedPool pool; return pool; }
 
 struct DevBuf {
     void* p = nullptr;
