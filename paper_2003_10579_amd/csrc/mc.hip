@@ -39,10 +39,10 @@ struct McArgs {
     int32_t variant, P, Kmin, Kmax, chain_len;
     int32_t nslices;     // block b takes the values K = Kmin + b % nslices, + nslices, ...: small accumulators, many waves per CU
     int64_t trial0, trials;
-    int32_t one_by_one;  // K-batch-async: delays may be below zero, so that a push can be earlier than the one before it
     double mean_delay;   // a rough value: first guess of a selection, size of the K-batch-async lists
     double* partial;     // [blocks][nK*chain_len][2]
     double* per_trial;   // nullable
+    int32_t one_by_one;  // K-batch-async: delays may be below zero, so that a push can be earlier than the one before it
 };
 
 typedef unsigned long long u64;
