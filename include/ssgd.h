@@ -55,7 +55,7 @@ typedef enum {
     SSGD_K_BATCH_ASYNC = 3 /* first K mini-batches, nobody is cancelled: a worker that pushes re-reads the
                               current parameters and starts its next mini-batch at once.  Fixed K or
                               AdaSync mode 1.  Linear models: d % 4 == 0, at most 15 classes,
-                              K <= 64 (any m); MLP2: its usual limits, K <= 256;
+                              K <= 64 (any m), N d 4 < 2^32; MLP2: its usual limits, K <= 256;
                               else SSGD_EINVAL */
 } ssgd_variant;
 
@@ -203,7 +203,8 @@ ssgd_status ssgd_get_workers(ssgd_ctx *ctx, int32_t replica, int32_t *tau, int32
  * SSGD_EINVAL, context unchanged), replaces that context's state and trace, and the updates that
  * follow are those the original context would have run.  A device error while the state is
  * copied leaves the context unusable (SSGD_ESTATE from then on).  The data set is not part of
- * the snapshot. */
+ * the snapshot and has to be the one that the snapshot was taken with: the rows of mini-batches in
+ * flight of SSGD_MLP2 are read from it again. */
 ssgd_status ssgd_state_bytes(ssgd_ctx *ctx, int64_t *bytes);
 ssgd_status ssgd_get_state(ssgd_ctx *ctx, void *host_buf, int64_t bytes);
 ssgd_status ssgd_set_state(ssgd_ctx *ctx, const void *host_buf, int64_t bytes);

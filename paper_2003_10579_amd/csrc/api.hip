@@ -465,7 +465,7 @@ ssgd_status run_updates(ssgd_ctx* c, int64_t J, float* agg_out) {
         // CU).  The pieces of the linear models are long, since every piece is a launch of its own (20 to 40 us)
         // that reads the gradients in flight from HBM and writes them back; the first one is short, since nothing hides
         // its schedule, and each of the next is three times the one before, since an update's schedule takes at most a
-        // third of its gradients (0.6 of 4.0 us at P = 8; K-batch-async with 8 workers 1.4 of 4.2, P = 20, K = 5 2 of 20).
+        // third of its gradients (0.6 of 4.0 us at P = 8; K-batch-async with 8 workers 1.4 of 4.3, P = 20, K = 5 2 of 17).
         const bool linear_async = c->model.kind != SSGD_MLP2 && (c->variant == SSGD_K_ASYNC || c->variant == SSGD_K_BATCH_ASYNC);
         // Where the steady-state kernel of K-async fills the chip, the schedule's wavefront disturbs a cluster: worth it for one
         // launch per piece at most (d = 768, 64 replicas, 3000 updates: 4.20 us per update piece by piece, 4.40 in one go; 200

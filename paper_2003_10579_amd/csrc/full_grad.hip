@@ -10,7 +10,8 @@
 // block over exactly (every sum has one term that is not zero), and its result registers are the operand of the four
 // steps that follow.  The registers of a block are refilled with the next 16 rows as soon as it has been turned over, so
 // the loads travel behind the rest of the gradient pass and the next forward pass.  The gradient stays in registers (96
-// more) until the run of rows ends.  Matrix time is 12 steps per 16 x 16 block, 18 000 cycles per 16 rows of d = 3072
+// more) until the run of rows ends.  (The widest softmax form needs six registers more than there are: 28 bytes per lane of
+// scratch memory.)  Matrix time is 12 steps per 16 x 16 block, 18 000 cycles per 16 rows of d = 3072
 // and CU, below the 23 000 cycles that the rows take to arrive.
 // full_grad_reduce_kernel adds the workgroups' partial gradients in order in fp64.
 // N = 50000, d = 3072, 10 classes: 199 us (3.1 TB/s) + 10 us for the reduction, where the two passes below took 518 +

@@ -4,7 +4,7 @@
 // mini-batches 64 at a time, the gradient is summed over the tiles and the update follows the last
 // one; the asynchronous ones take whole records per tile, or 64-row blocks of one record.
 // (K-async of several tiles and rows of odd length took the general kernel before: P = 20, K = 5, m = 25, d = 785,
-// 10 classes, 8 replicas: 50 us per update there, 23 here.)
+// 10 classes, 8 replicas: 50 us per update there, 17 here.)
 // Same cluster decomposition, state layout and arithmetic as the general kernel (linear.hip),
 // which runs every other shape and may be mixed with this one launch by launch; what differs
 // is the schedule inside a step:
@@ -101,8 +101,8 @@ __device__ __forceinline__ void lds_barrier() {
 // ONE: the cluster is one workgroup (d <= 256).  Its partial logits are the logits: they change lanes inside the wave
 // instead of going out to the exchange, and only the 64-column blocks that exist are loaded, written and contracted.
 // Bound by the chain of one step, TU -> logits -> delta -> gradient -> update, beside the chain lists -> sample ids ->
-// gather of the next tile.  (Least squares, d = 64, two mini-batches of 16, one replica: 2.2 us per update where the
-// exchange through memory of the general kernel takes 8.5.)
+// gather of the next tile.  (Least squares, d = 64, two mini-batches of 16, one replica: 2.4 us per update where the
+// exchange through memory of the general kernel takes 8.6.)
 // ROOMY: every workgroup takes a CU for itself.  Two waves per SIMD then have 256 registers each and nothing is spilled; a
 // spilled word that a loader wave reads back would wait for the gathers in front of it.  (1 to 4 % at d = 3072.  Not for
 // clusters so wide that those of several launches could keep each other from becoming complete: LinArgs::whole_cus.  Not
