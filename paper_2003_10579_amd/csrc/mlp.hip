@@ -395,15 +395,16 @@ __global__ __launch_bounds__(256, 2) void mlp_contract_kernel(MlpArgs a) {
 // its workgroups, for which the others had to wait) and nothing is kept per slot for it.
 // K = 128, H = 512, d = 3072: this kernel 41 us either way (630 TFLOP/s), the forward kernel 64 -> 41 us.
 // The 16-byte chunks of both tiles are permuted by row so that the lanes of a read hit different banks: unpadded, the two
-// stages and the ids of the longest share (64 slots) are half the LDS of a CU to the byte, so two workgroups fit; the slots
-// themselves are in registers for that reason (a list of them in LDS left one workgroup per CU where shares are full, K = 128 at
-// H = 1024).
+// stages and the ids of the longest share (64 slots) are half the LDS of a CU to the byte, so two workgroups fit; for that one
+// share length the slots themselves are in a register, one per lane (a list of them in LDS leaves one workgroup per CU where shares are
+// full: H = 1024, K = 128 213 us per update, 196 without), for the others in a list behind the ids (H = 512, K = 128: 109.1 us, 109.8
+// with the register).
 // BT x BT output tile per workgroup; the two halves of a launch that differ:
 // SPLIT: a share of the consumed slots per workgroup, partial sums left in dw_part, which mlp_w1_update_kernel adds in
 // order; otherwise the epilogue applies the update.
 template <int BT> __device__ __forceinline__ int row_key(int s) { return BT == 128 ? 4 * (s & 3) : 4 * ((s >> 1) & 1); }
 typedef short s16x4 __attribute__((ext_vector_type(4)));
-template <int BT, bool SPLIT>
+template <int BT, bool SPLIT, bool LIST>
 __global__ __launch_bounds__(256, 2) void mlp_grad_kernel(MlpArgs a) {
     constexpr int WT = BT / 2;          // rows and columns per wave
     constexpr int NF = WT / 32;         // 32 x 32 MFMA tiles per wave and dimension
@@ -450,8 +451,14 @@ __global__ __launch_bounds__(256, 2) void mlp_grad_kernel(MlpArgs a) {
             wpre[j] = *reinterpret_cast<const f32x4*>(a.params + (int64_t)(bm * BT + row) * d + bn * BT + 4 * c4);
         }
     }
-    // slots (lane l of every wave: entry l) and sample ids of the share, once
-    const int slot_of_lane = lane < stages ? consumed_slot(a, stage0 + lane) : 0;
+    // slots (LIST: behind the ids, else lane l of every wave: entry l) and sample ids of the share, once
+    int* slot_list = reinterpret_cast<int*>(ids + stages * MP);
+    int slot_of_lane = 0;
+    if constexpr (LIST) {
+        if (tid < stages) slot_list[tid] = consumed_slot(a, stage0 + tid);
+    } else {
+        slot_of_lane = lane < stages ? consumed_slot(a, stage0 + lane) : 0;
+    }
     for (int q = tid; q < stages * (MP / 4); q += 256)
         *reinterpret_cast<uint4*>(ids + 4 * q) = consumed_ids(a, stage0 + q / (MP / 4), q % (MP / 4));
     __syncthreads();
@@ -469,13 +476,13 @@ __global__ __launch_bounds__(256, 2) void mlp_grad_kernel(MlpArgs a) {
     int next_slot = 0;
     auto look_up = [&](int stage) {
         const int st = min(stage, stages - 1);
-        next_slot = __builtin_amdgcn_readlane(slot_of_lane, st);
+        next_slot = LIST ? slot_list[st] : __builtin_amdgcn_readlane(slot_of_lane, st);
 #pragma unroll
         for (int i = 0; i < LP; ++i) next_id[i] = ids[st * MP + brow + RB * i];
     };
     auto fetch = [&](auto slot) {
         constexpr int Q = decltype(slot)::value;
-        const int64_t at = (int64_t)next_slot * H * MP;
+        const int64_t at = (int64_t)__builtin_amdgcn_readfirstlane(next_slot) * H * MP;
 #pragma unroll
         for (int i = 0; i < LP; ++i) {
             ra[Q][i] = *reinterpret_cast<const u16x8*>(a_base + at + 32 * i * MP);
@@ -1201,9 +1208,13 @@ __global__ void mlp_init_kernel(float* params, uint64_t seed, int64_t nw, int64_
 
 // operand double buffer; the epilogue's fp32 tile [BT][BT + 4] fits inside it
 size_t contract_lds(int bt) { return (size_t)4 * bt * LDT * 2; }
-// gradient contraction: unpadded double buffer and the sample ids of `slots` slots, or the epilogue's tile
-static_assert(2 * (4 * 128 * KT * 2 + kShareSlots * MP * 4) <= 160 * 1024, "two workgroups per CU with the longest share");
-size_t grad_lds(int bt, int slots) { return std::max((size_t)4 * bt * KT * 2 + (size_t)slots * MP * 4, sizeof(float) * (size_t)bt * (bt + 4)); }
+// gradient contraction: unpadded double buffer, the sample ids of `slots` slots and a list of the slots (not of a full share), or
+// the epilogue's tile
+constexpr size_t grad_lds(int bt, int slots) {
+    const size_t operands = (size_t)4 * bt * KT * 2 + (size_t)slots * (MP + (slots < kShareSlots ? 1 : 0)) * 4, tile = sizeof(float) * (size_t)bt * (bt + 4);
+    return operands > tile ? operands : tile;
+}
+static_assert(2 * grad_lds(128, kShareSlots) <= 160 * 1024 && 2 * grad_lds(128, kShareSlots - 1) <= 160 * 1024, "two workgroups per CU with the longest shares");
 // Forward streams of the overlapped updates.  With the caller's stream and the stream of the schedule they are four:
 // a process has four hardware queues here, and streams that share one run their kernels one after the other (a long
 // schedule kernel in front of a forward kernel, say).
@@ -1314,8 +1325,9 @@ hipError_t mlp_create(MlpState** out, const ssgd_model& model, int P, int m, int
     TRY(hipGetLastError());
     TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_contract_kernel<128>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)contract_lds(128)));
     TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_contract_kernel<64>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)contract_lds(64)));
-    TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_grad_kernel<64, false>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)grad_lds(64, 32)));
-    TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_grad_kernel<128, true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)grad_lds(128, kShareSlots)));
+    TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_grad_kernel<64, false, true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)grad_lds(64, 32)));
+    TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_grad_kernel<128, true, true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)grad_lds(128, kShareSlots)));
+    TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_grad_kernel<128, true, false>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)grad_lds(128, kShareSlots)));
     TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_mid_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)mid_lds_bytes(1024)));
     TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_fwd_gather_kernel<128, false>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)contract_lds(128)));
     TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_fwd_gather_kernel<64, true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)contract_lds(64)));
@@ -1373,13 +1385,15 @@ void launch_backward(MlpArgs& a, hipStream_t stream, hipEvent_t done = nullptr) 
         // workgroups costs more than the shorter shares gain; more only where a share would be longer than its id list)
         const int tiles = (a.H / 128) * (a.d / 128);
         a.nsplit = std::max({1, std::min({kMaxSplit, a.Kv / 8, 512 / tiles}), (a.Kv + kShareSlots - 1) / kShareSlots});
-        hipLaunchKernelGGL((mlp_grad_kernel<128, true>), dim3((a.H / 128) * 8 * (((a.d / 128) * a.nsplit + 7) / 8)), dim3(256),
-                           grad_lds(128, (a.Kv + a.nsplit - 1) / a.nsplit), stream, a);
+        const int share = (a.Kv + a.nsplit - 1) / a.nsplit;
+        const dim3 grid((a.H / 128) * 8 * (((a.d / 128) * a.nsplit + 7) / 8));
+        if (share < kShareSlots) hipLaunchKernelGGL((mlp_grad_kernel<128, true, true>), grid, dim3(256), grad_lds(128, share), stream, a);
+        else hipLaunchKernelGGL((mlp_grad_kernel<128, true, false>), grid, dim3(256), grad_lds(128, share), stream, a);
         hipExtLaunchKernelGGL(mlp_w1_update_kernel, dim3(kW1Blocks + kSmallBlocks16), dim3(256), 0, stream, nullptr, done, 0, a);
     } else {
         // small tiles: 384 workgroups instead of 96 matter more than the reuse inside a larger tile; one more row of
         // workgroups takes the small parameters
-        hipExtLaunchKernelGGL((mlp_grad_kernel<64, false>), dim3(a.H / 64, a.d / 64 + 1), dim3(256), grad_lds(64, a.Kv), stream, nullptr, done, 0, a);
+        hipExtLaunchKernelGGL((mlp_grad_kernel<64, false, true>), dim3(a.H / 64, a.d / 64 + 1), dim3(256), grad_lds(64, a.Kv), stream, nullptr, done, 0, a);
     }
 }
 void launch_update(MlpArgs& a, hipStream_t stream) {
