@@ -510,10 +510,11 @@ __device__ __forceinline__ void slice_role(const LinArgs& a, int rep, int slice,
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int i = 0; i < LLOADS; ++i) {
-                // rows without a sample read row 0; their delta is zero
-                uint32_t id = (uint32_t)__builtin_amdgcn_readlane((int)row_id, lw + 4 * i);
-                id = (id == kNoRow) ? 0u : id;
-                pf[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, goff[i & 3], (int)(id * row_bytes), kStream));
+                // rows without a sample are zero: their delta is, but zero times an infinity is not
+                const uint32_t id = (uint32_t)__builtin_amdgcn_readlane((int)row_id, lw + 4 * i);
+                const bool none = id == kNoRow;
+                pf[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(xrsrc, none ? (int)kPastMatrix : goff[i & 3],
+                                                                                        none ? 0 : (int)(id * row_bytes), kStream));
             }
         };
         auto publish = [&](const TileMeta& t, const f32x4 (&pf)[LLOADS], int par) {

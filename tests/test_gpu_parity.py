@@ -949,6 +949,8 @@ def test_one_slice(ssgd, oracle, torch_cuda, monkeypatch, kind, variant, P, K, m
     ("softmax", "k_batch_sync", 3, 3, 22, 516, 4),  # the last tile half empty
     ("lsq", "k_async", 5, 2, 7, 35, 1),
     ("softmax", "k_batch_async", 4, 2, 70, 260, 3), # records of a full tile and one of 8 rows
+    ("softmax", "k_async", 6, 2, 13, 516, 3),       # gradients in flight in LDS: padded records, half a tile
+    ("lsq", "k_async", 6, 1, 30, 200, 1),           # the same for one slice
 ])
 def test_rows_that_no_sample_names_do_not_matter(ssgd, oracle, torch_cuda, kind, variant, P, K, m, d, classes):
     """The places of a tile that hold no sample contribute nothing, also where the data set holds infinities and NaN in rows
@@ -959,13 +961,13 @@ def test_rows_that_no_sample_names_do_not_matter(ssgd, oracle, torch_cuda, kind,
         bad = X.copy()
         bad[0], bad[1] = np.inf, np.nan
         orc = oracle.Trainer(oracle.Model(kind, bad, y, classes=classes), P, K, m, variant, od, 0.01, seed=seed)
-        orc.run(5)
+        orc.run(20)
         if np.all(np.isfinite(orc.params())):
             break
     assert np.all(np.isfinite(orc.params()))
     ctx = ssgd.Context(kind, torch_cuda.from_numpy(bad).cuda(), torch_cuda.from_numpy(y).cuda(), P, K, m, variant, gd, 0.01, seed=seed,
                        classes=classes)
-    ctx.run(5)
+    ctx.run(20)
     assert rel(ctx.params(), orc.params()) <= FP32_PARAM_TOL
 
 
