@@ -91,6 +91,7 @@ struct ssgd_ctx {
     int64_t nw = 0;
     int32_t Kcap = 0, S = 0, G = 0, nbw = 0, maxrows = 0, table_ord = 1;
     int tile_resident_groups = 0, defer_per_launch = 0, cu_count = 0;
+    int team = 1, spread = 0;       // linear models: clusters that share the tiles of an update (tile kernel), on XCDs of their own
     LinArgs lin{};
     int64_t j = 0;
     int32_t win_cnt = 0;
@@ -100,7 +101,7 @@ struct ssgd_ctx {
     DevBuf tr_t, tr_loss, tr_K, tr_sel, tr_tau, tr_ord;
     WorkerState ws{};
     DevBuf ws_finish, ws_tau, ws_ord, ws_clock, ws_curK, ws_winprev, ws_winidx, ws_F0, ws_intstart, ws_crossed, ws_ndone;
-    DevBuf params, park, park_small, zpart, zx, dx, fallback, arrive, abort_flag, xcc_ids, prof;
+    DevBuf params, park, park_small, zpart, zx, dx, tx, park2, park2_small, fallback, arrive, abort_flag, xcc_ids, prof;
     int resident_groups = 0;
     size_t lds_bytes = 0;
     std::vector<MlpState*> mlp;      // two-layer network: one state per replica
@@ -186,13 +187,14 @@ hipError_t read_flags(ssgd_ctx* c) {
 // The exchange buffers of the cluster kernels as they have to be when a launch begins: counters and flags zero, every
 // exchanged word the sentinel (all ones).  One launch instead of a memset each.
 __global__ __launch_bounds__(256) void arm_exchange_kernel(uint32_t* arrive, int64_t n_arrive, uint32_t* zx, int64_t n_zx, uint32_t* dx, int64_t n_dx,
-                                                           uint32_t* fallback, int64_t n_fallback) {
+                                                           uint32_t* tx, int64_t n_tx, uint32_t* fallback, int64_t n_fallback) {
     const int64_t q0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
     for (int64_t q = q0; q < n_arrive; q += step) arrive[q] = 0u;
     for (int64_t q = q0; q < n_fallback; q += step) fallback[q] = 0u;
     const uint4 ones = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
     for (int64_t q = q0; q < n_zx / 4; q += step) reinterpret_cast<uint4*>(zx)[q] = ones;
     for (int64_t q = q0; q < n_dx / 4; q += step) reinterpret_cast<uint4*>(dx)[q] = ones;
+    for (int64_t q = q0; q < n_tx / 4; q += step) reinterpret_cast<uint4*>(tx)[q] = ones;
 }
 
 __global__ void init_workers_kernel(WorkerState ws, Dist dist, uint64_t seed, int P, int R, int K, int variant,
@@ -304,10 +306,11 @@ int chunks_for(int n_rec, int mp) {
 }
 
 void arm_exchange(ssgd_ctx* c, bool tile, bool helper) {
-    const int64_t n_zx = tile ? 3 * 1024 * (int64_t)c->R * c->G : 0, n_dx = helper ? 4 * 1024 * (int64_t)c->R : 0;
-    const unsigned blocks = (unsigned)std::max<int64_t>(1, std::min<int64_t>(1024, (n_zx + n_dx) / 4096));
+    const int64_t n_zx = tile ? 3 * 1024 * (int64_t)c->R * c->G * c->team : 0, n_dx = helper ? 4 * 1024 * (int64_t)c->R : 0;
+    const int64_t n_tx = tile && c->team > 1 ? 3 * (int64_t)kTeamWords * c->R * c->G * c->team : 0;
+    const unsigned blocks = (unsigned)std::max<int64_t>(1, std::min<int64_t>(1024, (n_zx + n_dx + n_tx) / 4096));
     hipLaunchKernelGGL(arm_exchange_kernel, dim3(blocks), dim3(256), 0, c->stream, c->arrive.as<uint32_t>(), (int64_t)kArriveStride * c->R, c->zx.as<uint32_t>(), n_zx,
-                       c->dx.as<uint32_t>(), n_dx, c->fallback.as<uint32_t>(), helper ? (int64_t)c->R : (int64_t)0);
+                       c->dx.as<uint32_t>(), n_dx, c->tx.as<uint32_t>(), n_tx, c->fallback.as<uint32_t>(), helper ? (int64_t)c->R : (int64_t)0);
 }
 
 constexpr int64_t kShortSegment = 16;      // updates
@@ -319,7 +322,7 @@ ssgd_status launch_steps(ssgd_ctx* c, int64_t v0, int64_t n, float* agg_out, int
     const bool tile = mode != kGeneralKernel;
     // a cluster stays on one XCD (block ids congruent modulo 8), so the resident slots count per XCD
     const int resident = tile ? c->tile_resident_groups : c->resident_groups;
-    const int per_launch = mode == kDeferKernel ? c->defer_per_launch : std::max(1, 8 * ((resident / 8) / c->G));
+    const int per_launch = mode == kDeferKernel ? c->defer_per_launch : mode == kTileKernel && c->team > 1 ? c->R : std::max(1, 8 * ((resident / 8) / c->G));
     arm_exchange(c, tile, mode == kDeferKernel);
     HIP_OK(c, hipGetLastError());
     c->flags_seen = false;
@@ -334,12 +337,14 @@ ssgd_status launch_steps(ssgd_ctx* c, int64_t v0, int64_t n, float* agg_out, int
         a.agg_out = agg_out;
         a.pair_cus = 0; a.pair_layers = 0;
         a.shared_cus = ((a.replicas + 7) / 8 * 8 * c->G > c->cu_count) ? 1 : 0;      // an XCD takes an eighth of the clusters
-        a.whole_cus = !a.shared_cus && whole_cus(c->G, c->cu_count) ? 1 : 0;
+        // workgroups that wait for each other on an XCD; a team spread over XCDs: all of the launch
+        const int bound = c->spread && mode == kTileKernel ? (a.replicas * c->team + 7) / 8 * c->G : c->G * (mode == kTileKernel ? c->team : 1);
+        a.whole_cus = !a.shared_cus && whole_cus(bound, c->cu_count) ? 1 : 0;
         a.prof_wave = 0; a.prof_a = -1; a.prof_b = -1; a.prof_base = (int64_t)c->R * c->G * 20; a.prof_helper = (int64_t)c->R * c->G * 2;
         if (const char* e = getenv("SSGD_PHASE_PROFILE")) (void)sscanf(e, "%d,%d,%d", &a.prof_a, &a.prof_b, &a.prof_wave);
         a.debug_flags = 0;
         if (const char* e = getenv("SSGD_DEBUG_FLAGS")) a.debug_flags = atoi(e);
-        if (mode == kTileKernel && a.replicas == per_launch && c->cu_count % 8 == 0 && resident % c->cu_count == 0 && !getenv("SSGD_NO_PAIRING")) {
+        if (mode == kTileKernel && c->team == 1 && a.replicas == per_launch && c->cu_count % 8 == 0 && resident % c->cu_count == 0 && !getenv("SSGD_NO_PAIRING")) {
             a.pair_cus = c->cu_count / 8;
             a.pair_layers = resident / c->cu_count;
             // the dealt-out layout must hold as many clusters per XCD as the consecutive one
@@ -399,6 +404,14 @@ ssgd_status run_segment_linear(ssgd_ctx* c, int64_t v0, int64_t n, float* agg_ou
     a.zpart = c->zpart.as<float>(); a.maxrows = c->maxrows;
     a.zx = c->zx.as<uint32_t>();
     a.dx = c->dx.as<uint32_t>();
+    a.team = c->team; a.spread = c->spread; a.tx = c->tx.as<uint32_t>();
+    a.own_slots = c->spread || c->variant == SSGD_K_BATCH_ASYNC ? c->S : 0;
+    a.park2 = c->park2.as<float>(); a.park2_small = c->park2_small.as<float>();
+    {
+        // whole records per tile, shared out evenly
+        const int most = std::max(1, 64 / c->mp), turns = (c->Kcap + most * c->team - 1) / (most * c->team);
+        a.team_rpt = c->mp > 64 ? 1 : (c->Kcap + c->team * turns - 1) / (c->team * turns);
+    }
     a.fallback = c->fallback.as<int32_t>();
     a.arrive = c->arrive.as<unsigned int>();
     a.abort_flag = c->abort_flag.as<int32_t>();
@@ -717,15 +730,15 @@ ssgd_status ssgd_create(const ssgd_model* model, int32_t P, int32_t K, int32_t m
         c->lds_bytes = linear_lds_bytes(c->nbw, C, c->S, async);
         if (variant == SSGD_K_BATCH_ASYNC) {
             // the general kernel is never used for this variant; what has to fit is the steady-state kernel's LDS
-            if (linear_tile_lds_bytes(C, c->S, Kcap) > 160 * 1024) return bail(SSGD_EINVAL, "too many gradient slots for the LDS of one workgroup");
+            if (linear_tile_lds_bytes(C, c->S, Kcap, false) > 160 * 1024) return bail(SSGD_EINVAL, "too many gradient slots for the LDS of one workgroup");
             c->lds_bytes = std::min<size_t>(c->lds_bytes, 160 * 1024);
         }
         if (c->lds_bytes > 160 * 1024) return bail(SSGD_EINVAL, "too many gradient slots for the LDS of one workgroup");
         c->resident_groups = linear_max_resident_groups(c->nbw, c->lds_bytes);
         if (c->resident_groups < c->G) return bail(SSGD_EINVAL, "d is too large for a co-resident cluster of workgroups");
         { hipDeviceProp_t prop; HIP_C(hipGetDeviceProperties(&prop, c->device)); c->cu_count = prop.multiProcessorCount; }
-        if ((c->nbw == 4 || c->G == 1) && C <= 15 && linear_tile_lds_bytes(C, c->S, Kcap) <= 160 * 1024)
-            c->tile_resident_groups = linear_tile_resident_groups(linear_tile_lds_bytes(C, c->S, Kcap));
+        if ((c->nbw == 4 || c->G == 1) && C <= 15 && linear_tile_lds_bytes(C, c->S, Kcap, false) <= 160 * 1024)
+            c->tile_resident_groups = linear_tile_resident_groups(linear_tile_lds_bytes(C, c->S, Kcap, false));
         if (c->nbw == 4 && C <= 15 && variant == SSGD_K_ASYNC && c->S <= 8 && linear_defer_lds_bytes(C, c->S) <= 160 * 1024)
             c->defer_per_launch = linear_defer_replicas_per_launch(c->G, c->cu_count);
         // One slice has no exchange to hide, so the tile kernel, which needs no helper workgroup, is the better one where that
@@ -733,6 +746,14 @@ ssgd_status ssgd_create(const ssgd_model* model, int32_t P, int32_t K, int32_t m
         // mini-batches of their own version (P = 4, K = 2: 4.8 against 5.4, P = 8, K = 4: 5.7 against 6.3; P = 5, K = 2: 4.85
         // against 4.77, P = 8, K = 3: 4.95 against 4.78, P = 8, K = 2: 4.9 against 3.9).
         if (c->G == 1 && (R > c->defer_per_launch || 5 * Kcap > 2 * P)) c->defer_per_launch = 0;
+        // Updates of more than one tile are shared out where CUs are to spare.  (Not under AdaSync, whose updates may have one
+        // tile for most of a run.)
+        if (c->tile_resident_groups >= c->G && c->cu_count > 0 && ada.mode == 0) {
+            const int64_t tiles = async ? (c->mp > 64 ? Kcap : (Kcap + 64 / c->mp - 1) / (64 / c->mp)) : ((int64_t)Kcap * c->mp + 63) / 64;
+            const int per_cu = linear_tile_resident_groups(linear_tile_lds_bytes(C, c->S, Kcap, true)) / c->cu_count;
+            const TeamShape shape = team_shape(tiles, c->G, C, R, c->cu_count, per_cu);
+            c->team = shape.members; c->spread = shape.spread;
+        }
         HIP_C(c->params.alloc(sizeof(float) * R * c->nw));
         HIP_C(hipMemsetAsync(c->params.p, 0, sizeof(float) * R * c->nw, c->stream));
         const size_t park_n = (size_t)R * c->G * c->S * 16 * SL;
@@ -741,11 +762,18 @@ ssgd_status ssgd_create(const ssgd_model* model, int32_t P, int32_t K, int32_t m
         HIP_C(c->park_small.alloc(sizeof(float) * R * c->G * c->S * 17));
         HIP_C(hipMemsetAsync(c->park_small.p, 0, sizeof(float) * R * c->G * c->S * 17, c->stream));
         HIP_C(c->zpart.alloc(sizeof(float) * R * 2 * c->G * c->maxrows * 16));
-        HIP_C(c->zx.alloc(sizeof(uint32_t) * 3 * 1024 * (size_t)R * c->G));
+        HIP_C(c->zx.alloc(sizeof(uint32_t) * 3 * 1024 * (size_t)R * c->G * c->team));
+        if (c->team > 1) HIP_C(c->tx.alloc(sizeof(uint32_t) * 3 * kTeamWords * (size_t)R * c->G * c->team));
+        if (c->team > 1 && async) {
+            const size_t slots = (size_t)R * c->G * c->team * (1 + (c->spread || variant == SSGD_K_BATCH_ASYNC ? c->S : 0));
+            HIP_C(c->park2.alloc(sizeof(float) * slots * 16 * SL));
+            HIP_C(c->park2_small.alloc(sizeof(float) * slots * 17));
+        }
         HIP_C(c->dx.alloc(sizeof(uint32_t) * 4 * 1024 * (size_t)R));
         HIP_C(c->fallback.alloc(sizeof(int32_t) * (size_t)R));
-        HIP_C(c->xcc_ids.alloc(sizeof(int32_t) * R * (c->G + 1)));
-        HIP_C(hipMemsetAsync(c->xcc_ids.p, 0xFF, sizeof(int32_t) * R * (c->G + 1), c->stream));
+        const size_t n_ids = (size_t)R * std::max(c->G + 1, c->G * c->team);
+        HIP_C(c->xcc_ids.alloc(sizeof(int32_t) * n_ids));
+        HIP_C(hipMemsetAsync(c->xcc_ids.p, 0xFF, sizeof(int32_t) * n_ids, c->stream));
         if (getenv("SSGD_PHASE_PROFILE")) {
             HIP_C(c->prof.alloc(sizeof(unsigned long long) * (R * c->G * 22 + R)));
             HIP_C(hipMemsetAsync(c->prof.p, 0, sizeof(unsigned long long) * (R * c->G * 22 + R), c->stream));
@@ -1203,7 +1231,7 @@ void ssgd_destroy(ssgd_ctx* c) {
     pinned_pool().give(c->host_flags, c->host_flags_bytes, c->device);
     DevBuf* bufs[] = {&c->table, &c->tr_t, &c->tr_loss, &c->tr_K, &c->tr_sel, &c->tr_tau, &c->tr_ord, &c->ws_finish,
                       &c->ws_tau, &c->ws_ord, &c->ws_clock, &c->ws_curK, &c->ws_winprev, &c->ws_winidx, &c->ws_F0,
-                      &c->ws_intstart, &c->ws_crossed, &c->ws_ndone, &c->params, &c->park, &c->park_small, &c->zpart, &c->zx, &c->dx, &c->fallback,
+                      &c->ws_intstart, &c->ws_crossed, &c->ws_ndone, &c->params, &c->park, &c->park_small, &c->zpart, &c->zx, &c->dx, &c->tx, &c->park2, &c->park2_small, &c->fallback,
                       &c->arrive, &c->abort_flag, &c->xcc_ids, &c->prof, &c->fg_work};
     for (DevBuf* b : bufs) b->release();
     delete c;

@@ -17,6 +17,8 @@ constexpr int kMaxWorkers = 256;   // four workers per lane of one wavefront
 constexpr int kClassPad = 16;      // MFMA tile height that holds the class dimension
 constexpr int kArriveStride = 64;  // 32-bit words between the arrival counters of two replicas
 constexpr int kArriveFast = 32;
+constexpr int kArriveTeam = 16;
+constexpr int kTeamWords = 4 * 256 * 4 + 32;   // a team member's part of an exchange: 16 bytes per thread and class row, bias gradient and loss
 
 // Per-update records written by the schedule kernel (one row per update).
 struct Trace {
@@ -91,10 +93,18 @@ struct LinArgs {
     uint32_t* dx;            // [R][4][64][16] delta on its way from a cluster's helper workgroup to its slices, same convention
     int32_t* fallback;       // [R] set by a cluster that does not sit on one XCD: the replica was left untouched
     unsigned int* arrive;    // [R][kArriveStride] arrival counters of the cluster exchange, zero at launch:
-                             // word 0 fenced exchanges, word kArriveFast shared-L2 exchanges (a cache line each)
+                             // word 0 fenced exchanges, word kArriveFast shared-L2 exchanges (a cache line each), word kArriveTeam
+                             // the workgroups of a team
     int32_t* abort_flag;
     uint32_t spin_limit;
     float* agg_out;          // nullable: averaged gradient of the last update of replica 0
+    // Steady-state kernel: clusters per replica that share the tiles of an update (1: no team), and the whole records of a
+    // tile then (asynchronous variants)
+    int32_t team, team_rpt;
+    int32_t spread;          // the clusters of a team sit on XCDs of their own instead of one
+    int32_t own_slots;       // a member's slots for gradients in flight: S, or 0 where the team uses those of everyone
+    float *park2, *park2_small;   // [R][G][team][own_slots + 1] of the parked gradients' layout
+    uint32_t* tx;            // [R][G][3][team][kTeamWords] exchange of a team's gradient sums, armed like zx (which is then [R][team][3][G][64][16])
     int32_t* xcc_ids;        // [R][G + 1] XCD each workgroup of a cluster runs on (checked on the device); kernels without a helper use [R][G]
     int32_t allow_fast;      // 1: exchange through the shared L2 once a cluster is known to sit on one XCD
     // Steady-state kernel, full launches only: CUs per XCD and resident workgroups per CU.  When set, the
@@ -122,9 +132,10 @@ hipError_t launch_linear(const LinArgs& a, int nbw, hipStream_t s);
 // Single-tile steady-state kernel (256 columns per workgroup, same state layout as launch_linear with nbw = 4).
 // max_records: the most mini-batches any step of the segment computes.
 bool linear_tile_supports(const LinArgs& a, int max_records);
-size_t linear_tile_lds_bytes(int C, int S, int Kcap);
+size_t linear_tile_lds_bytes(int C, int S, int Kcap, bool team);
 int linear_tile_resident_groups(size_t lds_bytes);
 hipError_t launch_linear_tile(const LinArgs& a, hipStream_t s);
+hipError_t launch_linear_tile_lsq(const LinArgs& a, hipStream_t s);      // least squares, a translation unit of its own
 // Steady-state kernel of K-async with at most 8 workers (linear_defer.hip): one workgroup per CU, the gradients in
 // flight in LDS, the gradient contraction of a tile one version behind its forward pass.  Same state layout.
 bool linear_defer_supports(const LinArgs& a);

@@ -24,10 +24,20 @@
 //       compute waves: w -= (lr/K) * aggregate (after the last tile of the update);
 //       loader waves: next tile -> LDS
 //
+// An update of several tiles can be shared by several clusters of its replica, a team (TEAM): each takes every so-many-th tile
+// (whole records of the asynchronous variants), adds the gradients in flight that it has computed itself, and after its last
+// tile the members exchange their sums, 16 bytes per thread and class row, added by everyone in the members' order, so that the
+// weights, of which each has a copy, stay the same bit for bit.  The chain of an update is then one or two tiles long plus one
+// exchange (about 2500 cycles) instead of all of them: softmax, P = 20, K = 5, m = 25, d = 785, 8 replicas (three tiles, three
+// members) 17.4 -> 9.1 us per update; K-sync, K = 6, m = 84, d = 116, 6 replicas (eight tiles) 26.6 -> 5.5; K-batch-async,
+// K = 4, m = 115, d = 580, 15 replicas (four records of two tiles) 40.7 -> 14.2.
+//
 // Four compute waves, four loader waves.  A wave's vector-memory counter retires in order,
 // so the long HBM gathers live in waves of their own: the loader waves fetch everything of
 // the next tile (lists, sample ids, labels, rows) while the current one is computed, hold the
 // rows in registers, and copy them to LDS between B and TU.
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace ssgd {
@@ -43,6 +53,7 @@ constexpr int LLOADS = 16;      // 16-byte loads per loader lane per tile
 constexpr int KC = 64;          // list entries per step (one lane of a wave each)
 constexpr int kAgentLoad = 16;  // cache policy: served by the L2, never by a CU's L1
 constexpr int kStream = 2;      // cache policy: non-temporal
+constexpr int kOwnSlot = 1 << 19;     // in a slot's number (lists in LDS): among the slots of this member of the team
 constexpr uint32_t kNoRow = 0xFFFFFFFFu;
 constexpr int kOutOfRange = (int)0x80000000;   // offset past any buffer of exchanged words or parked gradients: loads give 0, stores are dropped
 
@@ -60,6 +71,8 @@ struct Lds {
     float* small;     // [S][17]   bias gradient and mean loss of every parked slot
     int* ctl;         // [8]: 0 stop, 1 exchange through the shared L2, 2 cluster shares an XCD, 3 exchanges seen by wave 0,
                       //      4 K, 5 records, 6 parked gradients that update v consumes
+                      //      TEAM: 2 the team as it runs: its members, or 1
+    uint8_t* own;     // TEAM, [S] (the place of `small`): 1 where this member has computed the gradient in flight, in this launch
     int* s_stale;     // [KC] slots of those parked gradients, in the order of the consume list
     int* s_rec;       // [KC] compute list of v: slot of record r; bit 16: consumed by update v itself
 };
@@ -77,6 +90,7 @@ __device__ __forceinline__ Lds carve(unsigned char* smem, int C, int S, int kc) 
     l.s_stale = l.ctl + 8;
     l.s_rec = l.s_stale + kc;
     l.small = reinterpret_cast<float*>(l.s_rec + kc);
+    l.own = reinterpret_cast<uint8_t*>(l.s_rec + kc);
     return l;
 }
 
@@ -87,8 +101,21 @@ __device__ __forceinline__ float quad_xor1(float x) {
 __device__ __forceinline__ float quad_xor2(float x) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
 }
-__device__ __forceinline__ float quad_lane0(float x) {
+[[maybe_unused]] __device__ __forceinline__ float quad_lane0(float x) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x00, 0xF, 0xF, false));   // quad_perm [0,0,0,0]
+}
+
+// value of lane ^ 16 / lane ^ 32
+template <int MASK>
+__device__ __forceinline__ float across(float x, int lane) {
+    const uint32_t v = __float_as_uint(x);
+    if constexpr (MASK == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        return __uint_as_float((lane & 16) ? r[0] : r[1]);
+    } else {
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        return __uint_as_float((lane & 32) ? r[0] : r[1]);
+    }
 }
 
 __device__ __forceinline__ void lds_barrier() {
@@ -114,13 +141,15 @@ __device__ __forceinline__ void lds_barrier() {
 // they go late wherever there is an exchange: softmax, d = 3072, two mini-batches of 32, 8 replicas: K-sync 5.46 -> 4.85 us per
 // update, K-batch-async 6.90 -> 6.05; early where nothing is waited for (one slice), and for synchronous iterations with two
 // workgroups per CU (K-batch-sync of 16 x 128, 40 replicas: 285 early, 281 to 292 late).
-template <int KIND, bool PROF, bool WHOLE, bool CHUNKED, bool BATCH, bool ONE, bool ROOMY, bool LATE>
+template <int KIND, bool PROF, bool WHOLE, bool CHUNKED, bool BATCH, bool ONE, bool ROOMY, bool LATE, bool TEAM>
 __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs a) {
     // consecutive block ids go to different XCDs: all slices of one cluster take block ids that
     // are congruent modulo 8 and share one L2
     const int xcd = blockIdx.x & 7, slot_in_xcd = blockIdx.x >> 3;
     int pos = slot_in_xcd / a.G, slice = slot_in_xcd % a.G;
-    if (a.pair_cus > 0) {
+    int member = 0;
+    if constexpr (TEAM) { if (!a.spread) { member = pos % a.team; pos /= a.team; } }
+    if (!TEAM && a.pair_cus > 0) {
         // The dispatcher hands the first pair_cus slots of an XCD to distinct CUs and the next pair_cus slots
         // to the same CUs again.  A cluster takes G CUs of one such layer, so the clusters on those G CUs
         // share them with each other only and run in alternation; the CUs left over hold one more cluster.
@@ -130,7 +159,8 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         if (cu < nb * a.G) { pos = (cu / a.G) * layers + layer; slice = cu % a.G; }
         else { const int rem = (cu - nb * a.G) + layer * Lr; pos = nb * layers + rem / a.G; slice = rem % a.G; }
     }
-    const int cluster = pos * 8 + xcd;
+    int cluster = pos * 8 + xcd;
+    if constexpr (TEAM) { if (a.spread) { member = cluster % a.team; cluster /= a.team; } }
     if (cluster >= a.replicas) return;
     const int rep = a.replica0 + cluster;
 
@@ -150,6 +180,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
     const int spr = (BATCH && mp > ROWS) ? (mp + ROWS - 1) / ROWS : 1;      // tiles per record
     const int mpt = (chunked || spr > 1) ? ROWS : mp;
     const int nblk = ONE ? (d + 63) >> 6 : SL / 64;      // 64-column blocks in use
+    const int crew = TEAM ? rep * a.team + member : rep;  // whose exchange buffers of partial logits
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int kc = Kcap > 32 ? KC : 32;      // places of the lists in LDS
@@ -225,7 +256,9 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         int h_first = 0, h_trig = 0, h_trig_fresh = 0, h_nstale = 0;
         int h_rw = 0, h_ro = 0, h_rf = 0;        // lane j: worker, ordinal, consumed-by-this-update flag of restart j
         int h_csel = -1, h_ctau = -1, h_cord = 0;   // lane l: entry l of the consume list of the version
-        const int rpt = spr > 1 ? 1 : ROWS / mp; // K-batch-async: whole records per tile (or one block of a record)
+        const int rpt = TEAM && BATCH ? a.team_rpt : (spr > 1 ? 1 : ROWS / mp); // whole records per tile (or one block of a record)
+        const int own_slots = TEAM && BATCH && a.own_slots > 0 ? kOwnSlot : 0;
+        int team = 1, h_total = 1;               // TEAM: members; tiles of the version over all of them (records of several tiles: records)
         auto take_lists = [&](int64_t ver) {
             const int l_sel = lane < Kcap ? q_sel : -1, l_tau = lane < Kcap ? q_tau : -1, l_ord = lane < Kcap ? q_ord : 0;
             const int K = __popcll(__ballot(l_sel >= 0));
@@ -267,10 +300,40 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
             }
             n_K = K;
             // parked gradients that update ver consumes: entries whose version is older, compacted
-            const bool is_stale = lane < K && l_tau != (int32_t)ver;
+            bool is_stale = lane < K && l_tau != (int32_t)ver;
+            int l_own = 0;
+            if constexpr (TEAM && BATCH) {
+                // each by the member that computed it: nobody reads what another CU has written.  Who computed those of earlier
+                // launches follows from their place among the records of their version, so that the sums do not depend on
+                // where a launch ended.
+                if (lw == 0) {
+                    const int q = is_stale ? l_sel : 0;
+                    bool mine = is_stale && L.own[q] != 0;
+                    if (mine) { L.own[q] = 0; l_own = own_slots; }
+                    for (unsigned long long old = __ballot(is_stale && l_tau < (int32_t)a.v0); old != 0; old &= old - 1) {
+                        const int l = __builtin_ctzll(old);
+                        const int w = __builtin_amdgcn_readlane(l_sel, l), tau = __builtin_amdgcn_readlane(l_tau, l);
+                        int place = w;
+                        if (async) {
+                            if (tau > 0) place = __builtin_ctzll(__ballot(tr_sel[(int64_t)(tau - 1) * Kcap + q_lane] == w) | (1ull << 63));
+                        } else {
+                            // a restart during update tau, or what its trigger (tau = 0: the worker) began at tau
+                            const int o = __builtin_amdgcn_readlane(l_ord, l);
+                            const int s_ = tr_sel[(int64_t)tau * Kcap + q_lane], t_ = tr_tau[(int64_t)tau * Kcap + q_lane],
+                                      o_ = tr_ord[(int64_t)tau * Kcap + q_lane];
+                            const int pushes = __popcll(__ballot(lane < Kcap && s_ >= 0));
+                            const unsigned long long at = __ballot(lane < pushes - 1 && s_ == w && (t_ == tau ? o_ + 1 : 0) == o);
+                            if (at != 0) place = (tau > 0 ? 1 : a.P) + __builtin_ctzll(at);
+                            else if (tau > 0) place = 0;
+                        }
+                        if (lane == l) mine = (place / rpt) % team == member;
+                    }
+                    is_stale = mine;
+                }
+            }
             const unsigned long long smask = __ballot(is_stale);
             n_nstale = __popcll(smask);
-            n_stale = (async || BATCH) ? l_sel : lane;
+            n_stale = (async || BATCH) ? (l_sel | l_own) : lane;
             n_stale_pos = is_stale ? __popcll(smask & ((1ull << lane) - 1ull)) : KC;
             if (chunked) {
                 // every tile is one record of 64 rows that update ver consumes itself
@@ -288,20 +351,28 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                 h_nstale = n_nstale;
                 h_tiles = spr > 1 ? max(1, nrec * spr) : max(1, (nrec + rpt - 1) / rpt);
             }
+            if constexpr (TEAM) {
+                // every team-th tile, or every team-th record of several tiles; an empty tile where none is left
+                h_total = BATCH && spr > 1 ? nrec : h_tiles;
+                h_tiles = max(1, (BATCH && spr > 1 ? spr : 1) * ((h_total - member + team - 1) / team));
+            }
             cur_sel = l_sel;
             if constexpr (chunked) asm volatile("" : "+v"(h_worker), "+v"(h_ord) : : "memory");
             else asm volatile("" : "+v"(n_stale), "+v"(n_stale_pos), "+v"(n_rec_word), "+v"(cur_sel), "+v"(h_worker), "+v"(h_ord) : : "memory");
             if constexpr (BATCH) asm volatile("" : "+v"(h_rw), "+v"(h_ro), "+v"(h_rf), "+v"(h_csel), "+v"(h_ctau), "+v"(h_cord) : : "memory");
         };
         // Tile `t` of version `ver`: sample ids, lists; leaves the labels in flight.
-        auto describe_tile = [&](int64_t ver, int t) {
+        auto describe_tile = [&](int64_t ver, int t_mine) {
             n_ver = ver;
-            n_flags = (t + 1 == h_tiles ? 1 : 0) | (t == 0 ? 2 : 0);      // bit 0 last tile of its update, bit 1 first
+            n_flags = (t_mine + 1 == h_tiles ? 1 : 0) | (t_mine == 0 ? 2 : 0);      // bit 0 last tile of its update, bit 1 first
+            int t = t_mine;
+            if constexpr (TEAM) t = BATCH && spr > 1 ? (member + team * (t_mine / spr)) * spr + t_mine % spr : member + team * t_mine;
             n_rows = mpt;                                                 // rows per record in this tile
             int rec = r_of, smp = s_of;
             if (chunked) {
                 // one record; the contraction takes 32 rows at a time
                 n_rows = (min(ROWS, h_nrec * mp - t * ROWS) > 32) ? ROWS : 32;
+                if constexpr (TEAM) n_nrec = t < h_total ? 1 : 0;
                 if (t > 0) { const int q = t * ROWS + lane; rec = q / mp; smp = q - rec * mp; }
             }
             int worker, ordinal;
@@ -312,7 +383,8 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                 rec = (r_of < rpt) ? tr0 + r_of : 0x7FFFFFF;
                 if (spr > 1) { rec = tr0; smp = ROWS * blk + lane; n_rows = WHOLE ? ROWS : min(ROWS, mp - ROWS * blk); }
                 n_nrec = spr > 1 ? 1 : min(rpt, h_nrec - t * rpt);
-                n_nstale = (t == 0) ? h_nstale : 0;
+                if constexpr (TEAM) n_nrec = spr > 1 ? (tr0 < h_nrec ? 1 : 0) : max(0, n_nrec);
+                n_nstale = (t_mine == 0) ? h_nstale : 0;
                 // worker, ordinal and consumed-by-this-update flag of record q
                 auto describe = [&](int q, int& w, int& o, int& f) {
                     const int j = min(max(q - h_first, 0), 63);
@@ -337,6 +409,12 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                 // bit 16: consumed by the update of its own version; bit 17: the record goes on in the next tile; bit 18: it
                 // began in an earlier tile
                 n_rec_word = (lane < n_nrec) ? (qw | (qf << 16) | ((blk + 1 < spr ? 1 : 0) << 17) | ((blk > 0 ? 1 : 0) << 18)) : 0;
+                if constexpr (TEAM) {
+                    if (lw == 0 && lane < n_nrec && qf == 0) {
+                        L.own[qw] = 1;
+                        n_rec_word |= own_slots;
+                    }
+                }
             } else {
                 worker = __shfl(h_worker, min(rec, 63), 64);
                 ordinal = __shfl(h_ord, min(rec, 63), 64);
@@ -463,6 +541,11 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         lds_barrier();                               // the compute waves have set up the control words
         if (L.ctl[0] != 0) return;
         if ((async || BATCH) && a.v0 >= 1 && lane < Kcap) cur_sel = tr_sel[(a.v0 - 1) * Kcap + lane];
+        if constexpr (TEAM) team = __builtin_amdgcn_readfirstlane(L.ctl[2]);
+        if constexpr (TEAM && BATCH) {
+            if (lw == 0)
+                for (int q = lane; q < S; q += 64) L.own[q] = 0;
+        }
         int64_t at = 0;                              // update and tile described last
         int at_tile = 0;
         issue_lists(a.v0);
@@ -494,7 +577,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
             lmark(1);
             lds_barrier();                           // D
             if (L.ctl[0] != 0) return false;
-            if (lw == 0) bias_and_loss(v, flags);
+            if (!TEAM && lw == 0) bias_and_loss(v, flags);
             lmark(2);
             lds_barrier();                           // B
             lmark(3);
@@ -516,7 +599,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
             if (!rest(v, flags)) return;
         }
         if constexpr (PROF) {
-            if (lprof && lane == 0) a.prof[(int64_t)a.prof_base + ((int64_t)rep * G + slice) * 2 + 1] += lp_acc;
+            if (lprof && lane == 0 && member == 0) a.prof[(int64_t)a.prof_base + ((int64_t)rep * G + slice) * 2 + 1] += lp_acc;
         }
         lds_barrier();                               // the compute waves' last LDS writes
         return;
@@ -548,7 +631,8 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         }
     }
     if (tid < 16) L.bias[tid] = (KIND == kSoftmax && tid < C) ? params[(int64_t)C * d + tid] : 0.0f;
-    for (int q = tid; q < S * 17; q += NTC) L.small[q] = small_g[q];
+    if constexpr (!TEAM)
+        for (int q = tid; q < S * 17; q += NTC) L.small[q] = small_g[q];
     if (tid == 0) {
         L.ctl[0] = __hip_atomic_load(a.abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         L.ctl[1] = 0;   // fenced until the cluster is known to share an XCD
@@ -557,16 +641,58 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         // XCC_ID in the low byte (what the same-XCD check compares); HW_ID (CU, shader engine) above it, for diagnostics
         const int my_xcc = (int)(__builtin_amdgcn_s_getreg((3 << 11) | 20) & 0xF);
         const int hw_id = (int)__builtin_amdgcn_s_getreg((15 << 11) | 4);
-        __hip_atomic_store(a.xcc_ids + (int64_t)rep * G + slice, my_xcc | (hw_id << 8), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(a.xcc_ids + (int64_t)crew * G + slice, my_xcc | (hw_id << 8), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if constexpr (TEAM) {
+            // The team meets once: with every cluster on one XCD it goes on as a team; else its first member goes on alone and
+            // the others leave.
+            const int all = a.team * G;
+            unsigned int* met = a.arrive + kArriveStride * rep + kArriveTeam;
+            __hip_atomic_fetch_add(met, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            uint32_t spins = 0;
+            while (L.ctl[0] == 0 && __hip_atomic_load(met, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)all) {
+                __builtin_amdgcn_s_sleep(8);
+                ++spins;
+                if (spins > a.spin_limit || ((spins & 63u) == 0 && __hip_atomic_load(a.abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
+                    __hip_atomic_store(a.abort_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    L.ctl[0] = 1;
+                }
+            }
+            int same = a.allow_fast, first = 0;
+            for (int q = 0; q < all; ++q) {
+                const int id = __hip_atomic_load(a.xcc_ids + (int64_t)rep * all + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xFF;
+                if (q % G == 0) first = id;
+                if (id != first) same = 0;
+            }
+            if ((a.debug_flags & 1) != 0 && (rep & 1) != 0) same = 0;
+            L.ctl[1] = same;
+            L.ctl[2] = same ? a.team : 1;
+            if (!same && member > 0) L.ctl[0] = 1;
+        }
     }
     __syncthreads();
     if (L.ctl[0] != 0) return;
 
     const __amdgpu_buffer_rsrc_t zrsrc = make_rsrc(zpart, (uint32_t)(2u * G * a.maxrows * 16u * sizeof(float)));
     // shared-L2 exchange: three buffers of G x 64 x 16 words used in turn; a word is the sentinel until written
-    const __amdgpu_buffer_rsrc_t ersrc = make_rsrc(a.zx + (int64_t)rep * 3 * G * 1024, (uint32_t)(3u * G * 4096u));
+    const __amdgpu_buffer_rsrc_t ersrc = make_rsrc(a.zx + (int64_t)crew * 3 * G * 1024, (uint32_t)(3u * G * 4096u));
     constexpr uint32_t kSentinel = 0xFFFFFFFFu;
     // parked gradients of this workgroup: class own_cls + vv of slot s, 4 columns: 16 bytes at ((s*4 + vv)*nt + tid)*16
+    // TEAM: slots of this member.  K-batch-async, where a worker's gradient can be added by one member in the update in which
+    // another parks the worker's next one, and teams on several XCDs, whose L2s must not hold the same slot, park here and put
+    // what is in flight at the end of a launch where everyone finds it.  Behind them one slot in which a record of several
+    // tiles is summed, since several records of a worker may be under way.
+    const int64_t own_base = (((int64_t)rep * G + slice) * a.team + member) * (a.own_slots + 1);
+    float* park2 = TEAM && BATCH ? a.park2 + own_base * 16 * nt : nullptr;
+    float* small2 = TEAM && BATCH ? a.park2_small + own_base * 17 : nullptr;
+    auto small_of = [&](int word) {      // bias gradients and losses
+        const bool own = (word & kOwnSlot) != 0;
+        return make_rsrc(own ? small2 : small_g, (uint32_t)(own ? a.own_slots + 1 : S) * 68u);
+    };
+    auto park_of = [&](int word) {
+        const bool own = (word & kOwnSlot) != 0;
+        return make_rsrc(own ? park2 : park, (uint32_t)(own ? a.own_slots + 1 : S) * 16u * nt * 4u);
+    };
+    const int scratch = a.own_slots | kOwnSlot;
     const __amdgpu_buffer_rsrc_t prsrc = make_rsrc(park, (uint32_t)S * 16u * nt * 4u);
     int pk_off[4];
 #pragma unroll
@@ -605,7 +731,114 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         }
     };
 
+    // TEAM: exchange of the members' gradient sums, three buffers used in turn: member q's word of thread tid and class
+    // own_cls + vv at (buffer * team + q) * kTeamWords + (vv * 256 + tid) * 4, its bias gradient and loss behind them
+    const int team = TEAM ? __builtin_amdgcn_readfirstlane(L.ctl[2]) : 1;
+    const __amdgpu_buffer_rsrc_t trsrc = make_rsrc(TEAM ? a.tx + ((int64_t)rep * G + slice) * 3 * a.team * kTeamWords : nullptr,
+                                                   TEAM ? (uint32_t)(3 * a.team * kTeamWords * 4) : 0u);
+    int tx_off[4];
+#pragma unroll
+    for (int vv = 0; vv < 4; ++vv) tx_off[vv] = own_cls + vv < C ? (vv * NTC + tid) * 16 : kOutOfRange;
+    const int tx_bias = tid < 16 ? (4 * NTC * 4 + tid) * 4 : kOutOfRange;
+    const int small_word = (lane & 15) == 15 ? 16 : (lane & 15);       // the slot record keeps the loss in word 16
+    uint32_t n_team = 0;
+    float gbias = 0.0f;      // TEAM: sum of the bias gradients (class 15: loss), class lane % 16
+
     float gsum[16];          // this thread's part of sum_l g_l of the update in progress: gsum[4 vv + c]
+    // TEAM: gsum and gbias become the sums over the members, added in their order by everyone.  A word is a sentinel until its
+    // member has written it, as in the exchange of the partial logits; a thread talks to the threads of its own number only.
+    // (through to memory if the members sit on several XCDs; 0.45 to 0.57 us from store to sight between two XCDs, 0.39 through
+    // the L2 of one)
+    auto put = [&](u32x4 v, int off) {
+        if (a.spread) __builtin_amdgcn_raw_buffer_store_b128(v, trsrc, off, 0, kAgentLoad);
+        else __builtin_amdgcn_raw_buffer_store_b128(v, trsrc, off, 0, 0);
+    };
+    auto put1 = [&](uint32_t v, int off) {
+        if (a.spread) __builtin_amdgcn_raw_buffer_store_b32((int)v, trsrc, off, 0, kAgentLoad);
+        else __builtin_amdgcn_raw_buffer_store_b32((int)v, trsrc, off, 0, 0);
+    };
+    auto team_sum = [&]() {
+        constexpr int NV = KIND == kLsq ? 1 : 4;      // class rows of a thread that can exist
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the re-arming stores of the last exchange have arrived
+        const int base = (int)(n_team % 3u) * team;
+        const int mine = (base + member) * (kTeamWords * 4);
+#pragma unroll
+        for (int vv = 0; vv < NV; ++vv) {
+            u32x4 ob;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const uint32_t bits = __float_as_uint(gsum[4 * vv + c]);
+                ob[c] = bits == kSentinel ? 0x7FC00000u : bits;
+            }
+            put(ob, tx_off[vv] + mine);
+        }
+        const uint32_t bias_bits = __float_as_uint(gbias);
+        put1(bias_bits == kSentinel ? 0x7FC00000u : bias_bits, tx_bias + mine);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) gsum[e] = 0.0f;
+        gbias = 0.0f;
+        uint32_t spins = 0;
+        // the parts of members q0 .. q0 + N - 1
+        auto take = [&](auto n, int q0) {
+            constexpr int N = decltype(n)::value;
+            u32x4 part[N][NV];
+            uint32_t pb[N];
+            for (;;) {
+#pragma unroll
+                for (int i = 0; i < N; ++i) {
+                    const int soff = (base + q0 + i) * (kTeamWords * 4);
+#pragma unroll
+                    for (int vv = 0; vv < NV; ++vv) part[i][vv] = __builtin_amdgcn_raw_buffer_load_b128(trsrc, tx_off[vv], soff, kAgentLoad);
+                    pb[i] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(trsrc, tx_bias, soff, kAgentLoad);
+                }
+                asm volatile("" ::: "memory");
+                uint32_t top = 0u;
+#pragma unroll
+                for (int i = 0; i < N; ++i) {
+                    top = max(top, pb[i]);
+#pragma unroll
+                    for (int vv = 0; vv < NV; ++vv) top = max(max(top, max(part[i][vv].x, part[i][vv].y)), max(part[i][vv].z, part[i][vv].w));
+                }
+                if (__ballot(top == kSentinel) == 0ull) break;
+                __builtin_amdgcn_s_sleep(2);
+                ++spins;
+                if (spins > a.spin_limit ||
+                    ((spins & 63u) == 0 && __hip_atomic_load(a.abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
+                    if (lane == 0) {
+                        __hip_atomic_store(a.abort_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        L.ctl[0] = 1;
+                    }
+                    break;         // give up: the launch is aborted at the next barrier D
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+#pragma unroll
+                for (int vv = 0; vv < NV; ++vv)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) gsum[4 * vv + c] += __uint_as_float(part[i][vv][c]);
+                gbias += __uint_as_float(pb[i]);
+            }
+        };
+        constexpr int NB = KIND == kLsq ? 8 : (ROOMY ? 4 : 2);     // at most so many at a time
+        for (int q0 = 0; q0 < team;) {
+            const int left = team - q0;
+            if (left >= NB) { take(std::integral_constant<int, NB>{}, q0); q0 += NB; }
+            else if (NB > 4 && left >= 4) { take(std::integral_constant<int, 4>{}, q0); q0 += 4; }
+            else if (NB > 3 && left == 3) { take(std::integral_constant<int, 3>{}, q0); q0 += 3; }
+            else if (NB > 2 && left == 2) { take(std::integral_constant<int, 2>{}, q0); q0 += 2; }
+            else { take(std::integral_constant<int, 1>{}, q0); q0 += 1; }
+        }
+        // everyone has read the exchange before this one: its words of this thread are armed again
+        uint32_t sv = kSentinel;
+        asm volatile("" : "+v"(sv));
+        const u32x4 arm = {sv, sv, sv, sv};
+        const int prev = ((int)((n_team + 2u) % 3u) * team + member) * (kTeamWords * 4);
+#pragma unroll
+        for (int vv = 0; vv < NV; ++vv) put(arm, tx_off[vv] + prev);
+        put1(sv, tx_bias + prev);
+        ++n_team;
+    };
     for (int64_t step = 0; step < a.nsteps; ++step) {
       for (bool last_tile = false; !last_tile;) {           // the tiles of update a.v0 + step
         mark(14);
@@ -622,6 +855,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         const int rows = tile_flags >> 8;                   // per record
         last_tile = (tile_flags & 1) != 0;
         const int par = (int)(n_fenced & 1u);               // buffer of a fenced exchange: a step may have several of them
+        const bool work = !TEAM || n_rec > 0;               // an empty tile goes through the barriers alone
         // An opaque zero: addresses built from it are recomputed every step instead of being kept in
         // registers across the whole loop (they would be spilled to scratch memory).
         int opq = 0;
@@ -630,7 +864,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         f32x4 own_z = {0.f, 0.f, 0.f, 0.f};       // ONE: logits of row z_row
         // ---- partial logits of rows 16 wave ..: D[class][row] += W[class][k] X[row][k] over this slice;
         //      the operands of the next k-block are read from LDS before the MFMAs of this one are issued
-        {
+        if (work) {
             f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
             f32x4 wv = *reinterpret_cast<const f32x4*>(f_wa[0]);
             f32x4 xv = *reinterpret_cast<const f32x4*>(f_xa[0]);
@@ -676,21 +910,32 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         //      while the exchange stores are on their way
         auto park_load = [&](int slot, f32x4 (&pv)[4]) {
             // classes that do not exist are out of range and read as zero
-            const int soff = __builtin_amdgcn_readfirstlane(slot) * 16 * nt * 4;
+            const int word = __builtin_amdgcn_readfirstlane(slot);
+            const int soff = (word & 0xFFFF) * 16 * nt * 4;
+            const __amdgpu_buffer_rsrc_t rs = TEAM && BATCH ? park_of(word) : prsrc;
 #pragma unroll
             for (int vv = 0; vv < 4; ++vv)
-                pv[vv] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(prsrc, pk_off[vv], soff, 0));
+                pv[vv] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, pk_off[vv], soff, 0));
+        };
+        // (TEAM: bias gradient and loss of a parked mini-batch, class lane % 16)
+        auto park_bias = [&](int slot) {
+            const int word = __builtin_amdgcn_readfirstlane(slot);
+            return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(small_of(word), small_word * 4, (word & 0xFFFF) * 68, 0));
         };
         f32x4 pva[4], pvb[4];
+        float ba = 0.0f, bb = 0.0f;
 #pragma unroll
         for (int vv = 0; vv < 4; ++vv) { pva[vv] = f32x4{0.f, 0.f, 0.f, 0.f}; pvb[vv] = f32x4{0.f, 0.f, 0.f, 0.f}; }
         if (!chunked && n_stale > 0) park_load(st01.x, pva);
         if (!chunked && n_stale > 1) park_load(st01.y, pvb);
+        if constexpr (TEAM && !chunked) {
+            if (n_stale > 0) ba = park_bias(st01.x);
+            if (n_stale > 1) bb = park_bias(st01.y);
+        }
         mark(9);
-        // ---- arrival: this wave's stores are in the L2 (shared-L2 mode) or released to the device
         // ---- arrival.  Shared-L2 mode needs none: the readers poll the data words themselves.  Otherwise the
         //      wave's stores are released to the device and counted.
-        if (!ONE && !fast && lane == 0) __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        if (!ONE && !fast && work && lane == 0) __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         mark(1);
 
         // (waited for whether this is the update's first tile or not: where the compiler takes them to be in flight still, it
@@ -703,17 +948,19 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         if ((tile_flags & 2) != 0) {
 #pragma unroll
             for (int e = 0; e < 16; ++e) gsum[e] = pva[e >> 2][e & 3] + pvb[e >> 2][e & 3];
+            if constexpr (TEAM) gbias = ba + bb;
         }
         for (int i = 2; !chunked && i < n_stale; ++i) {     // further parked gradients (K > 2)
             park_load(L.s_stale[i], pva);
 #pragma unroll
             for (int e = 0; e < 16; ++e) gsum[e] += pva[e >> 2][e & 3];
+            if constexpr (TEAM) gbias += park_bias(L.s_stale[i]);
         }
         mark(2);
 
         // ---- wave 0 polls the counter in the L2 (all 4 G compute waves of the cluster have arrived) and
         //      relays the result through an LDS word, which the other waves poll
-        if (!ONE && !fast) {
+        if (!ONE && !fast && work) {
             const uint32_t target = (n_fenced + 1u) * (uint32_t)(4 * G);
             const int want = (int)(n_fenced + 1u);
             if (wave == 0) {
@@ -740,7 +987,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                     __builtin_amdgcn_s_sleep(1);
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
             }
-            if (a.allow_fast && tid == 0) {
+            if (!TEAM && a.allow_fast && tid == 0) {
                 // first exchange of the launch: do all slices of this cluster share an XCD (one L2)?
                 const int32_t* ids = a.xcc_ids + (int64_t)rep * G;
                 int same = 1;
@@ -754,7 +1001,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         mark(3);
 
         // ---- full logits of row z_row (sum of the G partials in slice order), then residual / softmax
-        {
+        if (work) {
             f32x4 zz = {0.f, 0.f, 0.f, 0.f};
             if constexpr (ONE) {
                 zz = own_z;
@@ -878,6 +1125,12 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
 #pragma unroll
             for (int c = 0; c < 4; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
             // record r is complete: add it to the aggregate of update v, or park it in its slot
+            float bsum = 0.0f;      // TEAM: column sums of delta, class lane % 16, rows lane / 16 modulo 4
+            auto whole_bias = [&]() {
+                bsum += across<16>(bsum, lane);
+                bsum += across<32>(bsum, lane);
+                return bsum;
+            };
             auto finish = [&](int r) {
                 if constexpr (PROF) { asm volatile("" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])); mark(11); }
                 const int word = __builtin_amdgcn_readfirstlane(r == 0 ? rec01.x : (r == 1 ? rec01.y : L.s_rec[r]));
@@ -887,15 +1140,27 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                     // by an earlier update or with the first tile of this one): later blocks add what is there, and
                     // only the last one goes to the aggregate if the update consumes the record itself.
                     if (((word >> 18) & 1) != 0) {
-                        const int soff = (word & 0xFFFF) * 16 * nt * 4;
+                        const int from = TEAM ? scratch : word;
+                        const int soff = (from & 0xFFFF) * 16 * nt * 4;
+                        const __amdgpu_buffer_rsrc_t rs = TEAM ? park_of(from) : prsrc;
 #pragma unroll
                         for (int vv = 0; vv < 4; ++vv) {
-                            const f32x4 pv = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(prsrc, pk_off[vv], soff, 0));
+                            const f32x4 pv = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, pk_off[vv], soff, 0));
 #pragma unroll
                             for (int c = 0; c < 4; ++c) acc[c][vv] += pv[c];
                         }
                     }
                     if (((word >> 17) & 1) != 0) to_sum = false;
+                }
+                const int dest = TEAM && ((word >> 17) & 1) != 0 ? scratch : word;
+                if constexpr (TEAM) {
+                    float b = whole_bias();
+                    const int off = tid < 16 ? small_word * 4 : kOutOfRange;
+                    if (((word >> 18) & 1) != 0)
+                        b += __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(small_of(scratch), off, (scratch & 0xFFFF) * 68, 0));
+                    if (to_sum) gbias += b;
+                    else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, b), small_of(dest), off + (dest & 0xFFFF) * 68, 0, 0);
+                    bsum = 0.0f;
                 }
                 if (to_sum) {
 #pragma unroll
@@ -903,11 +1168,12 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
 #pragma unroll
                         for (int c = 0; c < 4; ++c) gsum[vv * 4 + c] += acc[c][vv];
                 } else {
-                    const int soff = (word & 0xFFFF) * 16 * nt * 4;
+                    const int soff = (dest & 0xFFFF) * 16 * nt * 4;
+                    const __amdgpu_buffer_rsrc_t rs = TEAM && BATCH ? park_of(dest) : prsrc;
 #pragma unroll
                     for (int vv = 0; vv < 4; ++vv) {
                         const f32x4 gv = {acc[0][vv], acc[1][vv], acc[2][vv], acc[3][vv]};
-                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, gv), prsrc, pk_off[vv] + soff, 0, 0);
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, gv), rs, pk_off[vv] + soff, 0, 0);
                     }
                 }
 #pragma unroll
@@ -933,6 +1199,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                     }
                 };
                 auto mac = [&](bool first, const float (&dv)[2], const f32x4 (&xv)[2]) {
+                    if constexpr (TEAM) bsum = (first ? 0.0f : bsum) + (dv[0] + dv[1]);
 #pragma unroll
                     for (int u = 0; u < 2; ++u) {
 #pragma unroll
@@ -945,6 +1212,12 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                 auto done = [&](int r) {
                     if constexpr (PROF) { asm volatile("" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])); mark(11); }
                     const int word = __builtin_amdgcn_readfirstlane(r == 0 ? rec01.x : rec01.y);
+                    if constexpr (TEAM) {
+                        const float b = whole_bias();
+                        const int off = tid < 16 ? small_word * 4 : kOutOfRange;
+                        if (((word >> 16) & 1) != 0) gbias += b;
+                        else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, b), small_of(word), off + (word & 0xFFFF) * 68, 0, 0);
+                    }
                     if (((word >> 16) & 1) != 0) {
 #pragma unroll
                         for (int vv = 0; vv < 4; ++vv)
@@ -952,10 +1225,11 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                             for (int c = 0; c < 4; ++c) gsum[vv * 4 + c] += acc[c][vv];
                     } else {
                         const int soff = (word & 0xFFFF) * 16 * nt * 4;
+                        const __amdgpu_buffer_rsrc_t rs = TEAM && BATCH ? park_of(word) : prsrc;
 #pragma unroll
                         for (int vv = 0; vv < 4; ++vv) {
                             const f32x4 gv = {acc[0][vv], acc[1][vv], acc[2][vv], acc[3][vv]};
-                            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, gv), prsrc, pk_off[vv] + soff, 0, 0);
+                            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, gv), rs, pk_off[vv] + soff, 0, 0);
                         }
                     }
                     mark(12);
@@ -1010,6 +1284,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
                         if (g0 + u < steps) {
+                            if constexpr (TEAM) bsum += dv[u];
 #pragma unroll
                             for (int c = 0; c < 4; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(dv[u], xv[u][c], acc[c], 0, 0, 0);
                             if (g0 + u + 1 == end) { finish(r); ++r; end += kpr; }
@@ -1023,6 +1298,9 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         mark(6);
         lds_barrier();                                      // B: the loader waves may rewrite the tile and the lists
         // ---- update v: each compute thread owns its weights; nobody reads them before TU
+        if constexpr (TEAM) {
+            if (last_tile && team > 1) team_sum();
+        }
         if (last_tile) {
             const float scale = a.lr / (float)Kv;
             int och = own_ch, ocl = own_cls;
@@ -1038,7 +1316,15 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                     *wp = w;
                 }
             }
-            if (a.agg_out != nullptr && rep == 0) {
+            if constexpr (TEAM) {
+                if (tid < 16) {
+                    if (KIND == kSoftmax && tid < C) L.bias[tid] -= scale * gbias;
+                    if (tid == 15 && slice == 0 && member == 0) a.tr.loss[(int64_t)rep * cap + a.v0 + step] = gbias * (1.0f / (float)Kv);
+                    if (KIND == kSoftmax && a.agg_out != nullptr && rep == 0 && slice == 0 && member == 0 && tid < C)
+                        a.agg_out[(int64_t)C * d + tid] = gbias * (1.0f / (float)Kv);
+                }
+            }
+            if (a.agg_out != nullptr && rep == 0 && member == 0) {
                 // the averaged gradient of replica 0, when the caller asked for it
                 const float invK = 1.0f / (float)Kv;
 #pragma unroll
@@ -1051,16 +1337,29 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                 }
             }
         }
-        if (tid == 0 && L.ctl[2] != 0) L.ctl[1] = 1;   // later exchanges of this launch use the shared L2
+        if (!TEAM && tid == 0 && L.ctl[2] != 0) L.ctl[1] = 1;   // later exchanges of this launch use the shared L2
         mark(7);
       }
     }
     if constexpr (PROF) {
-        if (profiling && lane == 0) a.prof[(int64_t)a.prof_base + ((int64_t)rep * G + slice) * 2] += p_acc;
+        if (profiling && lane == 0 && member == 0) a.prof[(int64_t)a.prof_base + ((int64_t)rep * G + slice) * 2] += p_acc;
     }
     lds_barrier();
 
     // ---- leave the state in HBM for the next launch
+    if constexpr (TEAM && BATCH) {
+        // (written through: a line may hold bias gradients of several members)
+        for (int q = 0; a.own_slots > 0 && q < S; ++q) {
+            if (__builtin_amdgcn_readfirstlane(L.own[q]) == 0) continue;
+            const int soff = q * 16 * nt * 4, off = tid < 16 ? small_word * 4 : kOutOfRange;
+#pragma unroll
+            for (int vv = 0; vv < 4; ++vv)
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_amdgcn_raw_buffer_load_b128(park_of(kOwnSlot), pk_off[vv], soff, 0), prsrc,
+                                                       pk_off[vv] + soff, 0, kAgentLoad);
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_amdgcn_raw_buffer_load_b32(small_of(kOwnSlot), off, q * 68, 0), small_of(0), off + q * 68, 0, kAgentLoad);
+        }
+    }
+    if (TEAM && member > 0) return;
 #pragma unroll
     for (int vv = 0; vv < 4; ++vv) {
         const int cls = own_cls + vv;
@@ -1072,22 +1371,30 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         }
     }
     if (KIND == kSoftmax && slice == 0 && tid < C) params[(int64_t)C * d + tid] = L.bias[tid];
-    for (int q = tid; q < S * 17; q += NTC) small_g[q] = L.small[q];
+    if constexpr (!TEAM)
+        for (int q = tid; q < S * 17; q += NTC) small_g[q] = L.small[q];
 }
 
-template <int KIND, bool PROF, bool WHOLE, bool CHUNKED, bool BATCH, bool ONE, bool ROOMY, bool LATE>
+template <int KIND, bool PROF, bool WHOLE, bool CHUNKED, bool BATCH, bool ONE, bool ROOMY, bool LATE, bool TEAM = false>
 hipError_t launch_r(const LinArgs& a, size_t lds, hipStream_t s) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(linear_tile_kernel<KIND, PROF, WHOLE, CHUNKED, BATCH, ONE, ROOMY, LATE>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    constexpr auto kernel = linear_tile_kernel<KIND, PROF, WHOLE, CHUNKED, BATCH, ONE, ROOMY, LATE, TEAM>;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     const int groups = (a.replicas + 7) / 8;
-    const int blocks = a.pair_cus > 0 ? 8 * a.pair_cus * a.pair_layers : groups * 8 * a.G;
-    hipLaunchKernelGGL((linear_tile_kernel<KIND, PROF, WHOLE, CHUNKED, BATCH, ONE, ROOMY, LATE>), dim3(blocks), dim3(512), lds, s, a);
+    const int blocks = TEAM ? (a.spread ? (a.replicas * a.team + 7) / 8 : groups * a.team) * 8 * a.G : (a.pair_cus > 0 ? 8 * a.pair_cus * a.pair_layers : groups * 8 * a.G);
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(512), lds, s, a);
     return hipGetLastError();
 }
 
 template <int KIND, bool PROF, bool WHOLE, bool CHUNKED, bool BATCH>
 hipError_t launch_w(const LinArgs& a, size_t lds, hipStream_t s) {
+    if constexpr (CHUNKED || BATCH)
+        if (a.team > 1) {
+            if (a.G == 1) return a.whole_cus ? launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, true, true, true, true>(a, lds, s)
+                                             : launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, true, false, true, true>(a, lds, s);
+            return a.whole_cus ? launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, false, true, true, true>(a, lds, s)
+                               : launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, false, false, true, true>(a, lds, s);
+        }
     if (a.G == 1) return a.shared_cus ? launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, true, false, false>(a, lds, s)
                                       : launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, true, true, false>(a, lds, s);
     if (a.whole_cus) return launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, false, true, true>(a, lds, s);
@@ -1111,8 +1418,14 @@ hipError_t launch_k(const LinArgs& a, size_t lds, hipStream_t s) {
 
 }  // namespace
 
-size_t linear_tile_lds_bytes(int C, int S, int Kcap) {
-    const size_t words = (size_t)ROWS * SL + (size_t)C * SL + ROWS * 16 + 2 * ROWS + 16 + 8 + 2 * (Kcap > 32 ? 64 : 32) + (size_t)S * 17;
+#ifdef SSGD_TILE_LSQ
+hipError_t launch_linear_tile_lsq(const LinArgs& a, hipStream_t s) {
+    const size_t lds = linear_tile_lds_bytes(a.C, a.S, a.tr.Kcap, a.team > 1);
+    return a.prof != nullptr ? launch_k<kLsq, true>(a, lds, s) : launch_k<kLsq, false>(a, lds, s);
+}
+#else
+size_t linear_tile_lds_bytes(int C, int S, int Kcap, bool team) {
+    const size_t words = (size_t)ROWS * SL + (size_t)C * SL + ROWS * 16 + 2 * ROWS + 16 + 8 + 2 * (Kcap > 32 ? 64 : 32) + (team ? ((size_t)S + 3) / 4 : (size_t)S * 17);
     return sizeof(float) * words;
 }
 
@@ -1122,24 +1435,24 @@ bool linear_tile_supports(const LinArgs& a, int max_records) {
     const bool synchronous = a.variant == kSync || a.variant == kBatchSync;
     if (synchronous != (a.chunked != 0)) return false;
     if (!one_descriptor_spans(a.N, (uint64_t)a.d)) return false;
-    return linear_tile_lds_bytes(a.C, a.S, a.tr.Kcap) <= 160 * 1024;
+    return linear_tile_lds_bytes(a.C, a.S, a.tr.Kcap, false) <= 160 * 1024;
 }
 
 int linear_tile_resident_groups(size_t lds_bytes) {
     int dev = 0, per_cu = 0;
     hipDeviceProp_t prop;
     if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(linear_tile_kernel<kSoftmax, false, false, false, false, false, false, true>),
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(linear_tile_kernel<kSoftmax, false, false, false, false, false, false, true, false>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, linear_tile_kernel<kSoftmax, false, false, false, false, false, false, true>, 512, lds_bytes) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, linear_tile_kernel<kSoftmax, false, false, false, false, false, false, true, false>, 512, lds_bytes) != hipSuccess) return 0;
     return per_cu * prop.multiProcessorCount;
 }
 
 hipError_t launch_linear_tile(const LinArgs& a, hipStream_t s) {
-    const size_t lds = linear_tile_lds_bytes(a.C, a.S, a.tr.Kcap);
-    const bool prof = a.prof != nullptr;
-    if (a.kind == kLsq) return prof ? launch_k<kLsq, true>(a, lds, s) : launch_k<kLsq, false>(a, lds, s);
-    return prof ? launch_k<kSoftmax, true>(a, lds, s) : launch_k<kSoftmax, false>(a, lds, s);
+    const size_t lds = linear_tile_lds_bytes(a.C, a.S, a.tr.Kcap, a.team > 1);
+    if (a.kind == kLsq) return launch_linear_tile_lsq(a, s);
+    return a.prof != nullptr ? launch_k<kSoftmax, true>(a, lds, s) : launch_k<kSoftmax, false>(a, lds, s);
 }
+#endif
 
 }  // namespace ssgd

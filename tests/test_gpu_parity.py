@@ -905,6 +905,52 @@ def test_several_tiles_and_odd_row_lengths(ssgd, oracle, torch_cuda, monkeypatch
               classes=classes, check_steps=30)
 
 
+@pytest.mark.parametrize("kind,variant,P,K,m,d,classes,R", [
+    ("softmax", "k_async", 20, 5, 25, 785, 10, 8),     # three members of four slices; two records each, the last has one
+    ("softmax", "k_async", 9, 6, 32, 300, 15, 3),      # whole records, two slices
+    ("lsq", "k_async", 9, 3, 72, 515, 1, 2),           # records of two tiles, a member each
+    ("softmax", "k_async", 7, 7, 64, 130, 4, 1),       # nothing is ever parked; one slice
+    ("lsq", "k_async", 70, 64, 5, 60, 1, 2),           # 70 records at version 0, eight rows of a tile each
+    ("lsq", "k_sync", 6, 5, 30, 64, 1, 9),             # 160 rows: two tiles and a half; two replicas on one XCD
+    ("softmax", "k_batch_sync", 5, 12, 64, 260, 3, 1), # twelve tiles for eight workgroups: four members of two slices
+    ("softmax", "k_batch_sync", 5, 9, 64, 100, 3, 1),  # nine tiles for eight members: five members, the last with one tile less
+    ("softmax", "k_sync", 4, 2, 33, 1030, 10, 17),     # one row more than a tile after padding; three replicas on one XCD: no team
+    ("softmax", "k_batch_async", 9, 6, 32, 300, 15, 3),   # two copies of every slot
+    ("lsq", "k_batch_async", 2, 9, 20, 64, 1, 5),      # workers that push several times in an update
+    ("lsq", "k_batch_async", 6, 4, 100, 516, 1, 1),    # records of two tiles, summed by their member
+    ("softmax", "k_batch_async", 20, 5, 24, 2052, 4, 2),  # clusters of nine, spread over XCDs
+    ("softmax", "k_sync", 5, 5, 64, 3000, 3, 1),       # clusters of twelve, a member per XCD
+    ("lsq", "k_async", 90, 60, 70, 1200, 1, 1),        # 60 records of two tiles for 24 members, 90 at version 0
+])
+def test_updates_shared_by_a_team(ssgd, oracle, torch_cuda, monkeypatch, kind, variant, P, K, m, d, classes, R):
+    """Tiles of an update dealt to several clusters of a replica: parity, and the same bits whatever the calls are cut into
+    (who adds which gradient in flight does not depend on where a launch ends); without a shared L2 the first cluster goes on
+    alone."""
+    torch = torch_cuda
+    X, y = synth.lsq_data(700, d, 8)[:2] if kind == "lsq" else synth.mixture_data(700, d, classes, seed=8)
+    Xd, yd = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
+    gd, od = dist_pair(ssgd, oracle, ("shifted_exp", 0.5, 1.0))
+    mk = lambda: ssgd.Context(kind, Xd, yd, P, K, m, variant, gd, 0.01, seed=9, classes=classes, replicas=R)
+    a, b = mk(), mk()
+    a.run(90)
+    for J in (1, 3, 40, 46):
+        b.run(J)
+    monkeypatch.setenv("SSGD_EXCHANGE", "fenced")
+    c = mk()
+    c.run(90)
+    for r in sorted({0, R // 2, R - 1}):
+        tr = oracle.Trainer(oracle.Model(kind, X, y, classes=classes), P, K, m, variant, od, 0.01, seed=9, replica=r)
+        tr.run(90)
+        assert np.array_equal(a.params(r), b.params(r)), r
+        for ctx in (a, c):
+            g, o = ctx.trace(r), tr.trace()
+            assert_trace_equal(g, o)
+            assert np.allclose(g["loss"], o["loss"], rtol=FP32_LOSS_RTOL, atol=1e-6)
+            assert rel(ctx.params(r), tr.params()) <= FP32_PARAM_TOL, r
+    for ctx in (a, b, c):
+        ctx.close()
+
+
 @pytest.mark.parametrize("kind,variant,P,K,m,d,classes", [
     ("lsq", "k_async", 8, 2, 32, 256, 1),            # the widest single slice, whole records
     ("softmax", "k_async", 8, 3, 16, 132, 10),       # the most contributors of eight workers with gradients in flight in LDS
@@ -1107,6 +1153,42 @@ def test_clusters_of_four_contexts_at_once(ssgd, torch_cuda, d, variant):
         assert np.array_equal(c.params(11), alone.params(11))
         c.close()
     alone.close()
+
+
+def test_teams_of_four_contexts_at_once(ssgd, torch_cuda):
+    """Four contexts from four threads, two with teams on one XCD and two with teams spread over all: none is kept waiting for
+    CUs until it gives up, and what one computes does not depend on the others."""
+    import threading
+    torch = torch_cuda
+    X, y = synth.mixture_data(600, 3000, 3, seed=3)
+    wide, narrow = torch.from_numpy(X).cuda(), torch.from_numpy(np.ascontiguousarray(X[:, :600])).cuda()
+    yd = torch.from_numpy(y).cuda()
+    shapes = [(wide, "k_sync", 1), (narrow, "k_batch_async", 8), (wide, "k_async", 1), (narrow, "k_batch_sync", 8)]
+    mk = lambda s, **kw: ssgd.Context("softmax", s[0], yd, 6, 5, 50, s[1], ssgd.delay_dist("exp", 1.0), 0.01, seed=5, classes=3, replicas=s[2], **kw)
+    streams = [torch.cuda.Stream() for _ in shapes]
+    torch.cuda.synchronize()
+    ctxs = [mk(s, stream=q.cuda_stream) for s, q in zip(shapes, streams)]
+    errors = []
+
+    def work(c):
+        try:
+            for _ in range(3):
+                c.run(50)
+        except ssgd.SsgdError as e:
+            errors.append(str(e))
+
+    threads = [threading.Thread(target=work, args=(c,)) for c in ctxs]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    for s, c in zip(shapes, ctxs):
+        alone = mk(s)
+        alone.run(150)
+        assert np.array_equal(c.params(s[2] - 1), alone.params(s[2] - 1)), s[1:]
+        alone.close()
+        c.close()
 
 
 def test_adasync_ksync_rule_with_growing_tile_count(ssgd, oracle, torch_cuda):

@@ -45,3 +45,25 @@ def test_clusters_of_four_launches_cannot_keep_each_other_incomplete(tmp_path):
     """Widths up to a whole XCD of 32 CUs: four launches that each hold all but one of the CUs of a cluster leave one free."""
     ok = _evaluate(tmp_path, "".join(f'printf("%d\\n", (int)whole_cus({G}, 256));\n' for G in range(1, 33)))
     assert ok == [1 if G == 1 or 4 * (G - 1) < 32 else 0 for G in range(1, 33)] and ok[:8] == [1] * 8 and not any(ok[8:])
+
+
+def test_teams_leave_room_for_the_schedule_and_for_other_launches(tmp_path):
+    """Every team over a range of shapes: a CU per workgroup and one per XCD free; on one XCD a team as a whole, spread over
+    XCDs a whole launch takes no more than a quarter of the places (so four launches cannot keep each other incomplete); a
+    member has a tile; alone where there is one tile or no room."""
+    cases = [(t, G, C, R, per_cu) for t in (1, 2, 3, 7, 32, 64, 256) for G in (1, 2, 3, 4, 7, 12, 16, 40) for C in (1, 10, 15)
+             for R in (1, 2, 7, 8, 9, 40, 300) for per_cu in (1, 2)]
+    body = "TeamShape t;\n" + "".join(f't = team_shape({t}, {G}, {C}, {R}, 256, {p}); printf("%d %d\\n", t.members, t.spread);\n' for t, G, C, R, p in cases)
+    got = _evaluate(tmp_path, body)
+    teams = 0
+    for (t, G, C, R, per_cu), members, spread in zip(cases, got[::2], got[1::2]):
+        assert 1 <= members <= max(1, t)
+        if members == 1:
+            assert not spread
+            continue
+        teams += 1
+        on_xcd = -(-R * members // 8) * G if spread else -(-R // 8) * G * members
+        waiting = on_xcd if spread else G * members
+        assert on_xcd <= 31 and 4 * (waiting - 1) < 32 * per_cu
+    assert teams > 100
+    assert got[:2] == [1, 0]
