@@ -6,15 +6,14 @@
 // takes 16 of them at a time, wave w the columns of its share (up to 384: 24 blocks of 16, held in 96 registers in the
 // layout of the MFMA operand).  Logits: fp32 MFMA 16x16x4 with the weights from LDS, the waves' partial sums meet in LDS
 // (one barrier per 16 rows), every wave takes softmax or residual itself.  Gradient: delta^T X needs the rows with the
-// lane on the column where the forward pass had it on the row; four MFMA steps with a selector of ones turn a 16 x 16
-// block over exactly (every sum has one term that is not zero), and its result registers are the operand of the four
-// steps that follow.  The registers of a block are refilled with the next 16 rows as soon as it has been turned over, so
-// the loads travel behind the rest of the gradient pass and the next forward pass.  The gradient stays in registers (96
-// more) until the run of rows ends.  (The widest softmax form needs six registers more than there are: 28 bytes per lane of
-// scratch memory.)  Matrix time is 12 steps per 16 x 16 block, 18 000 cycles per 16 rows of d = 3072
-// and CU, below the 23 000 cycles that the rows take to arrive.
+// lane on the column where the forward pass had it on the row; a block of 16 x 16 is turned over through a buffer of the
+// wave's own in LDS (one 16-byte store and four 4-byte loads per lane, all in different banks), one block ahead of its
+// contraction.  (By four MFMA steps with a selector of ones instead, matrix time was 18 000 cycles per 16 rows of d = 3072 and
+// CU where it is 12 000, and the pass took 197 us where it takes 165.)  The registers of a block are refilled with the next 16
+// rows as soon as it has been turned over, so the loads travel behind the rest of the gradient pass and the next forward pass.
+// The gradient stays in registers (96 more) until the run of rows ends.  The rows take 23 000 cycles to arrive.
 // full_grad_reduce_kernel adds the workgroups' partial gradients in order in fp64.
-// N = 50000, d = 3072, 10 classes: 199 us (3.1 TB/s) + 10 us for the reduction, where the two passes below took 518 +
+// N = 50000, d = 3072, 10 classes: 165 us (3.7 TB/s) + 10 us for the reduction, where the two passes below took 518 +
 // 297 + 35; N = 4096, d = 256, least squares: 5 + 3 us where they took 5 + 40 + 6 (32 workgroups in the second pass).
 //
 // Shapes whose weights do not fit the LDS beside that (more than about 11 classes at d = 3072, or d > 3072) take two
@@ -55,6 +54,13 @@ struct FullGradArgs {
 
 constexpr int FG_TSTRIDE = 20;    // words per sample in a wave's buffer for turning delta over: 16-byte rows in different banks
 
+// Orders the LDS accesses of one wavefront for the compiler.
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // BL: 16-column blocks of a wave's share (even); columns past d have zero weights in LDS and their loads are sent out
 // of range, so that no step is behind a branch (behind one the compiler waits for every load in flight).
 template <int KIND, int WAVES, int BL>
@@ -93,9 +99,6 @@ __global__ __launch_bounds__(64 * WAVES, BL <= 8 ? 4 : 2) void full_grad_fused_k
     if (KIND == kSoftmax)
         for (int v = 0; v < 4; ++v)
             if (4 * quarter + v < C) bias[v] = a.w[(int64_t)C * d + 4 * quarter + v];
-    float sel[4];                      // the selector that turns a block over: sel_c[k][col] = [col == 4 k + c]
-#pragma unroll
-    for (int v = 0; v < 4; ++v) sel[v] = (j == 4 * quarter + v) ? 1.0f : 0.0f;
     __syncthreads();
 
     f32x4 gb = {0.f, 0.f, 0.f, 0.f};   // bias gradient: classes 4 quarter .. + 3 of row j
@@ -153,34 +156,37 @@ __global__ __launch_bounds__(64 * WAVES, BL <= 8 ? 4 : 2) void full_grad_fused_k
         }
         // delta with the lane on the class (the buffer is the wave's own: no barrier)
         *reinterpret_cast<f32x4*>(turn + j * FG_TSTRIDE + 4 * quarter) = dl;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_fence();
         float dv[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) dv[v] = turn[(4 * quarter + v) * FG_TSTRIDE + j];
 
         const __amdgpu_buffer_rsrc_t rs = rows_at(r + 16);
         __builtin_amdgcn_sched_barrier(0);
+        // A block is turned over through the same buffer: a wave's LDS accesses happen in order, so nothing is waited for but
+        // the turned block, and that one is on its way while the block before it is contracted.
+        auto turn_over = [&](int u) {
+            wave_fence();
+            *reinterpret_cast<f32x4*>(turn + j * FG_TSTRIDE + 4 * quarter) = xq[u];
+            wave_fence();
+            f32x4 t;
 #pragma unroll
-        for (int u = 0; u < BL; u += 2) {
-            // two blocks at a time, their dependent steps interleaved
-            f32x4 t0 = {0.f, 0.f, 0.f, 0.f}, t1 = {0.f, 0.f, 0.f, 0.f};
+            for (int v = 0; v < 4; ++v) t[v] = turn[(4 * quarter + v) * FG_TSTRIDE + j];
+            return t;
+        };
+        f32x4 t = turn_over(0);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                t0 = __builtin_amdgcn_mfma_f32_16x16x4f32(xq[u][v], sel[v], t0, 0, 0, 0);
-                t1 = __builtin_amdgcn_mfma_f32_16x16x4f32(xq[u + 1][v], sel[v], t1, 0, 0, 0);
-            }
+        for (int u = 0; u < BL; ++u) {
+            f32x4 next = t;
+            if (u + 1 < BL) next = turn_over(u + 1);
             __builtin_amdgcn_sched_barrier(0);
             xq[u] = load(rs, u);
-            xq[u + 1] = load(rs, u + 1);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                g[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(dv[v], t0[v], g[u], 0, 0, 0);
-                g[u + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(dv[v], t1[v], g[u + 1], 0, 0, 0);
-            }
+            for (int v = 0; v < 4; ++v) g[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(dv[v], t[v], g[u], 0, 0, 0);
+            t = next;
         }
+        wave_fence();
     }
 
     float* dst = a.partial + (int64_t)blockIdx.x * C * (d + 1);
