@@ -174,6 +174,11 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
     // A tile holds whole records of mp rows; when an iteration spans several tiles, a tile is one block of 64 rows
     // of the iteration's mini-batches, all of them part of the update.
     constexpr bool chunked = CHUNKED;
+    // One slice, early gathers: the loader waves draw the ids of the tile after next while the gradient is contracted, and ask
+    // for the labels with the rows; wave 0, which takes the bias sums meanwhile, gets the ids from wave 1.  (With all of it in
+    // front of barrier D they took 2700 cycles there, the compute waves 1600: softmax, d = 60, 25 rows, 40 replicas
+    // 4.27 -> 4.07 us per update.)
+    constexpr bool SPLIT = ONE && !LATE;
     // Records described one by one (BATCH: K-batch-async, and K-async when a version may have more records than a tile
     // holds), mini-batches of more than 64 rows: a tile is one block of 64 rows of one record; the record's gradient is
     // summed over its tiles in the slot of its worker
@@ -362,7 +367,9 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
             if constexpr (BATCH) asm volatile("" : "+v"(h_rw), "+v"(h_ro), "+v"(h_rf), "+v"(h_csel), "+v"(h_ctau), "+v"(h_cord) : : "memory");
         };
         // Tile `t` of version `ver`: sample ids, lists; leaves the labels in flight.
-        auto describe_tile = [&](int64_t ver, int t_mine) {
+        // (SPLIT, in the loop: lists by wave 0, which publishes them and has the bias sums to take, ids by the others)
+        auto describe_tile = [&](int64_t ver, int t_mine, bool all) {
+            const bool lists = !SPLIT || all || lw == 0, draws = !SPLIT || all || lw != 0;
             n_ver = ver;
             n_flags = (t_mine + 1 == h_tiles ? 1 : 0) | (t_mine == 0 ? 2 : 0);      // bit 0 last tile of its update, bit 1 first
             int t = t_mine;
@@ -375,7 +382,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                 if constexpr (TEAM) n_nrec = t < h_total ? 1 : 0;
                 if (t > 0) { const int q = t * ROWS + lane; rec = q / mp; smp = q - rec * mp; }
             }
-            int worker, ordinal;
+            int worker = 0, ordinal = 0;
             if constexpr (BATCH) {
                 // records t * rpt .. of the version; the parked part of the update comes with the first tile
                 const int tr0 = spr > 1 ? t / spr : t * rpt;       // first record of the tile
@@ -394,7 +401,8 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                     else { w = q; o = 0; f = -1; }          // version 0: looked up below
                 };
                 int fr;
-                describe(rec, worker, ordinal, fr);
+                if (draws) describe(rec, worker, ordinal, fr);
+                if (lists) {
                 int qw, qo, qf;
                 describe(tr0 + lane, qw, qo, qf);
                 if (ver == 0) {
@@ -415,24 +423,29 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                         n_rec_word |= own_slots;
                     }
                 }
+                }
             } else {
                 worker = __shfl(h_worker, min(rec, 63), 64);
                 ordinal = __shfl(h_ord, min(rec, 63), 64);
             }
+            if (!draws) return;
             uint32_t seed_lo = (uint32_t)a.seed, seed_hi = (uint32_t)(a.seed >> 32);
             asm volatile("" : "+s"(seed_lo), "+s"(seed_hi));      // the round keys are rebuilt here: kept across the loop they are spilled
             const uint32_t id = batch_index(((uint64_t)seed_hi << 32) | seed_lo, (uint32_t)rep, (uint32_t)worker, (uint32_t)ordinal, (uint32_t)ver,
                                             (uint32_t)smp, a.N);
-            row_lab = reinterpret_cast<const float*>(a.y)[id];    // fp32 or int32: the word as it is
+            if constexpr (!SPLIT) row_lab = reinterpret_cast<const float*>(a.y)[id];    // fp32 or int32: the word as it is
             row_id = (smp < m && rec < h_nrec) ? id : kNoRow;
         };
         // The tile described last becomes the one whose rows are gathered.
         auto adopt = [&]() {
-            p_row_id = row_id; p_row_lab = row_lab;
+            p_row_id = row_id;
+            if constexpr (!SPLIT) p_row_lab = row_lab;
             p_K = n_K; p_nrec = n_nrec; p_nstale = n_nstale; p_stale = n_stale; p_stale_pos = n_stale_pos; p_rec_word = n_rec_word;
             p_rows = n_rows; p_flags = n_flags; p_ver = n_ver;
-            if constexpr (chunked) asm volatile("" : "+v"(p_row_id), "+v"(p_row_lab) : : "memory");
-            else asm volatile("" : "+v"(p_row_id), "+v"(p_row_lab), "+v"(p_stale), "+v"(p_stale_pos), "+v"(p_rec_word) : : "memory");
+            if constexpr (SPLIT) p_row_lab = reinterpret_cast<const float*>(a.y)[p_row_id == kNoRow ? 0u : p_row_id];
+            else asm volatile("" : "+v"(p_row_lab) : : "memory");
+            if constexpr (chunked) asm volatile("" : "+v"(p_row_id) : : "memory");
+            else asm volatile("" : "+v"(p_row_id), "+v"(p_stale), "+v"(p_stale_pos), "+v"(p_rec_word) : : "memory");
         };
         // Its gathers.  A wave's loads return in order, so what is asked for afterwards must not be needed before the rows are.
         auto gather = [&]() {
@@ -476,7 +489,8 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                 if (!chunked && p_stale_pos < kc) L.s_stale[p_stale_pos] = p_stale;
                 if (lane < kc) L.s_rec[lane] = chunked ? 1 << 16 : p_rec_word;       // (only the first entry is read)
             }
-            asm volatile("" : "+v"(q_sel), "+v"(q_tau), "+v"(q_ord), "+v"(row_lab) : : "memory");     // lists and labels asked for behind the rows
+            if constexpr (SPLIT) asm volatile("" : "+v"(q_sel), "+v"(q_tau), "+v"(q_ord) : : "memory");
+            else asm volatile("" : "+v"(q_sel), "+v"(q_tau), "+v"(q_ord), "+v"(row_lab) : : "memory");     // lists and labels asked for behind the rows
         };
 
         // Loader wave 0, between D and B: the column sums of the delta tile per record, i.e. the bias
@@ -551,7 +565,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         issue_lists(a.v0);
         take_lists(a.v0);
         issue_lists(a.v0 + min((int64_t)1, a.nsteps - 1));
-        describe_tile(a.v0, 0);
+        describe_tile(a.v0, 0, true);
         asm volatile("" : "+v"(q_sel), "+v"(q_tau), "+v"(q_ord), "+v"(row_lab) : : "memory");
         bool more = true;                            // the tile described last is still to be gathered
         auto turn = [&]() {
@@ -566,24 +580,32 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                 more = false;
             }
             issue_lists(a.v0 + min(at + 1, a.nsteps - 1));
-            describe_tile(a.v0 + at, at_tile);       // past the last tile: that tile again, never gathered
+            if constexpr (!SPLIT) describe_tile(a.v0 + at, at_tile, true);       // past the last tile: that tile again, never gathered
             if constexpr (LATE) {
                 asm volatile("" : "+v"(row_id) : : "memory");
                 gather();
             }
         };
         // the rest of the tile that the compute waves work on; false: the launch is aborted
-        auto rest = [&](int64_t v, int flags) -> bool {
+        auto rest = [&](int64_t v, int flags, bool turned) -> bool {
             lmark(1);
             lds_barrier();                           // D
             if (L.ctl[0] != 0) return false;
             if (!TEAM && lw == 0) bias_and_loss(v, flags);
+            if constexpr (SPLIT) {
+                if (turned) {
+                    describe_tile(a.v0 + at, at_tile, false);
+                    if (lw == 1) L.rowid[lane] = row_id;      // for wave 0; the compute waves are done with it
+                }
+            }
             lmark(2);
             lds_barrier();                           // B
+            if constexpr (SPLIT) { if (turned && lw == 0) row_id = L.rowid[lane]; }
             lmark(3);
             return true;
         };
         turn();
+        if constexpr (SPLIT) describe_tile(a.v0 + at, at_tile, true);
         for (;;) {
             lmark(4);
             publish();
@@ -592,11 +614,11 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
             const int flags = p_flags | (p_rows << 8);
             lds_barrier();                           // TU
             if (!more) {
-                if (!rest(v, flags)) return;
+                if (!rest(v, flags, false)) return;
                 break;
             }
             turn();
-            if (!rest(v, flags)) return;
+            if (!rest(v, flags, true)) return;
         }
         if constexpr (PROF) {
             if (lprof && lane == 0 && member == 0) a.prof[(int64_t)a.prof_base + ((int64_t)rep * G + slice) * 2 + 1] += lp_acc;
@@ -694,24 +716,22 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
     };
     const int scratch = a.own_slots | kOwnSlot;
     const __amdgpu_buffer_rsrc_t prsrc = make_rsrc(park, (uint32_t)S * 16u * nt * 4u);
-    int pk_off[4];
-#pragma unroll
-    for (int vv = 0; vv < 4; ++vv) pk_off[vv] = (own_cls + vv < C && (!ONE || tid < nt)) ? (vv * nt + tid) * 16 : kOutOfRange;
+    // (TEAM: offsets are derived from an opaque copy of the thread's number where they are used: kept across the loop they are
+    // spilled where 128 registers have to do, and a spilled word that is read back waits behind the gathers.)
+    auto myself = [&]() { int t = tid; asm volatile("" : "+v"(t)); return t; };
+    auto owner = [&]() { if constexpr (TEAM) return myself(); else return tid; };
+    auto pk_off = [&](int t, int vv) { return (4 * ((t & 63) >> 4) + vv < C && (!ONE || t < nt)) ? (vv * nt + t) * 16 : kOutOfRange; };
     // forward: rows 16 wave .. 16 wave + 15; row / class index of this lane in the MFMA operands
     const int f_row = 16 * wave + (lane & 15);
     // lanes of classes that do not exist read the last class: their logits are never used
     const int f_key = min(lane & 15, C - 1);
     // k-block s covers 16-byte chunks 4 s + lane/16 of the row; with the swizzle key split as
     // key = 4 k2 + k0 its position is 16 (s / 4) + 4 ((s % 4) ^ k2) + ((lane / 16) ^ k0): four base
-    // addresses per operand, the rest is a constant offset
-    const float* f_xa[4];
-    const float* f_wa[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int kx = f_row & 15;
-        f_xa[j] = L.tile + f_row * SL + ((4 * (j ^ (kx >> 2)) + ((lane >> 4) ^ (kx & 3))) << 2);
-        f_wa[j] = L.wlds + f_key * SL + ((4 * (j ^ (f_key >> 2)) + ((lane >> 4) ^ (f_key & 3))) << 2);
-    }
+    // addresses per operand, which differ in two bits, the rest is a constant offset
+    const int f_x0 = f_row * SL + ((4 * ((f_row & 15) >> 2) + ((lane >> 4) ^ (f_row & 3))) << 2);
+    const int f_w0 = f_key * SL + ((4 * (f_key >> 2) + ((lane >> 4) ^ (f_key & 3))) << 2);
+    auto f_xa = [&](int s) { return *reinterpret_cast<const f32x4*>(L.tile + (f_x0 ^ ((s & 3) << 4)) + (s >> 2) * 64); };
+    auto f_wa = [&](int s) { return *reinterpret_cast<const f32x4*>(L.wlds + (f_w0 ^ ((s & 3) << 4)) + (s >> 2) * 64); };
     // exchange: this lane's 16 bytes (4 classes of one row) inside one slice's block
     const int z_store = (f_row * 16 + 4 * (lane >> 4)) * 4;
     const int z_store_off = ((lane >> 4) < nquad) ? z_store : kOutOfRange;
@@ -736,15 +756,12 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
     const int team = TEAM ? __builtin_amdgcn_readfirstlane(L.ctl[2]) : 1;
     const __amdgpu_buffer_rsrc_t trsrc = make_rsrc(TEAM ? a.tx + ((int64_t)rep * G + slice) * 3 * a.team * kTeamWords : nullptr,
                                                    TEAM ? (uint32_t)(3 * a.team * kTeamWords * 4) : 0u);
-    int tx_off[4];
-#pragma unroll
-    for (int vv = 0; vv < 4; ++vv) tx_off[vv] = own_cls + vv < C ? (vv * NTC + tid) * 16 : kOutOfRange;
-    const int tx_bias = tid < 16 ? (4 * NTC * 4 + tid) * 4 : kOutOfRange;
     const int small_word = (lane & 15) == 15 ? 16 : (lane & 15);       // the slot record keeps the loss in word 16
     uint32_t n_team = 0;
     float gbias = 0.0f;      // TEAM: sum of the bias gradients (class 15: loss), class lane % 16
 
-    float gsum[16];          // this thread's part of sum_l g_l of the update in progress: gsum[4 vv + c]
+    constexpr int NV = KIND == kLsq ? 1 : 4;      // class rows of a thread that can exist
+    float gsum[4 * NV];      // this thread's part of sum_l g_l of the update in progress: gsum[4 vv + c]
     // TEAM: gsum and gbias become the sums over the members, added in their order by everyone.  A word is a sentinel until its
     // member has written it, as in the exchange of the partial logits; a thread talks to the threads of its own number only.
     // (through to memory if the members sit on several XCDs; 0.45 to 0.57 us from store to sight between two XCDs, 0.39 through
@@ -758,7 +775,9 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         else __builtin_amdgcn_raw_buffer_store_b32((int)v, trsrc, off, 0, 0);
     };
     auto team_sum = [&]() {
-        constexpr int NV = KIND == kLsq ? 1 : 4;      // class rows of a thread that can exist
+        const int me = myself();
+        auto tx_off = [&](int vv) { return 4 * ((me & 63) >> 4) + vv < C ? (vv * NTC + me) * 16 : kOutOfRange; };
+        const int tx_bias = me < 16 ? (4 * NTC * 4 + me) * 4 : kOutOfRange;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the re-arming stores of the last exchange have arrived
         const int base = (int)(n_team % 3u) * team;
         const int mine = (base + member) * (kTeamWords * 4);
@@ -770,12 +789,12 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                 const uint32_t bits = __float_as_uint(gsum[4 * vv + c]);
                 ob[c] = bits == kSentinel ? 0x7FC00000u : bits;
             }
-            put(ob, tx_off[vv] + mine);
+            put(ob, tx_off(vv) + mine);
         }
         const uint32_t bias_bits = __float_as_uint(gbias);
         put1(bias_bits == kSentinel ? 0x7FC00000u : bias_bits, tx_bias + mine);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) gsum[e] = 0.0f;
+        for (int e = 0; e < 4 * NV; ++e) gsum[e] = 0.0f;
         gbias = 0.0f;
         uint32_t spins = 0;
         // the parts of members q0 .. q0 + N - 1
@@ -788,7 +807,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                 for (int i = 0; i < N; ++i) {
                     const int soff = (base + q0 + i) * (kTeamWords * 4);
 #pragma unroll
-                    for (int vv = 0; vv < NV; ++vv) part[i][vv] = __builtin_amdgcn_raw_buffer_load_b128(trsrc, tx_off[vv], soff, kAgentLoad);
+                    for (int vv = 0; vv < NV; ++vv) part[i][vv] = __builtin_amdgcn_raw_buffer_load_b128(trsrc, tx_off(vv), soff, kAgentLoad);
                     pb[i] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(trsrc, tx_bias, soff, kAgentLoad);
                 }
                 asm volatile("" ::: "memory");
@@ -835,7 +854,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         const u32x4 arm = {sv, sv, sv, sv};
         const int prev = ((int)((n_team + 2u) % 3u) * team + member) * (kTeamWords * 4);
 #pragma unroll
-        for (int vv = 0; vv < NV; ++vv) put(arm, tx_off[vv] + prev);
+        for (int vv = 0; vv < NV; ++vv) put(arm, tx_off(vv) + prev);
         put1(sv, tx_bias + prev);
         ++n_team;
     };
@@ -865,16 +884,34 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         // ---- partial logits of rows 16 wave ..: D[class][row] += W[class][k] X[row][k] over this slice;
         //      the operands of the next k-block are read from LDS before the MFMAs of this one are issued
         if (work) {
+            f32x4 out;       // classes 4*(lane/16)+0..3 of row f_row
+            if constexpr (KIND == kLsq) {
+                // One class: on the matrix units fifteen sixteenths of the work would be padding (2350 cycles at 256 columns, one
+                // slice; 900 so).  A quarter of the row per lane, the four quarters added across the lanes.
+                f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int s = 0; s < SL / 16; ++s) {
+                    if (ONE && s > 0 && (s & 3) == 0 && s >= 4 * nblk) break;
+                    const f32x4 wv = f_wa(s);
+                    const f32x4 xv = f_xa(s);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) sum[c] = __builtin_fmaf(wv[c], xv[c], sum[c]);
+                }
+                float z = (sum.x + sum.y) + (sum.z + sum.w);
+                z += across<16>(z, lane);
+                z += across<32>(z, lane);
+                out = f32x4{z, 0.f, 0.f, 0.f};
+            } else {
             f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-            f32x4 wv = *reinterpret_cast<const f32x4*>(f_wa[0]);
-            f32x4 xv = *reinterpret_cast<const f32x4*>(f_xa[0]);
+            f32x4 wv = f_wa(0);
+            f32x4 xv = f_xa(0);
 #pragma unroll
             for (int s = 0; s < SL / 16; ++s) {
                 if (ONE && s > 0 && (s & 3) == 0 && s >= 4 * nblk) break;
                 f32x4 wn = wv, xn = xv;
                 if (s + 1 < SL / 16) {
-                    wn = *reinterpret_cast<const f32x4*>(f_wa[(s + 1) & 3] + ((s + 1) >> 2) * 64);
-                    xn = *reinterpret_cast<const f32x4*>(f_xa[(s + 1) & 3] + ((s + 1) >> 2) * 64);
+                    wn = f_wa(s + 1);
+                    xn = f_xa(s + 1);
                 }
                 __builtin_amdgcn_sched_barrier(0);   // keep the reads ahead of the MFMAs
                 acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.x, xv.x, acc0, 0, 0, 0);
@@ -883,11 +920,12 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                 acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.w, xv.w, acc1, 0, 0, 0);
                 wv = wn; xv = xn;
             }
-            const f32x4 out = acc0 + acc1;   // classes 4*(lane/16)+0..3 of row f_row
+            out = acc0 + acc1;
+            }
             mark(8);
             if constexpr (ONE) {
-                // thread tid takes class quad tid % 4 of row tid / 4, a row of this wave
-                const int from = ((lane & 3) * 16 + (lane >> 2)) * 4;
+                // thread tid takes class quad tid % 4 of row tid / 4, a row of this wave (one class: every lane of a row has it)
+                const int from = KIND == kLsq ? (lane >> 2) * 4 : ((lane & 3) * 16 + (lane >> 2)) * 4;
 #pragma unroll
                 for (int c = 0; c < (KIND == kLsq ? 1 : 4); ++c)
                     own_z[c] = __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(out[c])));
@@ -911,11 +949,11 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         auto park_load = [&](int slot, f32x4 (&pv)[4]) {
             // classes that do not exist are out of range and read as zero
             const int word = __builtin_amdgcn_readfirstlane(slot);
-            const int soff = (word & 0xFFFF) * 16 * nt * 4;
+            const int soff = (word & 0xFFFF) * 16 * nt * 4, me = owner();
             const __amdgpu_buffer_rsrc_t rs = TEAM && BATCH ? park_of(word) : prsrc;
 #pragma unroll
-            for (int vv = 0; vv < 4; ++vv)
-                pv[vv] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, pk_off[vv], soff, 0));
+            for (int vv = 0; vv < NV; ++vv)
+                pv[vv] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, pk_off(me, vv), soff, 0));
         };
         // (TEAM: bias gradient and loss of a parked mini-batch, class lane % 16)
         auto park_bias = [&](int slot) {
@@ -947,13 +985,13 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         }
         if ((tile_flags & 2) != 0) {
 #pragma unroll
-            for (int e = 0; e < 16; ++e) gsum[e] = pva[e >> 2][e & 3] + pvb[e >> 2][e & 3];
+            for (int e = 0; e < 4 * NV; ++e) gsum[e] = pva[e >> 2][e & 3] + pvb[e >> 2][e & 3];
             if constexpr (TEAM) gbias = ba + bb;
         }
         for (int i = 2; !chunked && i < n_stale; ++i) {     // further parked gradients (K > 2)
             park_load(L.s_stale[i], pva);
 #pragma unroll
-            for (int e = 0; e < 16; ++e) gsum[e] += pva[e >> 2][e & 3];
+            for (int e = 0; e < 4 * NV; ++e) gsum[e] += pva[e >> 2][e & 3];
             if constexpr (TEAM) gbias += park_bias(L.s_stale[i]);
         }
         mark(2);
@@ -1120,7 +1158,6 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         {
             const bool has_cols = !ONE || wave < nblk;      // a wave without columns contracts nothing
             const int n_own = has_cols ? n_rec : 0;
-            const int b_lo = lane >> 4, b_cls = lane & 15;
             f32x4 acc[4];
 #pragma unroll
             for (int c = 0; c < 4; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -1131,9 +1168,10 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                 bsum += across<32>(bsum, lane);
                 return bsum;
             };
-            auto finish = [&](int r) {
+            auto finish = [&](int rec_word) {         // its entry in the compute list
+                const int me = owner();
                 if constexpr (PROF) { asm volatile("" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])); mark(11); }
-                const int word = __builtin_amdgcn_readfirstlane(r == 0 ? rec01.x : (r == 1 ? rec01.y : L.s_rec[r]));
+                const int word = __builtin_amdgcn_readfirstlane(rec_word);
                 bool to_sum = ((word >> 16) & 1) != 0;
                 if constexpr (BATCH) {
                     // A record of several tiles is summed in its worker's slot (free by now: what it held was consumed
@@ -1144,8 +1182,8 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                         const int soff = (from & 0xFFFF) * 16 * nt * 4;
                         const __amdgpu_buffer_rsrc_t rs = TEAM ? park_of(from) : prsrc;
 #pragma unroll
-                        for (int vv = 0; vv < 4; ++vv) {
-                            const f32x4 pv = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, pk_off[vv], soff, 0));
+                        for (int vv = 0; vv < NV; ++vv) {
+                            const f32x4 pv = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, pk_off(me, vv), soff, 0));
 #pragma unroll
                             for (int c = 0; c < 4; ++c) acc[c][vv] += pv[c];
                         }
@@ -1164,33 +1202,72 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                 }
                 if (to_sum) {
 #pragma unroll
-                    for (int vv = 0; vv < 4; ++vv)
+                    for (int vv = 0; vv < NV; ++vv)
 #pragma unroll
                         for (int c = 0; c < 4; ++c) gsum[vv * 4 + c] += acc[c][vv];
                 } else {
                     const int soff = (dest & 0xFFFF) * 16 * nt * 4;
                     const __amdgpu_buffer_rsrc_t rs = TEAM && BATCH ? park_of(dest) : prsrc;
 #pragma unroll
-                    for (int vv = 0; vv < 4; ++vv) {
+                    for (int vv = 0; vv < NV; ++vv) {
                         const f32x4 gv = {acc[0][vv], acc[1][vv], acc[2][vv], acc[3][vv]};
-                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, gv), rs, pk_off[vv] + soff, 0, 0);
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, gv), rs, pk_off(me, vv) + soff, 0, 0);
                     }
                 }
 #pragma unroll
                 for (int c = 0; c < 4; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
                 mark(12);
             };
-            // The tile and delta addresses are four base addresses (one per k-step of 16 rows, carrying the swizzle key of
-            // its rows) plus constants.
-                            int olo = b_lo, och = own_ch, ocl = b_cls;
-                            asm volatile("" : "+v"(olo), "+v"(och), "+v"(ocl));   // rebuilt every step, not kept across the loop
-                            const float* bx[4];
-            #pragma unroll
-                            for (int u = 0; u < 4; ++u) bx[u] = L.tile + (4 * u + olo) * SL + ((och ^ (4 * u + olo)) << 2);
-                            const float* bz = L.zbuf + olo * 16 + ocl;
-            if constexpr (WHOLE) {
+            const int ome = myself(), olo = (ome & 63) >> 4, ocl = ome & 15, och = 16 * wave + ocl;
+            const float* bz = L.zbuf + olo * 16 + ocl;
+            if constexpr (KIND == kLsq) {
+                // One class: a lane adds up its four columns over every fourth row, the four lanes of a column are added at the
+                // end of a record (two records of 16 rows, 256 columns, one slice: 3500 cycles on the matrix units, 2400 so).
+                const float* dz = L.zbuf + olo * 16;
+                const float* xr = L.tile + olo * SL;
+                const int key = och ^ olo, kpr = rows >> 2;
+                int k = opq;
+#pragma unroll 1
+                for (int r = 0; r < n_own; ++r) {
+                    const int rec_word = L.s_rec[r];      // read ahead of its use
+                    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+                    auto add = [&](auto n, int k0) {
+                        constexpr int N = decltype(n)::value;
+                        float dv[N], lv[N];
+                        f32x4 xv[N];
+#pragma unroll
+                        for (int u = 0; u < N; ++u) {
+                            dv[u] = dz[(k0 + u) * 64];
+                            if constexpr (TEAM) lv[u] = dz[(k0 + u) * 64 + ocl];
+                            xv[u] = *reinterpret_cast<const f32x4*>(xr + (k0 + u) * 4 * SL + ((key ^ (4 * ((k0 + u) & 3))) << 2));
+                        }
+#pragma unroll
+                        for (int u = 0; u < N; ++u) {
+                            if constexpr (TEAM) bsum += lv[u];
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) sum[c] = __builtin_fmaf(dv[u], xv[u][c], sum[c]);
+                        }
+                    };
+                    const int end = k + kpr;
+#pragma unroll 1
+                    for (; k + 8 <= end; k += 8) add(std::integral_constant<int, 8>{}, k);
+                    if (k + 4 <= end) { add(std::integral_constant<int, 4>{}, k); k += 4; }
+#pragma unroll 1
+                    for (; k < end; ++k) add(std::integral_constant<int, 1>{}, k);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        sum[c] += across<16>(sum[c], lane);
+                        sum[c] += across<32>(sum[c], lane);
+                        acc[c][0] = sum[c];
+                    }
+                    finish(rec_word);
+                }
+            } else if constexpr (WHOLE) {
                 // Whole groups of 16 rows only, at most four of them: two register sets take turns, one being read from LDS while the MFMAs of the other are issued.
                 // half-group h: k-steps 2 h and 2 h + 1, i.e. rows 8 h .. 8 h + 7
+                const float* bx[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) bx[u] = L.tile + (4 * u + olo) * SL + ((och ^ (4 * u + olo)) << 2);
                 auto fetch = [&](int h, float (&dv)[2], f32x4 (&xv)[2]) {
 #pragma unroll
                     for (int u = 0; u < 2; ++u) {
@@ -1210,6 +1287,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                     }
                 };
                 auto done = [&](int r) {
+                    const int me = owner();
                     if constexpr (PROF) { asm volatile("" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])); mark(11); }
                     const int word = __builtin_amdgcn_readfirstlane(r == 0 ? rec01.x : rec01.y);
                     if constexpr (TEAM) {
@@ -1220,16 +1298,16 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                     }
                     if (((word >> 16) & 1) != 0) {
 #pragma unroll
-                        for (int vv = 0; vv < 4; ++vv)
+                        for (int vv = 0; vv < NV; ++vv)
 #pragma unroll
                             for (int c = 0; c < 4; ++c) gsum[vv * 4 + c] += acc[c][vv];
                     } else {
                         const int soff = (word & 0xFFFF) * 16 * nt * 4;
                         const __amdgpu_buffer_rsrc_t rs = TEAM && BATCH ? park_of(word) : prsrc;
 #pragma unroll
-                        for (int vv = 0; vv < 4; ++vv) {
+                        for (int vv = 0; vv < NV; ++vv) {
                             const f32x4 gv = {acc[0][vv], acc[1][vv], acc[2][vv], acc[3][vv]};
-                            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, gv), rs, pk_off[vv] + soff, 0, 0);
+                            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, gv), rs, pk_off(me, vv) + soff, 0, 0);
                         }
                     }
                     mark(12);
@@ -1270,10 +1348,13 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                         done(0);
                     }
                 }
-            } else {
+            } else if constexpr (!BATCH) {
                 // Records of any multiple of four rows, one behind the other, 16 rows a turn: a record ends where its rows do.
                 // Four register sets, each read again for the next turn as soon as its MFMAs are issued.
                 const int kpr = rows >> 2, steps = n_own * kpr;
+                const float* bx[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) bx[u] = L.tile + (4 * u + olo) * SL + ((och ^ (4 * u + olo)) << 2);
                 float dv[4];
                 f32x4 xv[4];
 #pragma unroll
@@ -1284,14 +1365,57 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
                         if (g0 + u < steps) {
-                            if constexpr (TEAM) bsum += dv[u];
 #pragma unroll
                             for (int c = 0; c < 4; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(dv[u], xv[u][c], acc[c], 0, 0, 0);
-                            if (g0 + u + 1 == end) { finish(r); ++r; end += kpr; }
+                            if (g0 + u + 1 == end) { finish(r == 0 ? rec01.x : (r == 1 ? rec01.y : L.s_rec[r])); ++r; end += kpr; }
                         }
                         dv[u] = bz[4 * (nx + u) * 16];
                         xv[u] = *reinterpret_cast<const f32x4*>(bx[u] + 4 * nx * SL);
                     }
+                }
+            } else {
+                // The same where records are described one by one and their ends are more code: two register sets take turns,
+                // one being read from LDS while the MFMAs of the other are issued, and the loops are kept rolled.  (Unrolled over
+                // the sixteen k-steps that a tile can have, with the end of a record behind each, they are 25 KB of code:
+                // softmax, P = 20, K = 5, m = 25, d = 785, 8 replicas 9.2 us per update, 8.8 so.  Without that code the unrolled loop is the
+                // better one: P = 11, K = 5, m = 12, d = 2420, one replica 7.4 us, 7.6 rolled.)
+                const int kpr = rows >> 2, last = n_own * kpr - 1;
+                const float* xr = L.tile + olo * SL;
+                const int key = och ^ olo;
+                auto fetch = [&](int k, float& dv, f32x4& xv) {
+                    dv = bz[64 * k];
+                    xv = *reinterpret_cast<const f32x4*>(xr + 4 * k * SL + ((key ^ (4 * (k & 3))) << 2));
+                };
+                auto mac = [&](float dv, const f32x4& xv) {
+                    if constexpr (TEAM) bsum += dv;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(dv, xv[c], acc[c], 0, 0, 0);
+                };
+                float da, db;
+                f32x4 xa, xb;
+                int k = opq;
+                fetch(0, da, xa);
+#pragma unroll 1
+                for (int r = 0; r < n_own; ++r) {
+                    const int rec_word = L.s_rec[r];      // read ahead of its use
+                    const int end = k + kpr;
+#pragma unroll 1
+                    for (; k + 2 <= end; k += 2) {
+                        fetch(k + 1, db, xb);
+                        __builtin_amdgcn_sched_barrier(0);
+                        mac(da, xa);
+                        fetch(min(k + 2, last), da, xa);
+                        __builtin_amdgcn_sched_barrier(0);
+                        mac(db, xb);
+                    }
+                    if (k < end) {
+                        fetch(min(k + 1, last), db, xb);
+                        __builtin_amdgcn_sched_barrier(0);
+                        mac(da, xa);
+                        da = db; xa = xb;
+                        ++k;
+                    }
+                    finish(rec_word);
                 }
             }
         }
@@ -1303,10 +1427,9 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         }
         if (last_tile) {
             const float scale = a.lr / (float)Kv;
-            int och = own_ch, ocl = own_cls;
-            asm volatile("" : "+v"(och), "+v"(ocl));   // the four addresses below are rebuilt here, not kept across the loop
+            const int me = myself(), och = 16 * wave + (me & 15), ocl = 4 * ((me & 63) >> 4);
 #pragma unroll
-            for (int vv = 0; vv < 4; ++vv) {
+            for (int vv = 0; vv < NV; ++vv) {
                 const int cls = ocl + vv;
                 if (cls < C) {
                     f32x4* wp = reinterpret_cast<f32x4*>(L.wlds + cls * SL + ((och ^ cls) << 2));
@@ -1328,7 +1451,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                 // the averaged gradient of replica 0, when the caller asked for it
                 const float invK = 1.0f / (float)Kv;
 #pragma unroll
-                for (int vv = 0; vv < 4; ++vv) {
+                for (int vv = 0; vv < NV; ++vv) {
                     const int cls = own_cls + vv;
                     if (cls < C)
 #pragma unroll
@@ -1354,8 +1477,8 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
             const int soff = q * 16 * nt * 4, off = tid < 16 ? small_word * 4 : kOutOfRange;
 #pragma unroll
             for (int vv = 0; vv < 4; ++vv)
-                __builtin_amdgcn_raw_buffer_store_b128(__builtin_amdgcn_raw_buffer_load_b128(park_of(kOwnSlot), pk_off[vv], soff, 0), prsrc,
-                                                       pk_off[vv] + soff, 0, kAgentLoad);
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_amdgcn_raw_buffer_load_b128(park_of(kOwnSlot), pk_off(tid, vv), soff, 0), prsrc,
+                                                       pk_off(tid, vv) + soff, 0, kAgentLoad);
             __builtin_amdgcn_raw_buffer_store_b32(__builtin_amdgcn_raw_buffer_load_b32(small_of(kOwnSlot), off, q * 68, 0), small_of(0), off + q * 68, 0, kAgentLoad);
         }
     }
