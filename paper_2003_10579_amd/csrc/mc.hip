@@ -586,6 +586,7 @@ __global__ __launch_bounds__(64, VARIANT == kBatchAsync ? 4 : 8) void mc_kernel(
 // loads in flight, and the runs' sums are added in order, pairs first.  (A single value of K has 16 words and 8192 blocks:
 // 64 words wide and four runs this took 120 us, as long as a small estimate itself.)
 constexpr int kReduceThreads = 1024;
+constexpr int64_t kReduceGroups = 32;      // workgroups wanted
 __global__ __launch_bounds__(kReduceThreads) void mc_reduce_kernel(McArgs a, int groups, int cells_max, int width, double* out) {
     __shared__ double runs[kReduceThreads];
     const int w = threadIdx.x & (width - 1), part = threadIdx.x / width, parts = kReduceThreads / width;
@@ -695,8 +696,9 @@ extern "C" __attribute__((visibility("default"))) ssgd_status ssgd_runtime_mc(in
         double* d_sums = a.partial + partial_words;
         hipError_t e = P <= 64 ? launch_mc<1>(a, (unsigned)blocks, lds, st) : (P <= 128 ? launch_mc<2>(a, (unsigned)blocks, lds, st) : launch_mc<4>(a, (unsigned)blocks, lds, st));
         if (e == hipSuccess) {
+            // (narrower where that leaves too few workgroups to keep enough loads in flight: 8192 blocks of 16 words 16 -> 4 us)
             int width = 2;
-            while (width < 64 && width < 2 * cells_max) width *= 2;
+            while (width < 64 && width < 2 * cells_max && (2 * cells_max / (2 * width)) * nslices >= kReduceGroups) width *= 2;
             hipLaunchKernelGGL(mc_reduce_kernel, dim3((unsigned)((2 * cells_max + width - 1) / width), (unsigned)nslices), dim3(kReduceThreads), 0, st,
                                a, (int)groups, (int)cells_max, width, d_sums);
             e = hipGetLastError();
