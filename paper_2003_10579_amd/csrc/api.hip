@@ -1,6 +1,7 @@
 // C ABI of the library (see include/ssgd.h): argument checks, device state, and the
 // host loop that alternates schedule segments with gradient/update launches.
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -85,6 +86,8 @@ struct ssgd_ctx {
     size_t host_out_bytes = 0;
     size_t host_flags_bytes = 0;
     int32_t* host_flags = nullptr;  // pinned: abort flag and one fall-back flag per replica, written by flags_kernel behind the kernels that raise them
+    uint32_t* done_word = nullptr;  // pinned (behind the flags): number of the last call whose results are in host memory
+    uint32_t done_number = 0;       // of the last such call
     bool flags_seen = false;        // host_flags holds the flags of everything queued so far (the stream has been waited for)
     DevBuf fg_work;                 // partial gradients of ssgd_full_gradient, kept from its first call on
     int device = 0;
@@ -138,6 +141,21 @@ hipError_t host_out_room(ssgd_ctx* c, size_t bytes) {
     return pinned_pool().take(bytes, c->device, &c->host_out, &c->host_out_bytes);
 }
 
+Done next_done(ssgd_ctx* c) { return {c->abort_flag.as<uint32_t>() + 1, c->done_word, ++c->done_number}; }
+
+// Waits for the kernel that was given next_done() last: short ones by watching the word, the others (and every 256th, so that
+// the runtime sees its queue empty now and then; and whatever has failed) by waiting for the stream.
+hipError_t wait_done(ssgd_ctx* c) {
+    if ((c->done_number & 255u) != 0) {
+        const auto t0 = std::chrono::steady_clock::now();
+        for (uint32_t spins = 1;; ++spins) {
+            if (__atomic_load_n(c->done_word, __ATOMIC_ACQUIRE) == c->done_number) return hipSuccess;
+            if ((spins & 63u) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(300)) break;
+        }
+    }
+    return hipStreamSynchronize(c->stream);
+}
+
 // Rows of several device arrays, one behind the other, to memory that the host reads: one launch and one wait where a
 // copy command per array takes 14 us each (a trace of six arrays: 90 us with commands).
 constexpr int kMaxSegments = 6;
@@ -146,11 +164,14 @@ struct Segments {
     int64_t dst[kMaxSegments], words[kMaxSegments];
     int n;
 };
-__global__ __launch_bounds__(256) void gather_segments_kernel(Segments g, uint32_t* out) {
+__global__ __launch_bounds__(256) void gather_segments_kernel(Segments g, uint32_t* out, Done done) {
     const int sgm = blockIdx.y;
     const uint32_t* src = g.src[sgm];
     uint32_t* dst = out + g.dst[sgm];
-    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < g.words[sgm]; q += (int64_t)gridDim.x * blockDim.x) dst[q] = src[q];
+    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < g.words[sgm]; q += (int64_t)gridDim.x * blockDim.x) store_result(dst + q, src[q]);
+    results_arrived();
+    __syncthreads();
+    if (threadIdx.x == 0) signal_done(done, gridDim.x * gridDim.y);
 }
 constexpr size_t kGatherBytes = 4 << 20;   // above this a copy command per array is as fast
 
@@ -161,25 +182,28 @@ hipError_t gather_to_host(ssgd_ctx* c, const Segments& g) {
     hipError_t e = host_out_room(c, sizeof(uint32_t) * (size_t)total);
     if (e != hipSuccess) return e;
     const unsigned blocks = (unsigned)std::max<int64_t>(1, std::min<int64_t>(256, (most + 1023) / 1024));
-    hipLaunchKernelGGL(gather_segments_kernel, dim3(blocks, g.n), dim3(256), 0, c->stream, g, static_cast<uint32_t*>(c->host_out));
+    hipLaunchKernelGGL(gather_segments_kernel, dim3(blocks, g.n), dim3(256), 0, c->stream, g, static_cast<uint32_t*>(c->host_out), next_done(c));
     e = hipGetLastError();
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    if (e == hipSuccess) e = wait_done(c);
     return e;
 }
 
-__global__ void flags_kernel(const int32_t* abort_flag, const int32_t* fallback, int R, int32_t* out) {
+__global__ void flags_kernel(const int32_t* abort_flag, const int32_t* fallback, int R, int32_t* out, Done done) {
     const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q == 0) out[0] = *abort_flag;
-    if (fallback != nullptr && q < R) out[1 + q] = fallback[q];
+    if (q == 0) store_result(out, *abort_flag);
+    if (fallback != nullptr && q < R) store_result(out + 1 + q, fallback[q]);
+    results_arrived();
+    __syncthreads();
+    if (threadIdx.x == 0) signal_done(done, gridDim.x);
 }
 
 // Waits for the stream with the flags in c->host_flags.
 hipError_t read_flags(ssgd_ctx* c) {
     if (c->flags_seen) return hipSuccess;
     const int32_t* fallback = c->fallback.as<int32_t>();
-    hipLaunchKernelGGL(flags_kernel, dim3((unsigned)(c->R + 255) / 256), dim3(256), 0, c->stream, c->abort_flag.as<int32_t>(), fallback, c->R, c->host_flags);
+    hipLaunchKernelGGL(flags_kernel, dim3((unsigned)(c->R + 255) / 256), dim3(256), 0, c->stream, c->abort_flag.as<int32_t>(), fallback, c->R, c->host_flags, next_done(c));
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    if (e == hipSuccess) e = wait_done(c);
     c->flags_seen = e == hipSuccess;
     return e;
 }
@@ -703,9 +727,12 @@ ssgd_status ssgd_create(const ssgd_model* model, int32_t P, int32_t K, int32_t m
         HIP_C(hipGetLastError());
     }
     c->tr.Kcap = Kcap; c->tr.cap = 0;
-    HIP_C(c->abort_flag.alloc(sizeof(int32_t)));
-    HIP_C(pinned_pool().take(sizeof(int32_t) * (size_t)(1 + R), c->device, (void**)&c->host_flags, &c->host_flags_bytes));
-    HIP_C(hipMemsetAsync(c->abort_flag.p, 0, sizeof(int32_t), c->stream));
+    HIP_C(c->abort_flag.alloc(2 * sizeof(int32_t)));         // and the count behind Done
+    const size_t n_flags = ((size_t)(1 + R) + 31) / 32 * 32;
+    HIP_C(pinned_pool().take(sizeof(int32_t) * (n_flags + 1), c->device, (void**)&c->host_flags, &c->host_flags_bytes));
+    c->done_word = reinterpret_cast<uint32_t*>(c->host_flags + n_flags);
+    *c->done_word = 0;
+    HIP_C(hipMemsetAsync(c->abort_flag.p, 0, 2 * sizeof(int32_t), c->stream));
 
     if (model->kind == SSGD_MLP2) {
         std::string msg;
@@ -912,8 +939,8 @@ ssgd_status ssgd_full_loss(ssgd_ctx* c, int32_t replica, double* loss_out) {
     HIP_OK(c, host_out_room(c, sizeof(double) * blocks));
     double* h = static_cast<double*>(c->host_out);
     hipError_t e = launch_full_loss(c->model.kind, c->model.X, c->model.y, c->model.N, c->model.d, C,
-                                    c->params.as<float>() + (int64_t)replica * c->nw, h, blocks, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+                                    c->params.as<float>() + (int64_t)replica * c->nw, h, blocks, c->stream, next_done(c));
+    if (e == hipSuccess) e = wait_done(c);
     if (e != hipSuccess) return fail(c, SSGD_EDEVICE, std::string("full objective: ") + hipGetErrorString(e));
     double s = 0.0;
     for (int b = 0; b < blocks; ++b) s += h[b];
@@ -946,8 +973,8 @@ ssgd_status ssgd_full_gradient(ssgd_ctx* c, int32_t replica, float* grad_out) {
     if (host_out_room(c, sizeof(float) * (size_t)c->nw) != hipSuccess) return fail(c, SSGD_ENOMEM, "full gradient: host allocation failed");
     hipError_t e = launch_full_grad(c->model.kind, c->model.X, c->model.y, c->model.N, c->model.d, C,
                                     c->params.as<float>() + (int64_t)replica * c->nw, c->fg_work.as<float>(),
-                                    static_cast<float*>(c->host_out), c->cu_count, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+                                    static_cast<float*>(c->host_out), c->cu_count, c->stream, next_done(c));
+    if (e == hipSuccess) e = wait_done(c);
     if (e != hipSuccess) return fail(c, SSGD_EDEVICE, std::string("full gradient: ") + hipGetErrorString(e));
     memcpy(grad_out, c->host_out, sizeof(float) * (size_t)c->nw);
     return SSGD_OK;
@@ -970,7 +997,7 @@ ssgd_status ssgd_full_gradient_static(ssgd_ctx* c, int32_t replica, float* grad_
     // every word of the scratch memory that the kernels read has been written by this call before (the per-sample
     // deltas of rows 0 .. N-1, the partial sums of all chunks, classes and columns), so nothing has to be cleared
     HIP_OK(c, launch_full_grad(c->model.kind, c->model.X, c->model.y, c->model.N, c->model.d, C,
-                               c->params.as<float>() + (int64_t)replica * c->nw, work, grad_out_device, c->cu_count, c->stream));
+                               c->params.as<float>() + (int64_t)replica * c->nw, work, grad_out_device, c->cu_count, c->stream, Done{}));
     return SSGD_OK;
 }
 

@@ -50,6 +50,7 @@ struct FullGradArgs {
     float* delta;        // [N][16], two-pass kernels
     float* partial;      // [chunks][C][d + 1]
     float* out;          // [C * d (+ C)], device memory or mapped host memory
+    Done done;
 };
 
 constexpr int FG_TSTRIDE = 20;    // words per sample in a wave's buffer for turning delta over: 16-byte rows in different banks
@@ -326,8 +327,13 @@ __global__ __launch_bounds__(64 * kReduceWaves) void full_grad_reduce_kernel(Ful
         for (int p = 1; p < kReduceWaves; ++p) sum += parts[p][lane];
         const int c = q / (d + 1), col = q - c * (d + 1);
         const float gr = (float)(sum / (double)a.N);
-        if (col < d) a.out[(int64_t)c * d + col] = gr;
-        else if (a.kind == kSoftmax) a.out[(int64_t)C * d + c] = gr;
+        if (col < d) store_result(a.out + (int64_t)c * d + col, gr);
+        else if (a.kind == kSoftmax) store_result(a.out + (int64_t)C * d + c, gr);
+    }
+    // (one wave has written)
+    if (part == 0) {
+        results_arrived();
+        if (lane == 0) signal_done(a.done, gridDim.x);
     }
 }
 
@@ -422,8 +428,9 @@ float* full_grad_static_scratch() {
 
 // `work`: full_grad_work_floats floats of device memory; `out`: |w| floats the device can write
 hipError_t launch_full_grad(int kind, const float* X, const void* y, int64_t N, int d, int C, const float* w,
-                            float* work, float* out, int cus, hipStream_t s) {
+                            float* work, float* out, int cus, hipStream_t s, const Done& done) {
     FullGradArgs a{};
+    a.done = done;
     a.X = X; a.y = y; a.w = w; a.N = N; a.d = d; a.C = C; a.kind = kind; a.out = out;
     const FusedShape f = fused_shape(N, d, C, cus);
     if (f.waves > 0) {

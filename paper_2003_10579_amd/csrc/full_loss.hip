@@ -34,6 +34,7 @@ struct FullLossArgs {
     int32_t d, C, kind;
     int32_t stride;      // words per weight row in LDS
     double* partial;     // [gridDim.x]
+    Done done;
 };
 
 template <int KIND, bool WHOLE>
@@ -184,7 +185,9 @@ __global__ __launch_bounds__(64 * FL_WAVES) void full_loss_kernel(FullLossArgs a
     if (tid == 0) {
         double s = 0.0;
         for (int q = 0; q < FL_WAVES; ++q) s += wave_sum[q];
-        a.partial[blockIdx.x] = s;
+        store_result(a.partial + blockIdx.x, s);
+        results_arrived();
+        signal_done(a.done, gridDim.x);
     }
 }
 
@@ -202,8 +205,9 @@ bool full_loss_supports(int kind, int d, int C) {
 }
 
 hipError_t launch_full_loss(int kind, const float* X, const void* y, int64_t N, int d, int C, const float* w, double* partial,
-                            int blocks, hipStream_t s) {
+                            int blocks, hipStream_t s, const Done& done) {
     FullLossArgs a{};
+    a.done = done;
     a.X = X; a.y = y; a.w = w; a.N = N; a.d = d; a.C = C; a.kind = kind; a.stride = full_loss_stride(d); a.partial = partial;
     const size_t lds = sizeof(float) * (size_t)C * a.stride + 2 * FL_WAVES * 64 * sizeof(f32x4);
     const bool whole = ((d + 15) / 16 + FL_WAVES - 1) / FL_WAVES <= FL_DEPTH;

@@ -1155,6 +1155,32 @@ def test_clusters_of_four_contexts_at_once(ssgd, torch_cuda, d, variant):
     alone.close()
 
 
+def test_many_short_calls_read_what_the_call_before_left(ssgd, torch_cuda):
+    """Results that the host sees by watching a word, over more calls than go between two waits for the stream, and one that
+    takes longer than the word is watched for: every call returns what its own kernels wrote."""
+    torch = torch_cuda
+    X, y, _ = synth.lsq_data(600, 24, 3)
+    Xd, yd = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
+    mk = lambda: ssgd.Context("lsq", Xd, yd, 4, 2, 8, "k_sync", ssgd.delay_dist("exp", 1.0), 0.01, seed=5, replicas=2)
+    a, b = mk(), mk()
+    seen = []
+    for j in range(90):
+        a.step()
+        seen.append((a.params(0), a.full_loss(1), a.full_gradient(0), a.trace(1, j)))
+    for j in range(90):                          # the same again with a wait for the device after every step
+        b.step()
+        torch.cuda.synchronize()
+        w, loss, grad, tr = seen[j]
+        assert np.array_equal(w, b.params(0)) and loss == b.full_loss(1) and np.array_equal(grad, b.full_gradient(0)), j
+        for k, v in b.trace(1, j).items():
+            assert np.array_equal(tr[k], v), (j, k)
+    a.run(4000)
+    b.run(4000)
+    assert a.updates == 4090 and np.array_equal(a.params(1), b.params(1))
+    a.close()
+    b.close()
+
+
 def test_teams_of_four_contexts_at_once(ssgd, torch_cuda):
     """Four contexts from four threads, two with teams on one XCD and two with teams spread over all: none is kept waiting for
     CUs until it gives up, and what one computes does not depend on the others."""
