@@ -174,11 +174,11 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
     // A tile holds whole records of mp rows; when an iteration spans several tiles, a tile is one block of 64 rows
     // of the iteration's mini-batches, all of them part of the update.
     constexpr bool chunked = CHUNKED;
-    // One slice, early gathers: the loader waves draw the ids of the tile after next while the gradient is contracted, and ask
-    // for the labels with the rows; wave 0, which takes the bias sums meanwhile, gets the ids from wave 1.  (With all of it in
-    // front of barrier D they took 2700 cycles there, the compute waves 1600: softmax, d = 60, 25 rows, 40 replicas
-    // 4.27 -> 4.07 us per update.)
-    constexpr bool SPLIT = ONE && !LATE;
+    // One slice: the loader waves draw the ids of the tile after next while the gradient is contracted, and ask for the labels
+    // with the rows; wave 0, which takes the bias sums meanwhile, gets the ids from wave 1.  (With all of it in front of barrier
+    // D they took 2700 cycles there, the compute waves 1600: softmax, d = 60, 25 rows, 40 replicas 4.27 -> 4.07 us per update; a team,
+    // least squares, d = 167, K-sync of 3 x 39 3.05 -> 2.64, softmax, d = 199, K-async of 2 x 62 6.0 -> 5.5.)
+    constexpr bool SPLIT = ONE;
     // Records described one by one (BATCH: K-batch-async, and K-async when a version may have more records than a tile
     // holds), mini-batches of more than 64 rows: a tile is one block of 64 rows of one record; the record's gradient is
     // summed over its tiles in the slot of its worker
@@ -582,7 +582,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
             issue_lists(a.v0 + min(at + 1, a.nsteps - 1));
             if constexpr (!SPLIT) describe_tile(a.v0 + at, at_tile, true);       // past the last tile: that tile again, never gathered
             if constexpr (LATE) {
-                asm volatile("" : "+v"(row_id) : : "memory");
+                if constexpr (!SPLIT) asm volatile("" : "+v"(row_id) : : "memory");
                 gather();
             }
         };
