@@ -766,13 +766,12 @@ ssgd_status ssgd_create(const ssgd_model* model, int32_t P, int32_t K, int32_t m
         { hipDeviceProp_t prop; HIP_C(hipGetDeviceProperties(&prop, c->device)); c->cu_count = prop.multiProcessorCount; }
         if ((c->nbw == 4 || c->G == 1) && C <= 15 && linear_tile_lds_bytes(C, c->S, Kcap, false) <= 160 * 1024)
             c->tile_resident_groups = linear_tile_resident_groups(linear_tile_lds_bytes(C, c->S, Kcap, false));
-        if (c->nbw == 4 && C <= 15 && variant == SSGD_K_ASYNC && c->S <= 8 && linear_defer_lds_bytes(C, c->S) <= 160 * 1024)
-            c->defer_per_launch = linear_defer_replicas_per_launch(c->G, c->cu_count);
-        // One slice has no exchange to hide, so the tile kernel, which needs no helper workgroup, is the better one where that
-        // would cost a second launch (136 replicas, d = 256: 5.6 against 8.5 us per update) and where many updates consume
-        // mini-batches of their own version (P = 4, K = 2: 4.8 against 5.4, P = 8, K = 4: 5.7 against 6.3; P = 5, K = 2: 4.85
-        // against 4.77, P = 8, K = 3: 4.95 against 4.78, P = 8, K = 2: 4.9 against 3.9).
-        if (c->G == 1 && (R > c->defer_per_launch || 5 * Kcap > 2 * P)) c->defer_per_launch = 0;
+        if (c->nbw == 4 && C <= 15 && variant == SSGD_K_ASYNC && c->S <= 8 && model->kind == SSGD_SOFTMAX && d % 4 == 0 && c->mp % 16 == 0 &&
+            Kcap * c->mp <= 64 && linear_defer_lds_bytes(C, c->S) <= 160 * 1024) {
+            const int launch = linear_defer_replicas_per_launch(c->G, c->cu_count), tiles = 8 * ((c->tile_resident_groups / 8) / c->G);
+            // (K may change: as if it were the smallest there is)
+            if (defer_pays(P, ada.mode != 0 ? K : Kcap, c->G, R, launch, tiles, c->cu_count)) c->defer_per_launch = launch;
+        }
         // Updates of more than one tile are shared out where CUs are to spare.  (Not under AdaSync, whose updates may have one
         // tile for most of a run.)
         if (c->tile_resident_groups >= c->G && c->cu_count > 0 && ada.mode == 0) {

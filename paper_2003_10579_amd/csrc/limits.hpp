@@ -52,4 +52,22 @@ inline TeamShape team_shape(int64_t tiles, int G, int C, int64_t replicas, int c
     return {(int)best, best > 1 && best > local ? 1 : 0};
 }
 
+// Which of the two steady-state kernels of K-async is the faster one, for softmax, P <= 8 and updates of one tile: the one that
+// keeps gradients in flight in LDS takes a CU per slice and one per replica, the tile kernel a CU or half of one per slice.  Times
+// of a launch's update, in hundredths of the tile kernel's with a CU per workgroup (5.3 to 5.8 us): the other kernel's chain is
+// shorter while updates rarely consume mini-batches of their own version (K = 2 of 8 workers, 16 replicas of d = 3072: 4.1 us; of 6: 5.9;
+// K = 1 of 2: 5.5; K = 3 of 8: 6.3); with two workgroups per CU an update of the tile kernel takes 9.4 to 11.3 us.  Where replicas
+// take several launches, these add up (40 replicas of d = 3072, K = 3 of 8: 18.3 us against 10.9; K = 2 of 8, 48 replicas: 12.4
+// against 17).  Models of one slice have no exchange to hide: K = 1 only (of 8 workers 3.4 us against 3.8; K = 2 4.45 against 4.16).
+inline bool defer_pays(int P, int K, int G, int64_t R, int defer_per_launch, int tile_per_launch, int cus) {
+    if (defer_per_launch < 1) return false;
+    if (tile_per_launch < 1) return true;
+    if (G == 1) return K == 1 && R <= defer_per_launch;
+    const int64_t one = 4 * K <= P ? 72 : (K == 1 ? 90 : 102);
+    const int64_t rest = R % tile_per_launch;
+    auto launch = [&](int64_t replicas) { return (replicas + kXcds - 1) / kXcds * kXcds * G > cus ? 170 : 100; };
+    const int64_t tile = R / tile_per_launch * launch(tile_per_launch) + (rest > 0 ? launch(rest) : 0);
+    return (R + defer_per_launch - 1) / defer_per_launch * one < tile;
+}
+
 }  // namespace ssgd

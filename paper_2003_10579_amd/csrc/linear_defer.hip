@@ -1,4 +1,4 @@
-// Steady-state kernel of K-async SGD on the linear models (Sec. 2.2, Eq. (3)) for the shapes of the headline
+// Steady-state kernel of K-async SGD on softmax regression (Sec. 2.2, Eq. (3)) for the shapes of the headline
 // configuration: at most 8 workers, mini-batches padded to a multiple of 16 rows, every version's mini-batches in one
 // 64-row tile.  Same state in HBM between launches and the same arithmetic as linear_tile.hip; what differs is who does
 // what, when, and where the gradients in flight live.
@@ -17,7 +17,7 @@
 //     when the launch starts, written back when it ends, never in between.
 //   * One helper workgroup on a CU of its own, whose memory pipeline carries no row gathers (a load that queues
 //     behind 64 KB of gathers waits for them).  It polls the partial logits of the G slices, adds them in slice
-//     order, takes residual / softmax and stores delta (64 x 16 words) for the slices to fetch; it owns the bias,
+//     order, takes the softmax and stores delta (64 x 16 words) for the slices to fetch; it owns the bias,
 //     the bias gradients in flight and the loss record.
 //
 // Slice workgroup, version v (four compute waves, four loader waves, no workgroup barrier between them: LDS counters):
@@ -60,9 +60,6 @@ __device__ __forceinline__ float quad_xor1(float x) {
 }
 __device__ __forceinline__ float quad_xor2(float x) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
-}
-__device__ __forceinline__ float quad_lane0(float x) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x00, 0xF, 0xF, false));   // quad_perm [0,0,0,0]
 }
 
 // a wave gives up its wait: the launch is aborted (every workgroup of every cluster sees the flag in its own waits)
@@ -155,7 +152,7 @@ __device__ __forceinline__ void bump(int* ctl, int which) {
 //   meta    = s + 1 by the clerk once bias and labels of version s are in LDS
 // LDS: colsum[2][4][16], biasbuf[2][16], labbuf[2][64], small[S][17], counters.
 // ============================================================================================================
-template <int KIND, bool PROF>
+template <bool PROF>
 __device__ __forceinline__ void helper_role(const LinArgs& a, int rep, unsigned char* smem) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -167,7 +164,7 @@ __device__ __forceinline__ void helper_role(const LinArgs& a, int rep, unsigned 
     int* cnt = reinterpret_cast<int*>(labbuf + 128);         // [4]: 0 stop, 1 sums, 2 meta
     float* small = reinterpret_cast<float*>(cnt + 4);        // [S][17]
     constexpr int kSums = 1, kMeta = 2;
-    const int64_t nw = (KIND == kLsq) ? d : (int64_t)C * d + C;
+    const int64_t nw = (int64_t)C * d + C;
     float* params = a.params + (int64_t)rep * nw;
     float* small_g = a.park_small + (int64_t)rep * G * S * 17;      // slice 0's copy is read; every slice's is written back
     for (int q = tid; q < S * 17; q += 5 * 64) small[q] = small_g[q];
@@ -201,7 +198,7 @@ __device__ __forceinline__ void helper_role(const LinArgs& a, int rep, unsigned 
             const uint32_t row_id = batch_index(a.seed, (uint32_t)rep, (uint32_t)worker, 0u, (uint32_t)ver, (uint32_t)smp_of, a.N);
             return reinterpret_cast<const uint32_t*>(a.y)[row_id];
         };
-        float bias_c = (KIND == kSoftmax && lane < C) ? params[(int64_t)C * d + lane] : 0.0f;     // lane c: bias of class c
+        float bias_c = (lane < C) ? params[(int64_t)C * d + lane] : 0.0f;     // lane c: bias of class c
         lists.start(a.v0);
         lists.take(cur, a.v0, a.nsteps > 1);
         labbuf[lane] = row_label(cur, a.v0);
@@ -241,10 +238,10 @@ __device__ __forceinline__ void helper_role(const LinArgs& a, int rep, unsigned 
                     else if (lane < 16) small[(word & 0xFFFF) * 17 + sidx] = prt;
                 }
                 const float invK = 1.0f / (float)cur.K;
-                if (KIND == kSoftmax && lane < C) bias_c -= (a.lr * invK) * tot;
+                if (lane < C) bias_c -= (a.lr * invK) * tot;
                 if (lane == 15) a.tr.loss[(int64_t)rep * cap + v] = tot * invK;
                 // the averaged gradient of replica 0, when the caller asked for it: bias part
-                if (KIND == kSoftmax && a.agg_out != nullptr && rep == 0 && lane < C) a.agg_out[(int64_t)C * d + lane] = tot * invK;
+                if (a.agg_out != nullptr && rep == 0 && lane < C) a.agg_out[(int64_t)C * d + lane] = tot * invK;
             }
             hmark(3);
             if (step + 1 < a.nsteps) {
@@ -259,7 +256,7 @@ __device__ __forceinline__ void helper_role(const LinArgs& a, int rep, unsigned 
         }
         hprof_out();
         // ---- leave the state in HBM for the next launch (every slice's copy of the bias gradients in flight)
-        if (KIND == kSoftmax && lane < C) params[(int64_t)C * d + lane] = bias_c;
+        if (lane < C) params[(int64_t)C * d + lane] = bias_c;
         for (int g = 0; g < G; ++g)
             for (int q = lane; q < S * 17; q += 64) small_g[(int64_t)g * S * 17 + q] = small[q];
         return;
@@ -343,12 +340,7 @@ __device__ __forceinline__ void helper_role(const LinArgs& a, int rep, unsigned 
         f32x4 dl = {0.f, 0.f, 0.f, 0.f};
         float loss = 0.0f;
         float s_den = 1.0f, s_lt = 0.0f;
-        if constexpr (KIND == kLsq) {
-            const float z0 = quad_lane0(zz.x);
-            const float r = z0 - __uint_as_float(lab_bits);
-            if (ok) loss = 0.5f * r * r;
-            if (z_qd == 0 && ok) dl.x = r * inv_m;
-        } else {
+        {
             const int lab = (int)lab_bits;
             float zmax = -3.0e38f;
 #pragma unroll
@@ -398,7 +390,7 @@ __device__ __forceinline__ void helper_role(const LinArgs& a, int rep, unsigned 
             if (step + 1 < a.nsteps) ask((int)((step + 1) % 3), 0);
         }
         // ---- row loss and column sums for the clerk
-        if constexpr (KIND == kSoftmax) {
+        {
             float lt_ = s_lt;
             lt_ += quad_xor1(lt_);
             lt_ += quad_xor2(lt_);
@@ -454,7 +446,7 @@ __device__ __forceinline__ Lds carve(unsigned char* smem, int C, int S) {
     return l;
 }
 
-template <int KIND, bool PROF, int MPK>
+template <bool PROF, int MPK>
 __device__ __forceinline__ void slice_role(const LinArgs& a, int rep, int slice, unsigned char* smem) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -565,7 +557,7 @@ __device__ __forceinline__ void slice_role(const LinArgs& a, int rep, int slice,
     }
 
     // ================================= compute waves =================================
-    const int64_t nw = (KIND == kLsq) ? d : (int64_t)C * d + C;
+    const int64_t nw = (int64_t)C * d + C;
     float* params = a.params + (int64_t)rep * nw;
     float* park_g = a.park + ((int64_t)rep * G + slice) * S * 16 * NTC;
     const int nquad = (C + 3) / 4;
@@ -889,7 +881,7 @@ __device__ __forceinline__ void slice_role(const LinArgs& a, int rep, int slice,
     }
 }
 
-template <int KIND, bool PROF, int MPK>
+template <bool PROF, int MPK>
 __global__ __launch_bounds__(512, 2) void linear_defer_kernel(LinArgs a) {
     // consecutive block ids go to different XCDs: all workgroups of one cluster take block ids that are congruent
     // modulo 8 and share one L2
@@ -938,28 +930,28 @@ __global__ __launch_bounds__(512, 2) void linear_defer_kernel(LinArgs a) {
         return;
     }
 
-    if (helper) helper_role<KIND, PROF>(a, rep, smem);
-    else slice_role<KIND, PROF, MPK>(a, rep, role, smem);
+    if (helper) helper_role<PROF>(a, rep, smem);
+    else slice_role<PROF, MPK>(a, rep, role, smem);
 }
 
-template <int KIND, bool PROF, int MPK>
+template <bool PROF, int MPK>
 hipError_t launch_m(const LinArgs& a, size_t lds, hipStream_t s) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(linear_defer_kernel<KIND, PROF, MPK>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(linear_defer_kernel<PROF, MPK>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     const int groups = (a.replicas + 7) / 8;
-    hipLaunchKernelGGL((linear_defer_kernel<KIND, PROF, MPK>), dim3(groups * 8 * (a.G + 1)), dim3(512), lds, s, a);
+    hipLaunchKernelGGL((linear_defer_kernel<PROF, MPK>), dim3(groups * 8 * (a.G + 1)), dim3(512), lds, s, a);
     return hipGetLastError();
 }
 
 // the padded mini-batch size is a compile-time constant for 16, 32 and 64 rows (48 runs through the general code)
-template <int KIND, bool PROF>
+template <bool PROF>
 hipError_t launch_d(const LinArgs& a, size_t lds, hipStream_t s) {
     switch (a.mp) {
-    case 16: return launch_m<KIND, PROF, 16>(a, lds, s);
-    case 32: return launch_m<KIND, PROF, 32>(a, lds, s);
-    case 64: return launch_m<KIND, PROF, 64>(a, lds, s);
-    default: return launch_m<KIND, PROF, 0>(a, lds, s);
+    case 16: return launch_m<PROF, 16>(a, lds, s);
+    case 32: return launch_m<PROF, 32>(a, lds, s);
+    case 64: return launch_m<PROF, 64>(a, lds, s);
+    default: return launch_m<PROF, 0>(a, lds, s);
     }
 }
 
@@ -972,7 +964,7 @@ size_t linear_defer_lds_bytes(int C, int S) {
 }
 
 bool linear_defer_supports(const LinArgs& a) {
-    if (a.variant != kAsync || a.v0 < 1 || a.chunked || !a.allow_fast) return false;     // step 0 of K-async starts all P workers
+    if (a.kind != kSoftmax || a.variant != kAsync || a.v0 < 1 || a.chunked || !a.allow_fast) return false;     // step 0 of K-async starts all P workers
     if (a.C > 15 || (a.d % 4) != 0 || (a.mp % 16) != 0 || a.mp > ROWS) return false;
     if (a.S > SMAX || a.P > SMAX || a.tr.Kcap > SMAX || a.tr.Kcap * a.mp > ROWS) return false;
     if (!one_descriptor_spans(a.N, (uint64_t)a.d)) return false;
@@ -991,8 +983,7 @@ int linear_defer_replicas_per_launch(int G, int cus) {
 hipError_t launch_linear_defer(const LinArgs& a, hipStream_t s) {
     const size_t lds = linear_defer_lds_bytes(a.C, a.S);
     const bool prof = a.prof != nullptr;
-    if (a.kind == kLsq) return prof ? launch_d<kLsq, true>(a, lds, s) : launch_d<kLsq, false>(a, lds, s);
-    return prof ? launch_d<kSoftmax, true>(a, lds, s) : launch_d<kSoftmax, false>(a, lds, s);
+    return prof ? launch_d<true>(a, lds, s) : launch_d<false>(a, lds, s);
 }
 
 }  // namespace ssgd

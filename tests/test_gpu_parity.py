@@ -905,6 +905,27 @@ def test_several_tiles_and_odd_row_lengths(ssgd, oracle, torch_cuda, monkeypatch
               classes=classes, check_steps=30)
 
 
+@pytest.mark.parametrize("P,K,m,d,R", [
+    (8, 2, 16, 516, 3), (8, 2, 32, 300, 90), (3, 1, 32, 516, 2), (8, 1, 64, 200, 3),      # gradients in flight in LDS
+    (8, 3, 16, 516, 3), (6, 2, 16, 300, 170), (2, 2, 32, 516, 2), (8, 2, 16, 200, 3),     # the tile kernel
+])
+def test_k_async_of_one_tile_on_either_kernel(ssgd, oracle, torch_cuda, P, K, m, d, R):
+    """Both sides of the rule that picks the kernel of K-async updates of one tile: parity of the first and the last replica."""
+    torch = torch_cuda
+    X, y = synth.mixture_data(500, d, 4, seed=8)
+    gd, od = dist_pair(ssgd, oracle, ("shifted_exp", 0.5, 1.0))
+    ctx = ssgd.Context("softmax", torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda(), P, K, m, "k_async", gd, 0.01, seed=9, classes=4, replicas=R)
+    for J in (1, 40, 30):
+        ctx.run(J)
+    for r in (0, R - 1):
+        tr = oracle.Trainer(oracle.Model("softmax", X, y, classes=4), P, K, m, "k_async", od, 0.01, seed=9, replica=r)
+        tr.run(71)
+        assert_trace_equal(ctx.trace(r), tr.trace())
+        assert np.allclose(ctx.trace(r)["loss"], tr.trace()["loss"], rtol=FP32_LOSS_RTOL, atol=1e-6)
+        assert rel(ctx.params(r), tr.params()) <= FP32_PARAM_TOL, r
+    ctx.close()
+
+
 @pytest.mark.parametrize("kind,variant,P,K,m,d,classes,R", [
     ("softmax", "k_async", 20, 5, 25, 785, 10, 8),     # three members of four slices; two records each, the last has one
     ("softmax", "k_async", 9, 6, 32, 300, 15, 3),      # whole records, two slices
