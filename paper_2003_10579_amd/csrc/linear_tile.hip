@@ -175,7 +175,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
     // of the iteration's mini-batches, all of them part of the update.
     constexpr bool chunked = CHUNKED;
     // One slice: the loader waves draw the ids of the tile after next while the gradient is contracted, and ask for the labels
-    // with the rows; wave 0, which takes the bias sums meanwhile, gets the ids from wave 1.  (With all of it in front of barrier
+    // with the rows; wave 3, which takes the bias sums meanwhile, and wave 0, which has the lists, get the ids from wave 1.  (With all of it in front of barrier
     // D they took 2700 cycles there, the compute waves 1600: softmax, d = 60, 25 rows, 40 replicas 4.27 -> 4.07 us per update; a team,
     // least squares, d = 167, K-sync of 3 x 39 3.05 -> 2.64, softmax, d = 199, K-async of 2 x 62 6.0 -> 5.5.)
     constexpr bool SPLIT = ONE;
@@ -367,9 +367,9 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
             if constexpr (BATCH) asm volatile("" : "+v"(h_rw), "+v"(h_ro), "+v"(h_rf), "+v"(h_csel), "+v"(h_ctau), "+v"(h_cord) : : "memory");
         };
         // Tile `t` of version `ver`: sample ids, lists; leaves the labels in flight.
-        // (SPLIT, in the loop: lists by wave 0, which publishes them and has the bias sums to take, ids by the others)
+        // (SPLIT, in the loop: lists by wave 0, which publishes them, ids by waves 1 and 2)
         auto describe_tile = [&](int64_t ver, int t_mine, bool all) {
-            const bool lists = !SPLIT || all || lw == 0, draws = !SPLIT || all || lw != 0;
+            const bool lists = !SPLIT || all || lw == 0, draws = !SPLIT || all || lw == 1 || lw == 2;
             n_ver = ver;
             n_flags = (t_mine + 1 == h_tiles ? 1 : 0) | (t_mine == 0 ? 2 : 0);      // bit 0 last tile of its update, bit 1 first
             int t = t_mine;
@@ -480,11 +480,18 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                 }
             }
             if (!ONE || lane < 16 * nblk) {
+                // (rows past the records have no sample: whatever is there, their logits are not used)
+                const int used = p_nrec * p_rows;
 #pragma unroll
-                for (int i = 0; i < LLOADS; ++i) *reinterpret_cast<f32x4*>(my_tile + 4 * i * SL) = pref[i];
+                for (int i0 = 0; i0 < LLOADS; i0 += 4) {
+                    if (4 * i0 >= used) break;
+#pragma unroll
+                    for (int i = i0; i < i0 + 4; ++i) *reinterpret_cast<f32x4*>(my_tile + 4 * i * SL) = pref[i];
+                }
             }
+            if (lw == (SPLIT ? 3 : 0)) L.ylab[lane] = p_row_lab;
             if (lw == 0) {
-                L.rowid[lane] = p_row_id; L.ylab[lane] = p_row_lab;
+                L.rowid[lane] = p_row_id;
                 if (lane == 0) { L.ctl[4] = p_K; L.ctl[5] = p_nrec; L.ctl[6] = p_nstale; L.ctl[7] = p_flags | (p_rows << 8); }
                 if (!chunked && p_stale_pos < kc) L.s_stale[p_stale_pos] = p_stale;
                 if (lane < kc) L.s_rec[lane] = chunked ? 1 << 16 : p_rec_word;       // (only the first entry is read)
@@ -591,16 +598,20 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
             lmark(1);
             lds_barrier();                           // D
             if (L.ctl[0] != 0) return false;
-            if (!TEAM && lw == 0) bias_and_loss(v, flags);
+            if (!TEAM && lw == (SPLIT ? 3 : 0)) bias_and_loss(v, flags);
             if constexpr (SPLIT) {
                 if (turned) {
                     describe_tile(a.v0 + at, at_tile, false);
-                    if (lw == 1) L.rowid[lane] = row_id;      // for wave 0; the compute waves are done with it
+                    // for waves 0 and 3, from whom the next words of these places come; the compute waves are done with them
+                    if (lw == 1) { L.rowid[lane] = row_id; L.ylab[lane] = __uint_as_float(row_id); }
                 }
             }
             lmark(2);
             lds_barrier();                           // B
-            if constexpr (SPLIT) { if (turned && lw == 0) row_id = L.rowid[lane]; }
+            if constexpr (SPLIT) {
+                if (turned && lw == 0) row_id = L.rowid[lane];
+                if (turned && lw == 3) row_id = __float_as_uint(L.ylab[lane]);
+            }
             lmark(3);
             return true;
         };
@@ -1518,8 +1529,8 @@ hipError_t launch_w(const LinArgs& a, size_t lds, hipStream_t s) {
             return a.whole_cus ? launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, false, true, true, true>(a, lds, s)
                                : launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, false, false, true, true>(a, lds, s);
         }
-    if (a.G == 1) return a.shared_cus ? launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, true, false, false>(a, lds, s)
-                                      : launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, true, true, false>(a, lds, s);
+    if (a.G == 1) return a.shared_cus ? launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, true, false, !CHUNKED>(a, lds, s)
+                                      : launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, true, true, !CHUNKED>(a, lds, s);
     if (a.whole_cus) return launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, false, true, true>(a, lds, s);
     if constexpr (CHUNKED)
         if (a.shared_cus) return launch_r<KIND, PROF, WHOLE, CHUNKED, BATCH, false, false, false>(a, lds, s);
