@@ -763,7 +763,7 @@ ssgd_status ssgd_create(const ssgd_model* model, int32_t P, int32_t K, int32_t m
         if (c->lds_bytes > 160 * 1024) return bail(SSGD_EINVAL, "too many gradient slots for the LDS of one workgroup");
         c->resident_groups = linear_max_resident_groups(c->nbw, c->lds_bytes);
         if (c->resident_groups < c->G) return bail(SSGD_EINVAL, "d is too large for a co-resident cluster of workgroups");
-        { hipDeviceProp_t prop; HIP_C(hipGetDeviceProperties(&prop, c->device)); c->cu_count = prop.multiProcessorCount; }
+        HIP_C(hipDeviceGetAttribute(&c->cu_count, hipDeviceAttributeMultiprocessorCount, c->device));
         if ((c->nbw == 4 || c->G == 1) && C <= 15 && linear_tile_lds_bytes(C, c->S, Kcap, false) <= 160 * 1024)
             c->tile_resident_groups = linear_tile_resident_groups(linear_tile_lds_bytes(C, c->S, Kcap, false));
         if (c->nbw == 4 && C <= 15 && variant == SSGD_K_ASYNC && c->S <= 8 && model->kind == SSGD_SOFTMAX && d % 4 == 0 && c->mp % 16 == 0 &&
@@ -776,7 +776,7 @@ ssgd_status ssgd_create(const ssgd_model* model, int32_t P, int32_t K, int32_t m
         // tile for most of a run.)
         if (c->tile_resident_groups >= c->G && c->cu_count > 0 && ada.mode == 0) {
             const int64_t tiles = async ? (c->mp > 64 ? Kcap : (Kcap + 64 / c->mp - 1) / (64 / c->mp)) : ((int64_t)Kcap * c->mp + 63) / 64;
-            const int per_cu = linear_tile_resident_groups(linear_tile_lds_bytes(C, c->S, Kcap, true)) / c->cu_count;
+            const int per_cu = tiles < 2 ? 0 : linear_tile_resident_groups(linear_tile_lds_bytes(C, c->S, Kcap, true)) / c->cu_count;
             const TeamShape shape = team_shape(tiles, c->G, C, R, c->cu_count, per_cu);
             c->team = shape.members; c->spread = shape.spread;
         }

@@ -867,10 +867,10 @@ size_t linear_lds_bytes(int nbw, int C, int S, bool parks) {
 
 int linear_max_resident_groups(int nbw, size_t lds_bytes) {
     int dev = 0;
-    hipDeviceProp_t prop;
-    if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
+    int cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
     const int per_cu = nbw == 1 ? resident_t<1>(lds_bytes) : (nbw == 2 ? resident_t<2>(lds_bytes) : resident_t<4>(lds_bytes));
-    return per_cu * prop.multiProcessorCount;
+    return per_cu * cus;
 }
 
 hipError_t launch_linear(const LinArgs& a, int nbw, hipStream_t s) {

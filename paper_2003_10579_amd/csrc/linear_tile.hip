@@ -139,8 +139,8 @@ __device__ __forceinline__ void lds_barrier() {
 // after it, some 3000 cycles later.  The gathers keep the memory path of the CU busy for 4000 cycles, and what the compute
 // waves have to wait for meanwhile (parked gradients, partial logits and the stores in front of them) queues behind them, so
 // they go late wherever there is an exchange: softmax, d = 3072, two mini-batches of 32, 8 replicas: K-sync 5.46 -> 4.85 us per
-// update, K-batch-async 6.90 -> 6.05; early where nothing is waited for (one slice), and for synchronous iterations with two
-// workgroups per CU (K-batch-sync of 16 x 128, 40 replicas: 285 early, 281 to 292 late).
+// update, K-batch-async 6.90 -> 6.05; early where nothing is waited for (synchronous iterations of one slice), and for
+// synchronous iterations with two workgroups per CU (K-batch-sync of 16 x 128, 40 replicas: 285 early, 281 to 292 late).
 template <int KIND, bool PROF, bool WHOLE, bool CHUNKED, bool BATCH, bool ONE, bool ROOMY, bool LATE, bool TEAM>
 __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs a) {
     // consecutive block ids go to different XCDs: all slices of one cluster take block ids that
@@ -1573,13 +1573,12 @@ bool linear_tile_supports(const LinArgs& a, int max_records) {
 }
 
 int linear_tile_resident_groups(size_t lds_bytes) {
-    int dev = 0, per_cu = 0;
-    hipDeviceProp_t prop;
-    if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
+    int dev = 0, per_cu = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(linear_tile_kernel<kSoftmax, false, false, false, false, false, false, true, false>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes) != hipSuccess) return 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, linear_tile_kernel<kSoftmax, false, false, false, false, false, false, true, false>, 512, lds_bytes) != hipSuccess) return 0;
-    return per_cu * prop.multiProcessorCount;
+    return per_cu * cus;
 }
 
 hipError_t launch_linear_tile(const LinArgs& a, hipStream_t s) {

@@ -887,11 +887,19 @@ __global__ __launch_bounds__(256) void mlp_mid_kernel(MlpArgs a) {
         if (lane == 0) red[wave] = ls;
     }
     __syncthreads();
-    // ---- delta1 and the quarter's sums: thread -> hidden units tid and tid + 256
+    // ---- delta1 and the quarter's sums: thread -> hidden units tid and tid + 256, and the same of every further 512
     const float inv_m = 1.0f / (float)m;
+#pragma unroll 1
+    for (int j0 = 0; j0 < H; j0 += 512) {
+    if (j0 > 0) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int c = 0; c < 16; ++c) w2c[u][c] = (c < C && j0 + tid + 256 * u < H) ? a.w2r[c * H + j0 + tid + 256 * u] : 0.0f;
+    }
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-        const int j = tid + 256 * u;
+        const int j = j0 + tid + 256 * u;
         if (j < H) {
             float gw[16];
 #pragma unroll
@@ -920,6 +928,7 @@ __global__ __launch_bounds__(256) void mlp_mid_kernel(MlpArgs a) {
             for (int c = 0; c < 16; ++c)
                 if (c < C) a.gw2[((int64_t)(slot * 4 + q) * C + c) * H + j] = gw[c];
         }
+    }
     }
     if (tid < 16) {
         float sum = 0.0f;

@@ -576,6 +576,25 @@ def test_mlp_gradients_teacher_forced(ssgd, oracle, torch_cuda, variant, P, K, m
     ctx.close()
 
 
+@pytest.mark.parametrize("P,K,m,d,hidden", [
+    (4, 2, 20, 128, 640),     # few records: the second round of 512 hidden units is a quarter full
+    (4, 2, 64, 128, 1024),    # two whole rounds
+    (40, 36, 9, 128, 640),    # more records
+    (40, 36, 9, 128, 1152),
+])
+def test_mlp_more_than_512_hidden_units(ssgd, oracle, torch_cuda, P, K, m, d, hidden):
+    """Teacher-forced gradients of wide hidden layers."""
+    torch = torch_cuda
+    X, y = synth.mixture_data(1500, d, 6, seed=4)
+    ctx, tr = _mlp_pair(ssgd, oracle, torch, X, y, P, K, m, "k_sync", ("exp", 1.0), 0.05, 6, hidden, seed=5)
+    agg = torch.zeros(ctx.nw, dtype=torch.float32, device="cuda")
+    for j in range(4):
+        ctx.set_params(tr.params())
+        ctx.step(agg)
+        assert rel(agg.cpu().numpy(), tr.step()) <= MLP_GRAD_TOL, j
+    ctx.close()
+
+
 def test_mlp_kasync_training_run(ssgd, oracle, torch_cuda):
     """Scaled copy of config 4 (d=512, hidden 128, 10 classes, P=32, m=64, K=4): 150 updates free-running."""
     X, y = synth.mixture_data(4000, 512, 10, seed=6)
