@@ -1265,12 +1265,29 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                     if (k + 4 <= end) { add(std::integral_constant<int, 4>{}, k); k += 4; }
 #pragma unroll 1
                     for (; k < end; ++k) add(std::integral_constant<int, 1>{}, k);
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        sum[c] += across<16>(sum[c], lane);
-                        sum[c] += across<32>(sum[c], lane);
-                        acc[c][0] = sum[c];
-                    }
+                    // (two columns at a time: after the swaps of halves and of rows each row of lanes has one column's sum; the
+                    // owners are the first row's lanes)
+                    auto halves = [](float& x, float& y) {
+                        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+                        x = __uint_as_float(r[0]); y = __uint_as_float(r[1]);
+                    };
+                    auto rows16 = [](float& x, float& y) {
+                        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+                        x = __uint_as_float(r[0]); y = __uint_as_float(r[1]);
+                    };
+                    float s0 = sum.x, s1 = sum.y, s2 = sum.z, s3 = sum.w;
+                    halves(s0, s1);
+                    halves(s2, s3);
+                    float lo = s0 + s1, hi = s2 + s3;                  // columns 0 | 1 and 2 | 3 in the two halves
+                    rows16(lo, hi);
+                    float t0 = lo + hi;                                // rows of lanes: columns 0, 2, 1, 3
+                    float t1 = t0;
+                    rows16(t0, t1);                                    // t1: columns 2 and 3 in the first row and the third
+                    acc[0][0] = t0;
+                    float u0 = t0, u1 = t1, v0 = t0, v1 = t1;
+                    halves(u0, v0);                                    // v0: the third row's column 1
+                    halves(u1, v1);                                    // v1: its column 3
+                    acc[1][0] = v0; acc[2][0] = t1; acc[3][0] = v1;
                     finish(rec_word);
                 }
             } else if constexpr (WHOLE) {

@@ -779,6 +779,7 @@ __global__ __launch_bounds__(256, 2) void mlp_fwd_gather_kernel(MlpArgs a) {
 // takes a quarter of the hidden units, the four partial results are added in order), softmax, delta2, loss,
 // delta1 = (W2^T delta2) * [h > 0] (bf16, transposed, for the gradient contraction) and the quarter's second-layer
 // gradients.
+template <bool WIDE>      // more than 512 hidden units
 __global__ __launch_bounds__(256) void mlp_mid_kernel(MlpArgs a) {
     extern __shared__ __attribute__((aligned(16))) float mid_lds[];
     const int H = a.H, C = a.C, m = a.m;
@@ -890,7 +891,7 @@ __global__ __launch_bounds__(256) void mlp_mid_kernel(MlpArgs a) {
     // ---- delta1 and the quarter's sums: thread -> hidden units tid and tid + 256, and the same of every further 512
     const float inv_m = 1.0f / (float)m;
 #pragma unroll 1
-    for (int j0 = 0; j0 < H; j0 += 512) {
+    for (int j0 = 0; j0 < (WIDE ? H : 1); j0 += 512) {
     if (j0 > 0) {
 #pragma unroll
         for (int u = 0; u < 2; ++u)
@@ -1337,7 +1338,7 @@ hipError_t mlp_create(MlpState** out, const ssgd_model& model, int P, int m, int
     TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_grad_kernel<64, false, true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)grad_lds(64, 32)));
     TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_grad_kernel<128, true, true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)grad_lds(128, kShareSlots)));
     TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_grad_kernel<128, true, false>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)grad_lds(128, kShareSlots)));
-    TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_mid_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)mid_lds_bytes(1024)));
+    TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_mid_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)mid_lds_bytes(1024)));
     TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_fwd_gather_kernel<128, false>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)contract_lds(128)));
     TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_fwd_gather_kernel<64, true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)contract_lds(64)));
     TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_fwd_gather_kernel<64, false>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)contract_lds(64)));
@@ -1371,7 +1372,8 @@ void launch_forward(MlpArgs& a, hipStream_t stream, hipEvent_t done = nullptr) {
         // few records: two launches; the depth is split so that two workgroups share every CU and none walks all of d
         a.fsplit = few_records_split(a, a.nrec);
         hipLaunchKernelGGL((mlp_fwd_gather_kernel<64, true>), dim3(a.nrec, a.H / 64, a.fsplit), dim3(256), contract_lds(64), stream, a);
-        hipExtLaunchKernelGGL(mlp_mid_kernel, dim3(a.nrec * 4), dim3(256), mid_lds_bytes(a.H), stream, nullptr, done, 0, a);
+        if (a.H > 512) hipExtLaunchKernelGGL(mlp_mid_kernel<true>, dim3(a.nrec * 4), dim3(256), mid_lds_bytes(a.H), stream, nullptr, done, 0, a);
+        else hipExtLaunchKernelGGL(mlp_mid_kernel<false>, dim3(a.nrec * 4), dim3(256), mid_lds_bytes(a.H), stream, nullptr, done, 0, a);
     } else if (a.nrec > 0 && ((a.nrec + 1) / 2) * (a.H / 128) >= 192) {
         // many records: large tiles, the rows again straight from the sample matrix
         hipLaunchKernelGGL((mlp_fwd_gather_kernel<128, false>), dim3((a.nrec + 1) / 2, a.H / 128), dim3(256), contract_lds(128), stream, a);
