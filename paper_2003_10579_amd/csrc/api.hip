@@ -144,7 +144,8 @@ hipError_t host_out_room(ssgd_ctx* c, size_t bytes) {
 Done next_done(ssgd_ctx* c) { return {c->abort_flag.as<uint32_t>() + 1, c->done_word, ++c->done_number}; }
 
 // Waits for the kernel that was given next_done() last: short ones by watching the word, the others (and every 256th, so that
-// the runtime sees its queue empty now and then; and whatever has failed) by waiting for the stream.
+// what the runtime keeps of the launches does not pile up; and whatever has failed) by waiting for the stream.  (Every 32nd: 64 gradients and
+// eight steps 1.63 ms instead of 1.53.)
 hipError_t wait_done(ssgd_ctx* c) {
     if ((c->done_number & 255u) != 0) {
         const auto t0 = std::chrono::steady_clock::now();
@@ -197,13 +198,16 @@ __global__ void flags_kernel(const int32_t* abort_flag, const int32_t* fallback,
     if (threadIdx.x == 0) signal_done(done, gridDim.x);
 }
 
-// Waits for the stream with the flags in c->host_flags.
-hipError_t read_flags(ssgd_ctx* c) {
+// Waits for the flags in c->host_flags.  brief: a few launches of a linear model are waited for like any short call (a step
+// 35 us instead of 55 among gradients seen that way); a run leaves many launches, and what the runtime keeps of them is to be given
+// up by the run itself.
+hipError_t read_flags(ssgd_ctx* c, bool brief) {
     if (c->flags_seen) return hipSuccess;
     const int32_t* fallback = c->fallback.as<int32_t>();
-    hipLaunchKernelGGL(flags_kernel, dim3((unsigned)(c->R + 255) / 256), dim3(256), 0, c->stream, c->abort_flag.as<int32_t>(), fallback, c->R, c->host_flags, next_done(c));
+    hipLaunchKernelGGL(flags_kernel, dim3((unsigned)(c->R + 255) / 256), dim3(256), 0, c->stream, c->abort_flag.as<int32_t>(), fallback, c->R, c->host_flags,
+                       brief ? next_done(c) : Done{});
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = wait_done(c);
+    if (e == hipSuccess) e = brief ? wait_done(c) : hipStreamSynchronize(c->stream);
     c->flags_seen = e == hipSuccess;
     return e;
 }
@@ -387,7 +391,7 @@ ssgd_status launch_steps(ssgd_ctx* c, int64_t v0, int64_t n, float* agg_out, int
     if (mode == kDeferKernel) {
         // A cluster that found itself spread over XCDs has left its replica untouched: those replicas take the same
         // updates through the kernel that can exchange across XCDs.
-        HIP_OK(c, read_flags(c));
+        HIP_OK(c, read_flags(c, false));
         const std::vector<int32_t> fb(c->host_flags + 1, c->host_flags + 1 + c->R);
         bool any = false;
         for (int r = 0; r < c->R; ++r) any = any || fb[r] != 0;
@@ -501,8 +505,11 @@ ssgd_status run_updates(ssgd_ctx* c, int64_t J, float* agg_out) {
         // on the linear models leaves CUs free as a rule, and so does the tile kernel where no two of its workgroups share a
         // CU).  The pieces of the linear models are long, since every piece is a launch of its own (20 to 40 us)
         // that reads the gradients in flight from HBM and writes them back; the first one is short, since nothing hides
-        // its schedule, and each of the next is three times the one before, since an update's schedule takes at most a
-        // third of its gradients (0.6 of 4.0 us at P = 8; K-batch-async with 8 workers 1.4 of 4.3, P = 20, K = 5 2 of 17).
+        // its schedule, and each of the next is longer than the one before by what its schedule allows: K-async three times, since
+        // an update's schedule takes at most a third of its gradients (0.6 of 3.6 us at P = 8, K = 2; P = 20, K = 5 1.6 of 7.9); K-batch-async,
+        // whose schedule goes push by push, half as long again (8 workers, K = 2 1.4 of 2.3 us; 600 updates of 16 replicas 2.77 ms with
+        // pieces three times as long, 2.64 so; P = 15, K = 15, d = 752 16.4 and 14.2 us per update; K-async prefers the fewer launches: one run of 2000
+        // updates 7.60 and 7.70 ms).
         const bool linear_async = c->model.kind != SSGD_MLP2 && (c->variant == SSGD_K_ASYNC || c->variant == SSGD_K_BATCH_ASYNC);
         // Where the steady-state kernel of K-async fills the chip, the schedule's wavefront disturbs a cluster: worth it for one
         // launch per piece at most (d = 768, 64 replicas, 3000 updates: 4.20 us per update piece by piece, 4.40 in one go; 200
@@ -542,9 +549,10 @@ ssgd_status run_updates(ssgd_ctx* c, int64_t J, float* agg_out) {
                 if (e == hipSuccess && c->j > 0)
                     e = hipMemcpyAsync(hsel, c->tr.sel + (size_t)(c->j - 1) * W, sizeof(int32_t) * W, hipMemcpyDeviceToHost, c->side);
             }
+            auto grown = [&](int64_t len) { return c->variant == SSGD_K_BATCH_ASYNC ? len + len / 2 : 3 * len; };
             std::vector<int64_t> lengths;        // of the pieces
             std::vector<int64_t> firsts;         // where they begin, and the end of the last one
-            for (int64_t off = 0, len = one_call ? kPiece / 4 : kPiece; off < seg; off += lengths.back(), len = one_call ? kPiece : std::min(3 * len, kLongest)) {
+            for (int64_t off = 0, len = one_call ? kPiece / 4 : kPiece; off < seg; off += lengths.back(), len = one_call ? kPiece : std::min(grown(len), kLongest)) {
                 firsts.push_back(off);
                 lengths.push_back(std::min(len, seg - off));
             }
@@ -629,7 +637,7 @@ ssgd_status run_updates(ssgd_ctx* c, int64_t J, float* agg_out) {
         }
     }
     if (c->ada.mode != 0) c->flags_seen = false;       // the controller's kernel is behind the flags
-    HIP_OK(c, read_flags(c));
+    HIP_OK(c, read_flags(c, J <= 4 && c->model.kind != SSGD_MLP2));
     for (auto& ev : events) {
         float ms = 0;
         if (hipEventElapsedTime(&ms, ev.first, ev.second) == hipSuccess) { c->last_ms += ms; c->last_launches += 1; }

@@ -696,7 +696,7 @@ extern "C" __attribute__((visibility("default"))) ssgd_status ssgd_runtime_mc(in
         double* d_sums = a.partial + partial_words;
         hipError_t e = P <= 64 ? launch_mc<1>(a, (unsigned)blocks, lds, st) : (P <= 128 ? launch_mc<2>(a, (unsigned)blocks, lds, st) : launch_mc<4>(a, (unsigned)blocks, lds, st));
         if (e == hipSuccess) {
-            // (narrower where that leaves too few workgroups to keep enough loads in flight: 8192 blocks of 16 words 16 -> 4 us)
+            // (narrower where that leaves too few workgroups to keep enough loads in flight: 8192 blocks of 16 words 16 -> 12 us)
             int width = 2;
             while (width < 64 && width < 2 * cells_max && (2 * cells_max / (2 * width)) * nslices >= kReduceGroups) width *= 2;
             hipLaunchKernelGGL(mc_reduce_kernel, dim3((unsigned)((2 * cells_max + width - 1) / width), (unsigned)nslices), dim3(kReduceThreads), 0, st,
