@@ -52,6 +52,21 @@ inline TeamShape team_shape(int64_t tiles, int G, int C, int64_t replicas, int c
     return {(int)best, best > 1 && best > local ? 1 : 0};
 }
 
+// Whether every workgroup of a team shares an L2 with those it exchanges with through one: the ids of their XCDs in the order
+// [member][slice].  Members that are spread over XCDs exchange their sums through memory, so only the slices of a cluster have to sit
+// together; a team that is not spread relies on one L2 as a whole (its sums, and gradients in flight in slots that all members use).
+template <typename Id>
+constexpr bool team_shares_l2(int members, int G, bool spread, Id id) {
+    int first = 0;
+    bool same = true;
+    for (int q = 0; q < members * G; ++q) {
+        const int xcd = id(q);
+        if (q == 0 || (spread && q % G == 0)) first = xcd;
+        same = same && xcd == first;
+    }
+    return same;
+}
+
 // Which of the two steady-state kernels of K-async is the faster one, for softmax, P <= 8 and updates of one tile: the one that
 // keeps gradients in flight in LDS takes a CU per slice and one per replica, the tile kernel a CU or half of one per slice.  Times
 // of a launch's update, in hundredths of the tile kernel's with a CU per workgroup (5.3 to 5.8 us): the other kernel's chain is

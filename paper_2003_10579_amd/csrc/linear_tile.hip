@@ -676,8 +676,8 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         const int hw_id = (int)__builtin_amdgcn_s_getreg((15 << 11) | 4);
         __hip_atomic_store(a.xcc_ids + (int64_t)crew * G + slice, my_xcc | (hw_id << 8), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if constexpr (TEAM) {
-            // The team meets once: with every cluster on one XCD it goes on as a team; else its first member goes on alone and
-            // the others leave.
+            // The team meets once: where those who exchange through an L2 share one it goes on as a team; else its first member
+            // goes on alone and the others leave.
             const int all = a.team * G;
             unsigned int* met = a.arrive + kArriveStride * rep + kArriveTeam;
             __hip_atomic_fetch_add(met, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
@@ -690,12 +690,10 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                     L.ctl[0] = 1;
                 }
             }
-            int same = a.allow_fast, first = 0;
-            for (int q = 0; q < all; ++q) {
-                const int id = __hip_atomic_load(a.xcc_ids + (int64_t)rep * all + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xFF;
-                if (q % G == 0) first = id;
-                if (id != first) same = 0;
-            }
+            const bool together = team_shares_l2(a.team, G, a.spread != 0, [&](int q) {
+                return __hip_atomic_load(a.xcc_ids + (int64_t)rep * all + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xFF;
+            });
+            int same = a.allow_fast && together ? 1 : 0;
             if ((a.debug_flags & 1) != 0 && (rep & 1) != 0) same = 0;
             L.ctl[1] = same;
             L.ctl[2] = same ? a.team : 1;

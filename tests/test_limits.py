@@ -67,3 +67,18 @@ def test_teams_leave_room_for_the_schedule_and_for_other_launches(tmp_path):
         assert on_xcd <= 31 and 4 * (waiting - 1) < 32 * per_cu
     assert teams > 100
     assert got[:2] == [1, 0]
+
+
+def test_a_team_goes_on_only_where_its_workgroups_share_the_l2_they_exchange_through(tmp_path):
+    """XCDs of the workgroups of made-up placements, [member][slice]: a team that is not spread sits on one XCD as a whole, one that
+    is has every cluster on one."""
+    cases = [(3, 1, [2, 2, 2]), (3, 1, [2, 2, 5]), (3, 1, [5, 2, 2]), (2, 4, [1] * 8), (2, 4, [1] * 4 + [6] * 4), (2, 4, [1] * 7 + [6]),
+             (2, 4, [1, 1, 6, 1] + [1] * 4), (2, 4, [6] + [1] * 7), (1, 3, [0, 0, 0]), (1, 3, [0, 0, 7]), (32, 1, list(range(8)) * 4)]
+    body = "".join("{ const int ids[] = {%s}; auto id = [&](int q) { return ids[q]; };\n"
+                   'printf("%%d %%d\\n", (int)team_shares_l2(%d, %d, false, id), (int)team_shares_l2(%d, %d, true, id)); }\n'
+                   % (", ".join(map(str, ids)), w, G, w, G) for w, G, ids in cases)
+    got = _evaluate(tmp_path, body)
+    for (w, G, ids), local, spread in zip(cases, got[::2], got[1::2]):
+        clusters = [set(ids[G * q:G * q + G]) for q in range(w)]
+        assert local == (len(set(ids)) == 1), ids
+        assert spread == all(len(c) == 1 for c in clusters), ids
