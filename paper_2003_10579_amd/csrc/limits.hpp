@@ -52,6 +52,13 @@ inline TeamShape team_shape(int64_t tiles, int G, int C, int64_t replicas, int c
     return {(int)best, best > 1 && best > local ? 1 : 0};
 }
 
+// The meeting of a team: a word counts its workgroups as they arrive.  Complete, it is a team; a workgroup that has waited too long
+// (CUs that another launch holds) closes an incomplete meeting, by a compare-and-swap of the very count that it saw, and then the first
+// member does the work alone whenever it gets its CUs: a cluster of one workgroup never gives up.  Whoever looks sees the same.
+constexpr uint32_t kMeetingClosed = 1u << 31;
+enum Meeting { kMeetingOpen = 0, kMeetingComplete = 1, kMeetingOff = 2 };
+constexpr Meeting meeting(uint32_t word, uint32_t all) { return (word & kMeetingClosed) != 0 ? kMeetingOff : (word == all ? kMeetingComplete : kMeetingOpen); }
+
 // Whether every workgroup of a team shares an L2 with those it exchanges with through one: the ids of their XCDs in the order
 // [member][slice].  Members that are spread over XCDs exchange their sums through memory, so only the slices of a cluster have to sit
 // together; a team that is not spread relies on one L2 as a whole (its sums, and gradients in flight in slots that all members use).

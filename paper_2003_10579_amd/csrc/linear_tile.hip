@@ -676,21 +676,26 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
         const int hw_id = (int)__builtin_amdgcn_s_getreg((15 << 11) | 4);
         __hip_atomic_store(a.xcc_ids + (int64_t)crew * G + slice, my_xcc | (hw_id << 8), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if constexpr (TEAM) {
-            // The team meets once: where those who exchange through an L2 share one it goes on as a team; else its first member
-            // goes on alone and the others leave.
+            // The team meets once: where everyone has come and those who exchange through an L2 share one it goes on as a team; else
+            // its first member goes on alone and the others leave.
             const int all = a.team * G;
             unsigned int* met = a.arrive + kArriveStride * rep + kArriveTeam;
+            if ((a.debug_flags & 4) != 0) __hip_atomic_fetch_or(met, kMeetingClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_fetch_add(met, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
             uint32_t spins = 0;
-            while (L.ctl[0] == 0 && __hip_atomic_load(met, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)all) {
+            Meeting seen = kMeetingOpen;
+            while (L.ctl[0] == 0) {
+                uint32_t word = __hip_atomic_load(met, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
+                seen = meeting(word, (uint32_t)all);
+                if (seen != kMeetingOpen) break;
                 __builtin_amdgcn_s_sleep(8);
                 ++spins;
-                if (spins > a.spin_limit || ((spins & 63u) == 0 && __hip_atomic_load(a.abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
-                    __hip_atomic_store(a.abort_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (spins > a.spin_limit)
+                    __hip_atomic_compare_exchange_strong(met, &word, word | kMeetingClosed, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                else if ((spins & 63u) == 0 && __hip_atomic_load(a.abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
                     L.ctl[0] = 1;
-                }
             }
-            const bool together = team_shares_l2(a.team, G, a.spread != 0, [&](int q) {
+            const bool together = seen == kMeetingComplete && team_shares_l2(a.team, G, a.spread != 0, [&](int q) {
                 return __hip_atomic_load(a.xcc_ids + (int64_t)rep * all + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xFF;
             });
             int same = a.allow_fast && together ? 1 : 0;

@@ -991,6 +991,41 @@ def test_updates_shared_by_a_team(ssgd, oracle, torch_cuda, monkeypatch, kind, v
         ctx.close()
 
 
+@pytest.mark.parametrize("kind,variant,P,K,m,d,classes,R", [
+    ("lsq", "k_sync", 6, 6, 84, 64, 1, 33),               # one slice, more tiles than members (with one each the sums are the same)
+    ("softmax", "k_batch_async", 8, 6, 32, 200, 15, 3),   # one slice, slots per member
+    ("softmax", "k_async", 9, 6, 32, 300, 15, 3),         # two slices
+    ("softmax", "k_batch_sync", 5, 9, 64, 3000, 3, 1),    # spread over XCDs
+])
+def test_a_team_that_does_not_get_its_cus_goes_on_without(ssgd, oracle, torch_cuda, monkeypatch, kind, variant, P, K, m, d, classes, R):
+    """A meeting that is closed before it is complete: the first member does the work, to the bits of a cluster that has no shared L2,
+    and the call succeeds; the next launch is a team again."""
+    torch = torch_cuda
+    X, y = synth.lsq_data(700, d, 8)[:2] if kind == "lsq" else synth.mixture_data(700, d, classes, seed=8)
+    Xd, yd = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
+    gd, od = dist_pair(ssgd, oracle, ("shifted_exp", 0.5, 1.0))
+    mk = lambda: ssgd.Context(kind, Xd, yd, P, K, m, variant, gd, 0.01, seed=9, classes=classes, replicas=R)
+    team, off, fenced = mk(), mk(), mk()
+    team.run(60)
+    monkeypatch.setenv("SSGD_DEBUG_FLAGS", "4")
+    off.run(60)
+    monkeypatch.delenv("SSGD_DEBUG_FLAGS")
+    monkeypatch.setenv("SSGD_EXCHANGE", "fenced")
+    fenced.run(60)
+    monkeypatch.delenv("SSGD_EXCHANGE")
+    assert any(not np.array_equal(team.params(r), off.params(r)) for r in range(R))       # other sums, other last bits
+    for r in range(R):
+        assert np.array_equal(off.params(r), fenced.params(r)), r
+    off.run(30)
+    for r in (0, R - 1):
+        tr = oracle.Trainer(oracle.Model(kind, X, y, classes=classes), P, K, m, variant, od, 0.01, seed=9, replica=r)
+        tr.run(90)
+        assert_trace_equal(off.trace(r), tr.trace())
+        assert rel(off.params(r), tr.params()) <= FP32_PARAM_TOL, r
+    for ctx in (team, off, fenced):
+        ctx.close()
+
+
 @pytest.mark.parametrize("kind,variant,P,K,m,d,classes", [
     ("lsq", "k_async", 8, 2, 32, 256, 1),            # the widest single slice, whole records
     ("softmax", "k_async", 8, 3, 16, 132, 10),       # the most contributors of eight workers with gradients in flight in LDS

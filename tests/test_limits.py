@@ -82,3 +82,35 @@ def test_a_team_goes_on_only_where_its_workgroups_share_the_l2_they_exchange_thr
         clusters = [set(ids[G * q:G * q + G]) for q in range(w)]
         assert local == (len(set(ids)) == 1), ids
         assert spread == all(len(c) == 1 for c in clusters), ids
+
+
+def test_everyone_sees_the_same_end_of_a_team_meeting(tmp_path):
+    """All interleavings of workgroups that arrive, look at the count and, after waiting too long, try to close the meeting they saw
+    incomplete: nobody goes on as a team while another takes the meeting to be off, a team has everyone, and nobody waits for ever."""
+    all_ = 3
+    closed = 1 << 31
+    words = [n | c for n in range(all_ + 1) for c in (0, closed)]
+    table = dict(zip(words, _evaluate(tmp_path, "".join(f'printf("%d\\n", (int)meeting({w}u, {all_}u));\n' for w in words))))
+    OPEN, TEAM = 0, 1
+    start = (0, (("out", None),) * all_)
+    reached, todo, ends = {start}, [start], set()
+    while todo:
+        word, groups = todo.pop()
+        said = {what for state, what in groups if state == "done"}
+        assert len(said) <= 1 and (TEAM not in said or all(state != "out" for state, _ in groups)), groups
+        if all(state == "done" for state, _ in groups):
+            ends |= said
+        for i, (state, what) in enumerate(groups):
+            nexts = []
+            if state == "out":
+                nexts.append((word + 1, ("in", None)))
+            elif state == "in":
+                nexts.append((word, ("in", word) if table[word] == OPEN else ("done", table[word])))
+                if what is not None:                                      # the compare-and-swap of the count seen last
+                    nexts.append((word | closed if word == what else word, ("in", None)))
+            for w, g in nexts:
+                new = (w, groups[:i] + (g,) + groups[i + 1:])
+                if new not in reached:
+                    reached.add(new)
+                    todo.append(new)
+    assert ends == {1, 2}
