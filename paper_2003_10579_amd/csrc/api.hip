@@ -95,6 +95,7 @@ struct ssgd_ctx {
     int32_t Kcap = 0, S = 0, G = 0, nbw = 0, maxrows = 0, table_ord = 1;
     int tile_resident_groups = 0, defer_per_launch = 0, cu_count = 0;
     int team = 1, spread = 0;       // linear models: clusters that share the tiles of an update (tile kernel), on XCDs of their own
+    int64_t team_updates = 0;       // the most updates of a team's launch
     LinArgs lin{};
     int64_t j = 0;
     int32_t win_cnt = 0;
@@ -476,7 +477,11 @@ ssgd_status run_segment_linear(ssgd_ctx* c, int64_t v0, int64_t n, float* agg_ou
         ssgd_status st = launch_steps(c, v0, std::min(head, n), agg_out, kGeneralKernel, events);
         if (st != SSGD_OK) return st;
     }
-    if (n > head) return launch_steps(c, v0 + head, n - head, agg_out, defer ? kDeferKernel : kTileKernel, events);
+    const int64_t most = !defer && c->team > 1 ? c->team_updates : n;
+    for (int64_t off = std::min(head, n); off < n; off += most) {
+        ssgd_status st = launch_steps(c, v0 + off, std::min(most, n - off), agg_out, defer ? kDeferKernel : kTileKernel, events);
+        if (st != SSGD_OK) return st;
+    }
     return SSGD_OK;
 }
 
@@ -787,6 +792,7 @@ ssgd_status ssgd_create(const ssgd_model* model, int32_t P, int32_t K, int32_t m
             const int per_cu = tiles < 2 ? 0 : linear_tile_resident_groups(linear_tile_lds_bytes(C, c->S, Kcap, true)) / c->cu_count;
             const TeamShape shape = team_shape(tiles, c->G, C, R, c->cu_count, per_cu);
             c->team = shape.members; c->spread = shape.spread;
+            c->team_updates = team_updates_per_launch(tiles, c->team);
         }
         HIP_C(c->params.alloc(sizeof(float) * R * c->nw));
         HIP_C(hipMemsetAsync(c->params.p, 0, sizeof(float) * R * c->nw, c->stream));

@@ -52,6 +52,14 @@ inline TeamShape team_shape(int64_t tiles, int G, int C, int64_t replicas, int c
     return {(int)best, best > 1 && best > local ? 1 : 0};
 }
 
+// Updates of one launch of a team, which others that want its CUs wait for: at most so many tiles of a member one after the other
+// (50 to 160 ms, a small part of the seconds after which a team that waits goes on without its members).
+constexpr int64_t kTeamTilesPerLaunch = 1 << 14;
+inline int64_t team_updates_per_launch(int64_t tiles, int members) {
+    const int64_t turns = (tiles + members - 1) / members;
+    return turns < kTeamTilesPerLaunch ? kTeamTilesPerLaunch / (turns > 0 ? turns : 1) : 1;
+}
+
 // The meeting of a team: a word counts its workgroups as they arrive.  Complete, it is a team; a workgroup that has waited too long
 // (CUs that another launch holds) closes an incomplete meeting, by a compare-and-swap of the very count that it saw, and then the first
 // member does the work alone whenever it gets its CUs: a cluster of one workgroup never gives up.  Whoever looks sees the same.

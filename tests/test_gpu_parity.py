@@ -1026,6 +1026,24 @@ def test_a_team_that_does_not_get_its_cus_goes_on_without(ssgd, oracle, torch_cu
         ctx.close()
 
 
+def test_a_long_run_of_a_team_is_several_launches(ssgd, torch_cuda):
+    """A synchronous segment of any length leaves the CUs to others now and then; its results are those of shorter calls."""
+    torch = torch_cuda
+    X, y = synth.mixture_data(500, 60, 3, seed=8)
+    Xd, yd = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
+    mk = lambda: ssgd.Context("softmax", Xd, yd, 6, 5, 30, "k_sync", ssgd.delay_dist("exp", 1.0), 0.01, seed=9, classes=3)
+    a, b = mk(), mk()
+    a.run(20000)                                  # three tiles, three members: one tile each per update
+    assert a.last_kernel_ms()[1] == 2
+    for J in (16000, 900, 3100):
+        b.run(J)
+    assert np.array_equal(a.params(), b.params())
+    for k, v in a.trace(0, 16000).items():
+        assert np.array_equal(v, b.trace(0, 16000)[k]), k
+    a.close()
+    b.close()
+
+
 @pytest.mark.parametrize("kind,variant,P,K,m,d,classes", [
     ("lsq", "k_async", 8, 2, 32, 256, 1),            # the widest single slice, whole records
     ("softmax", "k_async", 8, 3, 16, 132, 10),       # the most contributors of eight workers with gradients in flight in LDS

@@ -114,3 +114,12 @@ def test_everyone_sees_the_same_end_of_a_team_meeting(tmp_path):
                     reached.add(new)
                     todo.append(new)
     assert ends == {1, 2}
+
+
+def test_launches_of_a_team_are_bounded(tmp_path):
+    """At least one update and, from two on, no more tiles of a member than the limit."""
+    cases = [(t, w) for t in (1, 2, 3, 9, 64, 1000, 16384, 16385, 65536, 64 * 1024) for w in (2, 3, 8, 32)]
+    most, *got = _evaluate(tmp_path, 'printf("%lld\\n", (long long)kTeamTilesPerLaunch);\n' + "".join(f'printf("%lld\\n", (long long)team_updates_per_launch({t}, {w}));\n' for t, w in cases))
+    for (t, w), n in zip(cases, got):
+        turns = -(-t // w)
+        assert n >= 1 and (n == 1 or n * turns <= most) and (n + 1) * turns > most
