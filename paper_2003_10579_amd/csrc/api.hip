@@ -366,9 +366,10 @@ ssgd_status launch_steps(ssgd_ctx* c, int64_t v0, int64_t n, float* agg_out, int
         a.agg_out = agg_out;
         a.pair_cus = 0; a.pair_layers = 0;
         a.shared_cus = ((a.replicas + 7) / 8 * 8 * c->G > c->cu_count) ? 1 : 0;      // an XCD takes an eighth of the clusters
-        // workgroups that wait for each other on an XCD; a team spread over XCDs: all of the launch
-        const int bound = c->spread && mode == kTileKernel ? (a.replicas * c->team + 7) / 8 * c->G : c->G * (mode == kTileKernel ? c->team : 1);
-        a.whole_cus = !a.shared_cus && whole_cus(bound, c->cu_count) ? 1 : 0;
+        // (workgroups that wait for each other on an XCD; a team spread over XCDs: all of the launch)
+        const bool whole = c->spread && mode == kTileKernel ? whole_cus_spread((a.replicas * c->team + 7) / 8 * c->G, c->cu_count)
+                                                            : whole_cus(c->G * (mode == kTileKernel ? c->team : 1), c->cu_count);
+        a.whole_cus = !a.shared_cus && whole ? 1 : 0;
         a.prof_wave = 0; a.prof_a = -1; a.prof_b = -1; a.prof_base = (int64_t)c->R * c->G * 20; a.prof_helper = (int64_t)c->R * c->G * 2;
         if (const char* e = getenv("SSGD_PHASE_PROFILE")) (void)sscanf(e, "%d,%d,%d", &a.prof_a, &a.prof_b, &a.prof_wave);
         a.debug_flags = 0;

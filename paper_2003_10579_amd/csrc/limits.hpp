@@ -24,22 +24,26 @@ inline uint32_t sync_schedule_blocks(int64_t updates) { return (uint32_t)((updat
 // leave twice the room.
 constexpr int kXcds = 8, kHardwareQueues = 4;
 inline bool whole_cus(int G, int cus) { return G == 1 || kHardwareQueues * (G - 1) < cus / kXcds; }
+// Where workgroups wait for others on another XCD: a launch can hold all of its places on one XCD in vain.
+inline bool whole_cus_spread(int on_xcd, int cus) { return kHardwareQueues * on_xcd <= cus / kXcds; }
 
 // Clusters of G workgroups that share the tiles of a replica's update (a team).  Every workgroup gets a CU to itself, and one
 // CU per XCD stays free for the schedule.  A team on one XCD keeps to the rule above as a whole, in places of a CU (per_cu: 1
-// or 2 workgroups fit).  Where that gives too few, the clusters are spread over the XCDs; then a launch takes at most a quarter
-// of the places of an XCD, so that the launches of four queues fit side by side and none holds part of its places in vain.
+// or 2 workgroups fit).  Where that gives too few, the clusters are spread over the XCDs; then a launch, which can hold all of its
+// places on an XCD and wait for another, takes at most a quarter of the places of an XCD, so that the launches of four queues fit
+// side by side.
 // The size is the one with the least time per update, in cycles: the tiles of a member one after the other, and the members'
 // gradient sums that everyone reads (a kilobyte per class row and member, 16 bytes per cycle).  (21 tiles of one slice, 15
 // classes: 70 us per update alone, 12.8 with 8 members, 10.1 with 11.)
 constexpr int kMostMembers = 32;
 struct TeamShape { int members, spread; };
 inline TeamShape team_shape(int64_t tiles, int G, int C, int64_t replicas, int cus, int per_cu) {
-    const int64_t room = cus / kXcds, together = ((per_cu >= 2 ? 2 : 1) * room - 1) / kHardwareQueues + 1;
+    const int64_t room = cus / kXcds, places = (per_cu >= 2 ? 2 : 1) * room;
+    const int64_t together = (places - 1) / kHardwareQueues + 1, quarter = places / kHardwareQueues;
     const int64_t on_xcd = (replicas + kXcds - 1) / kXcds;
     const int64_t a = (room - 1) / (on_xcd * G), b = together / G;
     const int64_t local = a < b ? a : b;
-    const int64_t wide = kXcds * ((together < room - 1 ? together : room - 1) / G) / replicas;
+    const int64_t wide = kXcds * ((quarter < room - 1 ? quarter : room - 1) / G) / replicas;
     int64_t most = local > wide ? local : wide;
     if (most > kMostMembers) most = kMostMembers;
     if (most > tiles) most = tiles;

@@ -48,25 +48,33 @@ def test_clusters_of_four_launches_cannot_keep_each_other_incomplete(tmp_path):
 
 
 def test_teams_leave_room_for_the_schedule_and_for_other_launches(tmp_path):
-    """Every team over a range of shapes: a CU per workgroup and one per XCD free; on one XCD a team as a whole, spread over
-    XCDs a whole launch takes no more than a quarter of the places (so four launches cannot keep each other incomplete); a
-    member has a tile; alone where there is one tile or no room."""
-    cases = [(t, G, C, R, per_cu) for t in (1, 2, 3, 7, 32, 64, 256) for G in (1, 2, 3, 4, 7, 12, 16, 40) for C in (1, 10, 15)
-             for R in (1, 2, 7, 8, 9, 40, 300) for per_cu in (1, 2)]
-    body = "TeamShape t;\n" + "".join(f't = team_shape({t}, {G}, {C}, {R}, 256, {p}); printf("%d %d\\n", t.members, t.spread);\n' for t, G, C, R, p in cases)
+    """Every team over a range of shapes and CU counts: a CU per workgroup and one per XCD free; on one XCD four teams that each hold
+    all but one of their places leave one; spread over XCDs, where a launch can hold all of its places on one XCD and wait for
+    another, four whole launches fit; a member has a tile; alone where there is one tile or no room."""
+    cases = [(t, G, C, R, 8 * room, per_cu) for t in (1, 2, 3, 7, 32, 64, 256) for G in (1, 2, 3, 4, 7, 9, 10, 12, 16, 40) for C in (1, 10, 15)
+             for R in (1, 2, 7, 8, 9, 40, 300) for room in (10, 31, 32, 33, 38, 40) for per_cu in (1, 2)]
+    body = "TeamShape t;\n" + "".join(f't = team_shape({t}, {G}, {C}, {R}, {cus}, {p}); printf("%d %d\\n", t.members, t.spread);\n' for t, G, C, R, cus, p in cases)
     got = _evaluate(tmp_path, body)
-    teams = 0
-    for (t, G, C, R, per_cu), members, spread in zip(cases, got[::2], got[1::2]):
+    local = wide = 0
+    for (t, G, C, R, cus, per_cu), members, spread in zip(cases, got[::2], got[1::2]):
         assert 1 <= members <= max(1, t)
         if members == 1:
             assert not spread
             continue
-        teams += 1
+        room = cus // 8
+        places = room * per_cu
         on_xcd = -(-R * members // 8) * G if spread else -(-R // 8) * G * members
-        waiting = on_xcd if spread else G * members
-        assert on_xcd <= 31 and 4 * (waiting - 1) < 32 * per_cu
-    assert teams > 100
+        assert on_xcd <= room - 1
+        if spread:
+            wide += 1
+            assert 4 * on_xcd <= places, (t, G, C, R, cus, per_cu)
+        else:
+            local += 1
+            assert 4 * (G * members - 1) < places
+    assert local > 100 and wide > 100
     assert got[:2] == [1, 0]
+    whole = _evaluate(tmp_path, "".join(f'printf("%d\\n", (int)whole_cus_spread({n}, {8 * room}));\n' for room in (31, 32, 38) for n in range(1, 13)))
+    assert whole == [int(4 * n <= room) for room in (31, 32, 38) for n in range(1, 13)]
 
 
 def test_a_team_goes_on_only_where_its_workgroups_share_the_l2_they_exchange_through(tmp_path):
