@@ -96,6 +96,7 @@ struct ssgd_ctx {
     int tile_resident_groups = 0, defer_per_launch = 0, cu_count = 0;
     int team = 1, spread = 0;       // linear models: clusters that share the tiles of an update (tile kernel), on XCDs of their own
     int64_t team_updates = 0;       // the most updates of a team's launch
+    int placed = 0;                 // workgroups per replica of the last launch, whose places are in xcc_ids
     LinArgs lin{};
     int64_t j = 0;
     int32_t win_cnt = 0;
@@ -356,8 +357,9 @@ ssgd_status launch_steps(ssgd_ctx* c, int64_t v0, int64_t n, float* agg_out, int
     HIP_OK(c, hipGetLastError());
     c->flags_seen = false;
     if (getenv("SSGD_DEBUG"))
-        fprintf(stderr, "ssgd launch: v0=%lld n=%lld tile=%d resident=%d per_launch=%d R=%d\n", (long long)v0, (long long)n,
-                (int)tile, resident, per_launch, c->R);
+        fprintf(stderr, "ssgd launch: v0=%lld n=%lld tile=%d resident=%d per_launch=%d R=%d team=%d spread=%d\n", (long long)v0, (long long)n,
+                (int)tile, resident, per_launch, c->R, mode == kTileKernel ? c->team : 1, mode == kTileKernel ? c->spread : 0);
+    c->placed = mode == kDeferKernel ? c->G + 1 : (mode == kTileKernel ? c->G * c->team : c->G);
     for (int r0 = 0; r0 < c->R; r0 += per_launch) {
         LinArgs a = c->lin;
         a.replica0 = r0; a.replicas = std::min(per_launch, c->R - r0);
@@ -1253,13 +1255,15 @@ void ssgd_destroy(ssgd_ctx* c) {
         }
     }
     if (c->xcc_ids.p && getenv("SSGD_DEBUG")) {
-        // placement of the last launch: XCD, shader engine and CU of every workgroup of the first clusters
-        std::vector<int32_t> h((size_t)c->R * c->G);
-        if (hipMemcpy(h.data(), c->xcc_ids.p, h.size() * sizeof(int32_t), hipMemcpyDeviceToHost) == hipSuccess)
+        // placement of the last launch: XCD, shader engine and CU of every workgroup of a replica ([member][slice] of a team; slices
+        // and helper)
+        const size_t n = (size_t)c->placed;
+        std::vector<int32_t> h((size_t)c->R * n);
+        if (n > 0 && hipMemcpy(h.data(), c->xcc_ids.p, h.size() * sizeof(int32_t), hipMemcpyDeviceToHost) == hipSuccess)
             for (int r = 0; r < c->R; ++r) {
                 fprintf(stderr, "ssgd placement replica %d:", r);
-                for (int g = 0; g < c->G; ++g) {
-                    const int v = h[(size_t)r * c->G + g], hw = v >> 8;
+                for (size_t g = 0; g < n; ++g) {
+                    const int v = h[(size_t)r * n + g], hw = v >> 8;
                     fprintf(stderr, " x%d.se%d.cu%d", v & 0xFF, (hw >> 13) & 7, (hw >> 8) & 15);
                 }
                 fprintf(stderr, "\n");

@@ -127,7 +127,7 @@ struct LinArgs {
     int32_t own_slots;       // a member's slots for gradients in flight: S, or 0 where the team uses those of everyone
     float *park2, *park2_small;   // [R][G][team][own_slots + 1] of the parked gradients' layout
     uint32_t* tx;            // [R][G][3][team][kTeamWords] exchange of a team's gradient sums, armed like zx (which is then [R][team][3][G][64][16])
-    int32_t* xcc_ids;        // [R][G + 1] XCD each workgroup of a cluster runs on (checked on the device); kernels without a helper use [R][G]
+    int32_t* xcc_ids;        // XCD each workgroup runs on (checked on the device): [R][G], with a helper [R][G + 1], of teams [R][team][G]
     int32_t allow_fast;      // 1: exchange through the shared L2 once a cluster is known to sit on one XCD
     // Steady-state kernel, full launches only: CUs per XCD and resident workgroups per CU.  When set, the
     // workgroup slots of an XCD are dealt out so that the clusters that share CUs share all of them in pairs
@@ -139,7 +139,8 @@ struct LinArgs {
     int32_t shared_cus;
     int32_t whole_cus;                   // steady-state kernel: the form that takes a CU per workgroup
     int32_t prof_wave, prof_a, prof_b;   // diagnostics: wave and the pair of marks of the phase profile
-    int32_t debug_flags;                 // test switches set by the host (SSGD_DEBUG_FLAGS): bit 1 makes the odd replicas take the path of a cluster spread over XCDs
+    int32_t debug_flags;                 // test switches set by the host (SSGD_DEBUG_FLAGS): 1 and 2 make the odd replicas take the path of a team (tile
+                                         // kernel) and of a cluster (K-async kernel) whose workgroups do not share an L2, 4 closes the meetings of teams
     int64_t prof_base;                   // first word of the steady-state kernel's part of prof
     int64_t prof_helper;                 // offset, from prof_base, of the helper workgroups' words (one per replica)
     // Steady-state kernel: 1 for a synchronous variant.  The rows of the K mini-batches are then taken 64 at a time, each

@@ -19,7 +19,7 @@
 //       stores and an arrival counter instead, as does the first exchange of every launch.
 //   D   delta in LDS                                            (workgroup barrier)
 //       gradient slices delta^T X per record; added to the aggregate or parked;
-//       a loader wave sums delta's columns: bias gradient, loss, bias step
+//       a loader wave (of a team: the compute waves) sums delta's columns: bias gradient, loss, bias step
 //   B   the tile has been read                                   (workgroup barrier)
 //       compute waves: w -= (lr/K) * aggregate (after the last tile of the update);
 //       loader waves: next tile -> LDS
@@ -500,9 +500,10 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
             else asm volatile("" : "+v"(q_sel), "+v"(q_tau), "+v"(q_ord), "+v"(row_lab) : : "memory");     // lists and labels asked for behind the rows
         };
 
-        // Loader wave 0, between D and B: the column sums of the delta tile per record, i.e. the bias
+        // One loader wave (0; one slice: 3), between D and B: the column sums of the delta tile per record, i.e. the bias
         // gradient (classes 0..C-1) and the mean mini-batch loss (class 15), summed over the consume
-        // list of update v like the weight gradients; then the bias step and the loss record.
+        // list of update v like the weight gradients; then the bias step and the loss record.  (A team's compute waves take
+        // these sums themselves.)
         float run_tot = 0.0f;      // sums of the earlier tiles of the same update
         auto bias_and_loss = [&](int64_t v, int flags) {
             const int Kv = __builtin_amdgcn_readfirstlane(L.ctl[4]);

@@ -1026,6 +1026,39 @@ def test_a_team_that_does_not_get_its_cus_goes_on_without(ssgd, oracle, torch_cu
         ctx.close()
 
 
+def _placements(err):
+    """XCDs of every replica's workgroups, in order, as `SSGD_DEBUG` prints them when a context is given back."""
+    lines = [l for l in err.splitlines() if l.startswith("ssgd placement replica")]
+    return [[int(w[1:].split(".")[0]) for w in l.split(":")[1].split()] for l in lines]
+
+
+@pytest.mark.parametrize("kind,variant,P,K,m,d,classes,R,members,spread", [
+    ("softmax", "k_async", 20, 5, 25, 785, 10, 8, 3, 0),      # three members of four slices
+    ("lsq", "k_sync", 6, 5, 30, 64, 1, 9, 3, 0),              # one slice, two replicas on one XCD
+    ("softmax", "k_sync", 5, 5, 64, 3000, 3, 1, 5, 1),        # clusters of twelve, a member per XCD
+    ("softmax", "k_async", 8, 2, 16, 516, 4, 3, 1, 0),        # clusters of three with a helper
+])
+def test_placement_of_teams_is_printed_whole(ssgd, torch_cuda, monkeypatch, capfd, kind, variant, P, K, m, d, classes, R, members, spread):
+    """The diagnostics list every workgroup of a replica: of a team all members, each cluster on an XCD, the whole team on one unless it
+    is spread."""
+    torch = torch_cuda
+    X, y = synth.lsq_data(700, d, 8)[:2] if kind == "lsq" else synth.mixture_data(700, d, classes, seed=8)
+    ctx = ssgd.Context(kind, torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda(), P, K, m, variant, ssgd.delay_dist("exp", 1.0), 0.01, seed=9,
+                       classes=classes, replicas=R)
+    monkeypatch.setenv("SSGD_DEBUG", "1")
+    ctx.run(40)
+    ctx.close()
+    err = capfd.readouterr().err
+    G = -(-d // 256) if d > 128 else 1
+    assert f"team={members} spread={spread}" in err
+    rows = _placements(err)
+    assert len(rows) == R and all(len(r) == (G + 1 if members == 1 else G * members) for r in rows), rows
+    for r in rows:
+        for q in range(members):
+            assert len(set(r[G * q:G * q + G])) == 1, r
+        assert spread or len(set(r)) == 1, r
+
+
 def test_a_long_run_of_a_team_is_several_launches(ssgd, torch_cuda):
     """A synchronous segment of any length leaves the CUs to others now and then; its results are those of shorter calls."""
     torch = torch_cuda
