@@ -109,7 +109,10 @@ typedef struct {
  * variants, m >= 1, d >= 1, classes <= 16 for SOFTMAX; MLP2 needs bf16 = 1, m <= 64,
  * d % 128 == 0, hidden % 128 == 0, and with several replicas a fixed K or AdaSync mode 1;
  * SSGD_K_BATCH_ASYNC has the limits given with the enumeration.  Invalid arguments give
- * SSGD_EINVAL and leave *out untouched. */
+ * SSGD_EINVAL and leave *out untouched.
+ * Device memory of a linear model: for K-async and K-batch-async P gradients per replica, and up to
+ * 32 times as much (about one gigabyte at most on 256 CUs) where several clusters of workgroups share a replica's
+ * updates and keep gradients in flight each for itself; where that does not fit they do not share. */
 ssgd_status ssgd_create(const ssgd_model *model, int32_t P, int32_t K, int32_t m, int32_t variant,
                         const ssgd_delay_dist *dist, double lr, uint64_t seed, int32_t replicas,
                         const ssgd_adasync *adasync, void *hip_stream, ssgd_ctx **out);

@@ -805,24 +805,41 @@ ssgd_status ssgd_create(const ssgd_model* model, int32_t P, int32_t K, int32_t m
         HIP_C(c->park_small.alloc(sizeof(float) * R * c->G * c->S * 17));
         HIP_C(hipMemsetAsync(c->park_small.p, 0, sizeof(float) * R * c->G * c->S * 17, c->stream));
         HIP_C(c->zpart.alloc(sizeof(float) * R * 2 * c->G * c->maxrows * 16));
-        HIP_C(c->zx.alloc(sizeof(uint32_t) * 3 * 1024 * (size_t)R * c->G * c->team));
-        if (c->team > 1) HIP_C(c->tx.alloc(sizeof(uint32_t) * 3 * kTeamWords * (size_t)R * c->G * c->team));
-        if (c->team > 1 && async) {
-            const size_t slots = (size_t)R * c->G * c->team * (1 + (c->spread || variant == SSGD_K_BATCH_ASYNC ? c->S : 0));
-            HIP_C(c->park2.alloc(sizeof(float) * slots * 16 * SL));
-            HIP_C(c->park2_small.alloc(sizeof(float) * slots * 17));
-        }
         HIP_C(c->dx.alloc(sizeof(uint32_t) * 4 * 1024 * (size_t)R));
         HIP_C(c->fallback.alloc(sizeof(int32_t) * (size_t)R));
-        const size_t n_ids = (size_t)R * std::max(c->G + 1, c->G * c->team);
-        HIP_C(c->xcc_ids.alloc(sizeof(int32_t) * n_ids));
-        HIP_C(hipMemsetAsync(c->xcc_ids.p, 0xFF, sizeof(int32_t) * n_ids, c->stream));
         if (getenv("SSGD_PHASE_PROFILE")) {
             HIP_C(c->prof.alloc(sizeof(unsigned long long) * (R * c->G * 22 + R)));
             HIP_C(hipMemsetAsync(c->prof.p, 0, sizeof(unsigned long long) * (R * c->G * 22 + R), c->stream));
         }
         HIP_C(c->arrive.alloc(sizeof(unsigned int) * kArriveStride * R));
         HIP_C(hipMemsetAsync(c->arrive.p, 0, sizeof(unsigned int) * kArriveStride * R, c->stream));
+        // The buffers that depend on the team, behind everything else.  A team is a matter of speed alone: where its buffers do not
+        // fit, the replica's cluster does the work by itself.
+        const size_t n_park2 = c->team > 1 && async ? (size_t)R * c->G * c->team * (1 + (c->spread || variant == SSGD_K_BATCH_ASYNC ? c->S : 0)) : 0;
+        size_t n_ids = 0;
+        auto team_buffers = [&]() -> hipError_t {
+            const size_t members = (size_t)R * c->G * c->team;
+            n_ids = std::max((size_t)R * (c->G + 1), members);
+            hipError_t e = c->zx.alloc(sizeof(uint32_t) * 3 * 1024 * members);
+            if (e == hipSuccess) e = c->xcc_ids.alloc(sizeof(int32_t) * n_ids);
+            if (c->team == 1) return e;
+            const size_t tx_bytes = sizeof(uint32_t) * 3 * kTeamWords * members, park2_bytes = sizeof(float) * n_park2 * 16 * SL;
+            if (const char* env = getenv("SSGD_TEAM_MEMORY"))
+                if (tx_bytes + park2_bytes > strtoull(env, nullptr, 10)) return hipErrorOutOfMemory;
+            if (e == hipSuccess) e = c->tx.alloc(tx_bytes);
+            if (e == hipSuccess && n_park2 > 0) e = c->park2.alloc(park2_bytes);
+            if (e == hipSuccess && n_park2 > 0) e = c->park2_small.alloc(sizeof(float) * n_park2 * 17);
+            return e;
+        };
+        hipError_t te = team_buffers();
+        if (te == hipErrorOutOfMemory && c->team > 1) {
+            (void)hipGetLastError();
+            for (DevBuf* b : {&c->zx, &c->xcc_ids, &c->tx, &c->park2, &c->park2_small}) b->release();
+            c->team = 1; c->spread = 0;
+            te = team_buffers();
+        }
+        HIP_C(te);
+        HIP_C(hipMemsetAsync(c->xcc_ids.p, 0xFF, sizeof(int32_t) * n_ids, c->stream));
         // set-up for ssgd_full_gradient_static: this device's address of the library's static scratch array
         HIP_C(full_grad_static_scratch_prepare());
     }

@@ -1059,6 +1059,30 @@ def test_placement_of_teams_is_printed_whole(ssgd, torch_cuda, monkeypatch, capf
         assert spread or len(set(r)) == 1, r
 
 
+@pytest.mark.parametrize("kind,variant,P,K,m,d,classes,R", [
+    ("lsq", "k_batch_async", 40, 12, 20, 64, 1, 5),
+    ("softmax", "k_sync", 5, 5, 64, 3000, 3, 1),
+])
+def test_a_team_whose_buffers_do_not_fit_is_left_out(ssgd, oracle, torch_cuda, monkeypatch, capfd, kind, variant, P, K, m, d, classes, R):
+    """The context is made all the same, and its replicas' clusters do the work by themselves."""
+    torch = torch_cuda
+    X, y = synth.lsq_data(700, d, 8)[:2] if kind == "lsq" else synth.mixture_data(700, d, classes, seed=8)
+    Xd, yd = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
+    gd, od = dist_pair(ssgd, oracle, ("exp", 1.0))
+    monkeypatch.setenv("SSGD_DEBUG", "1")
+    for limit in (None, "1000"):
+        if limit is not None:
+            monkeypatch.setenv("SSGD_TEAM_MEMORY", limit)
+        ctx = ssgd.Context(kind, Xd, yd, P, K, m, variant, gd, 0.01, seed=9, classes=classes, replicas=R)
+        ctx.run(40)
+        assert ("team=1 spread=0" in capfd.readouterr().err) == (limit is not None)
+        tr = oracle.Trainer(oracle.Model(kind, X, y, classes=classes), P, K, m, variant, od, 0.01, seed=9, replica=R - 1)
+        tr.run(40)
+        assert_trace_equal(ctx.trace(R - 1), tr.trace())
+        assert rel(ctx.params(R - 1), tr.params()) <= FP32_PARAM_TOL
+        ctx.close()
+
+
 def test_a_long_run_of_a_team_is_several_launches(ssgd, torch_cuda):
     """A synchronous segment of any length leaves the CUs to others now and then; its results are those of shorter calls."""
     torch = torch_cuda
