@@ -357,8 +357,8 @@ ssgd_status launch_steps(ssgd_ctx* c, int64_t v0, int64_t n, float* agg_out, int
     HIP_OK(c, hipGetLastError());
     c->flags_seen = false;
     if (getenv("SSGD_DEBUG"))
-        fprintf(stderr, "ssgd launch: v0=%lld n=%lld tile=%d resident=%d per_launch=%d R=%d team=%d spread=%d\n", (long long)v0, (long long)n,
-                (int)tile, resident, per_launch, c->R, mode == kTileKernel ? c->team : 1, mode == kTileKernel ? c->spread : 0);
+        fprintf(stderr, "ssgd launch: v0=%lld n=%lld kernel=%s resident=%d per_launch=%d R=%d team=%d spread=%d\n", (long long)v0, (long long)n,
+                mode == kDeferKernel ? "defer" : (tile ? "tile" : "general"), resident, per_launch, c->R, mode == kTileKernel ? c->team : 1, mode == kTileKernel ? c->spread : 0);
     c->placed = mode == kDeferKernel ? c->G + 1 : (mode == kTileKernel ? c->G * c->team : c->G);
     for (int r0 = 0; r0 < c->R; r0 += per_launch) {
         LinArgs a = c->lin;

@@ -337,16 +337,17 @@ def config2_oracle_run(oracle, mixture_full):
     pool.shutdown(wait=False, cancel_futures=True)
 
 
-def test_config1_softmax_kasync_full_size(ssgd, oracle, torch_cuda, mixture_full, config2_oracle_run):
+def test_config1_softmax_kasync_full_size(ssgd, oracle, torch_cuda, monkeypatch, capfd, mixture_full, config2_oracle_run):
     """d=3072, N=50000, 10 classes, P=8, m=32, K=2, shifted-Exp(0.5, 1), lr=0.05, J=5000, in the benchmark's launch
-    configuration (many replicas in one launch).  The oracle follows replica 0 through all 5000 updates (30 of them
-    as single steps with the averaged gradient compared, from update 1 on through the steady-state kernel) and
-    replica 37 for the first 600; schedule, loss trace and the parameters at J against it."""
+    configuration (48 replicas, 16 to a launch of the kernel that keeps gradients in flight in LDS).  The oracle follows
+    replica 0 through all 5000 updates (30 of them as single steps with the averaged gradient compared, from update 1 on
+    through that kernel) and replica 37 for the first 600; schedule, loss trace and the parameters at J against it."""
     torch = torch_cuda
     X, y, Xd, yd = mixture_full
     gd, od = dist_pair(ssgd, oracle, ("shifted_exp", 0.5, 1.0))
-    R, J = 40, 5000
+    R, J = 48, 5000
     ctx = ssgd.Context("softmax", Xd, yd, 8, 2, 32, "k_async", gd, 0.05, seed=0, classes=10, replicas=R)
+    monkeypatch.setenv("SSGD_DEBUG", "1")
     agg = torch.zeros(ctx.nw, device="cuda")
     tr0 = oracle.Trainer(oracle.Model("softmax", X, y, classes=10), 8, 2, 32, "k_async", od, 0.05, seed=0, replica=0)
     worst = 0.0
@@ -355,6 +356,8 @@ def test_config1_softmax_kasync_full_size(ssgd, oracle, torch_cuda, mixture_full
         worst = max(worst, rel(agg.cpu().numpy(), tr0.step()))
     assert worst <= GRAD_TOL, worst
     ctx.run(570)
+    assert set(_kernels(capfd.readouterr().err)[1:]) == {"defer"}
+    monkeypatch.delenv("SSGD_DEBUG")
     tr37 = oracle.Trainer(oracle.Model("softmax", X, y, classes=10), 8, 2, 32, "k_async", od, 0.05, seed=0, replica=37)
     tr37.run(600)
     assert_trace_equal(ctx.trace(37), tr37.trace())
@@ -924,18 +927,20 @@ def test_several_tiles_and_odd_row_lengths(ssgd, oracle, torch_cuda, monkeypatch
               classes=classes, check_steps=30)
 
 
-@pytest.mark.parametrize("P,K,m,d,R", [
-    (8, 2, 16, 516, 3), (8, 2, 32, 300, 90), (3, 1, 32, 516, 2), (8, 1, 64, 200, 3),      # gradients in flight in LDS
-    (8, 3, 16, 516, 3), (6, 2, 16, 300, 170), (2, 2, 32, 516, 2), (8, 2, 16, 200, 3),     # the tile kernel
+@pytest.mark.parametrize("P,K,m,d,R,kernel", [
+    (8, 2, 16, 516, 3, "defer"), (8, 2, 32, 300, 80, "defer"), (3, 1, 32, 516, 2, "defer"), (8, 1, 64, 200, 3, "defer"),
+    (8, 3, 16, 516, 3, "tile"), (8, 2, 32, 300, 90, "tile"), (6, 2, 16, 300, 170, "tile"), (2, 2, 32, 516, 2, "tile"), (8, 2, 16, 200, 3, "tile"),
 ])
-def test_k_async_of_one_tile_on_either_kernel(ssgd, oracle, torch_cuda, P, K, m, d, R):
+def test_k_async_of_one_tile_on_either_kernel(ssgd, oracle, torch_cuda, monkeypatch, capfd, P, K, m, d, R, kernel):
     """Both sides of the rule that picks the kernel of K-async updates of one tile: parity of the first and the last replica."""
     torch = torch_cuda
     X, y = synth.mixture_data(500, d, 4, seed=8)
     gd, od = dist_pair(ssgd, oracle, ("shifted_exp", 0.5, 1.0))
     ctx = ssgd.Context("softmax", torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda(), P, K, m, "k_async", gd, 0.01, seed=9, classes=4, replicas=R)
+    monkeypatch.setenv("SSGD_DEBUG", "1")
     for J in (1, 40, 30):
         ctx.run(J)
+    assert _kernels(capfd.readouterr().err) == ["general", kernel, kernel]
     for r in (0, R - 1):
         tr = oracle.Trainer(oracle.Model("softmax", X, y, classes=4), P, K, m, "k_async", od, 0.01, seed=9, replica=r)
         tr.run(71)
@@ -945,28 +950,30 @@ def test_k_async_of_one_tile_on_either_kernel(ssgd, oracle, torch_cuda, P, K, m,
     ctx.close()
 
 
-@pytest.mark.parametrize("kind,variant,P,K,m,d,classes,R", [
-    ("softmax", "k_async", 20, 5, 25, 785, 10, 8),     # three members of four slices; two records each, the last has one
-    ("softmax", "k_async", 9, 6, 32, 300, 15, 3),      # whole records, two slices
-    ("lsq", "k_async", 9, 3, 72, 515, 1, 2),           # records of two tiles, a member each
-    ("softmax", "k_async", 7, 7, 64, 130, 4, 1),       # nothing is ever parked; one slice
-    ("lsq", "k_async", 70, 64, 5, 60, 1, 2),           # 70 records at version 0, eight rows of a tile each
-    ("lsq", "k_sync", 6, 5, 30, 64, 1, 9),             # 160 rows: two tiles and a half; two replicas on one XCD
-    ("softmax", "k_batch_sync", 5, 12, 64, 260, 3, 1), # twelve tiles for eight workgroups: four members of two slices
-    ("softmax", "k_batch_sync", 5, 9, 64, 100, 3, 1),  # nine tiles for eight members: five members, the last with one tile less
-    ("softmax", "k_sync", 4, 2, 33, 1030, 10, 17),     # one row more than a tile after padding; three replicas on one XCD: no team
-    ("softmax", "k_batch_async", 9, 6, 32, 300, 15, 3),   # two copies of every slot
-    ("lsq", "k_batch_async", 2, 9, 20, 64, 1, 5),      # workers that push several times in an update
-    ("lsq", "k_batch_async", 6, 4, 100, 516, 1, 1),    # records of two tiles, summed by their member
-    ("softmax", "k_batch_async", 20, 5, 24, 2052, 4, 2),  # clusters of nine, spread over XCDs
-    ("softmax", "k_sync", 5, 5, 64, 3000, 3, 1),       # clusters of twelve, a member per XCD
-    ("lsq", "k_async", 90, 60, 70, 1200, 1, 1),        # 60 records of two tiles for 24 members, 90 at version 0
+@pytest.mark.parametrize("kind,variant,P,K,m,d,classes,R,members,spread", [
+    ("softmax", "k_async", 20, 5, 25, 785, 10, 8, 3, 0),     # members of four slices; two records each, the last has one
+    ("softmax", "k_async", 9, 6, 32, 300, 15, 3, 3, 0),      # whole records, two slices
+    ("lsq", "k_async", 9, 3, 72, 515, 1, 2, 3, 0),           # records of two tiles, a member each
+    ("softmax", "k_async", 7, 7, 64, 130, 4, 1, 7, 0),       # nothing is ever parked; one slice
+    ("lsq", "k_async", 70, 64, 5, 60, 1, 2, 8, 0),           # eight rows of a tile per record; 70 records at version 0, nine tiles
+    ("lsq", "k_sync", 6, 5, 30, 64, 1, 9, 3, 0),             # 160 rows: two tiles and a half; two replicas on one XCD
+    ("softmax", "k_batch_sync", 5, 12, 64, 260, 3, 1, 12, 1),  # twelve tiles, members of two slices on eight XCDs
+    ("softmax", "k_batch_sync", 5, 9, 64, 100, 3, 1, 9, 0),  # nine tiles, a member each
+    ("softmax", "k_batch_sync", 5, 9, 64, 3000, 3, 1, 5, 1),  # the same for clusters of twelve: the last member has one tile less
+    ("softmax", "k_sync", 4, 2, 33, 1030, 10, 17, 2, 0),     # one row more than a tile after padding; three replicas on one XCD
+    ("softmax", "k_batch_async", 9, 6, 32, 300, 15, 3, 3, 0),  # two copies of every slot
+    ("lsq", "k_batch_async", 2, 9, 20, 64, 1, 5, 3, 0),      # workers that push several times in an update
+    ("lsq", "k_batch_async", 6, 4, 100, 516, 1, 1, 4, 0),    # records of two tiles, summed by their member
+    ("softmax", "k_batch_async", 20, 5, 24, 2052, 4, 2, 3, 1),  # clusters of nine, spread over XCDs
+    ("softmax", "k_sync", 5, 5, 64, 3000, 3, 1, 5, 1),       # clusters of twelve, a member per XCD
+    ("lsq", "k_async", 90, 60, 70, 1200, 1, 1, 20, 1),       # 60 records of two tiles, 90 at version 0
 ])
-def test_updates_shared_by_a_team(ssgd, oracle, torch_cuda, monkeypatch, kind, variant, P, K, m, d, classes, R):
+def test_updates_shared_by_a_team(ssgd, oracle, torch_cuda, monkeypatch, capfd, kind, variant, P, K, m, d, classes, R, members, spread):
     """Tiles of an update dealt to several clusters of a replica: parity, and the same bits whatever the calls are cut into
     (who adds which gradient in flight does not depend on where a launch ends); without a shared L2 the first cluster goes on
-    alone."""
+    alone, and a context without a team (as where CUs are short, or K changes) takes the tiles one after the other."""
     torch = torch_cuda
+    monkeypatch.setenv("SSGD_DEBUG", "1")
     X, y = synth.lsq_data(700, d, 8)[:2] if kind == "lsq" else synth.mixture_data(700, d, classes, seed=8)
     Xd, yd = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
     gd, od = dist_pair(ssgd, oracle, ("shifted_exp", 0.5, 1.0))
@@ -975,6 +982,14 @@ def test_updates_shared_by_a_team(ssgd, oracle, torch_cuda, monkeypatch, kind, v
     a.run(90)
     for J in (1, 3, 40, 46):
         b.run(J)
+    launches = [l for l in capfd.readouterr().err.splitlines() if l.startswith("ssgd launch")]
+    assert all(l.endswith(f"team={members} spread={spread}") for l in launches), launches
+    monkeypatch.setenv("SSGD_TEAM_MEMORY", "0")
+    single = mk()
+    single.run(90)
+    launches = [l for l in capfd.readouterr().err.splitlines() if l.startswith("ssgd launch")]
+    assert all("team=1 " in l and "kernel=tile" in l for l in launches), launches
+    monkeypatch.delenv("SSGD_TEAM_MEMORY")
     monkeypatch.setenv("SSGD_EXCHANGE", "fenced")
     c = mk()
     c.run(90)
@@ -982,12 +997,12 @@ def test_updates_shared_by_a_team(ssgd, oracle, torch_cuda, monkeypatch, kind, v
         tr = oracle.Trainer(oracle.Model(kind, X, y, classes=classes), P, K, m, variant, od, 0.01, seed=9, replica=r)
         tr.run(90)
         assert np.array_equal(a.params(r), b.params(r)), r
-        for ctx in (a, c):
+        for ctx in (a, c, single):
             g, o = ctx.trace(r), tr.trace()
             assert_trace_equal(g, o)
             assert np.allclose(g["loss"], o["loss"], rtol=FP32_LOSS_RTOL, atol=1e-6)
             assert rel(ctx.params(r), tr.params()) <= FP32_PARAM_TOL, r
-    for ctx in (a, b, c):
+    for ctx in (a, b, c, single):
         ctx.close()
 
 
@@ -1024,6 +1039,11 @@ def test_a_team_that_does_not_get_its_cus_goes_on_without(ssgd, oracle, torch_cu
         assert rel(off.params(r), tr.params()) <= FP32_PARAM_TOL, r
     for ctx in (team, off, fenced):
         ctx.close()
+
+
+def _kernels(err):
+    """The kernels of the launches that `SSGD_DEBUG` lists: general, tile, defer (gradients in flight in LDS)."""
+    return [l.split("kernel=")[1].split()[0] for l in err.splitlines() if l.startswith("ssgd launch")]
 
 
 def _placements(err):
@@ -1083,6 +1103,60 @@ def test_a_team_whose_buffers_do_not_fit_is_left_out(ssgd, oracle, torch_cuda, m
         ctx.close()
 
 
+@pytest.mark.parametrize("kind,variant,P,K,m,d,classes", [
+    ("softmax", "k_async", 20, 5, 25, 785, 10),
+    ("lsq", "k_batch_async", 6, 5, 40, 64, 1),
+    ("softmax", "k_batch_sync", 5, 9, 64, 100, 3),
+])
+def test_teams_beside_replicas_without_a_shared_l2(ssgd, oracle, torch_cuda, monkeypatch, kind, variant, P, K, m, d, classes):
+    """The odd replicas of a launch are told that their teams do not share an L2: their first members do the work, the even ones go on
+    as teams."""
+    torch = torch_cuda
+    X, y = synth.lsq_data(700, d, 8)[:2] if kind == "lsq" else synth.mixture_data(700, d, classes, seed=8)
+    gd, od = dist_pair(ssgd, oracle, ("shifted_exp", 0.5, 1.0))
+    Xd, yd = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
+    mk = lambda: ssgd.Context(kind, Xd, yd, P, K, m, variant, gd, 0.01, seed=9, classes=classes, replicas=5)
+    a, b = mk(), mk()
+    b.run(90)
+    monkeypatch.setenv("SSGD_DEBUG_FLAGS", "1")
+    a.run(50)
+    a.run(40)
+    for r in range(5):
+        tr = oracle.Trainer(oracle.Model(kind, X, y, classes=classes), P, K, m, variant, od, 0.01, seed=9, replica=r)
+        tr.run(90)
+        assert_trace_equal(a.trace(r), tr.trace())
+        assert rel(a.params(r), tr.params()) <= FP32_PARAM_TOL, r
+        assert r % 2 == 1 or np.array_equal(a.params(r), b.params(r)), r
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("kind,variant,P,K,m,d,classes", [
+    ("softmax", "k_async", 20, 6, 25, 785, 10),
+    ("lsq", "k_batch_async", 6, 6, 40, 64, 1),
+    ("softmax", "k_sync", 9, 9, 32, 100, 3),
+])
+def test_a_team_while_k_is_forced_below_its_size(ssgd, oracle, torch_cuda, monkeypatch, capfd, kind, variant, P, K, m, d, classes):
+    """Updates of fewer tiles than the team has members, down to one, and back: the members without a tile take part in the sums, and
+    gradients in flight from before are added by the members that computed them."""
+    torch = torch_cuda
+    X, y = synth.lsq_data(700, d, 8)[:2] if kind == "lsq" else synth.mixture_data(700, d, classes, seed=8)
+    gd, od = dist_pair(ssgd, oracle, ("shifted_exp", 0.5, 1.0))
+    ctx = ssgd.Context(kind, torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda(), P, K, m, variant, gd, 0.01, seed=9, classes=classes, replicas=3)
+    tr = oracle.Trainer(oracle.Model(kind, X, y, classes=classes), P, K, m, variant, od, 0.01, seed=9, replica=2)
+    monkeypatch.setenv("SSGD_DEBUG", "1")
+    for now, J in ((K, 20), (1, 21), (3, 150), (K, 20)):
+        ctx.force_K(now)
+        tr.force_K(now)
+        ctx.run(J)
+        tr.run(J)
+    assert "team=1 " not in capfd.readouterr().err
+    assert_trace_equal(ctx.trace(2), tr.trace())
+    assert np.allclose(ctx.trace(2)["loss"], tr.trace()["loss"], rtol=FP32_LOSS_RTOL, atol=1e-6)
+    assert rel(ctx.params(2), tr.params()) <= FP32_PARAM_TOL
+    ctx.close()
+
+
 def test_a_long_run_of_a_team_is_several_launches(ssgd, torch_cuda):
     """A synchronous segment of any length leaves the CUs to others now and then; its results are those of shorter calls."""
     torch = torch_cuda
@@ -1103,8 +1177,9 @@ def test_a_long_run_of_a_team_is_several_launches(ssgd, torch_cuda):
 
 @pytest.mark.parametrize("kind,variant,P,K,m,d,classes", [
     ("lsq", "k_async", 8, 2, 32, 256, 1),            # the widest single slice, whole records
-    ("softmax", "k_async", 8, 3, 16, 132, 10),       # the most contributors of eight workers with gradients in flight in LDS
-    ("softmax", "k_async", 8, 4, 16, 132, 10),       # one more: no longer
+    ("softmax", "k_async", 8, 1, 16, 132, 10),       # gradients in flight in LDS
+    ("softmax", "k_async", 8, 3, 16, 132, 10),
+    ("softmax", "k_async", 8, 4, 16, 132, 10),       # a full tile
     ("softmax", "k_async", 5, 3, 20, 65, 15),        # second 64-column block one column wide; 60 of 64 rows
     ("softmax", "k_async", 9, 4, 72, 190, 4),        # several tiles, records of two
     ("softmax", "k_sync", 4, 3, 64, 128, 10),        # three tiles per iteration, two column blocks
@@ -1112,7 +1187,7 @@ def test_a_long_run_of_a_team_is_several_launches(ssgd, torch_cuda):
     ("softmax", "k_batch_async", 6, 3, 16, 192, 7),
     ("softmax", "k_async", 3, 2, 8, 5, 2),           # the smallest odd row
 ])
-def test_one_slice(ssgd, oracle, torch_cuda, monkeypatch, kind, variant, P, K, m, d, classes):
+def test_one_slice(ssgd, oracle, torch_cuda, monkeypatch, capfd, kind, variant, P, K, m, d, classes):
     """Models of one slice: logits stay in the workgroup, only the column blocks that exist are worked on.  The layout of
     the state is that of the general kernel, which goes on from it."""
     if kind == "lsq":
@@ -1128,27 +1203,31 @@ def test_one_slice(ssgd, oracle, torch_cuda, monkeypatch, kind, variant, P, K, m
     ctx = ssgd.Context(kind, Xd, yd, P, K, m, variant, gd, 0.01, seed=3, classes=classes)
     orc = oracle.Trainer(oracle.Model(kind, X, y, classes=classes), P, K, m, variant, od, 0.01, seed=3)
     # (segments of 16 updates and more take the kernel that keeps gradients in flight in LDS where it has the shape)
+    monkeypatch.setenv("SSGD_DEBUG", "1")
     for kernel, J in ((None, 20), ("general", 15), (None, 7), ("tile", 20), (None, 18)):
         if kernel:
             monkeypatch.setenv("SSGD_KERNEL", kernel)
         else:
             monkeypatch.delenv("SSGD_KERNEL", raising=False)
         ctx.run(J)
+        assert _kernels(capfd.readouterr().err)[-1] == (kernel or ("defer" if K == 1 and J >= 16 else "tile")), J
     orc.run(80)
     assert_trace_equal(ctx.trace(), orc.trace())
     assert rel(ctx.params(), orc.params()) <= FP32_PARAM_TOL
 
 
-@pytest.mark.parametrize("kind,variant,P,K,m,d,classes", [
-    ("softmax", "k_async", 6, 3, 25, 261, 3),       # several tiles, rows of odd length, padded records
-    ("lsq", "k_sync", 4, 2, 5, 64, 1),              # one slice, a record of 32 rows of which 16 are there
-    ("softmax", "k_batch_sync", 3, 3, 22, 516, 4),  # the last tile half empty
-    ("lsq", "k_async", 5, 2, 7, 35, 1),
-    ("softmax", "k_batch_async", 4, 2, 70, 260, 3), # records of a full tile and one of 8 rows
-    ("softmax", "k_async", 6, 2, 13, 516, 3),       # gradients in flight in LDS: padded records, half a tile
-    ("lsq", "k_async", 6, 1, 30, 200, 1),           # the same for one slice
+@pytest.mark.parametrize("kind,variant,P,K,m,d,classes,team", [
+    ("softmax", "k_async", 6, 3, 25, 261, 3, 2),       # several tiles, rows of odd length, padded records
+    ("lsq", "k_sync", 4, 2, 5, 64, 1, 1),              # one slice, a record of 32 rows of which 16 are there
+    ("softmax", "k_batch_sync", 3, 3, 22, 516, 4, 2),  # the last tile half empty
+    ("lsq", "k_async", 5, 2, 7, 35, 1, 1),
+    ("softmax", "k_batch_async", 4, 2, 70, 260, 3, 2), # records of a full tile and one of 8 rows
+    ("softmax", "k_async", 8, 2, 13, 516, 3, 1),       # gradients in flight in LDS: padded records, half a tile
+    ("softmax", "k_async", 6, 1, 30, 200, 3, 1),       # the same for one slice
+    ("lsq", "k_async", 6, 1, 30, 200, 1, 1),           # records of two rows less than half a tile, one slice
+    ("lsq", "k_async", 9, 6, 27, 200, 1, 3),           # three members, the rest of each tile empty
 ])
-def test_rows_that_no_sample_names_do_not_matter(ssgd, oracle, torch_cuda, kind, variant, P, K, m, d, classes):
+def test_rows_that_no_sample_names_do_not_matter(ssgd, oracle, torch_cuda, monkeypatch, capfd, kind, variant, P, K, m, d, classes, team):
     """The places of a tile that hold no sample contribute nothing, also where the data set holds infinities and NaN in rows
     that were not drawn."""
     X, y = synth.lsq_data(3000, d, 8)[:2] if kind == "lsq" else synth.mixture_data(3000, d, classes, seed=8)
@@ -1163,7 +1242,10 @@ def test_rows_that_no_sample_names_do_not_matter(ssgd, oracle, torch_cuda, kind,
     assert np.all(np.isfinite(orc.params()))
     ctx = ssgd.Context(kind, torch_cuda.from_numpy(bad).cuda(), torch_cuda.from_numpy(y).cuda(), P, K, m, variant, gd, 0.01, seed=seed,
                        classes=classes)
+    monkeypatch.setenv("SSGD_DEBUG", "1")
     ctx.run(20)
+    err = capfd.readouterr().err
+    assert f"team={team} " in err and ("defer" in _kernels(err)) == (kind == "softmax" and variant == "k_async" and 4 * K <= P), err
     assert rel(ctx.params(), orc.params()) <= FP32_PARAM_TOL
 
 
@@ -1184,13 +1266,15 @@ def test_schedule_of_several_launches(ssgd, oracle, torch_cuda, variant):
     ctx.close()
 
 
-@pytest.mark.parametrize("kind,variant,P,K,m,N,d,classes", [
-    ("lsq", "k_sync", 4, 2, 14, 6_000_000, 100, 1),          # one slice; 2 of 16 places of a record without a sample
-    ("softmax", "k_async", 6, 3, 25, 700_000, 785, 3),       # several tiles, one column in the last chunk
-    ("softmax", "k_batch_async", 4, 2, 16, 720_000, 772, 3), # one slice of four that is four columns wide
-    ("softmax", "k_async", 5, 2, 32, 1_050_000, 516, 3),     # the kernel that keeps gradients in flight in LDS
+@pytest.mark.parametrize("kind,variant,P,K,m,N,d,classes,team", [
+    ("lsq", "k_sync", 4, 2, 14, 6_000_000, 100, 1, 1),          # one slice; 2 of 16 places of a record without a sample
+    ("softmax", "k_async", 6, 3, 25, 700_000, 785, 3, 2),       # several tiles, one column in the last chunk
+    ("softmax", "k_batch_async", 4, 2, 16, 720_000, 772, 3, 1), # one slice of four that is four columns wide
+    ("softmax", "k_async", 5, 2, 32, 1_050_000, 516, 3, 1),     # two mini-batches that fill a tile
+    ("softmax", "k_async", 8, 2, 32, 1_050_000, 516, 3, 1),     # the kernel that keeps gradients in flight in LDS
+    ("lsq", "k_batch_sync", 4, 6, 43, 6_000_000, 100, 1, 5),    # several tiles of one slice, a member each
 ])
-def test_sample_matrices_above_two_gib(ssgd, oracle, torch_cuda, kind, variant, P, K, m, N, d, classes):
+def test_sample_matrices_above_two_gib(ssgd, oracle, torch_cuda, monkeypatch, capfd, kind, variant, P, K, m, N, d, classes, team):
     """Columns past the end of a row and places without a sample read zeros, whatever lies 2 GiB behind the row.  The row at
     byte 2^31 holds infinities and is not drawn."""
     torch = torch_cuda
@@ -1203,7 +1287,10 @@ def test_sample_matrices_above_two_gib(ssgd, oracle, torch_cuda, kind, variant, 
     gd, od = dist_pair(ssgd, oracle, ("exp", 1.0))
     ctx = ssgd.Context(kind, Xd, yd, P, K, m, variant, gd, 0.002, seed=3, classes=classes)
     orc = oracle.Trainer(oracle.Model(kind, X, y, classes=classes), P, K, m, variant, od, 0.002, seed=3)
+    monkeypatch.setenv("SSGD_DEBUG", "1")
     ctx.run(60)
+    err = capfd.readouterr().err
+    assert f"team={team} " in err and ("defer" in _kernels(err)) == (P == 8), err
     orc.run(60)
     assert_trace_equal(ctx.trace(), orc.trace())
     assert np.all(np.isfinite(orc.params())) and rel(ctx.params(), orc.params()) <= FP32_PARAM_TOL
@@ -1235,18 +1322,19 @@ def test_contexts_one_after_the_other_and_side_by_side_share_no_results(ssgd, to
         assert len(got[s]) == 6 and all(g == alone[s] for g in got[s])
 
 
-@pytest.mark.parametrize("variant,P,K,m,d,R", [
-    ("k_sync", 4, 2, 16, 64, 1), ("k_async", 12, 2, 16, 100, 2), ("k_batch_async", 4, 2, 16, 36, 300),      # one slice
-    ("k_async", 20, 5, 25, 300, 1), ("k_batch_async", 4, 2, 16, 300, 1),                                    # records one by one
-    ("k_sync", 4, 2, 16, 300, 1), ("k_async", 6, 2, 16, 300, 1)])
-def test_phase_profile_of_every_form(ssgd, torch_cuda, monkeypatch, capfd, variant, P, K, m, d, R):
+@pytest.mark.parametrize("kind,variant,P,K,m,d,R", [
+    ("lsq", "k_sync", 4, 2, 16, 64, 1), ("lsq", "k_async", 12, 2, 16, 100, 2), ("lsq", "k_batch_async", 4, 2, 16, 36, 300),      # one slice
+    ("lsq", "k_async", 20, 5, 25, 300, 1), ("lsq", "k_batch_async", 4, 2, 16, 300, 1),                      # records one by one
+    ("lsq", "k_sync", 4, 2, 16, 300, 1), ("lsq", "k_async", 6, 2, 16, 300, 1),
+    ("softmax", "k_async", 8, 2, 16, 300, 1)])                                                              # gradients in flight in LDS
+def test_phase_profile_of_every_form(ssgd, torch_cuda, monkeypatch, capfd, kind, variant, P, K, m, d, R):
     """SSGD_PHASE_PROFILE prints the cycles of a whole step (from one mark to its next passing) for every kernel that runs
     the steady state."""
     import re
-    monkeypatch.setenv("SSGD_PHASE_PROFILE", "5,6,0" if variant != "k_async" or P > 8 else "4,5,0")
-    X, y, _ = synth.lsq_data(300, d, 8)
-    ctx = ssgd.Context("lsq", torch_cuda.from_numpy(X).cuda(), torch_cuda.from_numpy(y).cuda(), P, K, m, variant,
-                       ssgd.delay_dist("exp", 1.0), 0.01, seed=9, replicas=R)
+    monkeypatch.setenv("SSGD_PHASE_PROFILE", "4,5,0" if kind == "softmax" else "5,6,0")
+    X, y = synth.lsq_data(300, d, 8)[:2] if kind == "lsq" else synth.mixture_data(300, d, 3, seed=8)
+    ctx = ssgd.Context(kind, torch_cuda.from_numpy(X).cuda(), torch_cuda.from_numpy(y).cuda(), P, K, m, variant,
+                       ssgd.delay_dist("exp", 1.0), 0.01, seed=9, replicas=R, classes=1 if kind == "lsq" else 3)
     ctx.run(100)
     ctx.close()
     cycles = float(re.search(r"ssgd phase profile .*: (\d+) cycles", capfd.readouterr().err).group(1))
@@ -1306,8 +1394,8 @@ def test_clusters_of_four_contexts_at_once(ssgd, torch_cuda, d, variant):
 
 
 def test_many_short_calls_read_what_the_call_before_left(ssgd, torch_cuda):
-    """Results that the host sees by watching a word, over more calls than go between two waits for the stream, and one that
-    takes longer than the word is watched for: every call returns what its own kernels wrote."""
+    """Results that the host sees by watching a word, over more calls than go between two waits for the stream, and a run that waits
+    for its stream: every call returns what its own kernels wrote."""
     torch = torch_cuda
     X, y, _ = synth.lsq_data(600, 24, 3)
     Xd, yd = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
@@ -1329,6 +1417,32 @@ def test_many_short_calls_read_what_the_call_before_left(ssgd, torch_cuda):
     assert a.updates == 4090 and np.array_equal(a.params(1), b.params(1))
     a.close()
     b.close()
+
+
+def test_calls_that_outlast_the_watch_of_their_word(ssgd, torch_cuda):
+    """One pass over 2.5 GB takes longer than the 300 us for which the host watches the word (8 TB/s would be 307 us): objective and
+    gradient are those of the parameters set just before, not what an earlier call left in the same memory."""
+    torch = torch_cuda
+    N, d = 200_000, 3072
+    g = torch.Generator(device="cuda").manual_seed(5)
+    Xd = torch.randn(N, d, generator=g, device="cuda")
+    yd = torch.randn(N, generator=g, device="cuda")
+    ctx = ssgd.Context("lsq", Xd, yd, 8, 64, 2048, "k_batch_sync", ssgd.delay_dist("exp", 1.0), 0.01, seed=5)
+    w1 = torch.randn(d, generator=g, device="cuda") / d ** 0.5
+    for scale in (1.0, -2.0, 0.5):
+        w = w1 * scale
+        ctx.set_params(w.cpu().numpy())
+        loss, grad = ctx.full_loss(), ctx.full_gradient()
+        res = torch.cat([Xd[q:q + 20000].double() @ w.double() for q in range(0, N, 20000)]) - yd.double()
+        ref = sum((Xd[q:q + 20000].double() * res[q:q + 20000, None]).sum(0) for q in range(0, N, 20000)) / N
+        assert abs(loss - float((0.5 * res * res).mean())) <= 1e-5 * loss
+        assert rel(grad, ref.cpu().numpy()) <= 1e-5
+    ctx.run(4)                       # a short call by its updates, of 2048 tiles each
+    w, tr = ctx.params(), ctx.trace()
+    torch.cuda.synchronize()
+    assert np.array_equal(w, ctx.params()) and all(np.array_equal(v, ctx.trace()[k]) for k, v in tr.items())
+    assert ctx.last_kernel_ms()[0] > 0.3
+    ctx.close()
 
 
 def test_teams_of_four_contexts_at_once(ssgd, torch_cuda):
@@ -1414,8 +1528,11 @@ def test_workers_in_flight_bit_exact(ssgd, oracle, torch_cuda):
     ("softmax", "k_async", 8, 2, 32, 512, 10, None),                 # steady-state kernel, parked gradients in flight
     ("softmax", "k_batch_sync", 5, 6, 40, 260, 4, None),             # iterations of several tiles
     ("lsq", "k_async", 12, 2, 6, 30, 1, dict(mode=1, K0=2, Kmax=12, window=16, rel_tol=0.5)),   # general kernel, AdaSync window open
+    ("lsq", "k_async", 9, 3, 72, 515, 1, None),                      # a team, gradients in flight in slots of all members
+    ("softmax", "k_batch_async", 9, 6, 32, 300, 10, None),           # in slots of the members' own
+    ("softmax", "k_async", 20, 5, 25, 2052, 4, None),                # the same on several XCDs
 ])
-def test_snapshot_resume_continues_the_same_run(ssgd, oracle, torch_cuda, kind, variant, P, K, m, d, classes, ada):
+def test_snapshot_resume_continues_the_same_run(ssgd, oracle, torch_cuda, monkeypatch, capfd, kind, variant, P, K, m, d, classes, ada):
     """A run that is snapshotted and resumed in a new context is the run that was never interrupted: identical trace
     and parameters, bit for bit (every sum on the device is taken in a fixed order); the oracle agrees with both."""
     torch = torch_cuda
@@ -1427,7 +1544,11 @@ def test_snapshot_resume_continues_the_same_run(ssgd, oracle, torch_cuda, kind, 
     Xd, yd = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
     mk = lambda: ssgd.Context(kind, Xd, yd, P, K, m, variant, gd, 0.03, seed=13, classes=classes, replicas=3, adasync=ada)
     a = mk()
+    monkeypatch.setenv("SSGD_DEBUG", "1")
     a.run(57)
+    err = capfd.readouterr().err
+    assert ("team=1 " in err) == ((variant, m) == ("k_async", 32) or ada is not None) and ("spread=1" in err) == (d == 2052), err
+    monkeypatch.delenv("SSGD_DEBUG")
     blob = a.get_state()
     a.run(43)
     b = mk()
