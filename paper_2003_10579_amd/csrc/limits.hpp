@@ -34,7 +34,12 @@ inline bool whole_cus_spread(int on_xcd, int cus) { return kHardwareQueues * on_
 // side by side.
 // The size is the one with the least time per update, in cycles: the tiles of a member one after the other, and the members'
 // gradient sums that everyone reads (a kilobyte per class row and member, 16 bytes per cycle).  (21 tiles of one slice, 15
-// classes: 70 us per update alone, 12.8 with 8 members, 10.1 with 11.)
+// classes, one replica: 64 us per update alone, 9.3 with 11 members.)  A tile of least squares takes about half of what is counted
+// here, which still leaves every team that the rule makes the better choice: over 144 shapes of both models and three variants, two to
+// twelve tiles, runs are 1.08 (softmax, K-batch-async, 5 mini-batches of 16, d = 64: 7.2 -> 6.7 us per update) to 6.1 times
+// as fast with a team; least squares, two tiles, d = 64, 3.9 -> 2.6.  What loses is a call of a single update, of which a team's meeting and
+// the buffers armed for it are a larger part: up to 8 of 38 us (K-batch-async, 5 of 16, d = 200, 40 replicas), while the same call
+// of three slices gains 4 of 35; both go the same way, so that results do not depend on how a run is cut into calls.
 constexpr int kMostMembers = 32;
 struct TeamShape { int members, spread; };
 inline TeamShape team_shape(int64_t tiles, int G, int C, int64_t replicas, int cus, int per_cu) {
@@ -91,8 +96,8 @@ constexpr bool team_shares_l2(int members, int G, bool spread, Id id) {
 // of a launch's update, in hundredths of the tile kernel's with a CU per workgroup (5.3 to 5.8 us): the other kernel's chain is
 // shorter while updates rarely consume mini-batches of their own version (K = 2 of 8 workers, 16 replicas of d = 3072: 4.1 us; of 6: 5.9;
 // K = 1 of 2: 5.5; K = 3 of 8: 6.3); with two workgroups per CU an update of the tile kernel takes 9.4 to 11.3 us.  Where replicas
-// take several launches, these add up (40 replicas of d = 3072, K = 3 of 8: 18.3 us against 10.9; K = 2 of 8, 48 replicas: 12.4
-// against 17).  Models of one slice have no exchange to hide: K = 1 only (of 8 workers 3.4 us against 3.8; K = 2 4.45 against 4.16).
+// take several launches, these add up (40 replicas of d = 3072, K = 3 of 8: 18.3 us against 10.9; K = 2 of 8, 40 replicas: 11.8
+// against 11.0, 48 replicas: 12.2 against 17).  Models of one slice have no exchange to hide: K = 1 only (of 8 workers 3.4 us against 3.8; K = 2 4.45 against 4.16).
 inline bool defer_pays(int P, int K, int G, int64_t R, int defer_per_launch, int tile_per_launch, int cus) {
     if (defer_per_launch < 1) return false;
     if (tile_per_launch < 1) return true;

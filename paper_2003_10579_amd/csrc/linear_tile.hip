@@ -4,7 +4,7 @@
 // mini-batches 64 at a time, the gradient is summed over the tiles and the update follows the last
 // one; the asynchronous ones take whole records per tile, or 64-row blocks of one record.
 // (K-async of several tiles and rows of odd length took the general kernel before: P = 20, K = 5, m = 25, d = 785,
-// 10 classes, 8 replicas: 50 us per update there, 17 here.)
+// 10 classes, 8 replicas: 50 us per update there, 16 here and 8 with a team.)
 // Same cluster decomposition, state layout and arithmetic as the general kernel (linear.hip),
 // which runs every other shape and may be mixed with this one launch by launch; what differs
 // is the schedule inside a step:
@@ -28,9 +28,9 @@
 // (whole records of the asynchronous variants), adds the gradients in flight that it has computed itself, and after its last
 // tile the members exchange their sums, 16 bytes per thread and class row, added by everyone in the members' order, so that the
 // weights, of which each has a copy, stay the same bit for bit.  The chain of an update is then one or two tiles long plus one
-// exchange (about 2500 cycles) instead of all of them: softmax, P = 20, K = 5, m = 25, d = 785, 8 replicas (three tiles, three
-// members) 17.4 -> 9.1 us per update; K-sync, K = 6, m = 84, d = 116, 6 replicas (eight tiles) 26.6 -> 5.5; K-batch-async,
-// K = 4, m = 115, d = 580, 15 replicas (four records of two tiles) 40.7 -> 14.2.
+// exchange (about 2500 cycles) instead of all of them.  Softmax, 10 classes: K-async, P = 20, K = 5, m = 25, d = 785, 8 replicas
+// (three tiles, three members) 16.4 -> 8.0 us per update; K-sync, K = 6, m = 84, d = 116, 6 replicas (eight tiles) 24.4 -> 4.9;
+// K-batch-async, P = 8, K = 4, m = 115, d = 580, 15 replicas (four records of two tiles) 41.6 -> 14.4.
 //
 // Four compute waves, four loader waves.  A wave's vector-memory counter retires in order,
 // so the long HBM gathers live in waves of their own: the loader waves fetch everything of
@@ -128,10 +128,12 @@ __device__ __forceinline__ void lds_barrier() {
 // ONE: the cluster is one workgroup (d <= 256).  Its partial logits are the logits: they change lanes inside the wave
 // instead of going out to the exchange, and only the 64-column blocks that exist are loaded, written and contracted.
 // Bound by the chain of one step, TU -> logits -> delta -> gradient -> update, beside the chain lists -> sample ids ->
-// gather of the next tile.  (Least squares, d = 64, two mini-batches of 16, one replica: 2.4 us per update where the
+// gather of the next tile.  (Least squares, d = 64, two mini-batches of 16, one replica: 1.4 us per update where the
 // exchange through memory of the general kernel takes 8.6.)
-// ROOMY: every workgroup takes a CU for itself.  Two waves per SIMD then have 256 registers each and nothing is spilled; a
-// spilled word that a loader wave reads back would wait for the gathers in front of it.  (1 to 4 % at d = 3072.  Not for
+// ROOMY: every workgroup takes a CU for itself.  Two waves per SIMD then have 256 registers each and no vector register is
+// spilled; a spilled word that a loader wave reads back would wait for the gathers in front of it.  With 128, softmax spills 2 to 4 of
+// them where records fill one tile, 10 to 14 where they are described one by one; of a team's forms two do, 11 (synchronous) and 14
+// (whole records, several slices).  (1 to 4 % at d = 3072.  Not for
 // clusters so wide that those of several launches could keep each other from becoming complete: LinArgs::whole_cus.  Not
 // where a launch has more workgroups than the chip has CUs: 1024 replicas of least squares, d = 64, two mini-batches of 16,
 // take 6.4 us per update with two workgroups per CU and 10.2 in rounds of one.)
@@ -731,7 +733,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
     };
     const int scratch = a.own_slots | kOwnSlot;
     const __amdgpu_buffer_rsrc_t prsrc = make_rsrc(park, (uint32_t)S * 16u * nt * 4u);
-    // (TEAM: offsets are derived from an opaque copy of the thread's number where they are used: kept across the loop they are
+    // (TEAM: offsets are derived from an opaque copy of the thread's number where they are used: kept across the loop more of them are
     // spilled where 128 registers have to do, and a spilled word that is read back waits behind the gathers.)
     auto myself = [&]() { int t = tid; asm volatile("" : "+v"(t)); return t; };
     auto owner = [&]() { if constexpr (TEAM) return myself(); else return tid; };
@@ -1409,7 +1411,7 @@ __global__ __launch_bounds__(512, ROOMY ? 2 : 4) void linear_tile_kernel(LinArgs
                 // The same where records are described one by one and their ends are more code: two register sets take turns,
                 // one being read from LDS while the MFMAs of the other are issued, and the loops are kept rolled.  (Unrolled over
                 // the sixteen k-steps that a tile can have, with the end of a record behind each, they are 25 KB of code:
-                // softmax, P = 20, K = 5, m = 25, d = 785, 8 replicas 9.2 us per update, 8.8 so.  Without that code the unrolled loop is the
+                // softmax, P = 20, K = 5, m = 25, d = 785, 8 replicas 4 % more per update.  Without that code the unrolled loop is the
                 // better one: P = 11, K = 5, m = 12, d = 2420, one replica 7.4 us, 7.6 rolled.)
                 const int kpr = rows >> 2, last = n_own * kpr - 1;
                 const float* xr = L.tile + olo * SL;
