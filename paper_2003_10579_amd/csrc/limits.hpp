@@ -36,10 +36,10 @@ inline bool whole_cus_spread(int on_xcd, int cus) { return kHardwareQueues * on_
 // gradient sums that everyone reads (a kilobyte per class row and member, 16 bytes per cycle).  (21 tiles of one slice, 15
 // classes, one replica: 64 us per update alone, 9.3 with 11 members.)  A tile of least squares takes about half of what is counted
 // here, which still leaves every team that the rule makes the better choice: over 144 shapes of both models and three variants, two to
-// twelve tiles, runs are 1.08 (softmax, K-batch-async, 5 mini-batches of 16, d = 64: 7.2 -> 6.7 us per update) to 6.1 times
+// twelve tiles, runs are 1.10 (softmax, K-batch-async, 5 mini-batches of 16, d = 64: 7.2 -> 6.5 us per update) to 5.9 times
 // as fast with a team; least squares, two tiles, d = 64, 3.9 -> 2.6.  What loses is a call of a single update, of which a team's meeting and
-// the buffers armed for it are a larger part: up to 8 of 38 us (K-batch-async, 5 of 16, d = 200, 40 replicas), while the same call
-// of three slices gains 4 of 35; both go the same way, so that results do not depend on how a run is cut into calls.
+// the buffers armed for it are a larger part: up to 5 of 39 us (K-batch-async, 5 of 16, d = 200, 40 replicas), while with three
+// slices it gains (softmax, K-sync, 2 of 64, d = 516, 2 replicas 40 -> 36 us); both go the same way, so that results do not depend on how a run is cut into calls.
 constexpr int kMostMembers = 32;
 struct TeamShape { int members, spread; };
 inline TeamShape team_shape(int64_t tiles, int G, int C, int64_t replicas, int cus, int per_cu) {

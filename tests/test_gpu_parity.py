@@ -964,6 +964,7 @@ def test_k_async_of_one_tile_on_either_kernel(ssgd, oracle, torch_cuda, monkeypa
     ("softmax", "k_batch_async", 9, 6, 32, 300, 15, 3, 3, 0),  # two copies of every slot
     ("lsq", "k_batch_async", 2, 9, 20, 64, 1, 5, 3, 0),      # workers that push several times in an update
     ("lsq", "k_batch_async", 6, 4, 100, 516, 1, 1, 4, 0),    # records of two tiles, summed by their member
+    ("lsq", "k_batch_async", 130, 6, 16, 64, 1, 2, 2, 0),    # some sixty gradients of a member in flight when a launch ends, slots up to 129
     ("softmax", "k_batch_async", 20, 5, 24, 2052, 4, 2, 3, 1),  # clusters of nine, spread over XCDs
     ("softmax", "k_sync", 5, 5, 64, 3000, 3, 1, 5, 1),       # clusters of twelve, a member per XCD
     ("lsq", "k_async", 90, 60, 70, 1200, 1, 1, 20, 1),       # 60 records of two tiles, 90 at version 0
